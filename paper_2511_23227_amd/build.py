@@ -22,9 +22,8 @@ SOURCES = {
     "spatial_order.hip": [],
     "mvmr_generic.hip": [],
     "mvmr_weight.hip": [],
-    "mvmr_rows.hip": [],
-    # MFMA results in ordinary vector registers unless register pressure moves them (see the file header)
-    "mvmr_rows_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    # MFMA results in ordinary vector registers: other instructions read them next
+    "mvmr_rows_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "mvmr_rows_pc.hip": [],
     "tune.hip": [],
 }

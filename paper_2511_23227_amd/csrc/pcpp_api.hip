@@ -122,6 +122,19 @@ PlanSideView side_view(const void *plan, const SideLayout &s, bool spatial)
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)24 << 20;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
+// W or W^T in fragment order without padding (fp32: three bf16 terms)
+size_t rows_w_bytes(int c_in, int c_out, int K, int in_dtype)
+{
+    return align_up((size_t)K * c_out * c_in * (in_dtype == PCPP_F32 ? 6 : 2));
+}
+
+// Forward layers that have always needed the workspace and refuse a call without one; the others do without if they must.
+bool workspace_expected(int in_dtype, int c_in, int c_out)
+{
+    if (in_dtype == PCPP_F32) return c_in == c_out && (c_in == 32 || c_in == 64);
+    return (c_in == 64 && (c_out == 64 || c_out == 128)) || (c_in == 128 && c_out == 64) || (c_in == 256 && c_out == 256);
+}
+
 constexpr int MAX_DEVICES = 64;
 std::mutex scratch_mu;
 void *scratch_ptr[MAX_DEVICES];      // the array's address on each device, once asked for
@@ -161,7 +174,12 @@ size_t pcpp_mvmr_workspace_bytes(int op, int64_t n_in, int64_t n_out, int64_t n_
     if (n_in < 0 || n_out < 0 || n_triplets < 0 || c_in < 1 || c_out < 1 || K < 1) return 0;
     switch (op) {
     case 0:                                                                     // W in fragment order
-    case 1: return align_up((size_t)K * c_out * c_in * (in_dtype == PCPP_F32 ? 6 : 2));   // W / W^T in fragment order (fp32: up to three bf16 terms)
+    case 1: {                                                                   // W^T in fragment order
+        const size_t s = rows_w_bytes(c_in, c_out, K, in_dtype);
+        const size_t t = op == 0 ? mvmr_rows_tile_w_bytes(in_dtype == PCPP_F32, c_in, c_out, K)
+                                 : mvmr_rows_tile_w_bytes(in_dtype == PCPP_F32, c_out, c_in, K);
+        return align_up(s > t ? s : t);
+    }
     case 2: {                                                                   // partial dW per range of centres
         const size_t g = mvmr_weight_workspace_bytes(n_out, c_in, c_out, K);
         const size_t m = mvmr_weight_mfma_workspace_bytes(n_triplets, c_in, c_out, K, in_dtype);
@@ -189,22 +207,20 @@ int pcpp_mvmr_fwd(const void *x, const void *w, void *out, int in_dtype, int out
     a.n_src = n_in; a.n_centres = n_out; a.c_src = c_in; a.c_dst = c_out; a.K = K;
     a.side = side_view(plan, pl.fwd, spatial); a.gather = a.side.gather ? a.side.gather : tri_i;
     a.n_triplets = n_triplets;
-    const bool pc = mvmr_rows_pc_usable(a);
-    if (pc || mvmr_rows_sel_supported(a)) {
-        const size_t need = pcpp_mvmr_workspace_bytes(0, n_in, n_out, n_triplets, c_in, c_out, K, in_dtype);
-        if (!workspace || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255)) {
-            set_error("pcpp_mvmr_fwd: workspace missing, misaligned or smaller than %zu bytes", need);
-            return PCPP_ERR_WORKSPACE;
-        }
-        if (pc) {
-            if ((rc = mvmr_rows_pc_pack_w(w, workspace, K, c_in, c_out, c_in, 1, stream)) != PCPP_OK) return rc;
-            a.w = workspace;
-            return mvmr_rows_pc(a, stream);
-        }
-        if ((rc = mvmr_rows_sel_pack_w(w, workspace, K, c_in, c_out, c_in, 1, in_dtype, stream)) != PCPP_OK) return rc;
+    const bool pc = mvmr_rows_pc_usable(a), tile = !pc && mvmr_rows_tile_usable(a);
+    const size_t need = pc ? rows_w_bytes(c_in, c_out, K, in_dtype) : mvmr_rows_tile_w_bytes(in_dtype == PCPP_F32, c_in, c_out, K);
+    if ((pc || tile) && workspace && workspace_bytes >= need && (reinterpret_cast<uintptr_t>(workspace) & 255) == 0) {
+        rc = pc ? mvmr_rows_pc_pack_w(w, workspace, K, c_in, c_out, c_in, 1, stream)
+                : mvmr_rows_tile_pack_w(w, workspace, K, c_in, c_out, c_in, 1, in_dtype, stream);
+        if (rc != PCPP_OK) return rc;
         a.w = workspace;
-        return mvmr_rows_sel(a, stream);
+        return pc ? mvmr_rows_pc(a, stream) : mvmr_rows_tile(a, stream);
     }
+    if (pc || (tile && workspace_expected(in_dtype, c_in, c_out))) {
+        set_error("pcpp_mvmr_fwd: workspace missing, misaligned or smaller than %zu bytes", need);
+        return PCPP_ERR_WORKSPACE;
+    }
+    // tensors of 4 GiB and more, and callers without scratch memory: this kernel reads W as it is
     return mvmr_rows_generic(a, stream);
 }
 
@@ -236,9 +252,9 @@ int pcpp_mvmr_bwd_input(const void *dy, const void *w, void *dx, int in_dtype, i
         if ((rc = mvmr_rows_pc_pack_w(w, workspace, K, c_out, c_in, 1, c_in, stream)) != PCPP_OK) return rc;
         return mvmr_rows_pc(a, stream);
     }
-    if (mvmr_rows_sel_supported(a)) {
-        if ((rc = mvmr_rows_sel_pack_w(w, workspace, K, c_out, c_in, 1, c_in, in_dtype, stream)) != PCPP_OK) return rc;
-        return mvmr_rows_sel(a, stream);
+    if (mvmr_rows_tile_usable(a)) {
+        if ((rc = mvmr_rows_tile_pack_w(w, workspace, K, c_out, c_in, 1, c_in, in_dtype, stream)) != PCPP_OK) return rc;
+        return mvmr_rows_tile(a, stream);
     }
     if ((rc = transpose_w(w, workspace, K, c_out, c_in, in_dtype, stream)) != PCPP_OK) return rc;
     return mvmr_rows_generic(a, stream);
@@ -281,7 +297,7 @@ int pcpp_mvmr_fwd_static(const void *x, const void *w, void *out, int in_dtype, 
                          const int32_t *tri_k, const int64_t *seg_offsets, int64_t n_triplets, const void *plan,
                          size_t plan_bytes, int plan_flags, void *stream_)
 {
-    const size_t need = pcpp_mvmr_workspace_bytes(0, n_in, n_out, n_triplets, c_in, c_out, K, in_dtype);
+    const size_t need = rows_w_bytes(c_in > 0 ? c_in : 1, c_out > 0 ? c_out : 1, K > 0 ? K : 1, in_dtype);
     if (need > STATIC_SCRATCH_BYTES) {
         set_error("pcpp_mvmr_fwd_static: the packed weights need %zu bytes, the library's own scratch holds %zu", need,
                   STATIC_SCRATCH_BYTES);

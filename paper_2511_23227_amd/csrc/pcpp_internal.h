@@ -76,6 +76,11 @@ struct PlanSideView {
     int64_t n_tiles;
 };
 
+// Kernels for any channel count let a lane read nv consecutive channels of a row.  First channel of the lane at position
+// `pos`: nv pos, or the row's last nv channels where the row ends inside those (so that no read goes past a row; the
+// channels that the lane before it has read already are ignored).  Needs c >= nv.
+__host__ __device__ inline int lane_channel(int pos, int nv, int c) { return pos * nv + nv <= c ? pos * nv : c - nv; }
+
 // Raise a kernel's dynamic LDS limit to `bytes` (once per kernel and device; later calls with no more are free).
 int raise_lds_limit(const void *kernel, size_t bytes);
 
@@ -102,7 +107,7 @@ int scan_exclusive_u32(const uint32_t *in, uint32_t *out, int64_t n, void *scrat
 int fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t stream);
 int fill_u64(unsigned long long *p, unsigned long long v, int64_t n, hipStream_t stream);
 
-// ---- MVMR kernels (mvmr_generic.hip, mvmr_rows.hip, mvmr_weight.hip) -------------------------
+// ---- MVMR kernels (mvmr_generic.hip, mvmr_rows_tile.hip, mvmr_rows_pc.hip, mvmr_weight.hip) -------------------------
 struct MvmrArgs {
     const void *feat;        // gathered tensor: x (fwd, bwd_weight) or dy (bwd_input), [n_src, c_src]
     const void *w;           // fwd: W [K][c_dst][c_src];  bwd_input: W^T [K][c_dst][c_src] (already transposed)
@@ -118,16 +123,17 @@ struct MvmrArgs {
 };
 
 int mvmr_rows_generic(const MvmrArgs &a, hipStream_t stream);              // fwd and bwd_input
-// rows kernels with both the run sums and the W product on the matrix cores (mvmr_rows.hip)
-bool mvmr_rows_sel_supported(const MvmrArgs &a);
-int mvmr_rows_sel_pack_w(const void *w, void *packed, int K, int c_src, int c_dst, int stride_d, int stride_s,
-                         int dtype, hipStream_t stream);
-int mvmr_rows_sel(const MvmrArgs &a, hipStream_t stream);   // a.w = weights packed by mvmr_rows_sel_pack_w
 // wide layers with producer and consumer waves (mvmr_rows_pc.hip); needs a plan side with its own gather array
 bool mvmr_rows_pc_usable(const MvmrArgs &a);
 int mvmr_rows_pc_pack_w(const void *w, void *packed, int K, int c_src, int c_dst, int stride_d, int stride_s,
                         hipStream_t stream);
 int mvmr_rows_pc(const MvmrArgs &a, hipStream_t stream);   // a.w = weights packed by mvmr_rows_pc_pack_w
+// any channel counts, on the matrix cores (mvmr_rows_tile.hip)
+bool mvmr_rows_tile_usable(const MvmrArgs &a);
+size_t mvmr_rows_tile_w_bytes(bool f32, int c_src, int c_dst, int K);     // packed weights
+int mvmr_rows_tile_pack_w(const void *w, void *packed, int K, int c_src, int c_dst, int stride_d, int stride_s, int dtype,
+                          hipStream_t stream);
+int mvmr_rows_tile(const MvmrArgs &a, hipStream_t stream);   // a.w = weights packed by mvmr_rows_tile_pack_w
 int transpose_w(const void *w, void *wt, int K, int c_out, int c_in, int dtype, hipStream_t stream);
 int mvmr_weight_generic(const MvmrArgs &a, float *dw, void *workspace, size_t workspace_bytes,
                         hipStream_t stream);
