@@ -21,8 +21,8 @@ SOURCES = {
     "build_triplets.hip": ["-ffp-contract=off"],
     "spatial_order.hip": [],
     "mvmr_generic.hip": [],
-    "mvmr_weight.hip": [],
     # MFMA results in ordinary vector registers: other instructions read them next
+    "mvmr_weight.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "mvmr_rows_tile.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "mvmr_rows_pc.hip": [],
     "tune.hip": [],

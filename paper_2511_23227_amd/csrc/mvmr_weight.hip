@@ -1,371 +1,25 @@
 // Weight gradient (VVOR), Eq. (5) of Sec. 3.3.3, on the matrix cores: dW[k] = sum over cell k's run of
-// dy[o] (x) x[i].  The (k, o, i) ordered triplet list is cut into equal chunks, one per wave (per
-// sub-block of dW for wide layers); the reduction index of the MFMA is the triplet, both operands are
-// rows read straight from memory (lane <-> channel), chunk partial sums go to the workspace and are
+// dy[o] (x) x[i].  The (k, o, i) ordered triplet list is cut into equal chunks, one per block (per sub-block of dW for
+// wide layers); the reduction index of the MFMA is the triplet; chunk partial sums go to the workspace and are
 // added in a fixed order by a second kernel: no atomics, reproducible.
-#include <stdlib.h>
+//
+// Block c owns triplets [c*chunk, (c+1)*chunk) of the list.  A chunk usually lies inside one cell's run; where a run starts
+// inside the chunk the accumulator is flushed and restarted.  Slots of the partial buffer:
+//   slot c               sum for the cell of the chunk's first triplet
+//   slot n_chunks + k    sum for cell k over the part of its run that starts inside a chunk
+//
+// v_mfma_f32_16x16x32_bf16: A: lane (M = l%16, g = l/16) holds A[M][8g .. 8g+7]; B: lane (N = l%16, g) holds
+// B[8g .. 8g+7][N]; D: lane l, register j -> M = 4g + j, N = l%16.
 
-#include <type_traits>
-
-#include "pcpp_internal.h"
+#include "mvmr_stage.h"
 
 namespace pcpp {
 
 namespace {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-
 constexpr int WAVES = 4;
 
-
-// MFMA register layout used by the fp32 kernel (wave64):
-//   v_mfma_f32_32x32x2_f32: A: lane (m = l%32, h = l/32) gives A[m][h];  B: lane (n, h) gives B[h][n];
-//   D: lane l, register j -> row 8*(j/4) + 4*(l/32) + j%4, column l%32.
-
-// ---------------------------------------------------------------------------------------------
-// Weight gradient (VVOR), Eq. (5).  Wave c owns triplets [c*chunk, (c+1)*chunk) of the (k, o, i)
-// ordered list.  A chunk usually lies inside one cell's run; where a run starts inside the chunk the
-// accumulator is flushed and restarted.  Slots of the partial buffer:
-//   slot c               sum for the cell of the chunk's first triplet
-//   slot n_chunks + k    sum for cell k over the part of its run that starts inside a chunk
-// fp32 layers (this kernel): one MFMA step consumes 2 triplets: lane (c, h) supplies channel c of dy[o] and
-// of x[i] of triplet 2 s + h.  bf16 layers use weight_wide_kernel below.
-// Layers wider than one wave's accumulators: a wave owns a SUB_OUT x SUB_IN block of dW[k]; the waves that
-// share a chunk are consecutive, so their re-reads of the same rows are served by the L1 / L2 caches.
-// ---------------------------------------------------------------------------------------------
-template <bool BF16, int C_IN, int C_OUT, int SUB_IN, int SUB_OUT>
-__global__ __launch_bounds__(WAVES * 64, (!BF16 && C_IN == 32 && C_OUT == 32) ? 5 : 1) void weight_kernel(const void *__restrict__ x_, const void *__restrict__ dy_,
-                                                            float *__restrict__ part,
-                                                            const int32_t *__restrict__ tri_o,
-                                                            const int32_t *__restrict__ tri_i,
-                                                            const int64_t *__restrict__ seg, int K, int64_t n_triplets,
-                                                            int chunk, int64_t n_chunks)
-{
-    constexpr int NBI = SUB_IN / 32, NBO = SUB_OUT / 32;
-    constexpr int N_SUB_IN = C_IN / SUB_IN, N_SUB = N_SUB_IN * (C_OUT / SUB_OUT);
-    constexpr int STEP = BF16 ? 16 : 2;      // triplets per MFMA step
-    constexpr int NS = 32 / STEP;            // steps per batch of 32 triplets
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c = lane & 31, h = lane >> 5;
-    const int64_t gw = (int64_t)blockIdx.x * WAVES + wave;
-    const int64_t chunk_id = gw / N_SUB;
-    const int sub = (int)(gw % N_SUB);
-    const int ci0 = (sub % N_SUB_IN) * SUB_IN, co0 = (sub / N_SUB_IN) * SUB_OUT;
-    if (chunk_id >= n_chunks) return;
-    int64_t p = chunk_id * chunk;
-    int64_t p_end = p + chunk;
-    if (p_end > n_triplets) p_end = n_triplets;
-
-    // cell of the first triplet: the k with seg[k] <= p < seg[k+1]
-    int k = 0;
-    for (int kb = 0; kb < K; kb += 64) {
-        const int kk = kb + lane;
-        const bool hit = kk < K && seg[kk] <= p && p < seg[kk + 1];
-        const unsigned long long msk = __ballot(hit);
-        if (msk) { k = kb + __ffsll((long long)msk) - 1; break; }
-    }
-
-    v16f acc[NBO][NBI];
-    bool first = true;
-    while (p < p_end) {
-        int64_t q = seg[k + 1];
-        if (q > p_end) q = p_end;
-        if (q <= p) { ++k; continue; }       // empty run
-#pragma unroll
-        for (int bo = 0; bo < NBO; ++bo)
-#pragma unroll
-            for (int bi = 0; bi < NBI; ++bi)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) acc[bo][bi][j] = 0.f;
-
-        for (int64_t b0 = p; b0 < q; b0 += 32) {
-            const int n = (int)(q - b0 < 32 ? q - b0 : 32);
-            // lanes 0..31 hold o of triplet b0 + lane, lanes 32..63 hold i of triplet b0 + lane - 32
-            int32_t oi = 0;
-            if (c < n) oi = h == 0 ? tri_o[b0 + c] : tri_i[b0 + c];
-            static_assert(!BF16, "bf16 layers use weight_wide_kernel");
-            {
-                float a[NBO][NS], b[NBI][NS];
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    const int t = 2 * s + h;
-                    const int32_t o = __shfl(oi, t, 64), i = __shfl(oi, 32 + t, 64);
-                    const float *dyr = static_cast<const float *>(dy_) + (size_t)o * C_OUT + co0 + c;
-                    const float *xr = static_cast<const float *>(x_) + (size_t)i * C_IN + ci0 + c;
-#pragma unroll
-                    for (int bo = 0; bo < NBO; ++bo) a[bo][s] = t < n ? dyr[bo * 32] : 0.f;
-#pragma unroll
-                    for (int bi = 0; bi < NBI; ++bi) b[bi][s] = t < n ? xr[bi * 32] : 0.f;
-                }
-#pragma unroll
-                for (int s = 0; s < NS; ++s)
-#pragma unroll
-                    for (int bo = 0; bo < NBO; ++bo)
-#pragma unroll
-                        for (int bi = 0; bi < NBI; ++bi)
-                            acc[bo][bi] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[bo][s], b[bi][s], acc[bo][bi], 0, 0, 0);
-            }
-        }
-        // flush
-        float *dstp = part + (size_t)(first ? chunk_id : n_chunks + k) * C_OUT * C_IN;
-#pragma unroll
-        for (int bo = 0; bo < NBO; ++bo)
-#pragma unroll
-            for (int bi = 0; bi < NBI; ++bi)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const int r = 8 * (j / 4) + 4 * h + (j % 4);
-                    const int co = co0 + bo * 32 + r, ci = ci0 + bi * 32 + c;
-                    dstp[(size_t)co * C_IN + ci] = acc[bo][bi][j];
-                }
-        first = false;
-        p = q;
-        ++k;
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
-// fp32 layers, second form: v_mfma_f32_16x16x4_f32 (A: lane (M = l%16, g = l/16) gives A[M][g]; B: lane
-// (N = l%16, g) gives B[g][N]; D: lane l, register j -> M = 4g + j, N = l%16).  Lane (m, g) reads 8 bytes =
-// channels 2m, 2m+1 (+ 32 per 32-channel group) of the rows of triplets g, 4 + g, ..., 28 + g of a batch of 32:
-// one load instruction covers four rows, half the address-unit work of one channel per lane, and the loaded
-// values are MFMA operands as they are (row / column m of operand (group, q) is channel 32 group + 2m + q).
-// ---------------------------------------------------------------------------------------------
-typedef float v2f __attribute__((ext_vector_type(2)));
-
-template <int C_IN, int C_OUT>
-__global__ __launch_bounds__(WAVES * 64) void weight_f32_kernel(const float *__restrict__ x, const float *__restrict__ dy,
-                                                                float *__restrict__ part,
-                                                                const int32_t *__restrict__ tri_o,
-                                                                const int32_t *__restrict__ tri_i,
-                                                                const int64_t *__restrict__ seg, int K,
-                                                                int64_t n_triplets, int chunk, int64_t n_chunks)
-{
-    constexpr int QO = C_OUT / 32, QI = C_IN / 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = lane & 15, g = lane >> 4;
-    const int64_t chunk_id = (int64_t)blockIdx.x * WAVES + wave;
-    if (chunk_id >= n_chunks) return;
-    int64_t p = chunk_id * chunk;
-    int64_t p_end = p + chunk;
-    if (p_end > n_triplets) p_end = n_triplets;
-
-    // cell of the first triplet: the k with seg[k] <= p < seg[k+1]
-    int k = 0;
-    for (int kb = 0; kb < K; kb += 64) {
-        const int kk = kb + lane;
-        const bool hit = kk < K && seg[kk] <= p && p < seg[kk + 1];
-        const unsigned long long msk = __ballot(hit);
-        if (msk) { k = kb + __ffsll((long long)msk) - 1; break; }
-    }
-
-    v4f acc[QO][2][QI][2];
-    bool first = true;
-    // o (lanes 0..31) and i (lanes 32..63) of the 32 triplets from `pos` on, clamped to the list
-    auto load_oi = [&](int64_t pos) -> int32_t {
-        int64_t t = pos + (lane & 31);
-        t = t < n_triplets ? t : n_triplets - 1;
-        return lane < 32 ? tri_o[t] : tri_i[t];
-    };
-    int64_t pf_pos = p;
-    int32_t oi_pf = load_oi(p);
-    while (p < p_end) {
-        int64_t q_end = seg[k + 1];
-        if (q_end > p_end) q_end = p_end;
-        if (q_end <= p) { ++k; continue; }   // empty run
-#pragma unroll
-        for (int a = 0; a < QO; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int c = 0; c < QI; ++c)
-#pragma unroll
-                    for (int d = 0; d < 2; ++d) acc[a][b][c][d] = v4f{0.f, 0.f, 0.f, 0.f};
-
-        for (int64_t b0 = p; b0 < q_end; b0 += 32) {
-            const int n = (int)(q_end - b0 < 32 ? q_end - b0 : 32);
-            // lanes 0..31 hold o of triplet b0 + lane, lanes 32..63 hold i of triplet b0 + lane - 32: asked for one step
-            // ahead (the next step starts 32 triplets on, or where the next cell's run starts), so that a step's rows
-            // wait for one memory round trip, not for two in a row
-            const int32_t oi = pf_pos == b0 ? oi_pf : load_oi(b0);                 // wave-uniform
-            pf_pos = b0 + 32 < q_end ? b0 + 32 : q_end;
-            oi_pf = load_oi(pf_pos);
-            v2f dyw[QO][8], xw[QI][8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int t = 4 * e + g;
-                const int32_t o = __shfl(oi, t, 64), i = __shfl(oi, 32 + t, 64);
-                const v2f *dyr = reinterpret_cast<const v2f *>(dy + (size_t)o * C_OUT) + m;
-                const v2f *xr = reinterpret_cast<const v2f *>(x + (size_t)i * C_IN) + m;
-#pragma unroll
-                for (int qo = 0; qo < QO; ++qo) dyw[qo][e] = t < n ? dyr[qo * 16] : v2f{0.f, 0.f};
-#pragma unroll
-                for (int qi = 0; qi < QI; ++qi) xw[qi][e] = t < n ? xr[qi * 16] : v2f{0.f, 0.f};
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-#pragma unroll
-                for (int qo = 0; qo < QO; ++qo)
-#pragma unroll
-                    for (int qd = 0; qd < 2; ++qd)
-#pragma unroll
-                        for (int qi = 0; qi < QI; ++qi)
-#pragma unroll
-                            for (int qs = 0; qs < 2; ++qs)
-                                acc[qo][qd][qi][qs] = __builtin_amdgcn_mfma_f32_16x16x4f32(dyw[qo][e][qd], xw[qi][e][qs],
-                                                                                           acc[qo][qd][qi][qs], 0, 0, 0);
-        }
-        // flush: lane (m, g), register j of acc[qo][qd][qi][qs] is dW[32 qo + 2 (4g + j) + qd][32 qi + 2m + qs]
-        float *dstp = part + (size_t)(first ? chunk_id : n_chunks + k) * C_OUT * C_IN;
-#pragma unroll
-        for (int qo = 0; qo < QO; ++qo)
-#pragma unroll
-            for (int qd = 0; qd < 2; ++qd)
-#pragma unroll
-                for (int qi = 0; qi < QI; ++qi)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int co = 32 * qo + 2 * (4 * g + j) + qd, ci = 32 * qi + 2 * m;
-                        *reinterpret_cast<v2f *>(dstp + (size_t)co * C_IN + ci) = v2f{acc[qo][qd][qi][0][j], acc[qo][qd][qi][1][j]};
-                    }
-        first = false;
-        p = q_end;
-        ++k;
-    }
-}
-
-// ---------------------------------------------------------------------------------------------
-// bf16 layers: the same chunking, with v_mfma_f32_16x16x32_bf16 (A: lane (M = l%16, g = l/16) holds
-// A[M][8g .. 8g+7]; B: lane (N = l%16, g) holds B[8g .. 8g+7][N]; D: lane l, register j -> M = 4g + j,
-// N = l%16).  One step consumes 32 triplets; lane (m, g) reads 8 bytes = channels 4m .. 4m+3 (+ 64 per
-// 64-channel group) of the rows of triplets 8g .. 8g+7, so one load instruction covers four rows and the
-// address units do half the work of dword reads.  Element q of those four channels of the eight triplets is
-// one MFMA operand: row / column m of operand (group, q) is channel 64 group + 4m + q.
-// ---------------------------------------------------------------------------------------------
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
-
-template <int C_IN, int C_OUT, int SUB_IN, int SUB_OUT>
-__global__ __launch_bounds__(WAVES * 64) void weight_wide_kernel(const void *__restrict__ x_, const void *__restrict__ dy_,
-                                                                 float *__restrict__ part,
-                                                                 const int32_t *__restrict__ tri_o,
-                                                                 const int32_t *__restrict__ tri_i,
-                                                                 const int64_t *__restrict__ seg, int K,
-                                                                 int64_t n_triplets, int chunk, int64_t n_chunks)
-{
-    constexpr int QO = SUB_OUT / 64, QI = SUB_IN / 64;     // 64-channel groups of the sub-block
-    constexpr int N_SUB_IN = C_IN / SUB_IN, N_SUB = N_SUB_IN * (C_OUT / SUB_OUT);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = lane & 15, g = lane >> 4;
-    const int64_t gw = (int64_t)blockIdx.x * WAVES + wave;
-    const int64_t chunk_id = gw / N_SUB;
-    const int sub = (int)(gw % N_SUB);
-    const int ci0 = (sub % N_SUB_IN) * SUB_IN, co0 = (sub / N_SUB_IN) * SUB_OUT;
-    if (chunk_id >= n_chunks) return;
-    int64_t p = chunk_id * chunk;
-    int64_t p_end = p + chunk;
-    if (p_end > n_triplets) p_end = n_triplets;
-
-    // cell of the first triplet: the k with seg[k] <= p < seg[k+1]
-    int k = 0;
-    for (int kb = 0; kb < K; kb += 64) {
-        const int kk = kb + lane;
-        const bool hit = kk < K && seg[kk] <= p && p < seg[kk + 1];
-        const unsigned long long msk = __ballot(hit);
-        if (msk) { k = kb + __ffsll((long long)msk) - 1; break; }
-    }
-
-    v4f acc[QO][4][QI][4];
-    bool first = true;
-    // o (lanes 0..31) and i (lanes 32..63) of the 32 triplets from `pos` on, clamped to the list
-    auto load_oi = [&](int64_t pos) -> int32_t {
-        int64_t t = pos + (lane & 31);
-        t = t < n_triplets ? t : n_triplets - 1;
-        return lane < 32 ? tri_o[t] : tri_i[t];
-    };
-    int64_t pf_pos = p;
-    int32_t oi_pf = load_oi(p);
-    while (p < p_end) {
-        int64_t q_end = seg[k + 1];
-        if (q_end > p_end) q_end = p_end;
-        if (q_end <= p) { ++k; continue; }   // empty run
-#pragma unroll
-        for (int a = 0; a < QO; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-#pragma unroll
-                for (int c = 0; c < QI; ++c)
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) acc[a][b][c][d] = v4f{0.f, 0.f, 0.f, 0.f};
-
-        for (int64_t b0 = p; b0 < q_end; b0 += 32) {
-            const int n = (int)(q_end - b0 < 32 ? q_end - b0 : 32);
-            // lanes 0..31 hold o of triplet b0 + lane, lanes 32..63 hold i of triplet b0 + lane - 32: asked for one step
-            // ahead (the next step starts 32 triplets on, or where the next cell's run starts), so that a step's rows
-            // wait for one memory round trip, not for two in a row
-            const int32_t oi = pf_pos == b0 ? oi_pf : load_oi(b0);                 // wave-uniform
-            pf_pos = b0 + 32 < q_end ? b0 + 32 : q_end;
-            oi_pf = load_oi(pf_pos);
-            v2u dyw[QO][8], xw[QI][8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int t = 8 * g + e;
-                const int32_t o = __shfl(oi, t, 64), i = __shfl(oi, 32 + t, 64);
-                const v2u *dyr = reinterpret_cast<const v2u *>(static_cast<const uint16_t *>(dy_) + (size_t)o * C_OUT + co0) + m;
-                const v2u *xr = reinterpret_cast<const v2u *>(static_cast<const uint16_t *>(x_) + (size_t)i * C_IN + ci0) + m;
-#pragma unroll
-                for (int qo = 0; qo < QO; ++qo) dyw[qo][e] = t < n ? dyr[qo * 16] : v2u{0u, 0u};
-#pragma unroll
-                for (int qi = 0; qi < QI; ++qi) xw[qi][e] = t < n ? xr[qi * 16] : v2u{0u, 0u};
-            }
-            v4u bv[QI][4];
-#pragma unroll
-            for (int qi = 0; qi < QI; ++qi)
-#pragma unroll
-                for (int qs = 0; qs < 4; ++qs)
-#pragma unroll
-                    for (int wd = 0; wd < 4; ++wd)
-                        bv[qi][qs][wd] = __builtin_amdgcn_perm(xw[qi][2 * wd + 1][qs >> 1], xw[qi][2 * wd][qs >> 1],
-                                                               (qs & 1) ? 0x07060302u : 0x05040100u);
-#pragma unroll
-            for (int qo = 0; qo < QO; ++qo)
-#pragma unroll
-                for (int qd = 0; qd < 4; ++qd) {
-                    v4u av;
-#pragma unroll
-                    for (int wd = 0; wd < 4; ++wd)
-                        av[wd] = __builtin_amdgcn_perm(dyw[qo][2 * wd + 1][qd >> 1], dyw[qo][2 * wd][qd >> 1],
-                                                       (qd & 1) ? 0x07060302u : 0x05040100u);
-#pragma unroll
-                    for (int qi = 0; qi < QI; ++qi)
-#pragma unroll
-                        for (int qs = 0; qs < 4; ++qs)
-                            acc[qo][qd][qi][qs] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(v8bf, av), __builtin_bit_cast(v8bf, bv[qi][qs]), acc[qo][qd][qi][qs], 0, 0, 0);
-                }
-        }
-        // flush: lane (m, g), register j of acc[qo][qd][qi][qs] is dW[co0 + 64 qo + 4 (4g + j) + qd][ci0 + 64 qi + 4m + qs]
-        float *dstp = part + (size_t)(first ? chunk_id : n_chunks + k) * C_OUT * C_IN;
-#pragma unroll
-        for (int qo = 0; qo < QO; ++qo)
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd)
-#pragma unroll
-                for (int qi = 0; qi < QI; ++qi)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int co = co0 + 64 * qo + 4 * (4 * g + j) + qd;
-                        const int ci = ci0 + 64 * qi + 4 * m;
-                        *reinterpret_cast<v4f *>(dstp + (size_t)co * C_IN + ci) =
-                            v4f{acc[qo][qd][qi][0][j], acc[qo][qd][qi][1][j], acc[qo][qd][qi][2][j], acc[qo][qd][qi][3][j]};
-                    }
-        first = false;
-        p = q_end;
-        ++k;
-    }
-}
 
 // ---------------------------------------------------------------------------------------------
 // bf16 256 -> 256: one block of eight waves per chunk, wave w owning the 128 x 64 sub-block (output channels
@@ -392,8 +46,9 @@ __global__ __launch_bounds__(WAVES * 64) void weight_wide_kernel(const void *__r
 // (one for indices, four for rows; a batch that is short or empty re-reads its last triplet, or triplet 0): behind
 // the rows to wait for, eleven younger instructions may still be outstanding, behind the indices nine.  (The partial
 // sums' stores and the rare reads of a cell's bounds, which the compiler does see, only make these waits stricter.)
-// A batch never crosses the end of a cell's run.  The operands are read from LDS in the layout weight_wide_kernel
-// reads from memory.
+// A batch never crosses the end of a cell's run.  Lane (m, g) reads 8 bytes = channels 4m .. 4m+3 (+ 64 per 64-channel
+// group) of the rows of triplets 8g .. 8g+7; element q of those four channels of the eight triplets is one MFMA operand:
+// row / column m of operand (group, q) is channel 64 group + 4m + q.
 // ---------------------------------------------------------------------------------------------
 constexpr int LDS_WAVES = 8;
 constexpr int LDS_GROUP_PITCH = 8 * 512 + 128;    // eight rows of 512 B, then 128 B: the rows r, r + 8, r + 16, r + 24 that
@@ -628,6 +283,194 @@ __global__ __launch_bounds__(LDS_WAVES * 64, 2) void weight_lds_kernel(const uin
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // nothing of this wave is still on its way into LDS
 }
 
+// ---------------------------------------------------------------------------------------------
+// Any channel counts, fp32 or bf16.  A block of four waves owns a chunk of the triplet list and a sub-block of dW, up to
+// 128 x 64 channels (bf16) or 64 x 64 (fp32); the waves take the chunk's batches of 32 triplets in turn and their sums
+// are added through LDS, in wave order, where the sub-block is flushed (so there are a quarter as many partial sums as
+// waves).  The rows of a batch reach the matrix cores as mvmr_stage.h describes: dy as operand A, x as operand B, the
+// triplet as the reduction index.  fp32 rows are three bf16 terms there, and the six products of weight 2^-16 or more
+// relative to the leading one are kept (the rest is below 2^-24 of it).
+// Triplets past the batch's end get an offset past the buffer, whose reads return zeros and cost no traffic.  The rows
+// of the next batch are requested as soon as this one's have been passed on, so they are on their way while the matrix
+// cores work; the indices are requested a batch ahead of them.
+// What bounds it: bf16, the L1 cache, which serves four lanes per access (64 -> 64, 17 M triplets: 4 accesses per row of
+// 128 bytes with 8 bytes per lane, 294 us; 2 with 16 bytes, 220); fp32, the vector instructions that split
+// the rows into terms.  Before, with one wave per chunk, rows read as dwords or 8-byte pieces, fp32 products on the fp32
+// matrix instructions, and the partial sums: 331 + 35 us for that layer (now 220 + 7), 84 + 11 for a 32 -> 32 fp32 layer
+// with 2.4 M triplets (58 + 7), 146 + 24 for 64 -> 128 with 4.6 M (113 + 8), and on the vector ALUs 1715 for 128 -> 64 with
+// 2.3 M (77 + 8).
+// ---------------------------------------------------------------------------------------------
+struct WeightArgs {
+    const void *x, *dy;
+    float *part;
+    const int32_t *tri_o, *tri_i;
+    const int64_t *seg;
+    int64_t n_triplets, n_chunks;
+    uint32_t x_bytes, dy_bytes, tri_bytes;
+    int K, c_in, c_out, chunk, n_sub_in, n_sub;
+};
+
+// waves per SIMD that the register allocation must leave room for
+template <typename SO, typename SI> constexpr int any_min_waves() {
+    if (SO::NT * SI::NT >= 16 || SO::CHK + SI::CHK > 128) return 2;
+    return SO::PL > 1 && SO::NT * SI::NT >= 8 ? 3 : 4;
+}
+
+// SO, SI: how the rows of dy and x reach the matrix cores
+template <typename SO, typename SI>
+__global__ __launch_bounds__(WAVES * 64, (any_min_waves<SO, SI>())) void weight_any_kernel(const WeightArgs a)
+{
+    constexpr int ES = SO::ES, NTO = SO::NT, NTI = SI::NT, PL = SO::PL;
+    constexpr bool F32 = PL > 1;
+    extern __shared__ __attribute__((aligned(256))) char lds[];       // staged rows, [WAVES]; the sums of one row of tiles
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int m = lane & 15, g = lane >> 4;
+    // the sub-blocks of a chunk, which read the same rows, run on the same XCD (blocks go round the eight XCDs)
+    const int64_t per = 8 * (int64_t)a.n_sub;
+    const int64_t chunk_id = (int64_t)blockIdx.x / per * 8 + blockIdx.x % 8;
+    const int sub = (int)((int64_t)blockIdx.x % per / 8);
+    if (chunk_id >= a.n_chunks) return;                   // whole block, before any barrier
+    const int sub_i = sub % a.n_sub_in, sub_o = sub / a.n_sub_in;
+    const int64_t p0 = chunk_id * a.chunk;                // positions below are relative to it
+    const uint32_t p_end = (uint32_t)((p0 + a.chunk < a.n_triplets ? p0 + a.chunk : a.n_triplets) - p0);
+    const __amdgpu_buffer_rsrc_t xrs = make_rsrc(a.x, a.x_bytes), drs = make_rsrc(a.dy, a.dy_bytes);
+    const __amdgpu_buffer_rsrc_t irs = make_rsrc(a.tri_i, a.tri_bytes), ors = make_rsrc(a.tri_o, a.tri_bytes);
+    const uint32_t xrow = (uint32_t)a.c_in * ES, drow = (uint32_t)a.c_out * ES;
+    SO so;
+    SI si;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds + (uint32_t)wave * (SO::BYTES + SI::BYTES);
+    so.init(lds0, lane);
+    si.init(lds0 + SO::BYTES, lane);
+    so.set_chunk(sub_o, a.c_out, lane);
+    si.set_chunk(sub_i, a.c_in, lane);
+
+    // cell of the first triplet: the k with seg[k] <= p0 < seg[k+1]
+    int k = 0;
+    for (int kb = 0; kb < a.K; kb += 64) {
+        const int kk = kb + lane;
+        const bool hit = kk < a.K && a.seg[kk] <= p0 && p0 < a.seg[kk + 1];
+        const unsigned long long msk = __ballot(hit);
+        if (msk) { k = kb + __ffsll((long long)msk) - 1; break; }
+    }
+    k = __builtin_amdgcn_readfirstlane(k);
+
+    // indices of the batch whose rows are requested next, as they come: not touched before a whole batch has been multiplied
+    uint32_t ri, ro;
+    const uint32_t ti = SI::triplet_of_lane(m, g), to = SO::triplet_of_lane(m, g);
+    auto load_indices = [&](uint32_t pos) {
+        const int at = (int)(((uint32_t)p0 + pos) * 4u);
+        ri = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(irs, (int)(ti * 4u), at, 0);
+        ro = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(ors, (int)(to * 4u), at, 0);
+    };
+    auto load_rows = [&](uint32_t n) {
+        const uint32_t oi = ti < n ? ri * xrow : OOB_OFFSET, oo = to < n ? ro * drow : OOB_OFFSET;
+        so.load(drs, oo, a.c_out);
+        si.load(xrs, oi, a.c_in);
+    };
+    // This wave's batches: (position, triplets), run by run; a batch never crosses the end of a cell's run.
+    struct Cursor { uint32_t pos, end; int k; };
+    auto end_of = [&](int kk) -> uint32_t {               // end of cell kk's run inside the chunk
+        const int64_t e = a.seg[kk + 1] - p0;
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)(e < (int64_t)p_end ? (uint32_t)e : p_end));
+    };
+    auto settle = [&](Cursor &c, uint32_t start) {        // the first batch at or behind `start` of c's run, or of a later one
+        c.pos = start;
+        while (c.pos >= c.end && c.end < p_end) {
+            const uint32_t s = c.end;
+            ++c.k;
+            c.end = end_of(c.k);
+            c.pos = s + (uint32_t)(WINDOW * wave);
+        }
+    };
+    auto left = [&](const Cursor &c) -> uint32_t { return c.pos < c.end ? (c.end - c.pos < (uint32_t)WINDOW ? c.end - c.pos : (uint32_t)WINDOW) : 0u; };
+    Cursor nx{0u, end_of(k), k};
+    settle(nx, (uint32_t)(WINDOW * wave));
+    load_indices(nx.pos);
+    load_rows(left(nx));
+    settle(nx, nx.pos + WINDOW * WAVES);
+    load_indices(nx.pos);
+
+    bool first = true;
+    uint32_t p = 0u;
+    while (p < p_end) {
+        const uint32_t q_end = end_of(k);
+        if (q_end <= p) { ++k; continue; }                // empty run
+        v4f acc[NTO][NTI];
+#pragma unroll
+        for (int o = 0; o < NTO; ++o)
+#pragma unroll
+            for (int i = 0; i < NTI; ++i) acc[o][i] = v4f{0.f, 0.f, 0.f, 0.f};
+        for (uint32_t b = p + (uint32_t)(WINDOW * wave); b < q_end; b += WINDOW * WAVES) {
+            so.store();
+            si.store();
+            load_rows(left(nx));
+            settle(nx, nx.pos + WINDOW * WAVES);
+            load_indices(nx.pos);
+            if constexpr (!F32) {
+                constexpr int AT = NTO < 4 ? NTO : 4, BT = NTI < 4 ? NTI : 4;      // tiles of operands held at a time
+#pragma unroll
+                for (int i0 = 0; i0 < NTI; i0 += BT) {
+                    v4u bx[BT];
+                    si.tiles(0, i0, bx);
+#pragma unroll
+                    for (int o0 = 0; o0 < NTO; o0 += AT) {
+                        v4u av[AT];
+                        so.tiles(0, o0, av);
+#pragma unroll
+                        for (int o = 0; o < AT; ++o)
+#pragma unroll
+                            for (int i = 0; i < BT; ++i)
+                                acc[o0 + o][i0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    __builtin_bit_cast(v8bf, av[o]), __builtin_bit_cast(v8bf, bx[i]), acc[o0 + o][i0 + i], 0, 0, 0);
+                    }
+                }
+            } else {
+                v4u bx[PL][NTI];
+#pragma unroll
+                for (int pl = 0; pl < PL; ++pl) si.tiles(pl, 0, bx[pl]);
+#pragma unroll
+                for (int pl = PL - 1; pl >= 0; --pl) {    // smallest products first
+                    v4u av[NTO];
+                    so.tiles(pl, 0, av);
+#pragma unroll
+                    for (int q = PL - 1 - pl; q >= 0; --q)
+#pragma unroll
+                        for (int o = 0; o < NTO; ++o)
+#pragma unroll
+                            for (int i = 0; i < NTI; ++i)
+                                acc[o][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, av[o]),
+                                                                                    __builtin_bit_cast(v8bf, bx[q][i]), acc[o][i], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        // flush: the four waves' sums, one row of tiles at a time
+        float *dstp = a.part + (size_t)(first ? chunk_id : a.n_chunks + k) * a.c_out * a.c_in;
+        float (*red)[NTI][64][4] = reinterpret_cast<float (*)[NTI][64][4]>(lds);
+        const int el = threadIdx.x >> 2, ej = threadIdx.x & 3;            // lane and register of the values this thread adds
+#pragma unroll
+        for (int o = 0; o < NTO; ++o) {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NTI; ++i) *reinterpret_cast<v4f *>(red[wave][i][lane]) = acc[o][i];
+            __syncthreads();
+            const int co = SO::channel(sub_o, 16 * o + 4 * (el >> 4) + ej, a.c_out);
+#pragma unroll
+            for (int i = 0; i < NTI; ++i) {
+                const int ci = SI::channel(sub_i, 16 * i + (el & 15), a.c_in);
+                float v = red[0][i][el][ej];
+#pragma unroll
+                for (int w = 1; w < WAVES; ++w) v += red[w][i][el][ej];
+                if (co >= 0 && ci >= 0) dstp[(size_t)co * a.c_in + ci] = v;
+            }
+        }
+        __syncthreads();                                   // (the next rows go where these sums lie)
+        first = false;
+        p = q_end;
+        ++k;
+    }
+}
+
 // dw[k][e] = (partial of the run's head, if it starts inside a chunk) + partials of the chunks whose first
 // triplet lies in run k.  A block of four waves owns 64 consecutive elements of one cell: wave w adds chunks
 // c0 + w, c0 + w + 4, ... in ascending order (each read is 256 contiguous bytes) and the four sums are then
@@ -665,80 +508,119 @@ __global__ __launch_bounds__(REDUCE_WAVES * 64) void weight_reduce(const float *
     }
 }
 
-// Triplets per chunk.  The blocks of a launch (`per_block` chunks each) are spread evenly over the CUs, and the
-// kernels run at a fixed rate per CU, so a launch takes as long as the CU with the most blocks: the chunk length
-// is chosen so that the number of blocks is a whole multiple m of the CU count, with about a thousand triplets
-// per chunk and at most 8192 chunks (2048 for wide layers, whose partial sums are large).  Clouds too small for
-// one block per CU keep chunks of 512.
-constexpr int64_t DEVICE_CUS = 256;           // MI355X
+// Triplets per chunk of weight_lds_kernel.  Its blocks, one per chunk, are spread evenly over the CUs and run at a fixed
+// rate per CU, so a launch takes as long as the CU with the most blocks: the chunk length is chosen so that the number of
+// blocks is a whole multiple m of the CU count, with about a thousand triplets per chunk and at most 2048 chunks (each has
+// 256 KB of partial sums).  Clouds too small for one block per CU keep chunks of 512.
+constexpr int64_t DEVICE_CUS = 256, LDS_MAX_CHUNKS = 2048;           // MI355X
 
-int weight_chunk(int64_t n_triplets, int c_in, int c_out, int per_block)
+int lds_chunk(int64_t n_triplets)
 {
-    const int64_t max_chunks = (int64_t)c_in * c_out >= 128 * 128 ? 2048 : 8192;
-    const int64_t per_round = DEVICE_CUS * per_block;                  // chunks of one block on every CU
-    int64_t m = (n_triplets + per_round * 500) / (per_round * 1000);     // nearest whole number of rounds
-    if (m > max_chunks / per_round) m = max_chunks / per_round;
-    if (m < 1 || n_triplets < per_round * 512) {
-        int chunk = 512;
-        while ((n_triplets + chunk - 1) / chunk > max_chunks) chunk *= 2;
-        return chunk;
-    }
-    const int64_t chunk = ceil_div(n_triplets, per_round * m);
+    int64_t m = (n_triplets + DEVICE_CUS * 500) / (DEVICE_CUS * 1000);   // nearest whole number of rounds
+    if (m > LDS_MAX_CHUNKS / DEVICE_CUS) m = LDS_MAX_CHUNKS / DEVICE_CUS;
+    if (m < 1 || n_triplets < DEVICE_CUS * 512) return 512;
+    const int64_t chunk = ceil_div(n_triplets, DEVICE_CUS * m);
     return (int)((chunk + 31) / 32 * 32);
 }
 
-// chunks handled by one block of the kernel that serves the shape
-int weight_chunks_per_block(bool bf16, int c_in, int c_out)
-{
-    if (bf16 && c_in == 256 && c_out == 256) return 1;                 // weight_lds_kernel
-    if (bf16 && c_in >= 128 && c_out >= 128) return WAVES / 2;          // two sub-block waves per chunk
-    return WAVES;                                                       // one wave per chunk
-}
+bool lds_shape(int in_dtype, int c_in, int c_out) { return in_dtype == PCPP_BF16 && c_in == 256 && c_out == 256; }
 
-template <bool BF16, int C_IN, int C_OUT, int SUB_IN = C_IN, int SUB_OUT = C_OUT>
-int launch_weight(const MvmrArgs &a, float *dw, const int32_t *tri_o, const int64_t *seg, void *workspace,
-                  size_t workspace_bytes, hipStream_t stream)
+int launch_reduce(const float *part, float *dw, const int64_t *seg, int n_elem, int K, int chunk, int64_t n_chunks, hipStream_t stream)
 {
-    const int n_elem = C_IN * C_OUT;
-    const int chunk = weight_chunk(a.n_triplets, C_IN, C_OUT, weight_chunks_per_block(BF16, C_IN, C_OUT));
-    const int64_t n_chunks = ceil_div(a.n_triplets, chunk);
-    constexpr int N_SUB = (C_IN / SUB_IN) * (C_OUT / SUB_OUT);
-    const size_t need = (size_t)(n_chunks + a.K) * n_elem * sizeof(float);
-    if (workspace_bytes < need) {
-        set_error("pcpp_mvmr_bwd_weight: workspace has %zu bytes, needs %zu", workspace_bytes, need);
-        return PCPP_ERR_WORKSPACE;
-    }
-    float *part = static_cast<float *>(workspace);
-    if (n_chunks > 0) {
-        // (16-byte row reads: the entry point has checked that x and dy are 16-byte aligned, and rows are 512 bytes)
-        if constexpr (BF16 && C_IN == 256 && C_OUT == 256) {
-            if (int rc = raise_lds_limit(reinterpret_cast<const void *>(&weight_lds_kernel), LDS_WEIGHT_BYTES)) return rc;
-            weight_lds_kernel<<<(unsigned)n_chunks, LDS_WAVES * 64, LDS_WEIGHT_BYTES, stream>>>(
-                static_cast<const uint16_t *>(a.feat), static_cast<const uint16_t *>(a.dense), part, tri_o, a.gather, seg,
-                a.K, a.n_triplets, chunk, n_chunks);
-        } else if constexpr (!BF16 && SUB_IN == C_IN && SUB_OUT == C_OUT)
-            weight_f32_kernel<C_IN, C_OUT><<<(unsigned)ceil_div(n_chunks, WAVES), WAVES * 64, 0, stream>>>(
-                static_cast<const float *>(a.feat), static_cast<const float *>(a.dense), part, tri_o, a.gather, seg, a.K,
-                a.n_triplets, chunk, n_chunks);
-        else if constexpr (BF16)
-            weight_wide_kernel<C_IN, C_OUT, SUB_IN, SUB_OUT><<<(unsigned)ceil_div(n_chunks * N_SUB, WAVES), WAVES * 64, 0, stream>>>(
-                a.feat, a.dense, part, tri_o, a.gather, seg, a.K, a.n_triplets, chunk, n_chunks);
-        else
-            weight_kernel<BF16, C_IN, C_OUT, SUB_IN, SUB_OUT><<<(unsigned)ceil_div(n_chunks * N_SUB, WAVES), WAVES * 64, 0, stream>>>(
-                a.feat, a.dense, part, tri_o, a.gather, seg, a.K, a.n_triplets, chunk, n_chunks);
-        PCPP_HIP_CHECK(hipGetLastError());
-    }
-    dim3 grid((unsigned)ceil_div(n_elem, 64), (unsigned)a.K);
-    weight_reduce<<<grid, REDUCE_WAVES * 64, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
+    weight_reduce<<<dim3((unsigned)ceil_div(n_elem, 64), (unsigned)K), REDUCE_WAVES * 64, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
     PCPP_HIP_CHECK(hipGetLastError());
     return PCPP_OK;
 }
 
-bool weight_shape_supported(int in_dtype, int c_in, int c_out)
+// (16-byte row reads: the entry point has checked that x and dy are 16-byte aligned, and rows are 512 bytes)
+int launch_weight_lds(const MvmrArgs &a, float *dw, const int32_t *tri_o, const int64_t *seg, float *part, hipStream_t stream)
 {
-    if (in_dtype == PCPP_F32) return (c_in == 32 && c_out == 32) || (c_in == 64 && c_out == 64);
-    return (c_in == 64 && c_out == 64) || (c_in == 64 && c_out == 128) || (c_in == 128 && c_out == 128) ||
-           (c_in == 256 && c_out == 256);
+    const int chunk = lds_chunk(a.n_triplets);
+    const int64_t n_chunks = ceil_div(a.n_triplets, chunk);
+    if (n_chunks > 0) {
+        if (int rc = raise_lds_limit(reinterpret_cast<const void *>(&weight_lds_kernel), LDS_WEIGHT_BYTES)) return rc;
+        weight_lds_kernel<<<(unsigned)n_chunks, LDS_WAVES * 64, LDS_WEIGHT_BYTES, stream>>>(
+            static_cast<const uint16_t *>(a.feat), static_cast<const uint16_t *>(a.dense), part, tri_o, a.gather, seg, a.K,
+            a.n_triplets, chunk, n_chunks);
+        PCPP_HIP_CHECK(hipGetLastError());
+    }
+    return launch_reduce(part, dw, seg, a.c_src * a.c_dst, a.K, chunk, n_chunks, stream);
+}
+
+// The sub-block of dW that a block of weight_any_kernel owns, as channels of each side, and the chunk of the list.
+// Enough blocks for four per CU, unless that would leave a wave fewer than two batches.
+struct AnyShape { int co, ci, n_sub_in, n_sub, chunk; int64_t n_chunks; };
+
+AnyShape any_shape(bool f32, int64_t n_triplets, int c_in, int c_out)
+{
+    AnyShape s;
+    auto channels = [&](int c) { return c <= 32 ? 32 : (c <= 64 || f32 ? 64 : 128); };
+    s.co = channels(c_out);
+    s.ci = channels(c_in);
+    if (s.co == 128 && s.ci == 128) s.ci = 64;             // 128 x 64 channels: 128 accumulator registers
+    s.n_sub_in = (int)ceil_div(c_in, s.ci);
+    s.n_sub = s.n_sub_in * (int)ceil_div(c_out, s.co);
+    int64_t want = 1024 / s.n_sub;
+    if (want < 8) want = 8;
+    int64_t chunk = ceil_div(n_triplets > 0 ? n_triplets : 1, want);
+    if (chunk < 2 * WINDOW * WAVES) chunk = 2 * WINDOW * WAVES;
+    s.chunk = (int)((chunk + WINDOW * WAVES - 1) / (WINDOW * WAVES) * (WINDOW * WAVES));
+    s.n_chunks = ceil_div(n_triplets, s.chunk);
+    return s;
+}
+
+bool any_usable(int64_t n_in, int64_t n_out, int64_t n_triplets, int c_in, int c_out, int in_dtype)
+{
+    const size_t es = in_dtype == PCPP_F32 ? 4 : 2;
+    return n_triplets > 0 && (size_t)n_triplets * 4 <= MAX_BUFFER_BYTES && (size_t)n_in * c_in * es <= MAX_BUFFER_BYTES &&
+           (size_t)n_out * c_out * es <= MAX_BUFFER_BYTES;
+}
+
+template <typename SO, typename SI>
+int launch_any(const WeightArgs &w, float *dw, hipStream_t stream)
+{
+    constexpr size_t staged = WAVES * (SO::BYTES + SI::BYTES), sums = WAVES * SI::NT * 64 * 4 * sizeof(float);
+    constexpr size_t lds = staged > sums ? staged : sums;
+    const int64_t blocks = ceil_div(w.n_chunks, 8) * 8 * w.n_sub;
+    weight_any_kernel<SO, SI><<<(unsigned)blocks, WAVES * 64, lds, stream>>>(w);
+    PCPP_HIP_CHECK(hipGetLastError());
+    return launch_reduce(w.part, dw, w.seg, w.c_in * w.c_out, w.K, w.chunk, w.n_chunks, stream);
+}
+
+template <typename SO>
+int launch_any_in(const WeightArgs &w, float *dw, int ci, hipStream_t stream)
+{
+    if constexpr (SO::PL > 1) {
+        if (w.c_in < 2) return launch_any<SO, Direct<2, true>>(w, dw, stream);
+        return ci == 32 ? launch_any<SO, Direct<2, false>>(w, dw, stream) : launch_any<SO, Direct<4, false>>(w, dw, stream);
+    } else {
+        if (w.c_in < 8) return launch_any<SO, Stage<4, true>>(w, dw, stream);
+        if (ci == 32) return launch_any<SO, Stage<4, false>>(w, dw, stream);
+        if constexpr (SO::CHK < 128)
+            if (ci == 128) return launch_any<SO, Stage<16, false>>(w, dw, stream);
+        return launch_any<SO, Stage<8, false>>(w, dw, stream);
+    }
+}
+
+int launch_weight_any(const MvmrArgs &a, float *dw, const int32_t *tri_o, const int64_t *seg, float *part, hipStream_t stream)
+{
+    const bool f32 = a.in_dtype == PCPP_F32;
+    const AnyShape s = any_shape(f32, a.n_triplets, a.c_src, a.c_dst);
+    const size_t es = f32 ? 4 : 2;
+    WeightArgs w{};
+    w.x = a.feat; w.dy = a.dense; w.part = part;
+    w.tri_o = tri_o; w.tri_i = a.gather; w.seg = seg;
+    w.n_triplets = a.n_triplets; w.n_chunks = s.n_chunks;
+    w.x_bytes = (uint32_t)((size_t)a.n_src * a.c_src * es); w.dy_bytes = (uint32_t)((size_t)a.n_centres * a.c_dst * es);
+    w.tri_bytes = (uint32_t)((size_t)a.n_triplets * 4);
+    w.K = a.K; w.c_in = a.c_src; w.c_out = a.c_dst; w.chunk = s.chunk; w.n_sub_in = s.n_sub_in; w.n_sub = s.n_sub;
+    if (f32) {
+        if (a.c_dst < 2) return launch_any_in<Direct<2, true>>(w, dw, s.ci, stream);
+        return s.co == 32 ? launch_any_in<Direct<2, false>>(w, dw, s.ci, stream) : launch_any_in<Direct<4, false>>(w, dw, s.ci, stream);
+    }
+    if (a.c_dst < 8) return launch_any_in<Stage<4, true>>(w, dw, s.ci, stream);
+    if (s.co == 32) return launch_any_in<Stage<4, false>>(w, dw, s.ci, stream);
+    return s.co == 64 ? launch_any_in<Stage<8, false>>(w, dw, s.ci, stream) : launch_any_in<Stage<16, false>>(w, dw, s.ci, stream);
 }
 
 }  // namespace
@@ -747,25 +629,25 @@ bool weight_shape_supported(int in_dtype, int c_in, int c_out)
 int mvmr_weight_mfma(const MvmrArgs &a, float *dw, const int32_t *tri_o, const int64_t *seg, void *workspace,
                      size_t workspace_bytes, hipStream_t stream, bool *handled)
 {
-    *handled = true;
-    if (a.in_dtype == PCPP_F32) {
-        if (a.c_src == 32 && a.c_dst == 32) return launch_weight<false, 32, 32>(a, dw, tri_o, seg, workspace, workspace_bytes, stream);
-        if (a.c_src == 64 && a.c_dst == 64) return launch_weight<false, 64, 64>(a, dw, tri_o, seg, workspace, workspace_bytes, stream);
-    } else {
-        if (a.c_src == 64 && a.c_dst == 64) return launch_weight<true, 64, 64>(a, dw, tri_o, seg, workspace, workspace_bytes, stream);
-        if (a.c_src == 64 && a.c_dst == 128) return launch_weight<true, 64, 128>(a, dw, tri_o, seg, workspace, workspace_bytes, stream);
-        if (a.c_src == 128 && a.c_dst == 128) return launch_weight<true, 128, 128, 64, 128>(a, dw, tri_o, seg, workspace, workspace_bytes, stream);
-        if (a.c_src == 256 && a.c_dst == 256) return launch_weight<true, 256, 256, 64, 128>(a, dw, tri_o, seg, workspace, workspace_bytes, stream);
+    const bool lds = lds_shape(a.in_dtype, a.c_src, a.c_dst);
+    *handled = lds || any_usable(a.n_src, a.n_centres, a.n_triplets, a.c_src, a.c_dst, a.in_dtype);
+    if (!*handled) return PCPP_OK;
+    const size_t need = mvmr_weight_mfma_workspace_bytes(a.n_triplets, a.c_src, a.c_dst, a.K, a.in_dtype);
+    if (workspace_bytes < need) {
+        set_error("pcpp_mvmr_bwd_weight: workspace has %zu bytes, needs %zu", workspace_bytes, need);
+        return PCPP_ERR_WORKSPACE;
     }
-    *handled = false;
-    return PCPP_OK;
+    float *part = static_cast<float *>(workspace);
+    // 256 -> 256: 31 + 22 us for 0.12 M triplets, 576 + 132 for 4.6 M, 4382 + 174 for 32 M (weight_any_kernel and its sums:
+    // 54 + 21, 700 + 19, 8278 + 81, since each row is read by four sub-blocks)
+    return lds ? launch_weight_lds(a, dw, tri_o, seg, part, stream) : launch_weight_any(a, dw, tri_o, seg, part, stream);
 }
 
 size_t mvmr_weight_mfma_workspace_bytes(int64_t n_triplets, int c_in, int c_out, int K, int in_dtype)
 {
-    if (!weight_shape_supported(in_dtype, c_in, c_out)) return 0;
-    const int chunk = weight_chunk(n_triplets, c_in, c_out, weight_chunks_per_block(in_dtype == PCPP_BF16, c_in, c_out));
-    return align_up((size_t)(ceil_div(n_triplets, chunk) + K) * c_in * c_out * sizeof(float));
+    const int64_t slots = lds_shape(in_dtype, c_in, c_out) ? ceil_div(n_triplets, lds_chunk(n_triplets))
+                                                           : any_shape(in_dtype == PCPP_F32, n_triplets, c_in, c_out).n_chunks;
+    return align_up((size_t)(slots + K) * c_in * c_out * sizeof(float));
 }
 
 }  // namespace pcpp
