@@ -100,6 +100,13 @@ def _check(rc: int):
         raise PcppError(rc, library().pcpp_last_error().decode())
 
 
+def _capacity_error(capacity: int, needed: int) -> PcppError:
+    # (made here: an exception held by the frame that raises it would keep that frame's tensors until a collection)
+    err = PcppError(ERR_CAPACITY, f"capacity {capacity} too small, need {needed}")
+    err.needed = needed
+    return err
+
+
 def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else None
 
@@ -173,7 +180,9 @@ def pcpp_build_triplets(in_xyz: torch.Tensor, out_xyz: torch.Tensor, radius: flo
         except PcppError as e:
             if e.code != ERR_CAPACITY:
                 raise
-            return pcpp_build_triplets(in_xyz, out_xyz, radius, t, plan_flags, e.needed, buffers, in_offsets, out_offsets)
+            needed = e.needed
+        # outside the handler: the first attempt's buffers are free again
+        return pcpp_build_triplets(in_xyz, out_xyz, radius, t, plan_flags, needed, buffers, in_offsets, out_offsets)
     L = library()
     assert in_xyz.is_cuda and out_xyz.is_cuda and in_xyz.dtype == torch.float32 and out_xyz.dtype == torch.float32
     assert in_xyz.is_contiguous() and out_xyz.is_contiguous()
@@ -219,9 +228,7 @@ def pcpp_build_triplets(in_xyz: torch.Tensor, out_xyz: torch.Tensor, radius: flo
                                        _ptr(ws), ws.numel(), _stream())
     nt = int(n[0])
     if rc == ERR_CAPACITY:
-        err = PcppError(rc, f"capacity {cap} too small, need {nt}")
-        err.needed = nt
-        raise err
+        raise _capacity_error(cap, nt)
     _check(rc)
     return Triplets(tri_o[:nt], tri_i[:nt], tri_k[:nt], seg[:K + 1], nt, n_in, n_out, t, plan, plan_flags & PLAN_MASK)
 

@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -16,3 +17,11 @@ def pytest_configure(config):
 @pytest.fixture(scope="session")
 def golden_dir():
     return os.path.join(ROOT, "tests", "golden")
+
+
+@pytest.fixture(autouse=True)
+def _no_garbage_of_earlier_tests():
+    """Tensors held by reference cycles of earlier tests (tracebacks of expected errors) go now and not in the middle
+    of a test that compares how much memory is allocated."""
+    gc.collect()
+    yield
