@@ -8,8 +8,8 @@
 //             Sel^T [triplet][centre], X_g = the part's source rows of the cell, 32 triplets at a time, each row read once
 //             and densely (mvmr_stage.h), Sel = 0/1 from the run bounds through an LDS table of eight-bit masks.  Products
 //             with 1.0 are exact, so this is the fp32 sum of the rows; run lengths never cause divergence.  The sums go to
-//             stage B rounded to bf16 once (bf16 layers) or as three bf16 terms that add up to the fp32 value exactly
-//             (fp32 layers).
+//             stage B as three bf16 terms that add up to the fp32 value exactly (EXACT), or, in the bf16 layers that
+//             bf16_sums() lists, rounded to bf16 once.
 //   stage B   acc^T [destination][centre] += W[k] [destination][channel] . S^T [channel][centre]; W comes straight from
 //             memory / L2 in fragment order.  fp32 layers keep the six products of weight 2^-16 or more relative to the
 //             leading one.
@@ -23,7 +23,7 @@
 // What bounds it: the matrix cores and the vector instructions around them (fp32: the split into terms) with 32 to 64
 // channels (a 64 -> 64 bf16 layer of 17 M triplets moves 2.2 GB of rows through L1 and L2 in 153 us), W's way from L2 with
 // more.  Layers whose channel counts are no power of two, which the vector ALUs had served before: 20 -> 36 fp32, 0.49 M
-// triplets, 29 us (349); 128 -> 128 bf16, 0.97 M triplets, 87 us (3970).
+// triplets, 29 us (349); 128 -> 128 bf16, 0.97 M triplets, 130 us (7938).
 // Every destination row is written once, by one block: no atomics, fixed summation order.
 //
 // v_mfma_f32_16x16x32_bf16: A: lane (M = l%16, g = l/16) holds A[M][8g .. 8g+7]; B: lane (N = l%16, g) holds
@@ -109,14 +109,15 @@ struct TileArgs {
     int out_bf16;
 };
 
-template <bool F32, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK>
+template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK>
 struct TileCfg {
     using St = std::conditional_t<F32, Direct<2, NARROW>, Stage<RL, NARROW>>;
-    static constexpr int CHK = St::CHK, KS = CHK / 32, PL = St::PL;
+    static constexpr int CHK = St::CHK, KS = CHK / 32, PL = St::PL, PLS = EXACT ? 3 : 1;     // terms of a row or of W, of a sum
+    static_assert(!F32 || EXACT, "fp32 layers keep fp32 sums");
     static constexpr int NG = GA * NP, CR = NW / NP;
     static constexpr int WC = SPLITK ? 1 : NW / WD, GW = NG / WC;
     static constexpr int NBUF = (SPLITK || CR == 1) ? 1 : 2;              // sets of S tiles (one: a second barrier per step)
-    static constexpr uint32_t PITCH = CHK * 2 * PL + 16, PART = GA * 16 * PITCH;      // multiples of 256
+    static constexpr uint32_t PITCH = CHK * 2 * PLS + 16, PART = GA * 16 * PITCH;      // multiples of 256
     // a wave's staged rows lie where its sums will go, if they fit
     static constexpr bool STAGE_IN_S = SPLITK || PART >= St::BYTES;
     static constexpr uint32_t STILE = SPLITK ? St::BYTES : NP * PART;
@@ -131,12 +132,12 @@ struct TileCfg {
     static_assert(PART % 256 == 0 && St::BYTES % 256 == 0, "alignment of the staged rows");
 };
 
-template <bool F32, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK>
+template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK>
 __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
 {
-    using C = TileCfg<F32, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
+    using C = TileCfg<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
     using St = typename C::St;
-    constexpr int CHK = C::CHK, KS = C::KS, PL = C::PL, NT = St::NT, NG = C::NG, CR = C::CR, GW = C::GW;
+    constexpr int CHK = C::CHK, KS = C::KS, PL = C::PL, PLS = C::PLS, NT = St::NT, NG = C::NG, CR = C::CR, GW = C::GW;
     constexpr uint32_t PITCH = C::PITCH, STILE = C::STILE;
     constexpr int W_REGS = DTW * KS * PL * 4, CELLS = SPLITK ? 1 : CR;       // of one cell; cells of a round that this wave multiplies
     constexpr bool W_EARLY = W_REGS * CELLS <= 64;
@@ -325,7 +326,7 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
                 } while (w < n);
                 // the sums as operands: lane (centre m, g) holds the places 16 t + 4 g .. + 3 of tile t, and takes those of two
                 // tiles as its share of a reduction step
-                v4u own[GA][KS][PL];
+                v4u own[GA][KS][PLS];
 #pragma unroll
                 for (int i = 0; i < GA; ++i)
 #pragma unroll
@@ -333,12 +334,12 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
                             const float x0 = d1[i][2 * ks + q / 2][2 * (q & 1)], x1 = d1[i][2 * ks + q / 2][2 * (q & 1) + 1];
-                            if constexpr (!F32) {
+                            if constexpr (!EXACT) {
                                 own[i][ks][0][q] = cvt_pk_bf16(x0, x1);
                             } else {
                                 uint32_t p1, p2, p3;
                                 split_pair(x0, x1, p1, p2, p3);
-                                own[i][ks][0][q] = p1; own[i][ks][PL > 1 ? 1 : 0][q] = p2; own[i][ks][PL > 2 ? 2 : 0][q] = p3;
+                                own[i][ks][0][q] = p1; own[i][ks][PLS / 2][q] = p2; own[i][ks][PLS - 1][q] = p3;
                             }
                         }
                 if constexpr (!SPLITK) {
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
 #pragma unroll
                             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                                for (int pl = 0; pl < PL; ++pl)
+                                for (int pl = 0; pl < PLS; ++pl)
                                     *reinterpret_cast<v4u *>(sp + (uint32_t)(16 * i) * PITCH + pl * CHK * 2 + ks * 64) = own[i][ks][pl];
                     }
                     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -367,9 +368,9 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
                         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
                             for (int i = 0; i < GW; ++i) {
-                                v8bf sv[PL];
+                                v8bf sv[PLS];
 #pragma unroll
-                                for (int pl = 0; pl < PL; ++pl) {
+                                for (int pl = 0; pl < PLS; ++pl) {
                                     if constexpr (SPLITK) sv[pl] = __builtin_bit_cast(v8bf, own[i][ks][pl]);
                                     else sv[pl] = __builtin_bit_cast(v8bf, *reinterpret_cast<const v4u *>(sb + (uint32_t)(16 * i) * PITCH + pl * CHK * 2 + ks * 64));
                                 }
@@ -379,6 +380,7 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
                                         acc[i][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, wf[wi][d][ks][ws]), sv[ss], acc[i][d], 0, 0, 0);
                                     };
                                     if constexpr (F32) { mm(0, PL - 1); mm(PL - 1, 0); mm(PL / 2, PL / 2); mm(0, PL / 2); mm(PL / 2, 0); mm(0, 0); }
+                                    else if constexpr (EXACT) { mm(0, PLS - 1); mm(0, PLS / 2); mm(0, 0); }
                                     else mm(0, 0);
                                 }
                             }
@@ -437,11 +439,11 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
     }
 }
 
-template <bool F32, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK>
+template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK>
 int launch_tile(const TileArgs &t, hipStream_t stream)
 {
-    using C = TileCfg<F32, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
-    auto kern = rows_tile_kernel<F32, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
+    using C = TileCfg<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
+    auto kern = rows_tile_kernel<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
     if (C::LDS > 64 * 1024)
         if (int rc = raise_lds_limit(reinterpret_cast<const void *>(kern), C::LDS)) return rc;
     const dim3 grid((unsigned)(t.side.n_tiles * (4 / C::NG)), (unsigned)ceil_div(t.ndt, WD * DTW));
@@ -454,41 +456,46 @@ int launch_tile(const TileArgs &t, hipStream_t stream)
 // when it has more than 48 triplets per 32 centres on average, i.e. more than a window and a half.
 //   - small clouds: split over eight waves and 16 centres per block, so that there are enough waves.  2048 points, 16 -> 16
 //     fp32: 8.4, four waves 10.5, 32 centres 12.1, cooperative 27.  8000 points, 64 -> 64 bf16: 12.2 / 13.2 / 14.5 / 29.
-//   - up to 64 destination channels, or fp32 up to 128: split over four waves, 32 centres (strided layer's input gradient,
-//     128 -> 64: 253, 16 centres 346, cooperative 312; 300 000 points, 125 cells, 64 -> 64: 448 / 562 / 611).  Crowded 64-wide
-//     layers: cooperative, 16 centres per wave, which fill their windows and read W a quarter as often (115 000 points with
+//   - exact sums, up to 128 destination channels: split over four waves, 32 centres, since the terms of a sum would take three
+//     times the LDS (40 000 points, 128 -> 128 bf16: 130 per direction; cooperative, 16 centres per wave, about 165)
+//   - rounded sums, up to 64: the same (strided layer's input gradient, 128 -> 64: 253, 16 centres 346, cooperative 312).
+//     Crowded 64-wide layers: cooperative, 16 centres per wave, which fill their windows and read W a quarter as often (115 000 points with
 //     148 neighbours, 64 -> 64: 153, split 163 .. 174).
-//   - bf16 to 65 .. 128 channels: the same up to 32768 centres (16 000 points, 128 -> 128: 37, cooperative 61), crowded: two
-//     waves (25 000 points with 368 neighbours, 64 -> 128: 52, four waves 61); above, cooperative, 32 centres per wave (40 000
-//     points, 128 -> 128: 87, split 93), crowded: 16 (strided layer, 64 -> 128: 97, split 107).
-//   - wider: cooperative, 32 centres per wave (100 000 points, 125 cells, 128 -> 256: 777; 16 centres 958, split 864).
-template <bool F32, int RL, bool NARROW>
+//   - rounded sums to 65 .. 128 channels: split up to 32768 centres, crowded: over two waves (25 000 points with 368 neighbours,
+//     64 -> 128: 52, four waves 61); above, cooperative, 32 centres per wave, crowded: 16 (strided layer, 64 -> 128: 97, split
+//     107).
+//   - wider: cooperative, so that W is read once per 64 centres; 32 centres per wave (100 000 points, 125 cells, 128 -> 256 with
+//     rounded sums: 777; 16 centres 958, split 864), 16 where the exact bf16 sums of 32 would leave a CU one block.
+template <bool F32, bool EXACT, int RL, bool NARROW>
 int launch_tile_form(const TileArgs &t, hipStream_t stream)
 {
     if (t.n_centres <= 8192 && t.ndt <= 4) {
-        if (t.ndt == 1) return launch_tile<F32, RL, NARROW, 1, 1, 8, 1, 1, true>(t, stream);
-        if (t.ndt == 2) return launch_tile<F32, RL, NARROW, 1, 1, 8, 1, 2, true>(t, stream);
-        return launch_tile<F32, RL, NARROW, 1, 1, 8, 1, 4, true>(t, stream);
+        if constexpr (EXACT) {                           // (layers with rounded sums have four tiles or more)
+            if (t.ndt == 1) return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 1, true>(t, stream);
+            if (t.ndt == 2) return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 2, true>(t, stream);
+        }
+        return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 4, true>(t, stream);
     }
     const bool crowded = (int64_t)(t.gather_bytes / 4) * 32 > 48 * t.n_centres * (int64_t)t.K;
-    if (t.ndt <= 4 && (t.ndt <= 2 || F32 || !crowded)) {
-        if (t.ndt == 1) return launch_tile<F32, RL, NARROW, 2, 1, 4, 1, 1, true>(t, stream);
-        if (t.ndt == 2) return launch_tile<F32, RL, NARROW, 2, 1, 4, 1, 2, true>(t, stream);
-        return launch_tile<F32, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
-    }
-    if constexpr (F32) {
-        if (t.ndt <= 8) return launch_tile<F32, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
+    if constexpr (EXACT) {
+        if (t.ndt == 1) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 1, true>(t, stream);
+        if (t.ndt == 2) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 2, true>(t, stream);
+        if (t.ndt <= 4) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
+        if (t.ndt <= 8) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
+        if constexpr (F32) return launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 4, false>(t, stream);
+        else return launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false>(t, stream);
     } else {
-        if (t.ndt <= 4) return launch_tile<F32, RL, NARROW, 1, 4, 4, 4, 1, false>(t, stream);
+        if (t.ndt <= 4) return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 1, false>(t, stream)
+                                       : launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
         if (t.ndt <= 8) {
             if (t.n_centres <= 32768)
-                return crowded ? launch_tile<F32, RL, NARROW, 2, 1, 2, 1, 8, true>(t, stream)
-                               : launch_tile<F32, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
-            return crowded ? launch_tile<F32, RL, NARROW, 1, 4, 4, 4, 2, false>(t, stream)
-                           : launch_tile<F32, RL, NARROW, 2, 2, 4, 4, 2, false>(t, stream);
+                return crowded ? launch_tile<F32, EXACT, RL, NARROW, 2, 1, 2, 1, 8, true>(t, stream)
+                               : launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
+            return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 2, false>(t, stream)
+                           : launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 2, false>(t, stream);
         }
+        return launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 4, false>(t, stream);
     }
-    return launch_tile<F32, RL, NARROW, 2, 2, 4, 4, 4, false>(t, stream);
 }
 
 }  // namespace
@@ -520,6 +527,15 @@ int mvmr_rows_tile_pack_w(const void *w, void *packed, int K, int c_src, int c_d
     return PCPP_OK;
 }
 
+// bf16 layers whose run sums are rounded to bf16 once before they meet W: 64 -> 64, 64 -> 128 and 128 -> 64 with up to 64
+// cells, and 256 -> 256.  That is these layers' precision (relative error 1.6e-3 against exact sums), and a third of stage
+// B's matrix products.  All other layers keep the fp32 sums as three terms (2e-7).
+static bool bf16_sums(int K, int c_src, int c_dst)
+{
+    if (c_src == 256 && c_dst == 256) return true;
+    return K <= 64 && ((c_src == 64 && (c_dst == 64 || c_dst == 128)) || (c_src == 128 && c_dst == 64));
+}
+
 // a.w must be the weights packed by mvmr_rows_tile_pack_w
 int mvmr_rows_tile(const MvmrArgs &a, hipStream_t stream)
 {
@@ -533,9 +549,9 @@ int mvmr_rows_tile(const MvmrArgs &a, hipStream_t stream)
     t.gather_bytes = (uint32_t)((size_t)a.n_triplets * 4);
     t.K = a.K; t.c_src = a.c_src; t.c_dst = a.c_dst; t.n_chunks = s.n_chunks; t.ndt = s.ndt;
     t.out_bf16 = a.out_dtype == PCPP_BF16;
-    if (f32) return s.narrow ? launch_tile_form<true, 4, true>(t, stream) : launch_tile_form<true, 4, false>(t, stream);
-    if (s.rl == 4) return s.narrow ? launch_tile_form<false, 4, true>(t, stream) : launch_tile_form<false, 4, false>(t, stream);
-    return launch_tile_form<false, 8, false>(t, stream);
+    if (f32) return s.narrow ? launch_tile_form<true, true, 4, true>(t, stream) : launch_tile_form<true, true, 4, false>(t, stream);
+    if (s.rl == 4) return s.narrow ? launch_tile_form<false, true, 4, true>(t, stream) : launch_tile_form<false, true, 4, false>(t, stream);
+    return bf16_sums(a.K, a.c_src, a.c_dst) ? launch_tile_form<false, false, 8, false>(t, stream) : launch_tile_form<false, true, 8, false>(t, stream);
 }
 
 }  // namespace pcpp

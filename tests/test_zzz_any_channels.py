@@ -59,10 +59,13 @@ def test_any_channels(pcpp, n_in, n_out, r, t, shapes, dt, spatial):
         if dt == "bf16":
             x, w, dy, tdt = scenes.round_to_bf16(x), scenes.round_to_bf16(w), scenes.round_to_bf16(dy), torch.bfloat16
         what = f"{n_in}->{n_out} t={t} {c_in}->{c_out} {dt}"
+        # run sums are rounded to bf16 in the layers of 64 and 128 channels with up to 64 cells only; elsewhere they keep
+        # fp32 precision, and products with bf16 weights are exact
+        tol = TOL["bf16" if dt == "bf16" and K <= 64 and (c_in, c_out) in ((64, 64), (64, 128), (128, 64)) else "f32"]
         out = pcpp.pcpp_mvmr_fwd(dev(x, tdt), dev(w, tdt), T)
-        assert_close(out.cpu().numpy(), *oracle_fwd(x, w, o, i, k, n_out), TOL[dt], what + " fwd")
+        assert_close(out.cpu().numpy(), *oracle_fwd(x, w, o, i, k, n_out), tol, what + " fwd")
         gx = pcpp.pcpp_mvmr_bwd_input(dev(dy, tdt), dev(w, tdt), T)
-        assert_close(gx.cpu().numpy(), *oracle_bwd_input(dy, w, o, i, k, n_in), TOL[dt], what + " bwd_input")
+        assert_close(gx.cpu().numpy(), *oracle_bwd_input(dy, w, o, i, k, n_in), tol, what + " bwd_input")
         gw = pcpp.pcpp_mvmr_bwd_weight(dev(x, tdt), dev(dy, tdt), T)
         # bf16 products are exact in fp32 and fp32 layers keep all product terms above 2^-24, so the weight gradient
         # meets the fp32 tolerance whatever the storage type
