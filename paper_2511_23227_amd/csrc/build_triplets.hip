@@ -20,6 +20,10 @@ constexpr double CELL_CLAMP = (double)((1 << 20) - 2);   // +-1 stencil steps st
 constexpr int SEARCH_THREADS = 1024;                      // 16 waves share a tile of 64 centres: 4 centres each
 constexpr int SEARCH_WAVES = SEARCH_THREADS / 64;
 constexpr int LIST_CAP_MAX = 512;                         // neighbours of one centre kept in LDS (per wave)
+// Pitch of the [K][TILE] tables in LDS.  A wave works on one centre, so its lanes touch the words of one column, at most a
+// few of them in the same cell: with rows of 64 words they all lie in one bank.  The word behind a row holds the end of the
+// row's last run where the table holds starts of runs.
+constexpr int PITCH = TILE + 1;
 
 __device__ inline uint32_t hash_key(unsigned long long k)
 {
@@ -165,13 +169,16 @@ struct QueryParams {
     int n_batches;
 };
 
-__device__ inline uint32_t wave_incl_scan_u32(uint32_t v, int lane)
+__device__ inline uint32_t wave_incl_scan_u32(uint32_t v)
 {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t u = __shfl_up(v, d, 64);
-        if (lane >= d) v += u;
-    }
+    // DPP moves inside the adds (all 64 lanes must be active): shifts inside rows of 16 lanes, then the rows' last lanes to
+    // the rows behind them; no trip through LDS
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
     return v;
 }
 
@@ -223,9 +230,9 @@ struct Candidates {
                 slot = (slot + 1) & g.mask;
             }
         }
-        const uint32_t incl = wave_incl_scan_u32(cnt, lane);
+        const uint32_t incl = wave_incl_scan_u32(cnt);
         my_excl = incl - cnt;
-        total = __shfl(incl, 63, 64);
+        total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     }
 
     // Candidate number idx (idx may differ per lane).  Returns whether it is a neighbour;
@@ -345,14 +352,15 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_count(const float *__
                                                               CountOut side, CountOut mirror, uint32_t hit_stride,
                                                               const uint32_t *__restrict__ err, Reuse reuse)
 {
-    extern __shared__ uint32_t tbl[];          // [K][TILE], with BOTH followed by the mirror side's [K][TILE]
-    __shared__ uint32_t stage[(BOTH ? 2 : 1) * SEARCH_WAVES * KEEP_MAX];   // hit lists on their way to memory
+    // [K][PITCH], with BOTH followed by the mirror side's; then, when lists are kept, every wave's list (or two) on its way to
+    // memory: hit_stride words each, so that two blocks share a CU where the longest lists would leave room for one
+    extern __shared__ uint32_t tbl[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t tile = blockIdx.x;
-    uint32_t *tbl2 = tbl + K * TILE;
-    uint32_t *mine = stage + wave * KEEP_MAX, *mine2 = stage + (SEARCH_WAVES + wave) * KEEP_MAX;
+    uint32_t *tbl2 = tbl + K * PITCH, *stage = tbl + (BOTH ? 2 : 1) * K * PITCH;
+    uint32_t *mine = stage + wave * hit_stride, *mine2 = stage + (SEARCH_WAVES + wave) * hit_stride;
     if (*err) return;                              // block-uniform: the grid's offsets are not to be trusted
-    for (int idx = threadIdx.x; idx < (BOTH ? 2 : 1) * K * TILE; idx += SEARCH_THREADS) tbl[idx] = 0u;
+    for (int idx = threadIdx.x; idx < (BOTH ? 2 : 1) * K * PITCH; idx += SEARCH_THREADS) tbl[idx] = 0u;
     __syncthreads();
     const bool keep = side.hits != nullptr;
     // With lists to reuse, a centre costs two memory round trips (its list, the coordinates of the listed points) once
@@ -382,8 +390,8 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_count(const float *__
         // what is done for every neighbour: its cell's counter(s), and its place in the list that is kept
         auto account = [&](bool hit, int b, int k, int k2) {
             if (hit) {
-                atomicAdd(&tbl[k * TILE + al], 1u);
-                if constexpr (BOTH) atomicAdd(&tbl2[k2 * TILE + al], 1u);
+                atomicAdd(&tbl[k * PITCH + al], 1u);
+                if constexpr (BOTH) atomicAdd(&tbl2[k2 * PITCH + al], 1u);
             }
             if (keep) {                            // the centre's first hit_stride neighbours, in arrival order
                 const unsigned long long m = __ballot(hit);
@@ -452,10 +460,10 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_count(const float *__
         const uint32_t *t = sd == 0 ? tbl : tbl2;
         if (o.tile_cnt) {
             uint32_t *dst = o.tile_cnt + (size_t)tile * K * TILE;
-            for (int idx = threadIdx.x; idx < K * TILE; idx += SEARCH_THREADS) dst[idx] = t[idx];
+            for (int idx = threadIdx.x; idx < K * TILE; idx += SEARCH_THREADS) dst[idx] = t[idx / TILE * PITCH + idx % TILE];
         }
         for (int k = wave; k < K; k += SEARCH_WAVES) {
-            uint32_t v = t[k * TILE + lane];
+            uint32_t v = t[k * PITCH + lane];
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
             if (lane == 0) o.tile_k_cnt[(size_t)k * n_tiles + tile] = v;
@@ -488,7 +496,7 @@ struct FillOut {
 
 struct Emit {
     int32_t *out_c, *out_b, *out_k;
-    const uint32_t *cnt_tile;
+    const uint32_t *starts;      // the tile's table of run starts
     uint32_t cap;
     bool flag_last;
     __device__ inline void operator()(uint32_t run0, uint32_t rank, int al, int k, int32_t centre, uint32_t b) const
@@ -496,7 +504,7 @@ struct Emit {
         const uint32_t pos = run0 + rank;
         if (pos >= cap) return;
         if (out_c) out_c[pos] = centre;
-        if (out_b) out_b[pos] = (int32_t)((flag_last && rank + 1u == cnt_tile[k * TILE + al]) ? (b | GATHER_LAST) : b);
+        if (out_b) out_b[pos] = (int32_t)((flag_last && pos + 1u == starts[k * PITCH + al + 1]) ? (b | GATHER_LAST) : b);
         if (out_k) out_k[pos] = k;
     }
 };
@@ -513,15 +521,17 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
                                                              int64_t *__restrict__ seg_out,
                                                              int pack_ok, const uint32_t *__restrict__ err)
 {
-    extern __shared__ uint32_t tbl[];          // [K][TILE]: start of each (k, centre) run, then [SEARCH_WAVES][K] bucket words
+    // [K][PITCH]: start of each (k, centre) run, and behind a row the end of its last run; then [SEARCH_WAVES][K] bucket words
+    extern __shared__ uint32_t tbl[];
     __shared__ uint32_t list_all[SEARCH_WAVES][LIST_CAP_MAX];
+    __shared__ uint32_t centre_n[TILE];        // neighbours of each centre
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t tile = blockIdx.x;
     if (*err) return;                          // block-uniform: a prefix sum of this build gave up
     const uint32_t total = tile_ptr[(size_t)K * n_tiles];
     Emit emit;
     emit.out_c = fo.out_c; emit.out_b = fo.out_b; emit.out_k = fo.out_k;
-    emit.cnt_tile = tile_cnt + (size_t)tile * K * TILE;
+    emit.starts = tbl;
     emit.cap = total <= fo.out_cap ? fo.out_cap : 0u;
     emit.flag_last = false;
     if (fo.tail_index >= 0) {
@@ -532,17 +542,24 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
     if (seg_out && tile == 0)
         for (int k = threadIdx.x; k <= K; k += SEARCH_THREADS) seg_out[k] = (int64_t)tile_ptr[(size_t)k * n_tiles];
     const uint32_t *cnt_tile = tile_cnt + (size_t)tile * K * TILE;
-    for (int idx = threadIdx.x; idx < K * TILE; idx += SEARCH_THREADS) tbl[idx] = cnt_tile[idx];
+    for (int idx = threadIdx.x; idx < K * TILE; idx += SEARCH_THREADS) tbl[idx / TILE * PITCH + idx % TILE] = cnt_tile[idx];
+    if (threadIdx.x < TILE) centre_n[threadIdx.x] = 0u;
     __syncthreads();
+    uint32_t lane_n = 0;
     for (int k = wave; k < K; k += SEARCH_WAVES) {
-        const uint32_t v = tbl[k * TILE + lane];
-        const uint32_t inc = wave_incl_scan_u32(v, lane);
-        tbl[k * TILE + lane] = tile_ptr[(size_t)k * n_tiles + tile] + inc - v;
+        const uint32_t v = tbl[k * PITCH + lane];
+        const uint32_t end = tile_ptr[(size_t)k * n_tiles + tile] + wave_incl_scan_u32(v);
+        tbl[k * PITCH + lane] = end - v;
+        if (lane == TILE - 1) tbl[k * PITCH + TILE] = end;
+        lane_n += v;
     }
+    atomicAdd(&centre_n[lane], lane_n);
     __syncthreads();
+    // triplets of (cell k, centre al)
+    auto count_of = [&](int k, int al) -> uint32_t { return tbl[k * PITCH + al + 1] - tbl[k * PITCH + al]; };
     if (run_start_out) {
         uint32_t *dst = run_start_out + (size_t)tile * K * TILE;
-        for (int idx = threadIdx.x; idx < K * TILE; idx += SEARCH_THREADS) dst[idx] = tbl[idx];
+        for (int idx = threadIdx.x; idx < K * TILE; idx += SEARCH_THREADS) dst[idx] = tbl[idx / TILE * PITCH + idx % TILE];
     }
     uint32_t *list = list_all[wave];
     const unsigned long long lane_lt = (1ull << lane) - 1ull;
@@ -554,13 +571,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
 #pragma unroll
     for (int u = 0; u < PER_WAVE; ++u) {
         const int al = wave + u * SEARCH_WAVES;
-        const int64_t a = tile * TILE + al;
-        uint32_t nn = 0;
-        if (a < n_centres)
-            for (int k = lane; k < K; k += 64) nn += cnt_tile[k * TILE + al];
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) nn += __shfl_xor(nn, d, 64);
-        n_of[u] = nn;
+        n_of[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tile * TILE + al < n_centres ? centre_n[al] : 0u));
     }
     // Two centres at a time, one per half wave, while both of their kept lists fit 32 lanes (most do: the all-pairs
     // ranking then costs one pass for the two).  Centres done here are marked by a zero count.
@@ -589,7 +600,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
             }
             if (l < (int)n) {
                 const int k = (int)(key >> HIT_INDEX_BITS);
-                emit(tbl[k * TILE + al], rank, al, k, (int32_t)(perm ? (int64_t)perm[a] : a), rel);
+                emit(tbl[k * PITCH + al], rank, al, k, (int32_t)(perm ? (int64_t)perm[a] : a), rel);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -610,12 +621,12 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
             // bucket is whatever the adds made it), and each key's rank among the smaller keys of its own bucket
             // is its final slot: a key is compared with its cell's neighbours only.
             const uint32_t n = n_of[u];
-            uint32_t *wk = tbl + K * TILE + wave * K;
+            uint32_t *wk = tbl + K * PITCH + wave * K;
             uint32_t run = 0;
             for (int k0 = 0; k0 < K; k0 += 64) {
                 const int k = k0 + lane;
-                const uint32_t c1 = k < K ? cnt_tile[k * TILE + al] : 0u;
-                const uint32_t inc = wave_incl_scan_u32(c1, lane);
+                const uint32_t c1 = k < K ? count_of(k, al) : 0u;
+                const uint32_t inc = wave_incl_scan_u32(c1);
                 if (k < K) wk[k] = (run + inc - c1) << 16;
                 run += (uint32_t)__shfl((int)inc, 63, 64);
             }
@@ -653,7 +664,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
                     const uint32_t v = j < nk ? list[b0 + j] : 0xffffffffu;
                     rank += v < key ? 1u : 0u;
                 }
-                if (have) emit(tbl[k * TILE + al], rank, al, k, ac, key & HIT_INDEX_MASK);
+                if (have) emit(tbl[k * PITCH + al], rank, al, k, ac, key & HIT_INDEX_MASK);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -679,7 +690,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
                 }
                 for (; e2 < n; ++e2) rank += (list[e2] - kbase) < rel ? 1u : 0u;
                 const int k = (int)(key >> HIT_INDEX_BITS);
-                emit(tbl[k * TILE + al], rank, al, k, ac, rel);
+                emit(tbl[k * PITCH + al], rank, al, k, ac, rel);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
@@ -693,8 +704,8 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
             bcnt[gi] = 0; bbase[gi] = n; bcur[gi] = 0;
             if (gi * 64 < K) {                 // wave-uniform
                 const int k = gi * 64 + lane;
-                bcnt[gi] = k < K ? cnt_tile[k * TILE + al] : 0u;
-                const uint32_t inc = wave_incl_scan_u32(bcnt[gi], lane);
+                bcnt[gi] = k < K ? count_of(k, al) : 0u;
+                const uint32_t inc = wave_incl_scan_u32(bcnt[gi]);
                 bbase[gi] = n + inc - bcnt[gi];
                 n += __shfl(inc, 63, 64);
             }
@@ -729,7 +740,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
                 }
                 for (; e2 < n; ++e2) rank += ((keys[e2] - kbase) < rel) ? 1u : 0u;
                 const int k = (int)(key >> 32);
-                emit(tbl[k * TILE + al], rank, al, k, ac, (uint32_t)key);
+                emit(tbl[k * PITCH + al], rank, al, k, ac, (uint32_t)key);
             }
         } else if (n <= (uint32_t)list_cap) {
             for (uint32_t base = 0; base < c.total; base += 64) {
@@ -762,7 +773,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
                     occ &= occ - 1;
                     const int k = gi * 64 + kl;
                     const uint32_t nk = __shfl(bcnt[gi], kl, 64), b0 = __shfl(bbase[gi], kl, 64);
-                    const uint32_t run0 = tbl[k * TILE + al];
+                    const uint32_t run0 = tbl[k * PITCH + al];
                     for (uint32_t e0 = 0; e0 < nk; e0 += 64) {
                         const uint32_t e = e0 + lane;
                         const uint32_t mine = e < nk ? list[b0 + e] : 0xffffffffu;
@@ -790,7 +801,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
                     const bool hit2 = c.fetch(idx2, g, q, b2, k2);
                     rank += (hit2 && k2 == k && b2 < b) ? 1u : 0u;
                 }
-                if (hit) emit(tbl[k * TILE + al], rank, al, k, ac, (uint32_t)b);
+                if (hit) emit(tbl[k * PITCH + al], rank, al, k, ac, (uint32_t)b);
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1205,16 +1216,19 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         return rc;
 
     const int64_t nt_o = ceil_div(n_out, TILE), nt_i = ceil_div(n_in, TILE);
-    const size_t lds = (size_t)K * TILE * sizeof(uint32_t);
+    const size_t lds = (size_t)K * PITCH * sizeof(uint32_t);
+    // the first pass stages the lists that it keeps
+    const size_t lds_f = lds + (keep_hits ? (size_t)SEARCH_WAVES * bs.fwd_stride * sizeof(uint32_t) : 0);
+    const size_t lds_b = lds + (keep_hits ? (size_t)SEARCH_WAVES * bs.bwd_stride * sizeof(uint32_t) : 0);
     // the second pass also keeps one bucket word per (wave, cell); a key packs cell and candidate index into 32 bits
     const size_t lds_fill = lds + (size_t)SEARCH_WAVES * K * sizeof(uint32_t);
     const int pack_ok = !wide_keys && K <= 256 && n_in < (1 << HIT_INDEX_BITS) && n_out < (1 << HIT_INDEX_BITS);
-    if (lds > (size_t)32 * 1024) {
+    if (lds_f > (size_t)32 * 1024 || lds_b > (size_t)32 * 1024) {
         // large t: the per-tile table plus the neighbour lists exceed the default dynamic LDS limit
         if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&query_count<false, false, true>)
-                                      : reinterpret_cast<const void *>(&query_count<false, false, false>), lds)) != PCPP_OK) return rc;
+                                      : reinterpret_cast<const void *>(&query_count<false, false, false>), lds_f)) != PCPP_OK) return rc;
         if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&query_count<true, false, true>)
-                                      : reinterpret_cast<const void *>(&query_count<true, false, false>), lds)) != PCPP_OK) return rc;
+                                      : reinterpret_cast<const void *>(&query_count<true, false, false>), lds_b)) != PCPP_OK) return rc;
     }
     if (lds_fill > (size_t)32 * 1024) {
         if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&query_fill<false, true>)
@@ -1230,13 +1244,13 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     // A cloud queried against itself: one pass counts both sides of the plan (while two [K][64] tables fit the
     // LDS that one block may allocate, beside the lists).
     bool one_pass = want_bwd && self && 2 * lds <= (size_t)72 * 1024;
-    if (one_pass && 2 * lds > (size_t)32 * 1024) {
+    if (one_pass && 2 * lds_f > (size_t)32 * 1024) {
         int dev = 0, per_block = 0;
         PCPP_HIP_CHECK(hipGetDevice(&dev));
         PCPP_HIP_CHECK(hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-        if (2 * lds + (size_t)2 * SEARCH_WAVES * KEEP_MAX * sizeof(uint32_t) + 1024 > (size_t)per_block) one_pass = false;
+        if (2 * lds_f + 1024 > (size_t)per_block) one_pass = false;
         else if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&query_count<false, true, true>)
-                                           : reinterpret_cast<const void *>(&query_count<false, true, false>), 2 * lds)) != PCPP_OK)
+                                           : reinterpret_cast<const void *>(&query_count<false, true, false>), 2 * lds_f)) != PCPP_OK)
             return rc;
     }
 
@@ -1267,16 +1281,16 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         const CountOut fwd_out{count_only ? nullptr : f_cnt, f_ptr, pub_hits, pub_n};
         if (one_pass && !spatial)
             {
-                if (ext) query_count<false, true, true><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds, stream>>>(
+                if (ext) query_count<false, true, true><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds_f, stream>>>(
                 out_xyz, n_out, nullptr, grid_in, q, K, nt_o, fwd_out, CountOut{b_cnt, b_sum, b_hits}, bs.fwd_stride, err, no_reuse);
-                else query_count<false, true, false><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds, stream>>>(
+                else query_count<false, true, false><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds_f, stream>>>(
                 out_xyz, n_out, nullptr, grid_in, q, K, nt_o, fwd_out, CountOut{b_cnt, b_sum, b_hits}, bs.fwd_stride, err, no_reuse);
             }
         else
             {
-                if (ext) query_count<false, false, true><<<(unsigned)nt_o, SEARCH_THREADS, lds, stream>>>(
+                if (ext) query_count<false, false, true><<<(unsigned)nt_o, SEARCH_THREADS, lds_f, stream>>>(
                 out_xyz, n_out, nullptr, grid_in, q, K, nt_o, fwd_out, none, bs.fwd_stride, err, no_reuse);
-                else query_count<false, false, false><<<(unsigned)nt_o, SEARCH_THREADS, lds, stream>>>(
+                else query_count<false, false, false><<<(unsigned)nt_o, SEARCH_THREADS, lds_f, stream>>>(
                 out_xyz, n_out, nullptr, grid_in, q, K, nt_o, fwd_out, none, bs.fwd_stride, err, no_reuse);
             }
         PCPP_HIP_CHECK(hipGetLastError());
@@ -1372,16 +1386,16 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
             const CountOut fwd_out{f_cnt, f_ptr, f_hits};
             if (one_pass)
                 {
-                if (ext) query_count<false, true, true><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds, stream>>>(
+                if (ext) query_count<false, true, true><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds_f, stream>>>(
                     out_xyz, n_out, perm_o, grid_in, q, K, nt_o, fwd_out, CountOut{b_cnt, b_sum, b_hits}, bs.fwd_stride, err, from_public);
-                else query_count<false, true, false><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds, stream>>>(
+                else query_count<false, true, false><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds_f, stream>>>(
                     out_xyz, n_out, perm_o, grid_in, q, K, nt_o, fwd_out, CountOut{b_cnt, b_sum, b_hits}, bs.fwd_stride, err, from_public);
             }
             else
                 {
-                if (ext) query_count<false, false, true><<<(unsigned)nt_o, SEARCH_THREADS, lds, stream>>>(
+                if (ext) query_count<false, false, true><<<(unsigned)nt_o, SEARCH_THREADS, lds_f, stream>>>(
                     out_xyz, n_out, perm_o, grid_in, q, K, nt_o, fwd_out, none, bs.fwd_stride, err, from_public);
-                else query_count<false, false, false><<<(unsigned)nt_o, SEARCH_THREADS, lds, stream>>>(
+                else query_count<false, false, false><<<(unsigned)nt_o, SEARCH_THREADS, lds_f, stream>>>(
                     out_xyz, n_out, perm_o, grid_in, q, K, nt_o, fwd_out, none, bs.fwd_stride, err, from_public);
             }
             PCPP_HIP_CHECK(hipGetLastError());
@@ -1409,9 +1423,9 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         uint32_t *b_runs = reinterpret_cast<uint32_t *>(pb + pl.bwd.run_start_off);
         if (nt_i > 0 && !one_pass) {
             {
-                if (ext) query_count<true, false, true><<<(unsigned)nt_i, SEARCH_THREADS, lds, stream>>>(
+                if (ext) query_count<true, false, true><<<(unsigned)nt_i, SEARCH_THREADS, lds_b, stream>>>(
                 in_xyz, n_in, perm_i, grid_out, qs, K, nt_i, CountOut{b_cnt, b_sum, b_hits}, none, bs.bwd_stride, err, no_reuse);
-                else query_count<true, false, false><<<(unsigned)nt_i, SEARCH_THREADS, lds, stream>>>(
+                else query_count<true, false, false><<<(unsigned)nt_i, SEARCH_THREADS, lds_b, stream>>>(
                 in_xyz, n_in, perm_i, grid_out, qs, K, nt_i, CountOut{b_cnt, b_sum, b_hits}, none, bs.bwd_stride, err, no_reuse);
             }
             PCPP_HIP_CHECK(hipGetLastError());
