@@ -465,7 +465,9 @@ int launch_tile(const TileArgs &t, hipStream_t stream)
 //     64 -> 128: 52, four waves 61); above, cooperative, 32 centres per wave, crowded: 16 (strided layer, 64 -> 128: 97, split
 //     107).
 //   - wider: cooperative, so that W is read once per 64 centres; 32 centres per wave (100 000 points, 125 cells, 128 -> 256 with
-//     rounded sums: 777; 16 centres 958, split 864), 16 where the exact bf16 sums of 32 would leave a CU one block.
+//     rounded sums: 777; 16 centres 958, split 864), 16 where the exact bf16 sums of 32 would leave a CU one block, and in crowded
+//     layers with rounded sums (115 000 points with 148 neighbours, 256 -> 256: 907 in spatial order and 860 in index order,
+//     32 centres 1102 and 1026; 100 000 points with 24 neighbours, not crowded: 673, 32 centres 618).
 template <bool F32, bool EXACT, int RL, bool NARROW>
 int launch_tile_form(const TileArgs &t, hipStream_t stream)
 {
@@ -494,7 +496,8 @@ int launch_tile_form(const TileArgs &t, hipStream_t stream)
             return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 2, false>(t, stream)
                            : launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 2, false>(t, stream);
         }
-        return launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 4, false>(t, stream);
+        return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false>(t, stream)
+                       : launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 4, false>(t, stream);
     }
 }
 
