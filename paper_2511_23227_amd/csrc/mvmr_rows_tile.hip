@@ -458,6 +458,9 @@ int launch_tile(const TileArgs &t, hipStream_t stream)
 //     fp32: 8.4, four waves 10.5, 32 centres 12.1, cooperative 27.  8000 points, 64 -> 64 bf16: 12.2 / 13.2 / 14.5 / 29.
 //   - exact sums, up to 128 destination channels: split over four waves, 32 centres, since the terms of a sum would take three
 //     times the LDS (40 000 points, 128 -> 128 bf16: 130 per direction; cooperative, 16 centres per wave, about 165)
+//     fp32, 17 .. 32 destination channels, more than 65536 centres with up to 16 neighbours: 64 centres, which fill a window
+//     better (32 -> 32, 200 000 points with 10 neighbours: 120, 32 centres 132; 100 000 with 13.5: 74, 78; with 24: 90, 86;
+//     24 000 with 14.5, too few blocks: 28.6, 24.6).
 //   - rounded sums, up to 64: the same (strided layer's input gradient, 128 -> 64: 253, 16 centres 346, cooperative 312).
 //     Crowded 64-wide layers: cooperative, 16 centres per wave, which fill their windows and read W a quarter as often (115 000 points with
 //     148 neighbours, 64 -> 64: 153, split 163 .. 174).
@@ -479,8 +482,11 @@ int launch_tile_form(const TileArgs &t, hipStream_t stream)
         return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 4, true>(t, stream);
     }
     const bool crowded = (int64_t)(t.gather_bytes / 4) * 32 > 48 * t.n_centres * (int64_t)t.K;
+    [[maybe_unused]] const bool few = t.n_centres > 65536 && (int64_t)(t.gather_bytes / 4) <= 16 * t.n_centres;
     if constexpr (EXACT) {
         if (t.ndt == 1) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 1, true>(t, stream);
+        if constexpr (F32)
+            if (t.ndt == 2 && few) return launch_tile<F32, EXACT, RL, NARROW, 4, 1, 4, 1, 2, true>(t, stream);
         if (t.ndt == 2) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 2, true>(t, stream);
         if (t.ndt <= 4) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
         if (t.ndt <= 8) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);

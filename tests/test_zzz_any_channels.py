@@ -35,6 +35,7 @@ def dev(a, dtype=None):
     (400, 300, 0.2, 2, ((63, 65), (127, 129), (96, 260)), "f32"),
     (17000, 16300, 0.06, 3, ((20, 36), (15, 130), (128, 128)), "bf16"),       # split form one way, cooperative the other
     (16300, 17000, 0.06, 3, ((20, 36), (66, 15)), "f32"),
+    (300, 66000, 0.15, 3, ((20, 32), (32, 17)), "f32"),                       # many centres with few neighbours
     (2000, 2000, 0.15, 6, ((64, 64), (40, 24)), "bf16"),                       # 216 cells
     (40, 1, 0.5, 3, ((20, 20), (64, 64)), "bf16"),
     (1, 70, 0.5, 3, ((20, 20), (32, 32)), "f32"),
