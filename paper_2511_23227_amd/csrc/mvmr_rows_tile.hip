@@ -29,6 +29,7 @@
 // v_mfma_f32_16x16x32_bf16: A: lane (M = l%16, g = l/16) holds A[M][8g .. 8g+7]; B: lane (N = l%16, g) holds
 // B[8g .. 8g+7][N]; D: lane l, register j -> M = 4g + j, N = l%16.
 #include "mvmr_stage.h"
+#include "mvmr_walk.h"
 
 namespace pcpp {
 
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
     uint32_t raw;
     const uint32_t tl = St::triplet_of_lane(m, g);
     auto load_indices = [&](const Cursor &c) {
-        raw = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(grs, (int)(tl * 4u), (int)((c.bs + c.w) * 4u), 0);
+        raw = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(grs, (int)index_offset(c.bs + c.w, tl), 0, 0);
     };
     auto load_rows = [&](const Cursor &c) {
         const uint32_t offs = tl < c.n - c.w ? (raw & GATHER_INDEX) * a.row_bytes : OOB_OFFSET;

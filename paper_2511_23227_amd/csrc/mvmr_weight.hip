@@ -12,6 +12,7 @@
 // B[8g .. 8g+7][N]; D: lane l, register j -> M = 4g + j, N = l%16.
 
 #include "mvmr_stage.h"
+#include "mvmr_walk.h"
 
 namespace pcpp {
 
@@ -358,32 +359,22 @@ __global__ __launch_bounds__(WAVES * 64, (any_min_waves<SO, SI>())) void weight_
     uint32_t ri, ro;
     const uint32_t ti = SI::triplet_of_lane(m, g), to = SO::triplet_of_lane(m, g);
     auto load_indices = [&](uint32_t pos) {
-        const int at = (int)(((uint32_t)p0 + pos) * 4u);
-        ri = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(irs, (int)(ti * 4u), at, 0);
-        ro = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(ors, (int)(to * 4u), at, 0);
+        const uint32_t first = (uint32_t)p0 + pos;         // (up to 286 words past the list: the walk runs two batches ahead)
+        ri = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(irs, (int)index_offset(first, ti), 0, 0);
+        ro = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(ors, (int)index_offset(first, to), 0, 0);
     };
     auto load_rows = [&](uint32_t n) {
         const uint32_t oi = ti < n ? ri * xrow : OOB_OFFSET, oo = to < n ? ro * drow : OOB_OFFSET;
         so.load(drs, oo, a.c_out);
         si.load(xrs, oi, a.c_in);
     };
-    // This wave's batches: (position, triplets), run by run; a batch never crosses the end of a cell's run.
-    struct Cursor { uint32_t pos, end; int k; };
     auto end_of = [&](int kk) -> uint32_t {               // end of cell kk's run inside the chunk
         const int64_t e = a.seg[kk + 1] - p0;
         return (uint32_t)__builtin_amdgcn_readfirstlane((int)(e < (int64_t)p_end ? (uint32_t)e : p_end));
     };
-    auto settle = [&](Cursor &c, uint32_t start) {        // the first batch at or behind `start` of c's run, or of a later one
-        c.pos = start;
-        while (c.pos >= c.end && c.end < p_end) {
-            const uint32_t s = c.end;
-            ++c.k;
-            c.end = end_of(c.k);
-            c.pos = s + (uint32_t)(WINDOW * wave);
-        }
-    };
-    auto left = [&](const Cursor &c) -> uint32_t { return c.pos < c.end ? (c.end - c.pos < (uint32_t)WINDOW ? c.end - c.pos : (uint32_t)WINDOW) : 0u; };
-    Cursor nx{0u, end_of(k), k};
+    auto settle = [&](BatchCursor &c, uint32_t start) { settle_batch(c, start, p_end, (uint32_t)(WINDOW * wave), end_of); };
+    auto left = [&](const BatchCursor &c) -> uint32_t { return c.pos < c.end ? (c.end - c.pos < (uint32_t)WINDOW ? c.end - c.pos : (uint32_t)WINDOW) : 0u; };
+    BatchCursor nx{0u, end_of(k), k};
     settle(nx, (uint32_t)(WINDOW * wave));
     load_indices(nx.pos);
     load_rows(left(nx));
