@@ -128,9 +128,11 @@ size_t rows_w_bytes(int c_in, int c_out, int K, int in_dtype)
     return align_up((size_t)K * c_out * c_in * (in_dtype == PCPP_F32 ? 6 : 2));
 }
 
-// Forward layers that have always needed the workspace and refuse a call without one; the others do without if they must.
-bool workspace_expected(int in_dtype, int c_in, int c_out)
+// Forward layers that have always needed the workspace and refuse a call without one: 256 -> 256 bf16, and with up to 64
+// cells the shapes below.  The others do without if they must (mvmr_rows_generic, many times slower).
+bool workspace_expected(int in_dtype, int c_in, int c_out, int K)
 {
+    if (K > 64) return in_dtype == PCPP_BF16 && c_in == 256 && c_out == 256;
     if (in_dtype == PCPP_F32) return c_in == c_out && (c_in == 32 || c_in == 64);
     return (c_in == 64 && (c_out == 64 || c_out == 128)) || (c_in == 128 && c_out == 64) || (c_in == 256 && c_out == 256);
 }
@@ -216,7 +218,7 @@ int pcpp_mvmr_fwd(const void *x, const void *w, void *out, int in_dtype, int out
         a.w = workspace;
         return pc ? mvmr_rows_pc(a, stream) : mvmr_rows_tile(a, stream);
     }
-    if (pc || (tile && workspace_expected(in_dtype, c_in, c_out))) {
+    if (pc || (tile && workspace_expected(in_dtype, c_in, c_out, K))) {
         set_error("pcpp_mvmr_fwd: workspace missing, misaligned or smaller than %zu bytes", need);
         return PCPP_ERR_WORKSPACE;
     }
