@@ -220,11 +220,11 @@ PCPP_API int pcpp_mvmr_bwd_weight(const void *x, const void *dy, float *dw, int 
 /* ---------------------------------------------------------------------------------------------
  * pcpp_mvmr_fwd for callers that cannot provide scratch memory or let the library allocate it: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same operation, same arguments
- * and same results as pcpp_mvmr_fwd without the workspace: the packed weights go to a device array of
- * pcpp_static_scratch_bytes() bytes (24 MiB) that is part of the loaded library, one copy per GPU, held until
- * the process ends.  The call allocates nothing and creates nothing.
- * Limits: K * c_out * c_in * (2 bytes for bf16, 6 for fp32) must fit that array, otherwise UNSUPPORTED is
- * returned and nothing is launched.  Every call on a GPU uses that GPU's one array, so two calls that overlap
+ * and same results as pcpp_mvmr_fwd without the workspace: the packed weights go to a device array that is part
+ * of the loaded library, one copy per GPU (48 MiB), held until the process ends.  The call allocates nothing and
+ * creates nothing.
+ * Limits: K * c_out * c_in * (2 bytes for bf16, 6 for fp32) must not exceed pcpp_static_scratch_bytes() (24 MiB; the
+ * array is larger because weights are padded in it), otherwise UNSUPPORTED is returned and nothing is launched.  Every call on a GPU uses that GPU's one array, so two calls that overlap
  * in time on one GPU (different streams or threads) race; calls on one stream are ordered and safe.
  * ------------------------------------------------------------------------------------------- */
 PCPP_API size_t pcpp_static_scratch_bytes(void);

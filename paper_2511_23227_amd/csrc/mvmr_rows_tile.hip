@@ -35,21 +35,6 @@ namespace pcpp {
 
 namespace {
 
-// How rows of c_src channels are read (mvmr_stage.h), in chunks of `chk` channels.  bf16: four or eight lanes per row, 32 or
-// 64 channels (chunks of 128 need twice the registers and LDS and were slower except on small clouds); fp32: 32 channels.
-struct TileShape { int rl, chk, n_chunks, ndt; bool narrow; };
-
-TileShape tile_shape(bool f32, int c_src, int c_dst)
-{
-    TileShape s;
-    s.narrow = c_src < (f32 ? 2 : 8);
-    s.rl = c_src > 32 ? 8 : 4;
-    s.chk = f32 ? 32 : 8 * s.rl;
-    s.n_chunks = (int)ceil_div(c_src, s.chk);
-    s.ndt = (int)ceil_div(c_dst, 16);
-    return s;
-}
-
 // packed[(((k * ndt + d) * nks + ks) * planes + p) * 64 + lane], element e
 //     = term p of W(k, dst 16 d + lane%16, channel at place 32 ks + 16 (e/4) + 4 (lane/16) + e%4 of the chunks' operand
 // tiles), zero where there is none: in this order of the reduction index the sums of stage A, as the matrix cores leave
@@ -509,12 +494,6 @@ int launch_tile_form(const TileArgs &t, hipStream_t stream)
 }
 
 }  // namespace
-
-size_t mvmr_rows_tile_w_bytes(bool f32, int c_src, int c_dst, int K)
-{
-    const TileShape s = tile_shape(f32, c_src, c_dst);
-    return (size_t)K * s.ndt * 16 * s.n_chunks * s.chk * (f32 ? 6 : 2);
-}
 
 bool mvmr_rows_tile_usable(const MvmrArgs &a)
 {

@@ -119,14 +119,33 @@ PlanSideView side_view(const void *plan, const SideLayout &s, bool spatial)
 
 // Device memory that the entry point which allocates nothing uses in place of a caller's workspace (packed
 // weights).  One copy per device, held until the process ends; calls that overlap on one device would race on it.
-constexpr size_t STATIC_SCRATCH_BYTES = (size_t)24 << 20;
-static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
+// The entry point takes weights of up to STATIC_SCRATCH_BYTES without padding; the array has room for the padding too.
+constexpr size_t STATIC_SCRATCH_BYTES = (size_t)24 << 20, STATIC_ARRAY_BYTES = 2 * STATIC_SCRATCH_BYTES;
+static __device__ __align__(256) unsigned char scratch[STATIC_ARRAY_BYTES];
 
 // W or W^T in fragment order without padding (fp32: three bf16 terms)
-size_t rows_w_bytes(int c_in, int c_out, int K, int in_dtype)
+constexpr size_t rows_w_bytes(int c_in, int c_out, int K, int in_dtype)
 {
     return align_up((size_t)K * c_out * c_in * (in_dtype == PCPP_F32 ? 6 : 2));
 }
+
+// Largest packed weights of the layers that the entry point takes (216 cells, 65 -> 896 channels in bf16: 47.25 MiB)
+constexpr size_t largest_static_w()
+{
+    size_t most = 0;
+    for (int t = 1; t <= PCPP_MAX_T; ++t)
+        for (int dtype : {PCPP_F32, PCPP_BF16})
+            for (int c_in = 1; c_in <= 1024; ++c_in) {
+                const int K = t * t * t;
+                size_t c_out = STATIC_SCRATCH_BYTES / ((size_t)K * c_in * (dtype == PCPP_F32 ? 6 : 2));
+                if (c_out > 1024) c_out = 1024;
+                if (c_out < 1) continue;
+                const size_t bytes = mvmr_rows_tile_w_bytes(dtype == PCPP_F32, c_in, (int)c_out, K);
+                if (bytes > most) most = bytes;
+            }
+    return most;
+}
+static_assert(largest_static_w() <= STATIC_ARRAY_BYTES, "every layer that the static entry point takes fits, padded");
 
 // Forward layers that have always needed the workspace and refuse a call without one: 256 -> 256 bf16, and with up to 64
 // cells the shapes below.  The others do without if they must (mvmr_rows_generic, many times slower).
@@ -309,7 +328,7 @@ int pcpp_mvmr_fwd_static(const void *x, const void *w, void *out, int in_dtype, 
     const int rc = static_scratch(&ws);
     if (rc != PCPP_OK) return rc;
     return pcpp_mvmr_fwd(x, w, out, in_dtype, out_dtype, n_in, n_out, c_in, c_out, K, tri_o, tri_i, tri_k, seg_offsets,
-                         n_triplets, plan, plan_bytes, plan_flags, ws, STATIC_SCRATCH_BYTES, stream_);
+                         n_triplets, plan, plan_bytes, plan_flags, ws, STATIC_ARRAY_BYTES, stream_);
 }
 
 }  // extern "C"

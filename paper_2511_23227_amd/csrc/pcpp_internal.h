@@ -26,8 +26,8 @@ void set_error(const char *fmt, ...);
         }                                                                                 \
     } while (0)
 
-inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+constexpr size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
+constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // One side of a plan: triplets grouped around `n_centres` centres (outputs for the forward /
 // weight-gradient side, inputs for the input-gradient side).  A centre's position in the side's order is its
@@ -130,7 +130,21 @@ int mvmr_rows_pc_pack_w(const void *w, void *packed, int K, int c_src, int c_dst
 int mvmr_rows_pc(const MvmrArgs &a, hipStream_t stream);   // a.w = weights packed by mvmr_rows_pc_pack_w
 // any channel counts, on the matrix cores (mvmr_rows_tile.hip)
 bool mvmr_rows_tile_usable(const MvmrArgs &a);
-size_t mvmr_rows_tile_w_bytes(bool f32, int c_src, int c_dst, int K);     // packed weights
+// How that kernel reads rows of c_src channels (mvmr_stage.h), in chunks of `chk` channels.  bf16: four or eight lanes per
+// row, 32 or 64 channels (chunks of 128 need twice the registers and LDS and were slower except on small clouds); fp32: 32
+// channels.
+struct TileShape { int rl, chk, n_chunks, ndt; bool narrow; };
+constexpr TileShape tile_shape(bool f32, int c_src, int c_dst)
+{
+    const int rl = c_src > 32 ? 8 : 4, chk = f32 ? 32 : 8 * rl;
+    return TileShape{rl, chk, (int)ceil_div(c_src, chk), (int)ceil_div(c_dst, 16), c_src < (f32 ? 2 : 8)};
+}
+// its packed weights: whole chunks of source channels, whole tiles of destination channels
+constexpr size_t mvmr_rows_tile_w_bytes(bool f32, int c_src, int c_dst, int K)
+{
+    const TileShape s = tile_shape(f32, c_src, c_dst);
+    return (size_t)K * s.ndt * 16 * s.n_chunks * s.chk * (f32 ? 6 : 2);
+}
 int mvmr_rows_tile_pack_w(const void *w, void *packed, int K, int c_src, int c_dst, int stride_d, int stride_s, int dtype,
                           hipStream_t stream);
 int mvmr_rows_tile(const MvmrArgs &a, hipStream_t stream);   // a.w = weights packed by mvmr_rows_tile_pack_w

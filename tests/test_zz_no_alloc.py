@@ -59,6 +59,17 @@ def test_static_entry_point_matches_twice(pcpp):
         assert torch.equal(ref, got), (n, c_in, c_out)
 
 
+@pytest.mark.parametrize("n,c_in,c_out,dt,r,t", [
+    (900, 20, 36, torch.float32, 0.12, 3),            # weights padded to whole tiles of channels
+    (300, 180, 180, torch.float32, 0.2, 5),           # 23.2 MiB as given, 26.4 MiB padded
+    (300, 33, 1016, torch.float32, 0.2, 5),           # 24.0 and 46.9
+    (200, 65, 896, torch.bfloat16, 0.2, 6),           # 24.0 and 47.25, the largest there is
+])
+def test_static_entry_point_matches_for_padded_weights(pcpp, n, c_in, c_out, dt, r, t):
+    ref, got, T = run_pair(pcpp, n, c_in, c_out, dt, r, t, c_in)
+    assert T.n_triplets > 0 and torch.equal(ref, got)
+
+
 def test_static_entry_point_rejects_what_does_not_fit(pcpp):
     from paper_2511_23227_amd import binding as B
     L = pcpp.library()
