@@ -20,6 +20,13 @@
 // Cooperative form: the waves of a block share the S tiles of a round of cells in LDS (two sets, one barrier per round),
 // and each owns 16 DTW destination channels of its centre groups: W is read once per 64 centres and the accumulators
 // stay small, so several blocks per CU hide the gathers.
+// The products of the smaller terms have sums of their own (APART), which reach the accumulators as ordinary additions: the
+// matrix cores cut the low bits of an addend far below the accumulator, and with values of one sign these cuts add up
+// (relative errors with one accumulator, apart, and of fp32 sums on the vector ALUs, all values positive: 256 -> 256 fp32, 1.5 M
+// triplets, 8.9e-6, 4.2e-7, 1.06e-6; 512 -> 256 bf16 with 270 neighbours 2.1e-6, 6.4e-7, 1.6e-6).  fp32 layers take as long
+// either way; the cooperative exact bf16 form takes 8 % longer and has them apart in crowded layers only, where the sums have
+// low terms (128 -> 256, 37 neighbours, not crowded: 3.7e-7 without, vector ALUs 5.6e-7); a wave of the split one adds up too
+// few (1024 -> 64, 216 cells, crowded: 7.3e-7, vector ALUs 7.2e-6).
 // What bounds it: the matrix cores and the vector instructions around them (fp32: the split into terms) with 32 to 64
 // channels (a 64 -> 64 bf16 layer of 17 M triplets moves 2.2 GB of rows through L1 and L2 in 153 us), W's way from L2 with
 // more.  Layers whose channel counts are no power of two, which the vector ALUs had served before: 20 -> 36 fp32, 0.49 M
@@ -118,7 +125,7 @@ struct TileCfg {
     static_assert(PART % 256 == 0 && St::BYTES % 256 == 0, "alignment of the staged rows");
 };
 
-template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK>
+template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK, bool APART>
 __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
 {
     using C = TileCfg<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
@@ -128,6 +135,7 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
     constexpr int W_REGS = DTW * KS * PL * 4, CELLS = SPLITK ? 1 : CR;       // of one cell; cells of a round that this wave multiplies
     constexpr bool W_EARLY = W_REGS * CELLS <= 64;
     constexpr int CW = W_EARLY ? CELLS : 1;
+    static_assert(!APART || EXACT, "rounded sums have one term");
     static_assert(NG <= 4 && (SPLITK ? (WD == 1 && NP == 1) : NW % WD == 0 && NG % (NW / WD) == 0), "shape");
     extern __shared__ __attribute__((aligned(256))) char lds[];
     v4u *sel_tab = reinterpret_cast<v4u *>(lds);
@@ -365,8 +373,18 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
                                     auto mm = [&](int ws, int ss) {
                                         acc[i][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, wf[wi][d][ks][ws]), sv[ss], acc[i][d], 0, 0, 0);
                                     };
-                                    if constexpr (F32) { mm(0, PL - 1); mm(PL - 1, 0); mm(PL / 2, PL / 2); mm(0, PL / 2); mm(PL / 2, 0); mm(0, 0); }
-                                    else if constexpr (EXACT) { mm(0, PLS - 1); mm(0, PLS / 2); mm(0, 0); }
+                                    if constexpr (APART) {
+                                        v4f lo = {0.f, 0.f, 0.f, 0.f};
+                                        auto ml = [&](int ws, int ss) {
+                                            lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, wf[wi][d][ks][ws]), sv[ss], lo, 0, 0, 0);
+                                        };
+                                        ml(0, PLS - 1);
+                                        if constexpr (F32) { ml(PL - 1, 0); ml(PL / 2, PL / 2); }
+                                        ml(0, PLS / 2);
+                                        if constexpr (F32) ml(PL / 2, 0);
+                                        mm(0, 0);
+                                        acc[i][d] += lo;
+                                    } else if constexpr (EXACT) { mm(0, PLS - 1); mm(0, PLS / 2); mm(0, 0); }
                                     else mm(0, 0);
                                 }
                             }
@@ -425,11 +443,11 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
     }
 }
 
-template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK>
+template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK, bool APART = F32>
 int launch_tile(const TileArgs &t, hipStream_t stream)
 {
     using C = TileCfg<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
-    auto kern = rows_tile_kernel<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
+    auto kern = rows_tile_kernel<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK, APART>;
     if (C::LDS > 64 * 1024)
         if (int rc = raise_lds_limit(reinterpret_cast<const void *>(kern), C::LDS)) return rc;
     const dim3 grid((unsigned)(t.side.n_tiles * (4 / C::NG)), (unsigned)ceil_div(t.ndt, WD * DTW));
@@ -477,7 +495,8 @@ int launch_tile_form(const TileArgs &t, hipStream_t stream)
         if (t.ndt <= 4) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
         if (t.ndt <= 8) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
         if constexpr (F32) return launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 4, false>(t, stream);
-        else return launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false>(t, stream);
+        else return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false, true>(t, stream)
+                            : launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false>(t, stream);
     } else {
         if (t.ndt <= 4) return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 1, false>(t, stream)
                                        : launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
