@@ -317,12 +317,19 @@ template <typename SO, typename SI> constexpr int any_min_waves() {
     return SO::PL > 1 && SO::NT * SI::NT >= 8 ? 3 : 4;
 }
 
+// Longest part of a run that is summed in registers; the sums of a longer one go to its slot part by part, so that no sum in
+// 32 bits gets longer than those of the kernels for fp32 sums on the vector ALUs (relative errors with whole chunks, with parts,
+// and of those kernels: 64 -> 64 bf16, 16 M triplets, chunks of 15 900: 3.8e-7, 2.6e-7, 3.1e-7; 512 -> 256 bf16, 0.8 M, 25 600:
+// 2.9e-7, 2.2e-7, 2.1e-7).  It costs 5 % where a chunk has four parts (512 -> 512 bf16, 1 M: 685 and 719 us).
+constexpr uint32_t SEGMENT = 8192;
+
 // SO, SI: how the rows of dy and x reach the matrix cores
 template <typename SO, typename SI>
 __global__ __launch_bounds__(WAVES * 64, (any_min_waves<SO, SI>())) void weight_any_kernel(const WeightArgs a)
 {
     constexpr int ES = SO::ES, NTO = SO::NT, NTI = SI::NT, PL = SO::PL;
     constexpr bool F32 = PL > 1;
+    static_assert(SEGMENT % (WINDOW * WAVES) == 0, "the waves' batches of a run continue across segments");
     extern __shared__ __attribute__((aligned(256))) char lds[];       // staged rows, [WAVES]; the sums of one row of tiles
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int m = lane & 15, g = lane >> 4;
@@ -381,11 +388,12 @@ __global__ __launch_bounds__(WAVES * 64, (any_min_waves<SO, SI>())) void weight_
     settle(nx, nx.pos + WINDOW * WAVES);
     load_indices(nx.pos);
 
-    bool first = true;
+    bool first = true, more = false;                      // more: of the run whose sums so far are in its slot
     uint32_t p = 0u;
     while (p < p_end) {
-        const uint32_t q_end = end_of(k);
-        if (q_end <= p) { ++k; continue; }                // empty run
+        const uint32_t r_end = end_of(k);
+        if (r_end <= p) { ++k; continue; }                // empty run
+        const uint32_t q_end = r_end - p > SEGMENT ? p + SEGMENT : r_end;
         v4f acc[NTO][NTI];
 #pragma unroll
         for (int o = 0; o < NTO; ++o)
@@ -419,19 +427,20 @@ __global__ __launch_bounds__(WAVES * 64, (any_min_waves<SO, SI>())) void weight_
                 v4u bx[PL][NTI];
 #pragma unroll
                 for (int pl = 0; pl < PL; ++pl) si.tiles(pl, 0, bx[pl]);
+                v4u av[PL][NTO];
 #pragma unroll
-                for (int pl = PL - 1; pl >= 0; --pl) {    // smallest products first
-                    v4u av[NTO];
-                    so.tiles(pl, 0, av);
+                for (int pl = 0; pl < PL; ++pl) so.tiles(pl, 0, av[pl]);
 #pragma unroll
-                    for (int q = PL - 1 - pl; q >= 0; --q)
+                for (int o = 0; o < NTO; ++o)
 #pragma unroll
-                        for (int o = 0; o < NTO; ++o)
-#pragma unroll
-                            for (int i = 0; i < NTI; ++i)
-                                acc[o][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, av[o]),
-                                                                                    __builtin_bit_cast(v8bf, bx[q][i]), acc[o][i], 0, 0, 0);
-                }
+                    for (int i = 0; i < NTI; ++i) {
+                        auto mm = [&](int p, int q, const v4f &c) {
+                            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, av[p][o]), __builtin_bit_cast(v8bf, bx[q][i]), c, 0, 0, 0);
+                        };
+                        // the small products apart, as in the rows kernel: the matrix cores cut their low bits against a long sum
+                        const v4f lo = mm(1, 0, mm(0, 1, mm(1, 1, mm(2, 0, mm(0, 2, v4f{0.f, 0.f, 0.f, 0.f})))));
+                        acc[o][i] = mm(0, 0, acc[o][i]) + lo;
+                    }
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -452,20 +461,27 @@ __global__ __launch_bounds__(WAVES * 64, (any_min_waves<SO, SI>())) void weight_
                 float v = red[0][i][el][ej];
 #pragma unroll
                 for (int w = 1; w < WAVES; ++w) v += red[w][i][el][ej];
-                if (co >= 0 && ci >= 0) dstp[(size_t)co * a.c_in + ci] = v;
+                if (co >= 0 && ci >= 0) {
+                    float *at = dstp + (size_t)co * a.c_in + ci;
+                    *at = more ? *at + v : v;              // (written by this thread)
+                }
             }
         }
         __syncthreads();                                   // (the next rows go where these sums lie)
-        first = false;
         p = q_end;
-        ++k;
+        more = q_end < r_end;
+        if (!more) {
+            first = false;
+            ++k;
+        }
     }
 }
 
 // dw[k][e] = (partial of the run's head, if it starts inside a chunk) + partials of the chunks whose first
 // triplet lies in run k.  A block of four waves owns 64 consecutive elements of one cell: wave w adds chunks
-// c0 + w, c0 + w + 4, ... in ascending order (each read is 256 contiguous bytes) and the four sums are then
-// added in order of w, so the result is reproducible.  grid = (ceil(c_out*c_in / 64), K), block = 256
+// c0 + w, c0 + w + 4, ... in ascending order, 32 at a time (each read is 256 contiguous bytes), then these sums, and the four
+// waves' sums are added in order of w, so the result is reproducible.  (One long sum per wave loses precision: 20 -> 36 fp32, one
+// cell, 6.6 M triplets, 8562 chunks: relative error 1.65e-6, by 32 2.3e-7, vector ALUs 5.0e-7.)  grid = (ceil(c_out*c_in / 64), K), block = 256
 constexpr int REDUCE_WAVES = 4;
 
 __global__ __launch_bounds__(REDUCE_WAVES * 64) void weight_reduce(const float *__restrict__ part, float *__restrict__ dw,
@@ -477,19 +493,21 @@ __global__ __launch_bounds__(REDUCE_WAVES * 64) void weight_reduce(const float *
     const int e = blockIdx.x * 64 + lane;
     const int k = blockIdx.y;
     const int64_t s = seg[k], t = seg[k + 1];
-    float v = 0.f;
+    float v = 0.f, sum = 0.f;
     if (t > s && e < n_elem) {
         const int64_t c0 = (s + chunk - 1) / chunk, c1 = (t + chunk - 1) / chunk;
         const float *src = part + (size_t)e;
         int64_t c = c0 + wave;
+        int n = 0;
         for (; c + 3 * REDUCE_WAVES < c1; c += 4 * REDUCE_WAVES) {      // four independent reads in flight
             const float v0 = src[(size_t)c * n_elem], v1 = src[(size_t)(c + REDUCE_WAVES) * n_elem];
             const float v2 = src[(size_t)(c + 2 * REDUCE_WAVES) * n_elem], v3 = src[(size_t)(c + 3 * REDUCE_WAVES) * n_elem];
-            v = (((v + v0) + v1) + v2) + v3;
+            v += (v0 + v1) + (v2 + v3);
+            if (++n % 8 == 0) { sum += v; v = 0.f; }
         }
         for (; c < c1; c += REDUCE_WAVES) v += src[(size_t)c * n_elem];
     }
-    sums[wave][lane] = v;
+    sums[wave][lane] = sum + v;
     __syncthreads();
     if (wave == 0 && e < n_elem) {
         float r = (t > s && s % chunk != 0) ? part[(size_t)(n_chunks + k) * n_elem + e] : 0.f;
@@ -553,10 +571,11 @@ AnyShape any_shape(bool f32, int64_t n_triplets, int c_in, int c_out)
     s.n_sub = s.n_sub_in * (int)ceil_div(c_out, s.co);
     int64_t want = 1024 / s.n_sub;
     if (want < 8) want = 8;
-    // fp32: at most 768 triplets, i.e. six batches of six products per wave, so that the roundings along a sum stay below
-    // those of the vector ALUs' sums (256 -> 256, 0.47 M triplets: relative error 7.9e-7 with chunks of 7424,
-    // 3.1e-7 of 1024, 2.7e-7 of 768, 3.0e-7 on the vector ALUs; 32 -> 32, 2.4 M: 231 us for the whole step with 768, 237 with 512); as long as
-    // the partial sums stay below 256 MB.
+    // fp32: at most 768 triplets while the partial sums stay below 256 MB, as many as fit otherwise (256 -> 256 from 0.8 M
+    // triplets on; 32 -> 32, 2.4 M triplets: 231 us for the whole step with 768, 237 with 512).  Longer chunks lost precision
+    // when all six products went to one accumulator (256 -> 256, 0.47 M: relative error 7.9e-7 with chunks of 7424, 2.7e-7 of 768,
+    // 3.0e-7 on the vector ALUs); with the small products apart and parts of SEGMENT they do not (4.8 M, chunks of 4736: 2.4e-7,
+    // vector ALUs 8.6e-7).
     if (f32) {
         const int64_t short_chunks = ceil_div(n_triplets, 768), room = ((int64_t)1 << 26) / ((int64_t)c_in * c_out);
         if (short_chunks > want && want < room) want = short_chunks < room ? short_chunks : room;
