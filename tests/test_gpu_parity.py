@@ -370,8 +370,8 @@ def test_bf16_outputs(pcpp, c):
 
 
 def test_wide_layer_long_lists(pcpp):
-    """256 -> 256 with hundreds of triplets per (cell, 32-centre block): the wide kernel's path for lists longer
-    than its prefetch ring, and runs that straddle its 64-triplet groups."""
+    """256 -> 256 with hundreds of triplets per (cell, 32-centre block): the tile kernel's crowded form, many windows of 32
+    triplets per cell, and runs that straddle them."""
     rng = np.random.default_rng(21)
     p = np.concatenate([rng.normal(0.5, 0.03, (500, 3)), rng.uniform(0, 1, (300, 3))]).astype(np.float32)
     r, t, c = 0.12, 3, 256

@@ -74,11 +74,11 @@ def test_permutation_is_a_space_filling_order(pcpp):
 
 
 @pytest.mark.parametrize("case", [
-    dict(n_in=700, n_out=333, r=0.17, t=3, cin=5, cout=7, dt="f32"),          # generic kernels
-    dict(n_in=1501, n_out=1333, r=0.12, t=3, cin=32, cout=32, dt="f32"),      # matrix-core rows kernels
+    dict(n_in=700, n_out=333, r=0.17, t=3, cin=5, cout=7, dt="f32"),          # fewer channels than a lane reads, no power of two
+    dict(n_in=1501, n_out=1333, r=0.12, t=3, cin=32, cout=32, dt="f32"),      # whole tiles of channels
     dict(n_in=1300, n_out=1501, r=0.12, t=3, cin=64, cout=64, dt="bf16"),
     dict(n_in=2100, n_out=700, r=0.15, t=3, cin=64, cout=128, dt="bf16"),
-    dict(n_in=1500, n_out=1300, r=0.15, t=5, cin=256, cout=256, dt="bf16"),   # wide kernel
+    dict(n_in=1500, n_out=1300, r=0.15, t=5, cin=256, cout=256, dt="bf16"),   # producer/consumer kernel
     dict(n_in=1000, n_out=1000, r=0.2, t=6, cin=48, cout=24, dt="bf16"),
     dict(n_in=300, n_out=2000, r=0.15, t=4, cin=16, cout=130, dt="bf16"),
 ])
@@ -100,7 +100,8 @@ def test_small_shapes_spatial(pcpp, case):
 
 
 def test_wide_layer_clustered_spatial(pcpp):
-    """256 -> 256 on a clustered cloud: long runs, many triplets per (cell, block), empty cells for whole blocks."""
+    """256 -> 256 on a clustered cloud: long runs, many triplets per (cell, block), empty cells for whole blocks.  (More than
+    three triplets per cell and centre, so in the tile kernel; test_zzz_wide_lists.py has clouds for the other one.)"""
     rng = np.random.default_rng(21)
     p = np.concatenate([rng.normal(0.5, 0.03, (500, 3)), rng.uniform(0, 1, (600, 3)),
                         np.c_[rng.uniform(0, 1, (700, 2)), np.full(700, 0.25)]]).astype(np.float32)
