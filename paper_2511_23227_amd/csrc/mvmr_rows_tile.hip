@@ -20,13 +20,10 @@
 // Cooperative form: the waves of a block share the S tiles of a round of cells in LDS (two sets, one barrier per round),
 // and each owns 16 DTW destination channels of its centre groups: W is read once per 64 centres and the accumulators
 // stay small, so several blocks per CU hide the gathers.
-// The products of the smaller terms have sums of their own (APART), which reach the accumulators as ordinary additions: the
-// matrix cores cut the low bits of an addend far below the accumulator, and with values of one sign these cuts add up
-// (relative errors with one accumulator, apart, and of fp32 sums on the vector ALUs, all values positive: 256 -> 256 fp32, 1.5 M
-// triplets, 8.9e-6, 4.2e-7, 1.06e-6; 512 -> 256 bf16 with 270 neighbours 2.1e-6, 6.4e-7, 1.6e-6).  fp32 layers take as long
-// either way; the cooperative exact bf16 form takes 8 % longer and has them apart in crowded layers only, where the sums have
-// low terms (128 -> 256, 37 neighbours, not crowded: 3.7e-7 without, vector ALUs 5.6e-7); a wave of the split one adds up too
-// few (1024 -> 64, 216 cells, crowded: 7.3e-7, vector ALUs 7.2e-6).
+// Where a sum has many steps, the products of the smaller terms have sums of their own (APART), which reach the accumulators
+// as ordinary additions: the matrix cores cut the low bits of an addend far below the accumulator, and with values of one sign
+// these cuts add up (relative errors with one accumulator, apart, and of fp32 sums on the vector ALUs, all values positive:
+// 256 -> 256 fp32, 1.5 M triplets, 8.9e-6, 4.2e-7, 1.06e-6; 512 -> 256 bf16 with 270 neighbours 2.1e-6, 6.4e-7, 1.6e-6).
 // What bounds it: the matrix cores and the vector instructions around them (fp32: the split into terms) with 32 to 64
 // channels (a 64 -> 64 bf16 layer of 17 M triplets moves 2.2 GB of rows through L1 and L2 in 153 us), W's way from L2 with
 // more.  Layers whose channel counts are no power of two, which the vector ALUs had served before: 20 -> 36 fp32, 0.49 M
@@ -373,7 +370,7 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
                                     auto mm = [&](int ws, int ss) {
                                         acc[i][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, wf[wi][d][ks][ws]), sv[ss], acc[i][d], 0, 0, 0);
                                     };
-                                    if constexpr (APART) {
+                                    if constexpr (APART) {           // (smallest first)
                                         v4f lo = {0.f, 0.f, 0.f, 0.f};
                                         auto ml = [&](int ws, int ss) {
                                             lo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, wf[wi][d][ks][ws]), sv[ss], lo, 0, 0, 0);
@@ -384,7 +381,9 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
                                         if constexpr (F32) ml(PL / 2, 0);
                                         mm(0, 0);
                                         acc[i][d] += lo;
-                                    } else if constexpr (EXACT) { mm(0, PLS - 1); mm(0, PLS / 2); mm(0, 0); }
+                                    }
+                                    else if constexpr (F32) { mm(0, PL - 1); mm(PL - 1, 0); mm(PL / 2, PL / 2); mm(0, PL / 2); mm(PL / 2, 0); mm(0, 0); }
+                                    else if constexpr (EXACT) { mm(0, PLS - 1); mm(0, PLS / 2); mm(0, 0); }
                                     else mm(0, 0);
                                 }
                             }
@@ -443,10 +442,23 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
     }
 }
 
-template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK, bool APART = F32>
+// fp32, split form: small products apart from more than this many steps (cells times chunks) of a wave on.  The error of one
+// accumulator grows with the steps (all values positive: 7 steps, 32 -> 32 with 27 cells and 330 neighbours, 1.2e-7; 16 steps,
+// 32 -> 32 with 64 cells, 2.3e-7; 28 steps, 128 -> 128, 4.6e-7; 128 steps, 1024 -> 64, 2.7e-6), that of fp32 sums on the vector ALUs
+// with the square root (2.6e-7, 7.6e-7, 8.0e-7, 1.6e-6).  Apart: below 1.4e-7 at all of them, and up to 3 % of the time
+// (20 -> 36, 0.49 M triplets: 99 and 102 us for the whole training step).  The cooperative form always has them apart when fp32.
+// bf16: in crowded layers of the cooperative form only, where sums have low terms (8 % of its time; 128 -> 256 with 37
+// neighbours, not crowded: 3.7e-7, vector ALUs 7.0e-7); the split form's waves add up too few (1024 -> 64, 216 cells, crowded:
+// 7.3e-7, vector ALUs 7.2e-6).
+constexpr int64_t APART_FROM = 16;
+
+template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK, bool APART = F32 && !SPLITK>
 int launch_tile(const TileArgs &t, hipStream_t stream)
 {
     using C = TileCfg<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
+    if constexpr (F32 && SPLITK && !APART)
+        if (ceil_div(t.K, NW) * t.n_chunks > APART_FROM)
+            return launch_tile<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK, true>(t, stream);
     auto kern = rows_tile_kernel<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK, APART>;
     if (C::LDS > 64 * 1024)
         if (int rc = raise_lds_limit(reinterpret_cast<const void *>(kern), C::LDS)) return rc;
