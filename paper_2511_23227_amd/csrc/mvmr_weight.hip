@@ -317,11 +317,15 @@ template <typename SO, typename SI> constexpr int any_min_waves() {
     return SO::PL > 1 && SO::NT * SI::NT >= 8 ? 3 : 4;
 }
 
-// Longest part of a run that is summed in registers; the sums of a longer one go to its slot part by part, so that no sum in
-// 32 bits gets longer than those of the kernels for fp32 sums on the vector ALUs (relative errors with whole chunks, with parts,
-// and of those kernels: 64 -> 64 bf16, 16 M triplets, chunks of 15 900: 3.8e-7, 2.6e-7, 3.1e-7; 512 -> 256 bf16, 0.8 M, 25 600:
-// 2.9e-7, 2.2e-7, 2.1e-7).  It costs 5 % where a chunk has four parts (512 -> 512 bf16, 1 M: 685 and 719 us).
+// Triplets that are summed in registers at most, so that no sum in 32 bits loses more than those of the kernels for fp32 sums on
+// the vector ALUs or of one wave per chunk did: chunks hold no more while the partial sums stay below 256 MB, and beyond
+// that the sums of a run go to its slot part by part.  Relative errors with chunks of any length, now, and of those kernels: 64 ->
+// 64 bf16, 16 M triplets (15 900 each), 3.8e-7, 2.7e-7, 3.1e-7; 512 -> 512 bf16, 1 M (30 700), 4.9e-7, 2.6e-7, 6.4e-7.  The
+// former takes 365 us instead of 375, the latter, with 4 chunks for each before, 718 instead of 690.
 constexpr uint32_t SEGMENT = 8192;
+
+// fp32 chunks, within the same 256 MB (32 -> 32, 2.4 M triplets: 231 us for the whole step with 768, 237 with 512).
+constexpr int F32_CHUNK = 768;
 
 // SO, SI: how the rows of dy and x reach the matrix cores
 template <typename SO, typename SI>
@@ -427,6 +431,14 @@ __global__ __launch_bounds__(WAVES * 64, (any_min_waves<SO, SI>())) void weight_
                 v4u bx[PL][NTI];
 #pragma unroll
                 for (int pl = 0; pl < PL; ++pl) si.tiles(pl, 0, bx[pl]);
+                auto mm = [&](const v4u &av, int q, int i, const v4f &c) {
+                    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, av), __builtin_bit_cast(v8bf, bx[q][i]), c, 0, 0, 0);
+                };
+                // The five products with a smaller term in a sum of their own: against a long sum the matrix cores cut their low bits,
+                // and with crowded cells or values of one sign these cuts add up (relative errors in one accumulator, apart, and
+                // of one wave per chunk or fp32 sums on the vector ALUs: 20 -> 36, one cell, 6.6 M triplets, 1.4e-6, 2.3e-7, 5.0e-7;
+                // 256 -> 256, 4.8 M, chunks of 4736, values of one sign, 9.3e-7, 6.3e-8, 1.5e-7).  The time is the same for 32 -> 32,
+                // 1.5 us more of 42 for 20 -> 36 with 0.49 M triplets, 3260 and 3370 us for 256 -> 256.
                 v4u av[PL][NTO];
 #pragma unroll
                 for (int pl = 0; pl < PL; ++pl) so.tiles(pl, 0, av[pl]);
@@ -434,12 +446,11 @@ __global__ __launch_bounds__(WAVES * 64, (any_min_waves<SO, SI>())) void weight_
                 for (int o = 0; o < NTO; ++o)
 #pragma unroll
                     for (int i = 0; i < NTI; ++i) {
-                        auto mm = [&](int p, int q, const v4f &c) {
-                            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, av[p][o]), __builtin_bit_cast(v8bf, bx[q][i]), c, 0, 0, 0);
-                        };
-                        // the small products apart, as in the rows kernel: the matrix cores cut their low bits against a long sum
-                        const v4f lo = mm(1, 0, mm(0, 1, mm(1, 1, mm(2, 0, mm(0, 2, v4f{0.f, 0.f, 0.f, 0.f})))));
-                        acc[o][i] = mm(0, 0, acc[o][i]) + lo;
+                        v4f lo = {0.f, 0.f, 0.f, 0.f};
+                        lo = mm(av[2][o], 0, i, mm(av[0][o], 2, i, lo));
+                        lo = mm(av[0][o], 1, i, mm(av[1][o], 1, i, lo));
+                        lo = mm(av[1][o], 0, i, lo);
+                        acc[o][i] = mm(av[0][o], 0, i, acc[o][i]) + lo;
                     }
             }
             __builtin_amdgcn_wave_barrier();
@@ -557,7 +568,7 @@ int launch_weight_lds(const MvmrArgs &a, float *dw, const int32_t *tri_o, const 
 }
 
 // The sub-block of dW that a block of weight_any_kernel owns, as channels of each side, and the chunk of the list.
-// Enough blocks for four per CU, unless that would leave a wave fewer than two batches.
+// Enough blocks for four per CU, unless that would leave a wave fewer than two batches, and chunks no longer than the above.
 struct AnyShape { int co, ci, n_sub_in, n_sub, chunk; int64_t n_chunks; };
 
 AnyShape any_shape(bool f32, int64_t n_triplets, int c_in, int c_out)
@@ -571,15 +582,8 @@ AnyShape any_shape(bool f32, int64_t n_triplets, int c_in, int c_out)
     s.n_sub = s.n_sub_in * (int)ceil_div(c_out, s.co);
     int64_t want = 1024 / s.n_sub;
     if (want < 8) want = 8;
-    // fp32: at most 768 triplets while the partial sums stay below 256 MB, as many as fit otherwise (256 -> 256 from 0.8 M
-    // triplets on; 32 -> 32, 2.4 M triplets: 231 us for the whole step with 768, 237 with 512).  Longer chunks lost precision
-    // when all six products went to one accumulator (256 -> 256, 0.47 M: relative error 7.9e-7 with chunks of 7424, 2.7e-7 of 768,
-    // 3.0e-7 on the vector ALUs); with the small products apart and parts of SEGMENT they do not (4.8 M, chunks of 4736: 2.4e-7,
-    // vector ALUs 8.6e-7).
-    if (f32) {
-        const int64_t short_chunks = ceil_div(n_triplets, 768), room = ((int64_t)1 << 26) / ((int64_t)c_in * c_out);
-        if (short_chunks > want && want < room) want = short_chunks < room ? short_chunks : room;
-    }
+    const int64_t short_chunks = ceil_div(n_triplets, f32 ? F32_CHUNK : SEGMENT), room = ((int64_t)1 << 26) / ((int64_t)c_in * c_out);
+    if (short_chunks > want && want < room) want = short_chunks < room ? short_chunks : room;
     int64_t chunk = ceil_div(n_triplets > 0 ? n_triplets : 1, want);
     if (chunk < 2 * WINDOW * WAVES) chunk = 2 * WINDOW * WAVES;
     s.chunk = (int)((chunk + WINDOW * WAVES - 1) / (WINDOW * WAVES) * (WINDOW * WAVES));
