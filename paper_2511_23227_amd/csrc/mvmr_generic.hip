@@ -1,5 +1,6 @@
 // Shape-generic MVMR kernels (any channel counts, fp32 or bf16 storage, fp32 accumulation).
-// They are the fallback for shapes without a matrix-core kernel.
+// They run where the matrix-core kernels cannot: feature tensors or triplet lists past the 4 GiB of a buffer descriptor, and
+// forward calls without a workspace for the packed weights.
 //
 // All three operations start from the same step: for a cell k and a tile of TILE consecutive
 // centres, the source rows of every (k, centre) run are summed on chip,

@@ -182,9 +182,8 @@ __global__ __launch_bounds__(LDS_WAVES * 64, 2) void weight_lds_kernel(const uin
             if (t < 0) t = 0;
             load_to_lds_b32(tri_lane + t, (uint32_t)__builtin_amdgcn_readfirstlane((int)(ring0 + ((cur + 6) & 3) * 256)));
         }
-        // rows of batch s + 3, one request behind every four MFMAs of the first half of batch s (output channels
-        // co0 .. co0 + 63; its operands were read one step ago): a request can wait long for room in the memory
-        // pipeline, and the matrix pipe should have work meanwhile.  The reads for the second half go first.
+        // first half of batch s (output channels co0 .. co0 + 63; its operands were read one step ago).  The reads for the
+        // second half go first.
         const unsigned char *buf = stage + cur * LDS_BATCH_BYTES;
         v2u dyw1[8];
 #pragma unroll
@@ -221,7 +220,8 @@ __global__ __launch_bounds__(LDS_WAVES * 64, 2) void weight_lds_kernel(const uin
             dyn[e] = *reinterpret_cast<const v2u *>(nbuf + DY_OFF + g * GP + e * ROW + (co0 + 4 * m) * 2);
         {
             // rows of batch s + 4 into the buffer that batch s has just left (every wave has read its last operands
-            // of it before the barrier), one request behind every four MFMAs of the second half
+            // of it before the barrier), one request behind every four MFMAs of the second half: a request can wait long for
+            // room in the memory pipeline, and the matrix pipe should have work meanwhile
             const uint32_t dst = lds0 + (uint32_t)cur * LDS_BATCH_BYTES + (uint32_t)((wave >> 1) * GP + 4 * (wave & 1) * ROW);
             auto request = [&](int i) __attribute__((always_inline)) {
                 const int j = i >> 1;
