@@ -24,9 +24,9 @@
 // as ordinary additions: the matrix cores cut the low bits of an addend far below the accumulator, and with values of one sign
 // these cuts add up (relative errors with one accumulator, apart, and of fp32 sums on the vector ALUs, all values positive:
 // 256 -> 256 fp32, 1.5 M triplets, 8.9e-6, 4.2e-7, 1.06e-6; 512 -> 256 bf16 with 270 neighbours 2.1e-6, 6.4e-7, 1.6e-6).
-// What bounds it: the matrix cores and the vector instructions around them (fp32: the split into terms) with 32 to 64
-// channels (a 64 -> 64 bf16 layer of 17 M triplets moves 2.2 GB of rows through L1 and L2 in 153 us), W's way from L2 with
-// more.  Layers whose channel counts are no power of two, which the vector ALUs had served before: 20 -> 36 fp32, 0.49 M
+// What bounds it: with 32 to 64 channels in fp32 the vector instructions, most of which split rows and sums into terms (32 ->
+// 32: issued in 73 % of the cycles), in bf16 the latency of the rows (a 64 -> 64 layer of 17 M triplets moves 2.2 GB of them through
+// L1 and L2 in 153 us, 0.58 L1 accesses per cycle and CU, matrix pipe 12 %); with more channels W's way from L2.  Layers whose channel counts are no power of two, which the vector ALUs had served before: 20 -> 36 fp32, 0.49 M
 // triplets, 29 us (349); 128 -> 128 bf16, 0.97 M triplets, 130 us (7938).
 // Every destination row is written once, by one block: no atomics, fixed summation order.
 //
@@ -549,7 +549,7 @@ int mvmr_rows_tile_pack_w(const void *w, void *packed, int K, int c_src, int c_d
 
 // bf16 layers whose run sums are rounded to bf16 once before they meet W: 64 -> 64, 64 -> 128 and 128 -> 64 with up to 64
 // cells, and 256 -> 256.  That is these layers' precision (relative error 1.6e-3 against exact sums), and a third of stage
-// B's matrix products.  All other layers keep the fp32 sums as three terms (2e-7).
+// B's matrix products.  All other layers keep the fp32 sums as three terms (1e-7 to 1e-6, growing with the length of the sums).
 static bool bf16_sums(int K, int c_src, int c_dst)
 {
     if (c_src == 256 && c_dst == 256) return true;
