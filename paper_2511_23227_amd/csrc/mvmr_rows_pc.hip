@@ -460,9 +460,10 @@ __global__ __launch_bounds__(PC_THREADS) void rows_pc_kernel(const void *__restr
 
 // Crowded cells (more than 96 triplets per 32 centres on average) go to the tile kernel.  Where a few centres hold most of the
 // triplets the producers here fall behind (115 000 points of a spinning lidar, 148 neighbours: 1065 us, this kernel 3069); on an
-// even cloud they keep up (50 000 points with 100 neighbours in 27 cells: 507 .. 530, this kernel 485; 20 000 with 90: 275, 266).
-// The average does not tell the two apart, so the line gives up 3 to 9 % of the one for a factor of three of the other; below it
-// this kernel is the faster one on both (50 000 points with 60 neighbours: 409, 362).
+// even cloud they keep up (50 000 points with 100 neighbours in 27 cells: 507 .. 530, this kernel 485; 20 000 with 90: 275, 266;
+// 94 000 with 25 in 8 cells: 273, 243).  The average does not tell the two apart, so the line gives up 3 to 15 % of the one for a
+// factor of three of the other; below it this kernel is the faster one on even clouds by more (50 000 points with 60 neighbours:
+// 409, 362).
 bool mvmr_rows_pc_usable(const MvmrArgs &a)
 {
     return a.n_triplets > 0 && a.n_triplets <= 3 * a.n_centres * (int64_t)a.K && a.in_dtype == PCPP_BF16 && a.c_src == 256 && a.c_dst == 256 && a.side.gather != nullptr &&
