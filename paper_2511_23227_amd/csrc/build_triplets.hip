@@ -19,7 +19,6 @@ constexpr int CELL_BIAS = 1 << 20;
 constexpr double CELL_CLAMP = (double)((1 << 20) - 2);   // +-1 stencil steps stay inside 21 bits
 constexpr int SEARCH_THREADS = 1024;                      // 16 waves share a tile of 64 centres: 4 centres each
 constexpr int SEARCH_WAVES = SEARCH_THREADS / 64;
-constexpr int LIST_CAP_MAX = 512;                         // neighbours of one centre kept in LDS (per wave)
 // Pitch of the [K][TILE] tables in LDS.  A wave works on one centre, so its lanes touch the words of one column, at most a
 // few of them in the same cell: with rows of 64 words they all lie in one bank.  The word behind a row holds the end of the
 // row's last run where the table holds starts of runs.
@@ -320,9 +319,7 @@ struct Candidates {
     }
 };
 
-constexpr uint32_t SMALL_LIST = 160;      // up to this many neighbours the all-pairs rank is cheaper than bucketing
 constexpr uint32_t KEEP_MAX = 256;        // longest neighbour list the count pass keeps per centre
-constexpr uint32_t BUCKET_FROM = 64;      // ... and from here on bucketing through LDS adds is cheaper, when keys pack
 constexpr int HIT_INDEX_BITS = 24;         // a stored hit = cell << 24 | candidate index
 constexpr uint32_t HIT_INDEX_MASK = (1u << HIT_INDEX_BITS) - 1u;
 
@@ -476,11 +473,23 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_count(const float *__
 //   tile_ptr  [K * n_tiles + 1]   exclusive prefix sum of tile_k_cnt
 //   perm                          centre index of each slot (NULL: slots are centre indices); tables, lists and
 //                                 the centre's position in the order use the slot, coordinates and out_c the index
-// One wave per centre at a time.  The centre's neighbours are compacted into per-cell buckets of an
-// LDS list with wave ballots and prefix popcounts (the bucket sizes are the counts of pass 1), then
-// each neighbour's rank inside its bucket (number of smaller candidate indices) gives its final slot,
-// so ties between equal (k, centre) are ordered by the other index without any global sort.
-constexpr int KGROUPS = (MAX_K + 63) / 64;
+// One block per tile.  The neighbours of the tile's centres are dropped into buckets, one per (cell, centre), of a list in
+// LDS (an LDS add on the table of run starts hands out the places inside a bucket, in whatever order); a neighbour's rank
+// among the smaller candidate indices of its bucket is its final place, so ties between equal (k, centre) are ordered by the
+// other index without any global sort.  The list lies in (cell, centre) order, as the output does, so that a wave's stores
+// cover a few contiguous pieces of the output.
+constexpr int FILL_LDS = 79 * 1024;       // table and list together: two blocks of 16 waves share a CU
+constexpr uint32_t LIST_CAP_MAX = 16384;  // positions of the list
+
+// LDS of a block besides the list: table [K][PITCH], two words per cell
+constexpr size_t fill_table_bytes(int K) { return (size_t)K * (PITCH + 2) * sizeof(uint32_t); }
+// neighbours that the list holds (six bytes each)
+constexpr uint32_t fill_list_cap(int K)
+{
+    const size_t n = ((size_t)FILL_LDS - fill_table_bytes(K)) / 6 / 2 * 2;
+    return n < LIST_CAP_MAX ? (uint32_t)n : LIST_CAP_MAX;
+}
+static_assert(fill_table_bytes(MAX_K) + 6 * 1024 <= FILL_LDS, "the list has room beside the largest table");
 
 // Where the fill pass writes.  out_c / out_b / out_k: centre index, candidate index, cell of each triplet (any may
 // be NULL).  With tail_index >= 0 the candidate indices go to the tail_index-th |T|-sized array behind `tail`
@@ -494,21 +503,6 @@ struct FillOut {
     uint32_t out_cap;
 };
 
-struct Emit {
-    int32_t *out_c, *out_b, *out_k;
-    const uint32_t *starts;      // the tile's table of run starts
-    uint32_t cap;
-    bool flag_last;
-    __device__ inline void operator()(uint32_t run0, uint32_t rank, int al, int k, int32_t centre, uint32_t b) const
-    {
-        const uint32_t pos = run0 + rank;
-        if (pos >= cap) return;
-        if (out_c) out_c[pos] = centre;
-        if (out_b) out_b[pos] = (int32_t)((flag_last && pos + 1u == starts[k * PITCH + al + 1]) ? (b | GATHER_LAST) : b);
-        if (out_k) out_k[pos] = k;
-    }
-};
-
 template <bool SWAP, bool EXT>
 __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__restrict__ centres, int64_t n_centres,
                                                              const int32_t *__restrict__ perm,
@@ -516,296 +510,152 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__r
                                                              const uint32_t *__restrict__ tile_cnt,
                                                              const uint32_t *__restrict__ tile_ptr,
                                                              FillOut fo,
-                                                             uint32_t *__restrict__ run_start_out, int list_cap,
+                                                             uint32_t *__restrict__ run_start_out, uint32_t list_cap,
                                                              const uint32_t *__restrict__ hits, uint32_t hit_stride,
-                                                             int64_t *__restrict__ seg_out,
-                                                             int pack_ok, const uint32_t *__restrict__ err)
+                                                             int lanes_log2, int64_t *__restrict__ seg_out,
+                                                             const uint32_t *__restrict__ err)
 {
-    // [K][PITCH]: start of each (k, centre) run, and behind a row the end of its last run; then [SEARCH_WAVES][K] bucket words
+    // [K][PITCH] starts of the (k, centre) runs relative to the tile's first triplet of cell k, and behind a row the end of
+    // its last run; [K] that first triplet; [K] what turns a relative position into one of the list; then the list:
+    // candidate indices, and (cell | centre << 8)
     extern __shared__ uint32_t tbl[];
-    __shared__ uint32_t list_all[SEARCH_WAVES][LIST_CAP_MAX];
     __shared__ uint32_t centre_n[TILE];        // neighbours of each centre
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ int32_t centre_at[TILE];        // its own index
+    uint32_t *first = tbl + K * PITCH, *to_list = first + K, *list = to_list + K;
+    uint16_t *list_at = reinterpret_cast<uint16_t *>(list + list_cap);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
     const int64_t tile = blockIdx.x;
     if (*err) return;                          // block-uniform: a prefix sum of this build gave up
     const uint32_t total = tile_ptr[(size_t)K * n_tiles];
-    Emit emit;
-    emit.out_c = fo.out_c; emit.out_b = fo.out_b; emit.out_k = fo.out_k;
-    emit.starts = tbl;
-    emit.cap = total <= fo.out_cap ? fo.out_cap : 0u;
-    emit.flag_last = false;
-    if (fo.tail_index >= 0) {
-        emit.out_b = reinterpret_cast<int32_t *>(fo.tail + (size_t)fo.tail_index * (((size_t)total * 4 + 255) / 256 * 256));
-        emit.flag_last = true;
-    }
+    const uint32_t out_cap = total <= fo.out_cap ? fo.out_cap : 0u;
+    int32_t *out_b = fo.out_b;
+    const bool flag_last = fo.tail_index >= 0;
+    if (flag_last)
+        out_b = reinterpret_cast<int32_t *>(fo.tail + (size_t)fo.tail_index * (((size_t)total * 4 + 255) / 256 * 256));
     // start of every cell's segment (Sec. 3.3.2): the offset of its first tile; entry K is |T|
     if (seg_out && tile == 0)
-        for (int k = threadIdx.x; k <= K; k += SEARCH_THREADS) seg_out[k] = (int64_t)tile_ptr[(size_t)k * n_tiles];
+        for (int k = threadIdx.x; k <= K; k += blockDim.x) seg_out[k] = (int64_t)tile_ptr[(size_t)k * n_tiles];
     const uint32_t *cnt_tile = tile_cnt + (size_t)tile * K * TILE;
-    for (int idx = threadIdx.x; idx < K * TILE; idx += SEARCH_THREADS) tbl[idx / TILE * PITCH + idx % TILE] = cnt_tile[idx];
-    if (threadIdx.x < TILE) centre_n[threadIdx.x] = 0u;
+    for (int at = threadIdx.x; at < K * TILE; at += blockDim.x) tbl[at / TILE * PITCH + at % TILE] = cnt_tile[at];
+    for (int k = threadIdx.x; k < K; k += blockDim.x) first[k] = tile_ptr[(size_t)k * n_tiles + tile];
+    if (threadIdx.x < TILE) {
+        const int64_t a = tile * TILE + threadIdx.x;
+        centre_n[threadIdx.x] = 0u;
+        centre_at[threadIdx.x] = a < n_centres ? (perm ? perm[a] : (int32_t)a) : 0;
+    }
     __syncthreads();
     uint32_t lane_n = 0;
-    for (int k = wave; k < K; k += SEARCH_WAVES) {
+    for (int k = wave; k < K; k += n_waves) {
         const uint32_t v = tbl[k * PITCH + lane];
-        const uint32_t end = tile_ptr[(size_t)k * n_tiles + tile] + wave_incl_scan_u32(v);
+        const uint32_t end = wave_incl_scan_u32(v);
         tbl[k * PITCH + lane] = end - v;
         if (lane == TILE - 1) tbl[k * PITCH + TILE] = end;
+        if (run_start_out) run_start_out[((size_t)tile * K + k) * TILE + lane] = first[k] + end - v;
         lane_n += v;
     }
     atomicAdd(&centre_n[lane], lane_n);
     __syncthreads();
-    // triplets of (cell k, centre al)
-    auto count_of = [&](int k, int al) -> uint32_t { return tbl[k * PITCH + al + 1] - tbl[k * PITCH + al]; };
-    if (run_start_out) {
-        uint32_t *dst = run_start_out + (size_t)tile * K * TILE;
-        for (int idx = threadIdx.x; idx < K * TILE; idx += SEARCH_THREADS) dst[idx] = tbl[idx / TILE * PITCH + idx % TILE];
-    }
-    uint32_t *list = list_all[wave];
-    const unsigned long long lane_lt = (1ull << lane) - 1ull;
-    // A centre whose neighbours the count pass left in `hits` needs no second search.
-    constexpr int PER_WAVE = TILE / SEARCH_WAVES;
-    const uint32_t reuse_max = hits ? (hit_stride < KEEP_MAX ? hit_stride : KEEP_MAX) : 0u;
-    Candidates<SWAP, EXT> cand[1];
-    uint32_t n_of[PER_WAVE];
-#pragma unroll
-    for (int u = 0; u < PER_WAVE; ++u) {
-        const int al = wave + u * SEARCH_WAVES;
-        n_of[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tile * TILE + al < n_centres ? centre_n[al] : 0u));
-    }
-    // Two centres at a time, one per half wave, while both of their kept lists fit 32 lanes (most do: the all-pairs
-    // ranking then costs one pass for the two).  Centres done here are marked by a zero count.
-    if (reuse_max >= 32 && list_cap >= 64) {
-        const int half = lane >> 5, l = lane & 31;
-#pragma unroll
-        for (int u = 0; u + 1 < PER_WAVE; u += 2) {
-            const uint32_t n0 = n_of[u], n1 = n_of[u + 1];
-            if (n0 == 0 || n1 == 0 || n0 > 32 || n1 > 32) continue;       // wave-uniform
-            const int al = wave + (u + half) * SEARCH_WAVES;
-            const int64_t a = tile * TILE + al;                         // both exist: their counts are not zero
-            const uint32_t n = half ? n1 : n0, nmax = n0 > n1 ? n0 : n1;
-            const uint32_t key = l < (int)n ? hits[(size_t)a * hit_stride + l] : 0xffffffffu;   // padding ranks nobody
-            list[lane] = key;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t kbase = key & ~HIT_INDEX_MASK, rel = key & HIT_INDEX_MASK;
-            const uint32_t *other = list + 32 * half;
-            uint32_t rank = 0;
-            for (uint32_t e2 = 0; e2 < nmax; e2 += 8) {                 // reads past nmax see padding or real keys of
-                uint32_t v[8];                                          // this half only up to n: entries >= n are padding
-#pragma unroll
-                for (int w = 0; w < 8; ++w) v[w] = other[e2 + w];
-#pragma unroll
-                for (int w = 0; w < 8; ++w) rank += (v[w] - kbase) < rel ? 1u : 0u;
-            }
-            if (l < (int)n) {
-                const int k = (int)(key >> HIT_INDEX_BITS);
-                emit(tbl[k * PITCH + al], rank, al, k, (int32_t)(perm ? (int64_t)perm[a] : a), rel);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            n_of[u] = n_of[u + 1] = 0;
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < PER_WAVE; ++u) {
-        const int al = wave + u * SEARCH_WAVES;
-        const int64_t a = tile * TILE + al;    // slot
-        if (a >= n_centres) break;             // wave-uniform
-        if (n_of[u] == 0) continue;            // wave-uniform
-        const int32_t ac = (int32_t)(perm ? (int64_t)perm[a] : a);   // the centre's own index
-        if (pack_ok && n_of[u] > BUCKET_FROM && n_of[u] <= (uint32_t)list_cap) {
-            // Longer lists, when cell and candidate index fit one word (cell << 24 | index).  The keys -- read back from the count pass
-            // when it kept them, found again otherwise -- are dropped into per-cell buckets of the list through one
-            // LDS word per cell (bucket start << 16 | fill count, advanced with an LDS add; the order inside a
-            // bucket is whatever the adds made it), and each key's rank among the smaller keys of its own bucket
-            // is its final slot: a key is compared with its cell's neighbours only.
-            const uint32_t n = n_of[u];
-            uint32_t *wk = tbl + K * PITCH + wave * K;
-            uint32_t run = 0;
-            for (int k0 = 0; k0 < K; k0 += 64) {
-                const int k = k0 + lane;
-                const uint32_t c1 = k < K ? count_of(k, al) : 0u;
-                const uint32_t inc = wave_incl_scan_u32(c1);
-                if (k < K) wk[k] = (run + inc - c1) << 16;
-                run += (uint32_t)__shfl((int)inc, 63, 64);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            if (n <= reuse_max) {
-                const uint32_t *mine = hits + (size_t)a * hit_stride;
-                for (uint32_t e = lane; e < n; e += 64) {
-                    const uint32_t key = mine[e];
-                    const uint32_t old = atomicAdd(&wk[key >> HIT_INDEX_BITS], 1u);
-                    list[(old >> 16) + (old & 0xffffu)] = key;
-                }
-            } else {
-                Candidates<SWAP, EXT> &c = cand[0];
-                c.open(centres, ac, g, q, lane);
-                for (uint32_t base = 0; base < c.total; base += 64) {
-                    int b, k;
-                    if (c.fetch(base + lane, g, q, b, k)) {
-                        const uint32_t old = atomicAdd(&wk[k], 1u);
-                        list[(old >> 16) + (old & 0xffffu)] = ((uint32_t)k << HIT_INDEX_BITS) | (uint32_t)b;
-                    }
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            for (uint32_t e0 = 0; e0 < n; e0 += 64) {
-                const uint32_t e = e0 + lane;
-                const bool have = e < n;
-                const uint32_t key = have ? list[e] : 0u;
-                const int k = (int)(key >> HIT_INDEX_BITS);
-                const uint32_t w = have ? wk[k] : 0u;
-                const uint32_t b0 = w >> 16, nk = w & 0xffffu;
-                uint32_t rank = 0;
-                for (uint32_t j = 0; __ballot(j < nk) != 0ull; ++j) {
-                    const uint32_t v = j < nk ? list[b0 + j] : 0xffffffffu;
-                    rank += v < key ? 1u : 0u;
-                }
-                if (have) emit(tbl[k * PITCH + al], rank, al, k, ac, key & HIT_INDEX_MASK);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            continue;
-        }
-        if (n_of[u] <= reuse_max && n_of[u] <= (uint32_t)list_cap) {
-            // rank the stored (cell, index) keys by comparing all pairs
-            const uint32_t n = n_of[u];
-            const uint32_t *mine = hits + (size_t)a * hit_stride;
-            for (uint32_t e = lane; e < n; e += 64) list[e] = mine[e];
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            for (uint32_t e = lane; e < n; e += 64) {
-                const uint32_t key = list[e];
-                const uint32_t kbase = key & ~HIT_INDEX_MASK, rel = key & HIT_INDEX_MASK;
-                uint32_t rank = 0, e2 = 0;
-                for (; e2 + 8 <= n; e2 += 8) {
-                    uint32_t v[8];
-#pragma unroll
-                    for (int w = 0; w < 8; ++w) v[w] = list[e2 + w];
-#pragma unroll
-                    for (int w = 0; w < 8; ++w) rank += (v[w] - kbase) < rel ? 1u : 0u;
-                }
-                for (; e2 < n; ++e2) rank += (list[e2] - kbase) < rel ? 1u : 0u;
-                const int k = (int)(key >> HIT_INDEX_BITS);
-                emit(tbl[k * PITCH + al], rank, al, k, ac, rel);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            continue;
-        }
-        // bucket of cell k = [bbase, bbase + bcnt) in the list; lane (k % 64) of group (k / 64) holds it
-        uint32_t bcnt[KGROUPS], bbase[KGROUPS], bcur[KGROUPS];
-        uint32_t n = 0;
-#pragma unroll
-        for (int gi = 0; gi < KGROUPS; ++gi) {
-            bcnt[gi] = 0; bbase[gi] = n; bcur[gi] = 0;
-            if (gi * 64 < K) {                 // wave-uniform
-                const int k = gi * 64 + lane;
-                bcnt[gi] = k < K ? count_of(k, al) : 0u;
-                const uint32_t inc = wave_incl_scan_u32(bcnt[gi]);
-                bbase[gi] = n + inc - bcnt[gi];
-                n += __shfl(inc, 63, 64);
-            }
-        }
-        if (n == 0) continue;                  // wave-uniform
-        Candidates<SWAP, EXT> &c = cand[0];
-        c.open(centres, ac, g, q, lane);
-        if (n <= SMALL_LIST && n <= (uint32_t)list_cap) {
-            // few neighbours: one flat list of (cell, index) keys in arrival order, rank by comparing all pairs
-            unsigned long long *keys = reinterpret_cast<unsigned long long *>(list);
-            uint32_t filled = 0;
-            for (uint32_t base = 0; base < c.total; base += 64) {
-                int b, k;
-                const bool hit = c.fetch(base + lane, g, q, b, k);
-                const unsigned long long m = __ballot(hit);
-                if (hit) keys[filled + (uint32_t)__popcll(m & lane_lt)] = ((unsigned long long)(uint32_t)k << 32) | (uint32_t)b;
-                filled += (uint32_t)__popcll(m);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            for (uint32_t e = lane; e < n; e += 64) {
-                const unsigned long long key = keys[e];
-                const unsigned long long kbase = key & 0xffffffff00000000ull;
-                const unsigned long long rel = key - kbase;
-                uint32_t rank = 0, e2 = 0;
-                for (; e2 + 8 <= n; e2 += 8) {
-                    unsigned long long v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = keys[e2 + u];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) rank += ((v[u] - kbase) < rel) ? 1u : 0u;
-                }
-                for (; e2 < n; ++e2) rank += ((keys[e2] - kbase) < rel) ? 1u : 0u;
-                const int k = (int)(key >> 32);
-                emit(tbl[k * PITCH + al], rank, al, k, ac, (uint32_t)key);
-            }
-        } else if (n <= (uint32_t)list_cap) {
-            for (uint32_t base = 0; base < c.total; base += 64) {
-                int b, k;
-                const bool hit = c.fetch(base + lane, g, q, b, k);
-                unsigned long long rem = __ballot(hit);
-                while (rem) {                  // one round per distinct cell among this batch's hits
-                    const int kk = __shfl(k, __ffsll((long long)rem) - 1, 64);
-                    const unsigned long long mk = __ballot(hit && k == kk);
-                    uint32_t slot0 = 0;
-#pragma unroll
-                    for (int gi = 0; gi < KGROUPS; ++gi)
-                        if ((kk >> 6) == gi) {
-                            slot0 = __shfl(bbase[gi] + bcur[gi], kk & 63, 64);
-                            if (lane == (kk & 63)) bcur[gi] += (uint32_t)__popcll(mk);
-                        }
-                    if (hit && k == kk) list[slot0 + (uint32_t)__popcll(mk & lane_lt)] = (uint32_t)b;
-                    rem &= ~mk;
-                }
-            }
-            // the list was written by other lanes of this wave: LDS operations of one wave complete in
-            // order, the fence keeps the compiler from moving the reads above the writes
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int gi = 0; gi < KGROUPS; ++gi) {
-                unsigned long long occ = __ballot(bcnt[gi] != 0);
-                while (occ) {                  // buckets of this group, ascending cell
-                    const int kl = __ffsll((long long)occ) - 1;
-                    occ &= occ - 1;
-                    const int k = gi * 64 + kl;
-                    const uint32_t nk = __shfl(bcnt[gi], kl, 64), b0 = __shfl(bbase[gi], kl, 64);
-                    const uint32_t run0 = tbl[k * PITCH + al];
-                    for (uint32_t e0 = 0; e0 < nk; e0 += 64) {
-                        const uint32_t e = e0 + lane;
-                        const uint32_t mine = e < nk ? list[b0 + e] : 0xffffffffu;
-                        uint32_t rank = 0, e2 = 0;
-                        for (; e2 + 8 <= nk; e2 += 8) {
-                            uint32_t v[8];
-#pragma unroll
-                            for (int u = 0; u < 8; ++u) v[u] = list[b0 + e2 + u];
-#pragma unroll
-                            for (int u = 0; u < 8; ++u) rank += v[u] < mine ? 1u : 0u;
-                        }
-                        for (; e2 < nk; ++e2) rank += list[b0 + e2] < mine ? 1u : 0u;
-                        if (e < nk) emit(run0, rank, al, k, ac, mine);
-                    }
-                }
-            }
-        } else {
-            // more neighbours than the list holds: rank each one by scanning the candidates again
-            for (uint32_t base = 0; base < c.total; base += 64) {
+    const uint32_t complete = hits ? hit_stride : 0u;      // lists up to this long were kept whole by the count pass
+    const uint32_t upto = wave_incl_scan_u32(centre_n[lane]);       // neighbours of the centres 0 .. lane
+    // as many centres at a time as the list holds: usually all of them
+    int c0 = 0;
+    while (c0 < TILE) {
+        const uint32_t before = c0 > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto, c0 - 1) : 0u;
+        const int c1 = c0 + (int)__popcll(__ballot(lane >= c0 && upto - before <= list_cap));
+        if (c1 == c0) {
+            // a centre with more neighbours than the list holds: rank each one by scanning the candidates again
+            Candidates<SWAP, EXT> c;
+            c.open(centres, centre_at[c0], g, q, lane);
+            for (uint32_t base = (uint32_t)wave * 64u; base < c.total; base += (uint32_t)n_waves * 64u) {
                 int b, k;
                 const bool hit = c.fetch(base + lane, g, q, b, k);
                 uint32_t rank = 0;
-                for (uint32_t idx2 = 0; idx2 < c.total; ++idx2) {
+                for (uint32_t other = 0; other < c.total; ++other) {
                     int b2, k2;
-                    const bool hit2 = c.fetch(idx2, g, q, b2, k2);
+                    const bool hit2 = c.fetch(other, g, q, b2, k2);
                     rank += (hit2 && k2 == k && b2 < b) ? 1u : 0u;
                 }
-                if (hit) emit(tbl[k * PITCH + al], rank, al, k, ac, (uint32_t)b);
+                if (hit) {
+                    const uint32_t pos = first[k] + tbl[k * PITCH + c0] + rank;
+                    const bool last = tbl[k * PITCH + c0] + rank + 1u == tbl[k * PITCH + c0 + 1];
+                    if (pos < out_cap) {
+                        if (fo.out_c) fo.out_c[pos] = centre_at[c0];
+                        if (out_b) out_b[pos] = (int32_t)((flag_last && last) ? ((uint32_t)b | GATHER_LAST) : (uint32_t)b);
+                        if (fo.out_k) fo.out_k[pos] = k;
+                    }
+                }
             }
+            __syncthreads();
+            // (an entry whose centre is done holds the end of its run)
+            for (int k = threadIdx.x; k < K; k += blockDim.x) tbl[k * PITCH + c0] = tbl[k * PITCH + c0 + 1];
+            __syncthreads();
+            ++c0;
+            continue;
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)upto, c1 - 1) - before;
+        if (n > 0u) {                                      // block-uniform
+            if (wave == 0) {
+                uint32_t run = 0;
+                for (int k0 = 0; k0 < K; k0 += 64) {
+                    const int k = k0 + lane;
+                    const uint32_t s = k < K ? tbl[k * PITCH + c0] : 0u, e = k < K ? tbl[k * PITCH + c1] : 0u;
+                    const uint32_t inc = wave_incl_scan_u32(e - s);
+                    if (k < K) to_list[k] = run + inc - e;
+                    run += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+                }
+            }
+            __syncthreads();
+            auto place = [&](int al, int k, uint32_t b) {
+                const uint32_t p = to_list[k] + atomicAdd(&tbl[k * PITCH + al], 1u);
+                if (p < list_cap) {
+                    list[p] = b;
+                    list_at[p] = (uint16_t)(k | al << 8);
+                }
+            };
+            {   // neighbours that the count pass kept: 2^lanes_log2 lanes per centre
+                const int l = lane & ((1 << lanes_log2) - 1), per = 64 >> lanes_log2;
+                for (int al = c0 + wave * per + (lane >> lanes_log2); al < c1; al += n_waves * per) {
+                    const uint32_t m = centre_n[al];
+                    if (m > complete) continue;
+                    const uint32_t *mine = hits + (size_t)(tile * TILE + al) * hit_stride;
+                    for (uint32_t e = l; e < m; e += 1u << lanes_log2) {
+                        const uint32_t key = mine[e];
+                        place(al, (int)(key >> HIT_INDEX_BITS), key & HIT_INDEX_MASK);
+                    }
+                }
+            }
+            for (int al = c0 + wave; al < c1; al += n_waves) {      // others: searched again, one wave per centre
+                if ((uint32_t)__builtin_amdgcn_readfirstlane((int)centre_n[al]) <= complete) continue;
+                Candidates<SWAP, EXT> c;
+                c.open(centres, centre_at[al], g, q, lane);
+                for (uint32_t base = 0; base < c.total; base += 64) {
+                    int b, k;
+                    if (c.fetch(base + lane, g, q, b, k)) place(al, k, (uint32_t)b);
+                }
+            }
+            __syncthreads();
+            for (uint32_t p = threadIdx.x; p < n; p += blockDim.x) {
+                const uint32_t b = list[p], at = list_at[p];
+                const int k = (int)(at & 255u), al = (int)(at >> 8);
+                // every entry up to this centre's holds the end of its run by now
+                const uint32_t s = al > 0 ? tbl[k * PITCH + al - 1] : 0u, e = tbl[k * PITCH + al];
+                const uint32_t *run = list + to_list[k] + s;
+                uint32_t rank = 0, j = 0;
+                for (; j + 4 <= e - s; j += 4) {
+                    const uint32_t v0 = run[j], v1 = run[j + 1], v2 = run[j + 2], v3 = run[j + 3];
+                    rank += (v0 < b ? 1u : 0u) + (v1 < b ? 1u : 0u) + (v2 < b ? 1u : 0u) + (v3 < b ? 1u : 0u);
+                }
+                for (; j < e - s; ++j) rank += run[j] < b ? 1u : 0u;
+                const uint32_t pos = first[k] + s + rank;
+                if (pos < out_cap) {
+                    if (fo.out_c) fo.out_c[pos] = centre_at[al];
+                    if (out_b) out_b[pos] = (int32_t)((flag_last && s + rank + 1u == e) ? (b | GATHER_LAST) : b);
+                    if (fo.out_k) fo.out_k[pos] = k;
+                }
+            }
+            __syncthreads();
+        }
+        c0 = c1;
     }
 }
 
@@ -1166,7 +1016,8 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     const Reuse no_reuse{nullptr, nullptr, nullptr};
     uint32_t *err = reinterpret_cast<uint32_t *>(ws + bs.err_off);
     auto scan_scratch = [&](int which) -> void * { return ws + bs.scan_off + (size_t)which * bs.scan_stride; };
-    const int list_cap = (test_flags & PCPP_BUILD_TEST_SHORT_LISTS) ? 40 : LIST_CAP_MAX;
+    const uint32_t list_cap = (test_flags & PCPP_BUILD_TEST_SHORT_LISTS) ? 40 : fill_list_cap(K);
+    auto lanes_log2 = [](uint32_t stride) { return stride >= 256 ? 6 : (stride > 64 ? 5 : 4); };   // (lists are half full)
 
     // Where |T| lands.  Pinned host memory is written by the device itself (the prefix sum's last block), so the
     // host can pick the count up while the second pass is already running; pageable memory gets it through a
@@ -1220,9 +1071,7 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     // the first pass stages the lists that it keeps
     const size_t lds_f = lds + (keep_hits ? (size_t)SEARCH_WAVES * bs.fwd_stride * sizeof(uint32_t) : 0);
     const size_t lds_b = lds + (keep_hits ? (size_t)SEARCH_WAVES * bs.bwd_stride * sizeof(uint32_t) : 0);
-    // the second pass also keeps one bucket word per (wave, cell); a key packs cell and candidate index into 32 bits
-    const size_t lds_fill = lds + (size_t)SEARCH_WAVES * K * sizeof(uint32_t);
-    const int pack_ok = !wide_keys && K <= 256 && n_in < (1 << HIT_INDEX_BITS) && n_out < (1 << HIT_INDEX_BITS);
+    const size_t lds_fill = fill_table_bytes(K) + (size_t)fill_list_cap(K) * 6;
     if (lds_f > (size_t)32 * 1024 || lds_b > (size_t)32 * 1024) {
         // large t: the per-tile table plus the neighbour lists exceed the default dynamic LDS limit
         if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&query_count<false, false, true>)
@@ -1343,10 +1192,10 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         {
                 if (ext) query_fill<false, true><<<(unsigned)nt_o, SEARCH_THREADS, lds_fill, stream>>>(
             out_xyz, n_out, nullptr, grid_in, q, K, nt_o, f_cnt, f_off, FillOut{tri_o, tri_i, tri_k, nullptr, -1, tri_cap},
-            f_runs, list_cap, pub_hits, bs.fwd_stride, seg_offsets, pack_ok, err);
+            f_runs, list_cap, pub_hits, bs.fwd_stride, lanes_log2(bs.fwd_stride), seg_offsets, err);
                 else query_fill<false, false><<<(unsigned)nt_o, SEARCH_THREADS, lds_fill, stream>>>(
             out_xyz, n_out, nullptr, grid_in, q, K, nt_o, f_cnt, f_off, FillOut{tri_o, tri_i, tri_k, nullptr, -1, tri_cap},
-            f_runs, list_cap, pub_hits, bs.fwd_stride, seg_offsets, pack_ok, err);
+            f_runs, list_cap, pub_hits, bs.fwd_stride, lanes_log2(bs.fwd_stride), seg_offsets, err);
             }
         PCPP_HIP_CHECK(hipGetLastError());
     } else {
@@ -1407,11 +1256,11 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
                 if (ext) query_fill<false, true><<<(unsigned)nt_o, SEARCH_THREADS, lds_fill, stream>>>(
                 out_xyz, n_out, perm_o, grid_in, q, K, nt_o, f_cnt, sf_ptr,
                 FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.fwd.gather_index, tail_cap},
-                reinterpret_cast<uint32_t *>(pb + pl.fwd.run_start_off), list_cap, f_hits, bs.fwd_stride, nullptr, pack_ok, err);
+                reinterpret_cast<uint32_t *>(pb + pl.fwd.run_start_off), list_cap, f_hits, bs.fwd_stride, lanes_log2(bs.fwd_stride), nullptr, err);
                 else query_fill<false, false><<<(unsigned)nt_o, SEARCH_THREADS, lds_fill, stream>>>(
                 out_xyz, n_out, perm_o, grid_in, q, K, nt_o, f_cnt, sf_ptr,
                 FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.fwd.gather_index, tail_cap},
-                reinterpret_cast<uint32_t *>(pb + pl.fwd.run_start_off), list_cap, f_hits, bs.fwd_stride, nullptr, pack_ok, err);
+                reinterpret_cast<uint32_t *>(pb + pl.fwd.run_start_off), list_cap, f_hits, bs.fwd_stride, lanes_log2(bs.fwd_stride), nullptr, err);
             }
             PCPP_HIP_CHECK(hipGetLastError());
         }
@@ -1437,11 +1286,11 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
                 if (ext) query_fill<true, true><<<(unsigned)nt_i, SEARCH_THREADS, lds_fill, stream>>>(
                 in_xyz, n_in, perm_i, grid_out, qs, K, nt_i, b_cnt, b_ptr,
                 FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.bwd.gather_index, tail_cap}, b_runs, list_cap,
-                b_hits, bs.bwd_stride, nullptr, pack_ok, err);
+                b_hits, bs.bwd_stride, lanes_log2(bs.bwd_stride), nullptr, err);
                 else query_fill<true, false><<<(unsigned)nt_i, SEARCH_THREADS, lds_fill, stream>>>(
                 in_xyz, n_in, perm_i, grid_out, qs, K, nt_i, b_cnt, b_ptr,
                 FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.bwd.gather_index, tail_cap}, b_runs, list_cap,
-                b_hits, bs.bwd_stride, nullptr, pack_ok, err);
+                b_hits, bs.bwd_stride, lanes_log2(bs.bwd_stride), nullptr, err);
             }
             PCPP_HIP_CHECK(hipGetLastError());
         }
