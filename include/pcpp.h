@@ -59,7 +59,7 @@ extern "C" {
                                     neighbours in space whatever the caller's point order, which wide layers need
                                     (they share source rows and weight slices through the caches).  The public
                                     triplet arrays, every result and every tolerance are unchanged; the build
-                                    takes about a third longer. */
+                                    takes about twice as long. */
 /* testing aids, accepted in plan_flags by pcpp_build_triplets only; results are identical with or without */
 #define PCPP_BUILD_TEST_SHORT_LISTS  0x100  /* keep at most 40 neighbours of a centre on chip: longer lists take
                                                the path that ranks by scanning the candidates again          */
@@ -108,12 +108,11 @@ PCPP_API int pcpp_version(void);
  *                        triplets regrouped by (k, i, o) for the input gradient
  *                        (PCPP_PLAN_BWD_INPUT).  plan_flags selects the parts; NULL => none.
  *   workspace            scratch of pcpp_build_triplets_workspace_bytes(...) bytes, 256-byte
- *                        aligned; contents are undefined afterwards.  With at least
- *                        pcpp_build_triplets_workspace_bytes_for(..., capacity) bytes the neighbours
- *                        found while counting are kept and the second pass does not search again
- *                        (same results, about a third less time); a plan in spatial order, which groups
- *                        the same neighbourhoods a second time, then regroups those lists instead of
- *                        searching twice.
+ *                        aligned; contents are undefined afterwards.  With
+ *                        pcpp_build_triplets_workspace_bytes_for(..., capacity) bytes every centre's
+ *                        neighbours are searched once and kept, and all later passes read those lists;
+ *                        with less room the lists are shorter, and centres with more neighbours are
+ *                        searched again in each pass (same results).
  * in_xyz [n_in,3] and out_xyz [n_out,3] may alias (outputs at the inputs).
  * Errors: INVALID_ARG (null xyz with n > 0, radius not finite or <= 0, t outside 1..PCPP_MAX_T,
  * some but not all tri_* NULL, unknown flag bits), CAPACITY, WORKSPACE, UNSUPPORTED (|T| >= 2^31), HIP.

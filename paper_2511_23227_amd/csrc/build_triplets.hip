@@ -17,12 +17,6 @@ namespace {
 constexpr unsigned long long EMPTY_KEY = ~0ull;
 constexpr int CELL_BIAS = 1 << 20;
 constexpr double CELL_CLAMP = (double)((1 << 20) - 2);   // +-1 stencil steps stay inside 21 bits
-constexpr int SEARCH_THREADS = 1024;                      // 16 waves share a tile of 64 centres: 4 centres each
-constexpr int SEARCH_WAVES = SEARCH_THREADS / 64;
-// Pitch of the [K][TILE] tables in LDS.  A wave works on one centre, so its lanes touch the words of one column, at most a
-// few of them in the same cell: with rows of 64 words they all lie in one bank.  The word behind a row holds the end of the
-// row's last run where the table holds starts of runs.
-constexpr int PITCH = TILE + 1;
 
 __device__ inline uint32_t hash_key(unsigned long long k)
 {
@@ -85,6 +79,16 @@ __device__ inline void grid_cell3(float fx, float fy, float fz, const GridMap &m
         gx = grid_coord(fx, m.inv_g);
         gy = grid_coord(fy, m.inv_g);
         gz = grid_coord(fz, m.inv_g);
+    }
+}
+
+template <bool EXT>
+__device__ inline void grid_cell(float fx, float fy, float fz, const GridMap &m, int &gx, int &gy, int &gz)
+{
+    if constexpr (EXT) {
+        grid_cell3(fx, fy, fz, m, gx, gy, gz);
+    } else {
+        gx = grid_coord(fx, m.inv_g); gy = grid_coord(fy, m.inv_g); gz = grid_coord(fz, m.inv_g);
     }
 }
 
@@ -162,6 +166,7 @@ struct QueryParams {
     double R;         // (double)radius, or the voxel pitch
     double r2;        // R * R
     double inv_cell;  // t / (2 R)
+    double sign;      // offset input minus output = sign (candidate - centre): 1 where the centres are outputs, -1 inputs
     int t;
     int voxel_mode, h;
     const int32_t *c_off, *d_off;
@@ -181,42 +186,43 @@ __device__ inline uint32_t wave_incl_scan_u32(uint32_t v)
     return v;
 }
 
-// Candidates of one centre, held across the lanes of a wave: lane j < 27 owns stencil cell j.
+// the same within each half of the wave
+__device__ inline uint32_t half_incl_scan_u32(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+    return v;
+}
+
+// A value that the compiler has to work out at this place: what rarely taken code derives from it is not kept in registers
+// all along the loops around it (the fill pass spilled twenty for that).
+__device__ inline int here(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+__device__ inline uint32_t lane_value(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
+__device__ inline float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+
+// Candidates around one grid cell, held across the lanes of a wave: lane j < 27 owns stencil cell j.
 // Every method must be called by all 64 lanes of the wave (it uses cross-lane reads).
-// EXT: the voxel operator and batches of clouds are compiled in (the plain search kernels, which are bound by
-// instruction issue, do without their tests).
-template <bool SWAP, bool EXT>
-struct Candidates {
-    double cx, cy, cz;       // centre coordinate (ball mode) or its voxel (voxel mode)
+struct Stencil {
     uint32_t my_start;       // lane j: first candidate of stencil cell j
     uint32_t my_excl;        // lane j: candidates in cells before j
     uint32_t total;
-    int d_lo, d_hi;          // candidates of the centre's own cloud: indices [d_lo, d_hi)
 
-    __device__ inline void open(const float *__restrict__ centres, int64_t a, const GridView &g, const QueryParams &q,
-                                int lane)
+    // (gx, gy, gz): the middle cell; batch: the cloud's number, or -1 where there is one cloud
+    __device__ inline void open(int gx, int gy, int gz, int batch, const GridView &g, int lane)
     {
-        const float fx = centres[3 * a], fy = centres[3 * a + 1], fz = centres[3 * a + 2];
-        if (EXT && q.voxel_mode) { cx = voxel_of(fx, q.R); cy = voxel_of(fy, q.R); cz = voxel_of(fz, q.R); }
-        else { cx = (double)fx; cy = (double)fy; cz = (double)fz; }
-        int batch = 0;
-        d_lo = 0; d_hi = 0x7fffffff;
-        if (EXT && q.c_off) {
-            batch = find_batch(q.c_off, q.n_batches, (int)a);
-            d_lo = q.d_off[batch]; d_hi = q.d_off[batch + 1];
-        }
         uint32_t cnt = 0;
         my_start = 0;
         if (lane < 27) {
-            int gx, gy, gz;
-            if constexpr (EXT) {
-                grid_cell3(fx, fy, fz, g.map, gx, gy, gz);
-            } else {
-                gx = grid_coord(fx, g.map.inv_g); gy = grid_coord(fy, g.map.inv_g); gz = grid_coord(fz, g.map.inv_g);
-            }
-            gx += lane / 9 - 1; gy += (lane / 3) % 3 - 1; gz += lane % 3 - 1;
-            unsigned long long key = pack_key(gx, gy, gz);
-            if (EXT && q.c_off) key = mix_batch(key, batch);
+            unsigned long long key = pack_key(gx + lane / 9 - 1, gy + (lane / 3) % 3 - 1, gz + lane % 3 - 1);
+            if (batch >= 0) key = mix_batch(key, batch);
             uint32_t slot = hash_key(key) & g.mask;
             for (;;) {
                 const unsigned long long kk = g.keys[slot];
@@ -231,430 +237,609 @@ struct Candidates {
         }
         const uint32_t incl = wave_incl_scan_u32(cnt);
         my_excl = incl - cnt;
-        total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        total = lane_value(incl, 63);
     }
 
-    // Candidate number idx (idx may differ per lane).  Returns whether it is a neighbour;
-    // b = its original index, k = its kernel cell.  With MIRROR, k2 = the cell of the opposite offset, i.e.
-    // the cell this pair falls in when the roles of the two points are swapped.
-    __device__ inline bool fetch(uint32_t idx, const GridView &g, const QueryParams &q, int &b, int &k) const
+    // where candidate number idx < total (idx may differ per lane) lies among g.pts
+    __device__ inline uint32_t place(uint32_t idx) const
     {
-        int k2;
-        return fetch2<false>(idx, g, q, b, k, k2);
-    }
-
-    // Ball mode, the pieces of the test.  d = input - output, in binary64, no contraction.
-    __device__ inline void offset_of(const float4 &p, double &dx, double &dy, double &dz) const
-    {
-        dx = SWAP ? __dsub_rn(cx, (double)p.x) : __dsub_rn((double)p.x, cx);
-        dy = SWAP ? __dsub_rn(cy, (double)p.y) : __dsub_rn((double)p.y, cy);
-        dz = SWAP ? __dsub_rn(cz, (double)p.z) : __dsub_rn((double)p.z, cz);
-    }
-    __device__ static inline bool inside(double dx, double dy, double dz, const QueryParams &q)
-    {
-        return __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz)) <= q.r2;
-    }
-    // kernel cell of the offset, and with MIRROR of the exactly negated offset (what the swapped subtraction gives)
-    template <bool MIRROR>
-    __device__ static inline void cells_of(double dx, double dy, double dz, const QueryParams &q, int &k, int &k2)
-    {
-        const int tm1 = q.t - 1;
-        const double ux = floor(__dmul_rn(__dadd_rn(dx, q.R), q.inv_cell));
-        const double uy = floor(__dmul_rn(__dadd_rn(dy, q.R), q.inv_cell));
-        const double uz = floor(__dmul_rn(__dadd_rn(dz, q.R), q.inv_cell));
-        int kx = ux < 0.0 ? 0 : (int)fmin(ux, (double)tm1);
-        int ky = uy < 0.0 ? 0 : (int)fmin(uy, (double)tm1);
-        int kz = uz < 0.0 ? 0 : (int)fmin(uz, (double)tm1);
-        k = (kx * q.t + ky) * q.t + kz;
-        if constexpr (MIRROR) {
-            const double vx = floor(__dmul_rn(__dadd_rn(-dx, q.R), q.inv_cell));
-            const double vy = floor(__dmul_rn(__dadd_rn(-dy, q.R), q.inv_cell));
-            const double vz = floor(__dmul_rn(__dadd_rn(-dz, q.R), q.inv_cell));
-            const int mx = vx < 0.0 ? 0 : (int)fmin(vx, (double)tm1);
-            const int my = vy < 0.0 ? 0 : (int)fmin(vy, (double)tm1);
-            const int mz = vz < 0.0 ? 0 : (int)fmin(vz, (double)tm1);
-            k2 = (mx * q.t + my) * q.t + mz;
-        }
-    }
-
-    template <bool MIRROR>
-    __device__ inline bool fetch2(uint32_t idx, const GridView &g, const QueryParams &q, int &b, int &k, int &k2) const
-    {
-        const bool in_range = idx < total;
-        const uint32_t id = in_range ? idx : 0u;
         int j = 0;
 #pragma unroll
         for (int step = 16; step >= 1; step >>= 1) {
             const int c = j + step;
             const int cc = c <= 26 ? c : 26;
             const uint32_t e = __shfl(my_excl, cc, 64);
-            if (c <= 26 && e <= id) j = c;
+            if (c <= 26 && e <= idx) j = c;
         }
         const uint32_t s = __shfl(my_start, j, 64);
         const uint32_t e = __shfl(my_excl, j, 64);
+        return s + (idx - e);
+    }
+};
+
+// d = candidate - centre, in binary64, no contraction: the test of the ball, which does not depend on its sign
+__device__ inline bool inside_ball(double dx, double dy, double dz, const QueryParams &q)
+{
+    return __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz)) <= q.r2;
+}
+
+// Kernel cell of the offset d = input - output of a neighbour.  A neighbour's |d| exceeds R by rounding at most, so
+// (d + R) t / (2 R) lies above -1 and cutting the fraction off is floor and the clamp at 0 in one.
+__device__ inline int ball_cell(double dx, double dy, double dz, const QueryParams &q)
+{
+    const int tm1 = q.t - 1;
+    const int kx = (int)__dmul_rn(__dadd_rn(dx, q.R), q.inv_cell);
+    const int ky = (int)__dmul_rn(__dadd_rn(dy, q.R), q.inv_cell);
+    const int kz = (int)__dmul_rn(__dadd_rn(dz, q.R), q.inv_cell);
+    return __mul24(__mul24(kx < tm1 ? kx : tm1, q.t) + (ky < tm1 ? ky : tm1), q.t) + (kz < tm1 ? kz : tm1);
+}
+
+// Voxel mode: the offset of the voxels is an exact small integer in binary64
+__device__ inline bool inside_cube(double ox, double oy, double oz, const QueryParams &q)
+{
+    const double h = (double)q.h;
+    return fabs(ox) <= h && fabs(oy) <= h && fabs(oz) <= h;
+}
+__device__ inline int cube_cell(double ox, double oy, double oz, const QueryParams &q)
+{
+    return (((int)ox + q.h) * q.t + (int)oy + q.h) * q.t + (int)oz + q.h;
+}
+
+// One centre's search by a whole wave.  EXT: the voxel operator and batches of clouds are compiled in (the plain search,
+// which is bound by instruction issue, does without their tests).
+template <bool EXT>
+struct Candidates {
+    double cx, cy, cz;       // centre coordinate (ball mode) or its voxel (voxel mode)
+    Stencil st;
+    int d_lo, d_hi;          // candidates of the centre's own cloud: indices [d_lo, d_hi)
+
+    __device__ inline void open(const float *__restrict__ centres, int64_t a, const GridView &g, const QueryParams &q,
+                                int lane)
+    {
+        const float fx = centres[3 * a], fy = centres[3 * a + 1], fz = centres[3 * a + 2];
+        if (EXT && q.voxel_mode) { cx = voxel_of(fx, q.R); cy = voxel_of(fy, q.R); cz = voxel_of(fz, q.R); }
+        else { cx = (double)fx; cy = (double)fy; cz = (double)fz; }
+        int batch = -1;
+        d_lo = 0; d_hi = 0x7fffffff;
+        if (EXT && q.c_off) {
+            batch = find_batch(q.c_off, q.n_batches, (int)a);
+            d_lo = q.d_off[batch]; d_hi = q.d_off[batch + 1];
+        }
+        int gx, gy, gz;
+        grid_cell<EXT>(fx, fy, fz, g.map, gx, gy, gz);
+        st.open(gx, gy, gz, batch, g, lane);
+    }
+
+    // Candidate number idx (idx may differ per lane).  Returns whether it is a neighbour; b = its original index, k = its
+    // kernel cell, k2 = the cell of the opposite offset, i.e. the cell this pair falls in when the roles are swapped.
+    __device__ inline bool fetch(uint32_t idx, const GridView &g, const QueryParams &q, int &b, int &k, int &k2) const
+    {
+        const bool in_range = idx < st.total;
+        const uint32_t at = st.place(in_range ? idx : 0u);
         bool hit = false;
         b = 0; k = 0; k2 = 0;
         if (in_range) {
-            const float4 p = g.pts[s + (id - e)];
+            const float4 p = g.pts[at];
             b = __float_as_int(p.w);
             if (EXT && q.voxel_mode) {
-                // voxel offset, input minus output; exact small integers in binary64
-                const double vx = voxel_of(p.x, q.R), vy = voxel_of(p.y, q.R), vz = voxel_of(p.z, q.R);
-                const double ox = SWAP ? cx - vx : vx - cx, oy = SWAP ? cy - vy : vy - cy, oz = SWAP ? cz - vz : vz - cz;
-                const double hh = (double)q.h;
-                hit = fabs(ox) <= hh && fabs(oy) <= hh && fabs(oz) <= hh && b >= d_lo && b < d_hi;
-                if (hit) {
-                    const int ix = (int)ox, iy = (int)oy, iz = (int)oz;
-                    k = ((ix + q.h) * q.t + iy + q.h) * q.t + iz + q.h;
-                    if constexpr (MIRROR) k2 = ((q.h - ix) * q.t + q.h - iy) * q.t + q.h - iz;
-                }
+                const double ox = q.sign * (voxel_of(p.x, q.R) - cx), oy = q.sign * (voxel_of(p.y, q.R) - cy), oz = q.sign * (voxel_of(p.z, q.R) - cz);
+                hit = inside_cube(ox, oy, oz, q) && b >= d_lo && b < d_hi;
+                if (hit) { k = cube_cell(ox, oy, oz, q); k2 = cube_cell(-ox, -oy, -oz, q); }
                 return hit;
             }
-            double dx, dy, dz;
-            offset_of(p, dx, dy, dz);
-            hit = inside(dx, dy, dz, q) && (!EXT || (b >= d_lo && b < d_hi));
-            cells_of<MIRROR>(dx, dy, dz, q, k, k2);
+            const double dx = q.sign * __dsub_rn((double)p.x, cx), dy = q.sign * __dsub_rn((double)p.y, cy), dz = q.sign * __dsub_rn((double)p.z, cz);
+            hit = inside_ball(dx, dy, dz, q) && (!EXT || (b >= d_lo && b < d_hi));
+            if (hit) { k = ball_cell(dx, dy, dz, q); k2 = ball_cell(-dx, -dy, -dz, q); }
         }
         return hit;
     }
 };
 
-constexpr uint32_t KEEP_MAX = 256;        // longest neighbour list the count pass keeps per centre
-constexpr int HIT_INDEX_BITS = 24;         // a stored hit = cell << 24 | candidate index
+constexpr uint32_t KEEP_MAX = 512;        // longest neighbour list that is kept per centre
+constexpr int HIT_INDEX_BITS = 24;        // a stored hit = cell << 24 | candidate index
 constexpr uint32_t HIT_INDEX_MASK = (1u << HIT_INDEX_BITS) - 1u;
 
-// ---- pass 1: neighbours per (cell k, centre) --------------------------------------------------
-// One block per tile of TILE centres, one wave per centre at a time.  Outputs of one side:
-//   tile_cnt   [n_tiles][K][TILE]   (may be NULL: totals only)
-//   tile_k_cnt [K * n_tiles]        k-major, input of the prefix sum
-//   hits       [n_centres][hit_stride] (may be NULL): every centre's first neighbours, cell << 24 | index
-// With BOTH (a cloud queried against itself) the same pass also fills the tables of the side with the roles
-// swapped: the pair (centre c, candidate b) is the pair (centre c, other point b) of that side too, in the cell
-// of the opposite offset.
-struct CountOut {
-    uint32_t *tile_cnt, *tile_k_cnt, *hits;
-    uint32_t *n_hits;        // (may be NULL) [n_centres]: every centre's number of neighbours, with `hits`
-};
-// Lists that an earlier count pass over the same centres kept (indexed by centre, not by slot; same stride): a centre
-// whose list is complete is counted from it without a search.  cand_xyz: the candidates' coordinates by index.
-struct Reuse {
-    const uint32_t *hits, *n_hits;
-    const float *cand_xyz;
+// ---- search: every centre's neighbours, in arrival order ----------------------------------------
+//   hits   [n_centres][stride]   a centre's first neighbours, cell << 24 | index, where the centres are outputs
+//   mirror the same where they are inputs.  A cloud queried against itself has both: the pair (centre c, candidate b) is also
+//          the pair (c, b) of the side with the roles swapped, in the cell of the opposite offset
+//   n_hits [n_centres]           how many neighbours it has
+// A wave takes `per_wave` consecutive centres of `order`, which holds the centres grouped by grid cell (without it: in index
+// order), and those of one cell together: the stencil is probed and the candidates are read, placed and converted once for
+// all of them, 256 at a time in registers, and a centre costs its binary64 tests, the cells of its neighbours and the stores.
+// Bound by instruction issue.  One search per centre, in the order of the tiles and with the tiles' tables in LDS: 1 M points
+// of a ground scene, 32 neighbours in 125 cells, 1215 us.
+constexpr int GROUP_SETS = 4;             // sets of 64 candidates in registers
+constexpr int64_t SEARCH_WAVES = 8192;    // waves wanted before a wave takes more centres
+
+struct SearchArgs {
+    const float4 *order;
+    const float *centres;
+    int64_t n_centres;
+    GridView g;
+    QueryParams q;
+    uint32_t *hits, *mirror, *n_hits;
+    uint32_t stride;
+    int per_wave;
+    const uint32_t *err;
 };
 
-template <bool SWAP, bool BOTH, bool EXT>
-__global__ __launch_bounds__(SEARCH_THREADS, 8) void query_count(const float *__restrict__ centres, int64_t n_centres,
-                                                              const int32_t *__restrict__ perm,
-                                                              GridView g, QueryParams q, int K, int64_t n_tiles,
-                                                              CountOut side, CountOut mirror, uint32_t hit_stride,
-                                                              const uint32_t *__restrict__ err, Reuse reuse)
+// FORM: centres are outputs, centres are inputs (the offset input minus output is the other way round), or both in one.
+enum Form { OUTPUTS, INPUTS, BOTH };
+
+template <Form FORM, bool EXT>
+__global__ __launch_bounds__(256, 6) void search_cells(const SearchArgs a)
 {
-    // [K][PITCH], with BOTH followed by the mirror side's; then, when lists are kept, every wave's list (or two) on its way to
-    // memory: hit_stride words each, so that two blocks share a CU where the longest lists would leave room for one
-    extern __shared__ uint32_t tbl[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t tile = blockIdx.x;
-    uint32_t *tbl2 = tbl + K * PITCH, *stage = tbl + (BOTH ? 2 : 1) * K * PITCH;
-    uint32_t *mine = stage + wave * hit_stride, *mine2 = stage + (SEARCH_WAVES + wave) * hit_stride;
-    if (*err) return;                              // block-uniform: the grid's offsets are not to be trusted
-    for (int idx = threadIdx.x; idx < (BOTH ? 2 : 1) * K * PITCH; idx += SEARCH_THREADS) tbl[idx] = 0u;
-    __syncthreads();
-    const bool keep = side.hits != nullptr;
-    // With lists to reuse, a centre costs two memory round trips (its list, the coordinates of the listed points) once
-    // its own index, list length and coordinates are known: those of the wave's four centres are fetched together up
-    // front (lane j: index and length of the j-th, lane 3 j + axis: a coordinate).
-    constexpr int PER_WAVE = TILE / SEARCH_WAVES;
-    int pre_ac = 0;
-    uint32_t pre_n = ~0u;
-    float pre_xyz = 0.f;
-    if (!EXT && reuse.hits) {
-        const int64_t a_j = tile * TILE + wave + (int64_t)(lane < PER_WAVE ? lane : 0) * SEARCH_WAVES;
-        if (lane < PER_WAVE && a_j < n_centres) pre_ac = perm ? perm[a_j] : (int)a_j;
-        if (lane < PER_WAVE && a_j < n_centres) pre_n = reuse.n_hits[pre_ac];
-        const int of = lane / 3 < PER_WAVE ? lane / 3 : 0;
-        const int ac_of = __shfl(pre_ac, of, 64);
-        const int64_t a_of = tile * TILE + wave + (int64_t)of * SEARCH_WAVES;
-        if (lane < 3 * PER_WAVE && a_of < n_centres) pre_xyz = centres[3 * (int64_t)ac_of + lane % 3];
+    const int lane = threadIdx.x & 63;
+    const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t base = wave * a.per_wave;
+    if (*a.err || base >= a.n_centres) return;     // wave-uniform (nothing below is shared between waves)
+    // this lane's centre
+    const int64_t at = base + lane;
+    const bool mine = lane < a.per_wave && at < a.n_centres;
+    float fx = 0.f, fy = 0.f, fz = 0.f;
+    int index = 0, batch = -1, gx = 0, gy = 0, gz = 0;
+    if (mine) {
+        if (a.order) {
+            const float4 p = a.order[at];
+            fx = p.x; fy = p.y; fz = p.z; index = __float_as_int(p.w);
+        } else {
+            fx = a.centres[3 * at]; fy = a.centres[3 * at + 1]; fz = a.centres[3 * at + 2]; index = (int)at;
+        }
+        grid_cell<EXT>(fx, fy, fz, a.g.map, gx, gy, gz);
+        if (EXT && a.q.c_off) batch = find_batch(a.q.c_off, a.q.n_batches, index);
     }
-    int nth = 0;
-    for (int al = wave; al < TILE; al += SEARCH_WAVES, ++nth) {
-        const int64_t a = tile * TILE + al;        // slot; the tables and lists are indexed by it
-        if (a >= n_centres) break;                 // wave-uniform
-        const bool pre = !EXT && reuse.hits;
-        const int64_t ac = pre ? (int64_t)__shfl(pre_ac, nth, 64) : (perm ? (int64_t)perm[a] : a);     // the centre's index
-        Candidates<SWAP, EXT> c;
-        uint32_t filled = 0;
-        // what is done for every neighbour: its cell's counter(s), and its place in the list that is kept
-        auto account = [&](bool hit, int b, int k, int k2) {
-            if (hit) {
-                atomicAdd(&tbl[k * PITCH + al], 1u);
-                if constexpr (BOTH) atomicAdd(&tbl2[k2 * PITCH + al], 1u);
-            }
-            if (keep) {                            // the centre's first hit_stride neighbours, in arrival order
-                const unsigned long long m = __ballot(hit);
-                const uint32_t slot = filled + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-                if (hit && slot < hit_stride) {
-                    mine[slot] = ((uint32_t)k << HIT_INDEX_BITS) | (uint32_t)b;
-                    if constexpr (BOTH) mine2[slot] = ((uint32_t)k2 << HIT_INDEX_BITS) | (uint32_t)b;
-                }
-                filled += (uint32_t)__popcll(m);
-            }
-        };
-        bool searched = true;
-        if constexpr (!EXT) {
-            const uint32_t n_known = pre ? (uint32_t)__shfl((int)pre_n, nth, 64) : ~0u;      // wave-uniform
-            if (n_known <= hit_stride) {
-                // the whole neighbourhood is in the earlier pass's list, in the order in which a search finds it
-                searched = false;
-                c.cx = (double)__shfl(pre_xyz, 3 * nth, 64);
-                c.cy = (double)__shfl(pre_xyz, 3 * nth + 1, 64);
-                c.cz = (double)__shfl(pre_xyz, 3 * nth + 2, 64);
-                for (uint32_t e0 = 0; e0 < n_known; e0 += 64) {
-                    const uint32_t e = e0 + (uint32_t)lane;
-                    const bool on = e < n_known;
-                    int b = 0, k = 0, k2 = 0;
-                    if (on) {
-                        const uint32_t key = reuse.hits[(size_t)ac * hit_stride + e];
-                        b = (int)(key & HIT_INDEX_MASK);
-                        k = (int)(key >> HIT_INDEX_BITS);
-                        if constexpr (BOTH) {      // the mirrored cell needs the offset again
-                            const float *pp = reuse.cand_xyz + 3 * (size_t)b;
-                            const float4 p = float4{pp[0], pp[1], pp[2], 0.f};
-                            double dx, dy, dz;
-                            c.offset_of(p, dx, dy, dz);
-                            Candidates<SWAP, EXT>::template cells_of<true>(dx, dy, dz, q, k, k2);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    uint32_t filled_of = 0;                        // neighbours of this lane's centre so far
+    unsigned long long open = __ballot(mine);
+    while (open) {
+        const int lead = __builtin_ctzll(open);
+        const int lx = (int)lane_value((uint32_t)gx, lead), ly = (int)lane_value((uint32_t)gy, lead), lz = (int)lane_value((uint32_t)gz, lead);
+        const int lb = EXT ? (int)lane_value((uint32_t)batch, lead) : -1;
+        const unsigned long long group = __ballot(gx == lx && gy == ly && gz == lz && (!EXT || batch == lb)) & open;
+        open &= ~group;
+        Stencil st;
+        st.open(lx, ly, lz, lb, a.g, lane);
+        int d_lo = 0, d_hi = 0x7fffffff;
+        if (EXT && a.q.c_off) { d_lo = a.q.d_off[lb]; d_hi = a.q.d_off[lb + 1]; }
+        for (uint32_t first = 0; first < st.total; first += 64 * GROUP_SETS) {
+            double px[GROUP_SETS], py[GROUP_SETS], pz[GROUP_SETS];
+            uint32_t pb[GROUP_SETS];
+#pragma unroll
+            for (int s = 0; s < GROUP_SETS; ++s) {
+                px[s] = INFINITY; py[s] = 0.0; pz[s] = 0.0; pb[s] = 0u;       // infinitely far: no neighbour of any centre
+                const uint32_t idx = first + 64u * s + (uint32_t)lane;
+                if (first + 64u * s < st.total) {  // wave-uniform
+                    const uint32_t pos = st.place(idx < st.total ? idx : 0u);
+                    if (idx < st.total) {
+                        const float4 p = a.g.pts[pos];
+                        pb[s] = (uint32_t)__float_as_int(p.w);
+                        if (!EXT || ((int)pb[s] >= d_lo && (int)pb[s] < d_hi)) {
+                            if (EXT && a.q.voxel_mode) { px[s] = voxel_of(p.x, a.q.R); py[s] = voxel_of(p.y, a.q.R); pz[s] = voxel_of(p.z, a.q.R); }
+                            else { px[s] = (double)p.x; py[s] = (double)p.y; pz[s] = (double)p.z; }
                         }
                     }
-                    account(on, b, k, k2);
                 }
             }
-        }
-        if (searched) {
-            c.open(centres, ac, g, q, lane);
-            for (uint32_t base = 0; base < c.total; base += 64) {
-                int b, k, k2;
-                const bool hit = c.template fetch2<BOTH>(base + lane, g, q, b, k, k2);
-                account(hit, b, k, k2);
+            for (unsigned long long rest = group; rest; rest &= rest - 1) {
+                const int c = __builtin_ctzll(rest);
+                const float sx = lane_value(fx, c), sy = lane_value(fy, c), sz = lane_value(fz, c);
+                double cx, cy, cz;
+                if (EXT && a.q.voxel_mode) { cx = voxel_of(sx, a.q.R); cy = voxel_of(sy, a.q.R); cz = voxel_of(sz, a.q.R); }
+                else { cx = (double)sx; cy = (double)sy; cz = (double)sz; }
+                const size_t row = (size_t)lane_value((uint32_t)index, c) * a.stride;
+                uint32_t filled = lane_value(filled_of, c);
+#pragma unroll
+                for (int s = 0; s < GROUP_SETS; ++s) {
+                    if (first + 64u * s >= st.total) break;                   // wave-uniform
+                    const double dx = __dsub_rn(px[s], cx), dy = __dsub_rn(py[s], cy), dz = __dsub_rn(pz[s], cz);
+                    const bool hit = EXT && a.q.voxel_mode ? inside_cube(dx, dy, dz, a.q) : inside_ball(dx, dy, dz, a.q);
+                    const unsigned long long m = __ballot(hit);
+                    const uint32_t slot = filled + (uint32_t)__popcll(m & below);
+                    filled += (uint32_t)__popcll(m);
+                    if (hit && slot < a.stride) {
+                        const bool cube = EXT && a.q.voxel_mode;
+                        if constexpr (FORM != INPUTS) {
+                            const int k = cube ? cube_cell(dx, dy, dz, a.q) : ball_cell(dx, dy, dz, a.q);
+                            a.hits[row + slot] = ((uint32_t)k << HIT_INDEX_BITS) | pb[s];
+                        }
+                        if constexpr (FORM != OUTPUTS) {
+                            const int k2 = cube ? cube_cell(-dx, -dy, -dz, a.q) : ball_cell(-dx, -dy, -dz, a.q);
+                            a.mirror[row + slot] = ((uint32_t)k2 << HIT_INDEX_BITS) | pb[s];
+                        }
+                    }
+                }
+                if (lane == c) filled_of = filled;
             }
         }
-        if (side.n_hits && lane == 0) side.n_hits[a] = filled;
-        if (keep) {                                // one contiguous write per centre
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t n = filled < hit_stride ? filled : hit_stride;
-            for (uint32_t e = lane; e < n; e += 64) {
-                side.hits[(size_t)a * hit_stride + e] = mine[e];
-                if constexpr (BOTH) mirror.hits[(size_t)a * hit_stride + e] = mine2[e];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        }
     }
-    __syncthreads();
-#pragma unroll
-    for (int sd = 0; sd < (BOTH ? 2 : 1); ++sd) {
-        const CountOut &o = sd == 0 ? side : mirror;
-        const uint32_t *t = sd == 0 ? tbl : tbl2;
-        if (o.tile_cnt) {
-            uint32_t *dst = o.tile_cnt + (size_t)tile * K * TILE;
-            for (int idx = threadIdx.x; idx < K * TILE; idx += SEARCH_THREADS) dst[idx] = t[idx / TILE * PITCH + idx % TILE];
-        }
-        for (int k = wave; k < K; k += SEARCH_WAVES) {
-            uint32_t v = t[k * PITCH + lane];
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-            if (lane == 0) o.tile_k_cnt[(size_t)k * n_tiles + tile] = v;
-        }
-    }
+    if (mine) a.n_hits[index] = filled_of;
 }
 
-// ---- pass 2: write every triplet to its place in (k, centre, other) order ----------------------
-//   tile_cnt  [n_tiles][K][TILE]  counts from pass 1
-//   tile_ptr  [K * n_tiles + 1]   exclusive prefix sum of tile_k_cnt
-//   perm                          centre index of each slot (NULL: slots are centre indices); tables, lists and
-//                                 the centre's position in the order use the slot, coordinates and out_c the index
-// One block per tile.  The neighbours of the tile's centres are dropped into buckets, one per (cell, centre), of a list in
-// LDS (an LDS add on the table of run starts hands out the places inside a bucket, in whatever order); a neighbour's rank
-// among the smaller candidate indices of its bucket is its final place, so ties between equal (k, centre) are ordered by the
-// other index without any global sort.  The list lies in (cell, centre) order, as the output does, so that a wave's stores
-// cover a few contiguous pieces of the output.
-constexpr int FILL_LDS = 79 * 1024;       // table and list together: two blocks of 16 waves share a CU
-constexpr uint32_t LIST_CAP_MAX = 16384;  // positions of the list
-
-// LDS of a block besides the list: table [K][PITCH], two words per cell
-constexpr size_t fill_table_bytes(int K) { return (size_t)K * (PITCH + 2) * sizeof(uint32_t); }
-// neighbours that the list holds (six bytes each)
-constexpr uint32_t fill_list_cap(int K)
-{
-    const size_t n = ((size_t)FILL_LDS - fill_table_bytes(K)) / 6 / 2 * 2;
-    return n < LIST_CAP_MAX ? (uint32_t)n : LIST_CAP_MAX;
-}
-static_assert(fill_table_bytes(MAX_K) + 6 * 1024 <= FILL_LDS, "the list has room beside the largest table");
-
-// Where the fill pass writes.  out_c / out_b / out_k: centre index, candidate index, cell of each triplet (any may
-// be NULL).  With tail_index >= 0 the candidate indices go to the tail_index-th |T|-sized array behind `tail`
-// instead (each align_up(|T| * 4) bytes, |T| read from the prefix sum's last entry), with GATHER_LAST set on the
-// last triplet of every run.  Nothing is written at or beyond position out_cap, and nothing at all when |T|
-// exceeds it (the pass is queued before the host has compared the count with what the caller provided).
+// ---- one side's order of the triplets -------------------------------------------------------------
+// The public list (centres = outputs in index order) and the plan's sides.  Tile = 64 consecutive slots.
+//   perm     centre index of each slot (NULL: slots are centre indices); lists are indexed by centre
+//   hits     the centres' neighbours as the search left them; a centre with more than `stride` is searched again, every
+//            centre where there are no lists (stride 0).  n_hits: how many neighbours each has (without lists the count pass
+//            writes it, and where mirror_sums is given, the sums of the swapped side too)
+//   sums     [K * n_tiles]      k-major: neighbours of tile's centres in cell k
+//   ptr      [K * n_tiles + 1]  exclusive prefix sum of `sums`
 struct FillOut {
+    // Where the fill pass writes.  out_c / out_b / out_k: centre index, candidate index, cell of each triplet (any may
+    // be NULL).  With tail_index >= 0 the candidate indices go to the tail_index-th |T|-sized array behind `tail`
+    // instead (each align_up(|T| * 4) bytes, |T| read from the prefix sum's last entry), with GATHER_LAST set on the
+    // last triplet of every run.  Nothing is written when |T| exceeds out_cap (the pass is
+    // queued before the host has compared the count with what the caller provided).
     int32_t *out_c, *out_b, *out_k;
     char *tail;
     int tail_index;
     uint32_t out_cap;
 };
+struct Side {
+    const float *centres;
+    const int32_t *perm;
+    int64_t n_centres, n_tiles;
+    GridView g;
+    QueryParams q;
+    const uint32_t *hits;
+    uint32_t *n_hits;
+    uint32_t stride;
+    int lanes_log2;               // lanes that read one list
+    uint32_t *sums, *mirror_sums;
+    const uint32_t *ptr;
+    uint32_t *run_start;          // [n_tiles][K][TILE], NULL: not wanted
+    int64_t *seg_out;             // [K + 1], NULL: not wanted
+    FillOut out;
+};
+constexpr int MAX_SIDES = 3;
+struct Sides { Side s[MAX_SIDES]; };
 
-template <bool SWAP, bool EXT>
-__global__ __launch_bounds__(SEARCH_THREADS, 8) void query_fill(const float *__restrict__ centres, int64_t n_centres,
-                                                             const int32_t *__restrict__ perm,
-                                                             GridView g, QueryParams q, int K, int64_t n_tiles,
-                                                             const uint32_t *__restrict__ tile_cnt,
-                                                             const uint32_t *__restrict__ tile_ptr,
-                                                             FillOut fo,
-                                                             uint32_t *__restrict__ run_start_out, uint32_t list_cap,
-                                                             const uint32_t *__restrict__ hits, uint32_t hit_stride,
-                                                             int lanes_log2, int64_t *__restrict__ seg_out,
-                                                             const uint32_t *__restrict__ err)
+// What the passes keep in LDS of a tile's centres.
+struct TileCentres {
+    uint32_t n[TILE], off[TILE];  // neighbours of each, and of the centres before it
+    int32_t at[TILE];             // its own index
+    uint32_t searched;            // centres without a complete list: whether there are any
+
+    // by wave 0; a barrier follows.  `whole`: centres without a complete list count with what they have, else with nothing.
+    __device__ inline void open(const Side &s, int64_t tile, bool whole, int lane)
+    {
+        const int64_t slot = tile * TILE + lane;
+        const bool on = slot < s.n_centres;
+        const int32_t c = on ? (s.perm ? s.perm[slot] : (int32_t)slot) : 0;
+        uint32_t m = on && (whole || s.stride) ? s.n_hits[c] : 0u;
+        const unsigned long long past = __ballot(on && (m > s.stride || !s.stride));
+        if (!whole && m > s.stride) m = 0u;
+        at[lane] = c;
+        n[lane] = m;
+        off[lane] = wave_incl_scan_u32(m) - m;
+        if (lane == 0) searched = past != 0ull;
+    }
+    // the centre that a neighbour of the tile belongs to, for a thread that goes through consecutive ones
+    struct Cursor { int al; uint32_t end; };
+    __device__ inline Cursor cursor(uint32_t p) const
+    {
+        int al = 0;
+#pragma unroll
+        for (int step = TILE / 2; step >= 1; step >>= 1)
+            if (off[al + step] <= p) al += step;
+        return Cursor{al, off[al] + n[al]};
+    }
+    __device__ inline void advance(Cursor &c, uint32_t p) const
+    {
+        while (p >= c.end) {               // (p is below the tile's number of neighbours)
+            ++c.al;
+            c.end = off[c.al] + n[c.al];
+        }
+    }
+};
+
+// ---- pass 1: neighbours per (cell, tile) ----------------------------------------------------------
+// A thread takes four consecutive neighbours of the tile, whose list words are on their way at a time.  Consecutive neighbours
+// often fall in one cell, so that every lane of a half wave has a column of counters of its own.
+constexpr int COUNT_THREADS = 512;
+constexpr int COUNT_COLS = 32, COUNT_PITCH = COUNT_COLS + 1;
+constexpr int COUNT_AHEAD = 4;                             // list words in flight per thread
+constexpr size_t count_lds_bytes(int K, bool mirror) { return (size_t)K * COUNT_PITCH * sizeof(uint32_t) * (mirror ? 2 : 1); }
+
+template <bool EXT>
+__global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides, int K, const uint32_t *__restrict__ err)
 {
-    // [K][PITCH] starts of the (k, centre) runs relative to the tile's first triplet of cell k, and behind a row the end of
-    // its last run; [K] that first triplet; [K] what turns a relative position into one of the list; then the list:
-    // candidate indices, and (cell | centre << 8)
-    extern __shared__ uint32_t tbl[];
-    __shared__ uint32_t centre_n[TILE];        // neighbours of each centre
-    __shared__ int32_t centre_at[TILE];        // its own index
-    uint32_t *first = tbl + K * PITCH, *to_list = first + K, *list = to_list + K;
-    uint16_t *list_at = reinterpret_cast<uint16_t *>(list + list_cap);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+    extern __shared__ uint32_t tbl[];                      // [K][COUNT_PITCH], twice with mirror_sums
+    __shared__ TileCentres tc;
+    const Side &s = sides.s[blockIdx.y];
     const int64_t tile = blockIdx.x;
-    if (*err) return;                          // block-uniform: a prefix sum of this build gave up
-    const uint32_t total = tile_ptr[(size_t)K * n_tiles];
-    const uint32_t out_cap = total <= fo.out_cap ? fo.out_cap : 0u;
-    int32_t *out_b = fo.out_b;
-    const bool flag_last = fo.tail_index >= 0;
-    if (flag_last)
-        out_b = reinterpret_cast<int32_t *>(fo.tail + (size_t)fo.tail_index * (((size_t)total * 4 + 255) / 256 * 256));
+    if (*err || tile >= s.n_tiles) return;                 // block-uniform: the grid's offsets are not to be trusted
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    constexpr int PITCH = COUNT_PITCH, WAVES = COUNT_THREADS / 64;
+    const bool mirror = s.mirror_sums != nullptr;
+    uint32_t *tbl2 = tbl + K * PITCH, *col = tbl + (threadIdx.x & 31);
+    if (wave == 0) tc.open(s, tile, false, lane);
+    for (int i = threadIdx.x; i < K * PITCH * (mirror ? 2 : 1); i += COUNT_THREADS) tbl[i] = 0u;
+    __syncthreads();
+    const uint32_t listed = tc.off[TILE - 1] + tc.n[TILE - 1];
+    for (uint32_t p0 = COUNT_AHEAD * threadIdx.x; p0 < listed; p0 += COUNT_AHEAD * COUNT_THREADS) {
+        uint32_t key[COUNT_AHEAD];
+        TileCentres::Cursor c = tc.cursor(p0);
+#pragma unroll
+        for (int j = 0; j < COUNT_AHEAD; ++j)
+            if (p0 + j < listed) {
+                tc.advance(c, p0 + j);
+                key[j] = s.hits[(size_t)tc.at[c.al] * s.stride + (p0 + j - tc.off[c.al])];
+            }
+#pragma unroll
+        for (int j = 0; j < COUNT_AHEAD; ++j)
+            if (p0 + j < listed) atomicAdd(&col[(key[j] >> HIT_INDEX_BITS) * PITCH], 1u);
+    }
+    if (tc.searched)                                       // (block-uniform)
+        for (int al = wave; al < TILE; al += WAVES) {
+            const int64_t slot = tile * TILE + al;
+            if (slot >= s.n_centres) break;                // wave-uniform
+            const int64_t c = tc.at[al];
+            if (s.stride && (uint32_t)__builtin_amdgcn_readfirstlane((int)s.n_hits[c]) <= s.stride) continue;
+            Candidates<EXT> cand;
+            cand.open(s.centres, c, s.g, s.q, lane);
+            uint32_t n = 0;
+            for (uint32_t base = 0; base < cand.st.total; base += 64) {
+                int b, k, k2;
+                const bool hit = cand.fetch(base + lane, s.g, s.q, b, k, k2);
+                if (hit) {
+                    atomicAdd(&col[k * PITCH], 1u);
+                    if (mirror) atomicAdd(&tbl2[k2 * PITCH + (threadIdx.x & 31)], 1u);
+                }
+                n += (uint32_t)__popcll(__ballot(hit));
+            }
+            if (!s.stride && s.n_hits && lane == 0) s.n_hits[c] = n;
+        }
+    __syncthreads();
+    for (int k0 = 2 * wave; k0 < K; k0 += 2 * WAVES) {     // a half wave per cell
+        const int k = k0 + (lane >> 5), l = lane & 31;
+        const uint32_t v = half_incl_scan_u32(k < K ? tbl[k * PITCH + l] : 0u);
+        if (k < K && l == 31) s.sums[(size_t)k * s.n_tiles + tile] = v;
+        if (mirror) {
+            const uint32_t v2 = half_incl_scan_u32(k < K ? tbl2[k * PITCH + l] : 0u);
+            if (k < K && l == 31) s.mirror_sums[(size_t)k * s.n_tiles + tile] = v2;
+        }
+    }
+}
+
+// ---- pass 2: write every triplet to its place in (k, centre, other) order ----------------------
+// One block per tile.  A thread takes up to FILL_ROUNDS neighbours of the tile's centres; an LDS add per neighbour counts its
+// (cell, centre) run and hands it a place there, in whatever order; the counts become run starts; the neighbours go to a list
+// in LDS, run by run; and a neighbour's rank among the smaller candidate indices of its run is its final place, so ties between
+// equal (k, centre) are ordered by the other index without any global sort.  The list lies in (cell, centre) order, as the
+// output does, so that a wave's stores cover a few contiguous pieces of the output.  Tiles with more neighbours than the list holds are done some
+// centres at a time.
+//   LDS: [K][FILL_PITCH] runs, two centres to a word (a list has fewer than 2^16 places); [K] first triplet of the tile (or of
+//   its part) in cell k; [K] how many there are; [K] where they start in the list; the list: candidate index, (cell | centre << 8)
+// What bounds it: the table (1 M points, 125 cells: 500 MB of run starts) and the barriers between the phases.
+constexpr int FILL_PITCH = TILE / 2 + 1;  // (a half wave works on one centre, i.e. one column)
+constexpr int FILL_ROUNDS = 8;           // places of the list per thread
+constexpr size_t fill_table_bytes(int K) { return (size_t)K * (FILL_PITCH + 3) * sizeof(uint32_t); }
+// A block's threads and places: four blocks of 8 waves share a CU, or two of 16 where a tile's neighbours need the room.
+struct FillShape { int threads; uint32_t list_cap; size_t lds; };
+constexpr FillShape fill_shape_of(int K, int threads)
+{
+    const size_t most = threads == 512 ? 39 * 1024 : 79 * 1024, table = fill_table_bytes(K);
+    size_t n = (most - table) / 6 / 2 * 2;
+    if (n > (size_t)FILL_ROUNDS * threads) n = (size_t)FILL_ROUNDS * threads;
+    return FillShape{threads, (uint32_t)n, table + n * 6};
+}
+static_assert(fill_table_bytes(MAX_K) + 6 * 1024 <= 39 * 1024, "the list has room beside the largest table");
+static_assert(FILL_ROUNDS * 1024 < 65536, "runs count in 16 bits");
+
+template <bool EXT>
+__global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, uint32_t list_cap, const uint32_t *__restrict__ err)
+{
+    extern __shared__ uint32_t tbl[];
+    __shared__ TileCentres tc;
+    const Side &s = sides.s[blockIdx.y];
+    const int64_t tile = blockIdx.x;
+    if (*err || tile >= s.n_tiles) return;                 // block-uniform: a prefix sum of this build gave up
+    uint32_t *first = tbl + K * FILL_PITCH, *row_n = first + K, *to_list = row_n + K, *list = to_list + K;
+    uint16_t *list_at = reinterpret_cast<uint16_t *>(list + list_cap);
+    const int threads = blockDim.x, n_waves = threads >> 6;
+    int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t total = s.ptr[(size_t)K * s.n_tiles];
     // start of every cell's segment (Sec. 3.3.2): the offset of its first tile; entry K is |T|
-    if (seg_out && tile == 0)
-        for (int k = threadIdx.x; k <= K; k += blockDim.x) seg_out[k] = (int64_t)tile_ptr[(size_t)k * n_tiles];
-    const uint32_t *cnt_tile = tile_cnt + (size_t)tile * K * TILE;
-    for (int at = threadIdx.x; at < K * TILE; at += blockDim.x) tbl[at / TILE * PITCH + at % TILE] = cnt_tile[at];
-    for (int k = threadIdx.x; k < K; k += blockDim.x) first[k] = tile_ptr[(size_t)k * n_tiles + tile];
-    if (threadIdx.x < TILE) {
-        const int64_t a = tile * TILE + threadIdx.x;
-        centre_n[threadIdx.x] = 0u;
-        centre_at[threadIdx.x] = a < n_centres ? (perm ? perm[a] : (int32_t)a) : 0;
-    }
+    if (s.seg_out && tile == 0)
+        for (int k = tid; k <= K; k += threads) s.seg_out[k] = (int64_t)s.ptr[(size_t)k * s.n_tiles];
+    if (total > s.out.out_cap) return;                     // no room: the call is going to say so
+    const uint32_t out_cap = s.out.out_cap;
+    int32_t *out_b = s.out.out_b;
+    const bool flag_last = s.out.tail_index >= 0;
+    if (flag_last)
+        out_b = reinterpret_cast<int32_t *>(s.out.tail + (size_t)s.out.tail_index * (((size_t)total * 4 + 255) / 256 * 256));
+    int32_t *out_c = s.out.out_c, *out_k = s.out.out_k;
+    auto emit = [&](uint32_t pos, int al, int k, uint32_t b, bool last) {
+        if (pos >= out_cap) return;
+        if (out_c) out_c[pos] = tc.at[al];
+        if (out_b) out_b[pos] = (int32_t)(flag_last && last ? b | GATHER_LAST : b);
+        if (out_k) out_k[pos] = k;
+    };
+    for (int i = tid; i < K * FILL_PITCH; i += threads) tbl[i] = 0u;
+    for (int k = tid; k < K; k += threads) first[k] = s.ptr[(size_t)k * s.n_tiles + tile];
+    if (wave == 0) tc.open(s, tile, true, lane);
     __syncthreads();
-    uint32_t lane_n = 0;
-    for (int k = wave; k < K; k += n_waves) {
-        const uint32_t v = tbl[k * PITCH + lane];
-        const uint32_t end = wave_incl_scan_u32(v);
-        tbl[k * PITCH + lane] = end - v;
-        if (lane == TILE - 1) tbl[k * PITCH + TILE] = end;
-        if (run_start_out) run_start_out[((size_t)tile * K + k) * TILE + lane] = first[k] + end - v;
-        lane_n += v;
-    }
-    atomicAdd(&centre_n[lane], lane_n);
-    __syncthreads();
-    const uint32_t complete = hits ? hit_stride : 0u;      // lists up to this long were kept whole by the count pass
-    const uint32_t upto = wave_incl_scan_u32(centre_n[lane]);       // neighbours of the centres 0 .. lane
+    const uint32_t upto = tc.off[lane] + tc.n[lane];
+    uint32_t *run_start = s.run_start ? s.run_start + (size_t)tile * K * TILE : nullptr;
     // as many centres at a time as the list holds: usually all of them
     int c0 = 0;
-    while (c0 < TILE) {
-        const uint32_t before = c0 > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto, c0 - 1) : 0u;
+    for (;;) {
+        tid = here(tid);
+        lane = tid & 63;
+        const uint32_t before = c0 > 0 ? lane_value(upto, c0 - 1) : 0u;
         const int c1 = c0 + (int)__popcll(__ballot(lane >= c0 && upto - before <= list_cap));
         if (c1 == c0) {
             // a centre with more neighbours than the list holds: rank each one by scanning the candidates again
-            Candidates<SWAP, EXT> c;
-            c.open(centres, centre_at[c0], g, q, lane);
-            for (uint32_t base = (uint32_t)wave * 64u; base < c.total; base += (uint32_t)n_waves * 64u) {
-                int b, k;
-                const bool hit = c.fetch(base + lane, g, q, b, k);
-                uint32_t rank = 0;
-                for (uint32_t other = 0; other < c.total; ++other) {
-                    int b2, k2;
-                    const bool hit2 = c.fetch(other, g, q, b2, k2);
-                    rank += (hit2 && k2 == k && b2 < b) ? 1u : 0u;
-                }
-                if (hit) {
-                    const uint32_t pos = first[k] + tbl[k * PITCH + c0] + rank;
-                    const bool last = tbl[k * PITCH + c0] + rank + 1u == tbl[k * PITCH + c0 + 1];
-                    if (pos < out_cap) {
-                        if (fo.out_c) fo.out_c[pos] = centre_at[c0];
-                        if (out_b) out_b[pos] = (int32_t)((flag_last && last) ? ((uint32_t)b | GATHER_LAST) : (uint32_t)b);
-                        if (fo.out_k) fo.out_k[pos] = k;
-                    }
-                }
+            for (int k = tid; k < K; k += threads) row_n[k] = 0u;
+            __syncthreads();
+            Candidates<EXT> cand;
+            cand.open(s.centres, tc.at[c0], s.g, s.q, lane);
+            for (uint32_t base = (uint32_t)wave * 64u; base < cand.st.total; base += (uint32_t)threads) {
+                int b, k, k2;
+                if (cand.fetch(base + lane, s.g, s.q, b, k, k2)) atomicAdd(&row_n[k], 1u);
             }
             __syncthreads();
-            // (an entry whose centre is done holds the end of its run)
-            for (int k = threadIdx.x; k < K; k += blockDim.x) tbl[k * PITCH + c0] = tbl[k * PITCH + c0 + 1];
+            for (uint32_t base = (uint32_t)wave * 64u; base < cand.st.total; base += (uint32_t)threads) {
+                int b, k, k2;
+                const bool hit = cand.fetch(base + lane, s.g, s.q, b, k, k2);
+                uint32_t rank = 0;
+                for (uint32_t other = 0; other < cand.st.total; ++other) {
+                    int b2, k3, k4;
+                    const bool hit2 = cand.fetch(other, s.g, s.q, b2, k3, k4);
+                    rank += (hit2 && k3 == k && b2 < b) ? 1u : 0u;
+                }
+                if (hit) emit(first[k] + rank, c0, k, (uint32_t)b, rank + 1u == row_n[k]);
+            }
+            if (run_start)
+                for (int k = tid; k < K; k += threads) run_start[k * TILE + c0] = first[k];
             __syncthreads();
-            ++c0;
+            for (int k = tid; k < K; k += threads) first[k] += row_n[k];
+            if (++c0 == TILE) break;
+            __syncthreads();
             continue;
         }
-        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)upto, c1 - 1) - before;
-        if (n > 0u) {                                      // block-uniform
-            if (wave == 0) {
-                uint32_t run = 0;
-                for (int k0 = 0; k0 < K; k0 += 64) {
-                    const int k = k0 + lane;
-                    const uint32_t s = k < K ? tbl[k * PITCH + c0] : 0u, e = k < K ? tbl[k * PITCH + c1] : 0u;
-                    const uint32_t inc = wave_incl_scan_u32(e - s);
-                    if (k < K) to_list[k] = run + inc - e;
-                    run += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-                }
-            }
-            __syncthreads();
-            auto place = [&](int al, int k, uint32_t b) {
-                const uint32_t p = to_list[k] + atomicAdd(&tbl[k * PITCH + al], 1u);
-                if (p < list_cap) {
-                    list[p] = b;
-                    list_at[p] = (uint16_t)(k | al << 8);
-                }
-            };
-            {   // neighbours that the count pass kept: 2^lanes_log2 lanes per centre
-                const int l = lane & ((1 << lanes_log2) - 1), per = 64 >> lanes_log2;
-                for (int al = c0 + wave * per + (lane >> lanes_log2); al < c1; al += n_waves * per) {
-                    const uint32_t m = centre_n[al];
-                    if (m > complete) continue;
-                    const uint32_t *mine = hits + (size_t)(tile * TILE + al) * hit_stride;
-                    for (uint32_t e = l; e < m; e += 1u << lanes_log2) {
-                        const uint32_t key = mine[e];
-                        place(al, (int)(key >> HIT_INDEX_BITS), key & HIT_INDEX_MASK);
+        const uint32_t n = lane_value(upto, c1 - 1) - before;
+        // ---- neighbours without a list: searched again, one wave per centre, left in the list for the threads that take them --
+        if (tc.searched) {                                 // (block-uniform)
+            for (int al = c0 + wave; al < c1; al += n_waves) {
+                const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)tc.n[al]);
+                if (m == 0u || m <= s.stride) continue;
+                const int lane = here(tid & 63);
+                Candidates<EXT> cand;
+                cand.open(s.centres, tc.at[al], s.g, s.q, lane);
+                uint32_t at = tc.off[al] - before;
+                for (uint32_t base = 0; base < cand.st.total; base += 64) {
+                    int b, k, k2;
+                    const bool hit = cand.fetch(base + lane, s.g, s.q, b, k, k2);
+                    const unsigned long long mask = __ballot(hit);
+                    const uint32_t p = at + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+                    if (hit && p < list_cap) {
+                        list[p] = (uint32_t)b;
+                        list_at[p] = (uint16_t)k;
                     }
-                }
-            }
-            for (int al = c0 + wave; al < c1; al += n_waves) {      // others: searched again, one wave per centre
-                if ((uint32_t)__builtin_amdgcn_readfirstlane((int)centre_n[al]) <= complete) continue;
-                Candidates<SWAP, EXT> c;
-                c.open(centres, centre_at[al], g, q, lane);
-                for (uint32_t base = 0; base < c.total; base += 64) {
-                    int b, k;
-                    if (c.fetch(base + lane, g, q, b, k)) place(al, k, (uint32_t)b);
-                }
-            }
-            __syncthreads();
-            for (uint32_t p = threadIdx.x; p < n; p += blockDim.x) {
-                const uint32_t b = list[p], at = list_at[p];
-                const int k = (int)(at & 255u), al = (int)(at >> 8);
-                // every entry up to this centre's holds the end of its run by now
-                const uint32_t s = al > 0 ? tbl[k * PITCH + al - 1] : 0u, e = tbl[k * PITCH + al];
-                const uint32_t *run = list + to_list[k] + s;
-                uint32_t rank = 0, j = 0;
-                for (; j + 4 <= e - s; j += 4) {
-                    const uint32_t v0 = run[j], v1 = run[j + 1], v2 = run[j + 2], v3 = run[j + 3];
-                    rank += (v0 < b ? 1u : 0u) + (v1 < b ? 1u : 0u) + (v2 < b ? 1u : 0u) + (v3 < b ? 1u : 0u);
-                }
-                for (; j < e - s; ++j) rank += run[j] < b ? 1u : 0u;
-                const uint32_t pos = first[k] + s + rank;
-                if (pos < out_cap) {
-                    if (fo.out_c) fo.out_c[pos] = centre_at[al];
-                    if (out_b) out_b[pos] = (int32_t)((flag_last && s + rank + 1u == e) ? (b | GATHER_LAST) : b);
-                    if (fo.out_k) fo.out_k[pos] = k;
+                    at += (uint32_t)__popcll(mask);
                 }
             }
             __syncthreads();
         }
+        // ---- a thread's consecutive neighbours: candidate index; cell | centre << 8 | place in the run << 14 -----------------
+        const int rounds = (int)((n + (uint32_t)threads - 1u) / (uint32_t)threads);       // at most FILL_ROUNDS
+        const uint32_t p0 = (uint32_t)(tid * rounds), mine = p0 < n ? (n - p0 < (uint32_t)rounds ? n - p0 : (uint32_t)rounds) : 0u;
+        uint32_t b_of[FILL_ROUNDS], at_of[FILL_ROUNDS];
+        if (mine > 0u) {
+            TileCentres::Cursor c = tc.cursor(p0 + before);
+#pragma unroll
+            for (int j = 0; j < FILL_ROUNDS; ++j) {
+                b_of[j] = at_of[j] = 0u;
+                if (j < rounds && (uint32_t)j < mine) {    // (the first: block-uniform)
+                    const uint32_t p = p0 + before + j;
+                    tc.advance(c, p);
+                    at_of[j] = (uint32_t)c.al << 8;
+                    if (c.end - tc.off[c.al] <= s.stride) {
+                        b_of[j] = s.hits[(size_t)tc.at[c.al] * s.stride + (p - tc.off[c.al])];
+                    } else {
+                        b_of[j] = list[p0 + j];
+                        at_of[j] |= list_at[p0 + j] | 1u << 31;
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < FILL_ROUNDS; ++j)
+                if (j < rounds && (uint32_t)j < mine) {
+                    if (!(at_of[j] >> 31)) {
+                        at_of[j] |= b_of[j] >> HIT_INDEX_BITS;
+                        b_of[j] &= HIT_INDEX_MASK;
+                    }
+                    const uint32_t al = (at_of[j] >> 8) & 63u, sh = 16u * (al & 1u);
+                    const uint32_t was = atomicAdd(&tbl[(at_of[j] & 255u) * FILL_PITCH + (al >> 1)], 1u << sh);
+                    at_of[j] = (at_of[j] & 0x3fffu) | ((was >> sh) & 0xffffu) << 14;
+                }
+        }
+        __syncthreads();
+        // ---- counts -> starts within the part's triplets of the cell, eight cells per wave --------------------------------
+        for (int k0 = 8 * wave; k0 < K; k0 += 8 * n_waves) {
+            const int k = k0 + (lane >> 3), l = lane & 7;  // eight lanes per cell, eight centres per lane
+            const int kc = k < K ? k : K - 1;
+            uint32_t *word = tbl + kc * FILL_PITCH + 4 * l;
+            uint32_t v[4], s0[4], s1[4], sum = 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = word[i];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s0[i] = sum;
+                s1[i] = sum + (v[i] & 0xffffu);
+                sum = s1[i] + (v[i] >> 16);
+            }
+            uint32_t incl = sum;                           // over the eight lanes: shifts inside a row of sixteen, for both halves
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) {
+                const uint32_t u = __shfl_up(incl, d, 8);
+                if (l >= d) incl += u;
+            }
+            const uint32_t lead = incl - sum;
+            if (k < K) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) word[i] = (lead + s0[i]) | (lead + s1[i]) << 16;
+                if (l == 7) { row_n[k] = incl; tbl[k * FILL_PITCH + 32] = incl; }
+                if (run_start) {
+                    const uint32_t f = first[k] + lead;
+                    uint32_t *at = run_start + k * TILE + 8 * l;
+                    if (c0 == 0 && c1 == TILE) {
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+                            reinterpret_cast<uint4 *>(at)[i] = make_uint4(f + s0[2 * i], f + s1[2 * i], f + s0[2 * i + 1], f + s1[2 * i + 1]);
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)
+                            if (8 * l + i >= c0 && 8 * l + i < c1) at[i] = f + (i & 1 ? s1[i / 2] : s0[i / 2]);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        // ---- places ----------------------------------------------------------------------------------------------------
+        if (wave == 0) {
+            uint32_t run = 0;
+            for (int k0 = 0; k0 < K; k0 += 64) {
+                const int k = k0 + lane;
+                const uint32_t m = k < K ? row_n[k] : 0u;
+                const uint32_t incl = wave_incl_scan_u32(m);
+                if (k < K) to_list[k] = run + incl - m;
+                run += lane_value(incl, 63);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < FILL_ROUNDS; ++j)
+            if (j < rounds && (uint32_t)j < mine) {
+                const uint32_t k = at_of[j] & 255u, al = (at_of[j] >> 8) & 63u;
+                const uint32_t place = to_list[k] + ((tbl[k * FILL_PITCH + (al >> 1)] >> (16u * (al & 1u))) & 0xffffu) + (at_of[j] >> 14);
+                list[place] = b_of[j];
+                list_at[place] = (uint16_t)(at_of[j] & 0x3fffu);
+            }
+        __syncthreads();
+        // ---- ranks, and out ----------------------------------------------------------------------------------------------
+        for (uint32_t p = tid; p < n; p += threads) {
+            const uint32_t b = list[p], at = list_at[p];
+            const int k = (int)(at & 255u), al = (int)(at >> 8);
+            const uint32_t *word = tbl + k * FILL_PITCH + (al >> 1);       // (behind the last centre: the end of its run)
+            const uint32_t prev = al & 1 ? word[0] >> 16 : word[0] & 0xffffu;
+            const uint32_t m = (al & 1 ? word[1] & 0xffffu : word[0] >> 16) - prev;
+            const uint32_t *run = list + to_list[k] + prev;
+            uint32_t rank = 0;
+            for (uint32_t j = 0; j < m; j += 4) {          // (reads past the run stay inside the block's LDS)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) rank += (uint32_t)(run[j + i] < b) & (uint32_t)(j + i < m);
+            }
+            emit(first[k] + prev + rank, al, k, b, rank + 1u == m);
+        }
+        if (c1 == TILE) break;
+        __syncthreads();
+        for (int i = tid; i < K * FILL_PITCH; i += threads) tbl[i] = 0u;
+        for (int k = tid; k < K; k += threads) first[k] += row_n[k];
+        __syncthreads();
         c0 = c1;
     }
 }
@@ -772,31 +957,27 @@ struct BuildScratch {
     size_t total_off;                // |T| as the prefix sum leaves it, when the caller's landing word is pageable
     size_t scan_off;                 // status words of the prefix sums: N_SCANS regions of scan_stride bytes
     size_t scan_stride;
-    size_t fwd_ptr_off, fwd_cnt_off; // per-(k, tile) sums / offsets and per-(k, centre) counts of the pass in flight
-    size_t bwd_ptr_off, bwd_cnt_off;
+    size_t fwd_ptr_off, bwd_ptr_off; // per-(k, tile) sums; of the public list, their offsets
     size_t sort_off;                 // scratch of the spatial sorts
-    size_t end;                      // without hit lists
-    // Optional, after `end`: the first hit_stride neighbours of every centre as found by the count pass, so
-    // that the fill pass need not search again (needs the triplet capacity to size the lists).
+    size_t end;                      // what a call needs
+    // The centres' neighbour lists and their lengths.  With a workspace made for the triplet capacity they lie behind `end`;
+    // otherwise a length per centre and K - 1 words of list fit the per-centre tables.
     uint32_t fwd_stride = 0, bwd_stride = 0;
-    size_t fwd_hits_off = 0, bwd_hits_off = 0, end_with_hits = 0;
-    // Optional, after that: a second set of lists of the outputs and their lengths.  A plan in spatial order counts
-    // the same neighbourhoods twice, once in index order for the public list and once in slot order; with these the
-    // second count reads the first one's lists instead of searching again.
-    size_t pub_hits_off = 0, n_hits_off = 0, end_with_reuse = 0;
+    size_t fwd_n_off, bwd_n_off, fwd_hits_off = 0, bwd_hits_off = 0, end_with_lists = 0;
 };
 
-// list length per centre: twice the mean neighbour count, within [32, KEEP_MAX]
-uint32_t hit_stride_for(int64_t capacity, int64_t n_centres)
+// list length per centre: twice the mean neighbour count, within [32, most]
+uint32_t hit_stride_for(int64_t capacity, int64_t n_centres, int64_t most)
 {
     if (n_centres <= 0 || capacity <= 0) return 0;
     int64_t s = (2 * ceil_div(capacity, n_centres) + 15) / 16 * 16;
     if (s < 32) s = 32;
-    if (s > (int64_t)KEEP_MAX) s = KEEP_MAX;
+    if (s > most) s = most;
     return (uint32_t)s;
 }
 
-BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K, int64_t capacity = -1)
+// Lists of at most `most` neighbours behind `end`.
+BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K, int64_t capacity = -1, int64_t most = KEEP_MAX)
 {
     BuildScratch b;
     b.grid_in = grid_scratch(0, n_in);
@@ -813,23 +994,41 @@ BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K, int64_t capacity 
     b.scan_stride = scan_scratch_bytes(scan_n);
     b.scan_off = off;    off += N_SCANS * b.scan_stride;
     b.fwd_ptr_off = off; off += align_up((size_t)(K * nt_o + 1) * 4);
-    b.fwd_cnt_off = off; off += align_up((size_t)(nt_o > 0 ? nt_o : 1) * K * TILE * 4);
+    b.fwd_n_off = off;   off += align_up((size_t)(nt_o > 0 ? nt_o : 1) * K * TILE * 4);
     b.bwd_ptr_off = off; off += align_up((size_t)(K * nt_i + 1) * 4);
-    b.bwd_cnt_off = off; off += align_up((size_t)(nt_i > 0 ? nt_i : 1) * K * TILE * 4);
+    b.bwd_n_off = off;   off += align_up((size_t)(nt_i > 0 ? nt_i : 1) * K * TILE * 4);
     b.sort_off = off;    off += spatial_order_scratch_bytes(n_max);
     b.end = off;
-    b.end_with_hits = off;
+    b.end_with_lists = off;
     // stored hits carry the candidate index in HIT_INDEX_BITS bits
-    if (capacity > 0 && n_in < (1 << HIT_INDEX_BITS) && n_out < (1 << HIT_INDEX_BITS)) {
-        b.fwd_stride = hit_stride_for(capacity, n_out);
-        b.bwd_stride = hit_stride_for(capacity, n_in);
+    if (n_in >= (1 << HIT_INDEX_BITS) || n_out >= (1 << HIT_INDEX_BITS)) return b;
+    if (capacity > 0) {
+        b.fwd_stride = hit_stride_for(capacity, n_out, most);
+        b.bwd_stride = hit_stride_for(capacity, n_in, most);
         b.fwd_hits_off = off; off += align_up((size_t)n_out * b.fwd_stride * 4);
         b.bwd_hits_off = off; off += align_up((size_t)n_in * b.bwd_stride * 4);
-        b.end_with_hits = off;
-        b.n_hits_off = off;   off += align_up((size_t)n_out * 4);
-        b.pub_hits_off = off; off += align_up((size_t)n_out * b.fwd_stride * 4);
+        b.end_with_lists = off;
     }
-    b.end_with_reuse = off;
+    return b;
+}
+
+// The scratch of a call whose workspace has `bytes` bytes: as long lists as fit.  With fewer than 27 cells the lists inside
+// the per-centre tables would mostly be too short to spare the later passes their search (8 cells: 7 neighbours); such a
+// call does without.
+BuildScratch build_scratch_within(int64_t n_in, int64_t n_out, int K, int64_t capacity, size_t bytes)
+{
+    if (capacity > 0)
+        for (int64_t most = KEEP_MAX; most >= 32; most /= 2) {
+            const BuildScratch b = build_scratch(n_in, n_out, K, capacity, most);
+            if (b.fwd_stride == 0 && b.bwd_stride == 0) break;
+            if (bytes >= b.end_with_lists) return b;
+        }
+    BuildScratch b = build_scratch(n_in, n_out, K);
+    if (capacity > 0 && K >= 27 && n_in < (1 << HIT_INDEX_BITS) && n_out < (1 << HIT_INDEX_BITS)) {
+        b.fwd_stride = b.bwd_stride = (uint32_t)(K - 1);
+        b.fwd_hits_off = b.fwd_n_off + (size_t)n_out * 4;
+        b.bwd_hits_off = b.bwd_n_off + (size_t)n_in * 4;
+    }
     return b;
 }
 
@@ -919,7 +1118,7 @@ size_t pcpp_build_triplets_workspace_bytes(int64_t n_in, int64_t n_out, int t)
 size_t pcpp_build_triplets_workspace_bytes_for(int64_t n_in, int64_t n_out, int t, int64_t capacity)
 {
     if (n_in < 0 || n_out < 0 || t < 1 || t > PCPP_MAX_T || capacity < 0) return 0;
-    return build_scratch(n_in, n_out, t * t * t, capacity).end_with_reuse;
+    return build_scratch(n_in, n_out, t * t * t, capacity).end_with_lists;
 }
 
 size_t pcpp_plan_bytes(int64_t n_in, int64_t n_out, int t, int64_t n_triplets, int plan_flags)
@@ -998,7 +1197,8 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         return PCPP_ERR_INVALID_ARG;
     }
     const int K = t * t * t;
-    const BuildScratch bs = build_scratch(n_in, n_out, K, count_only ? -1 : capacity);
+    const bool wide_keys = (test_flags & PCPP_BUILD_TEST_WIDE_KEYS) != 0;
+    const BuildScratch bs = build_scratch_within(n_in, n_out, K, count_only || wide_keys ? -1 : capacity, workspace_bytes);
     if (!workspace || workspace_bytes < bs.end || (reinterpret_cast<uintptr_t>(workspace) & 255)) {
         set_error("pcpp_build_triplets: workspace missing, misaligned or smaller than %zu bytes", bs.end);
         return PCPP_ERR_WORKSPACE;
@@ -1009,15 +1209,8 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     }
     *n_triplets = 0;
     char *ws = static_cast<char *>(workspace);
-    const bool wide_keys = (test_flags & PCPP_BUILD_TEST_WIDE_KEYS) != 0;
-    const bool keep_hits = bs.fwd_stride != 0 && workspace_bytes >= bs.end_with_hits && !wide_keys;
-    uint32_t *f_hits = keep_hits ? reinterpret_cast<uint32_t *>(ws + bs.fwd_hits_off) : nullptr;
-    uint32_t *b_hits = keep_hits ? reinterpret_cast<uint32_t *>(ws + bs.bwd_hits_off) : nullptr;
-    const Reuse no_reuse{nullptr, nullptr, nullptr};
     uint32_t *err = reinterpret_cast<uint32_t *>(ws + bs.err_off);
     auto scan_scratch = [&](int which) -> void * { return ws + bs.scan_off + (size_t)which * bs.scan_stride; };
-    const uint32_t list_cap = (test_flags & PCPP_BUILD_TEST_SHORT_LISTS) ? 40 : fill_list_cap(K);
-    auto lanes_log2 = [](uint32_t stride) { return stride >= 256 ? 6 : (stride > 64 ? 5 : 4); };   // (lists are half full)
 
     // Where |T| lands.  Pinned host memory is written by the device itself (the prefix sum's last block), so the
     // host can pick the count up while the second pass is already running; pageable memory gets it through a
@@ -1048,12 +1241,14 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     q.r2 = R * R;
     q.inv_cell = (double)t / (2.0 * R);
     q.t = t;
+    q.sign = 1.0;
     q.voxel_mode = voxel ? 1 : 0;
     q.h = (t - 1) / 2;
     q.c_off = out_batch_offsets;         // forward orientation: centres = outputs, candidates = inputs
     q.d_off = in_batch_offsets;
     q.n_batches = n_batches;
     QueryParams qs = q;                  // roles swapped: centres = inputs, candidates = outputs
+    qs.sign = -1.0;
     qs.c_off = in_batch_offsets;
     qs.d_off = out_batch_offsets;
 
@@ -1067,41 +1262,10 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         return rc;
 
     const int64_t nt_o = ceil_div(n_out, TILE), nt_i = ceil_div(n_in, TILE);
-    const size_t lds = (size_t)K * PITCH * sizeof(uint32_t);
-    // the first pass stages the lists that it keeps
-    const size_t lds_f = lds + (keep_hits ? (size_t)SEARCH_WAVES * bs.fwd_stride * sizeof(uint32_t) : 0);
-    const size_t lds_b = lds + (keep_hits ? (size_t)SEARCH_WAVES * bs.bwd_stride * sizeof(uint32_t) : 0);
-    const size_t lds_fill = fill_table_bytes(K) + (size_t)fill_list_cap(K) * 6;
-    if (lds_f > (size_t)32 * 1024 || lds_b > (size_t)32 * 1024) {
-        // large t: the per-tile table plus the neighbour lists exceed the default dynamic LDS limit
-        if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&query_count<false, false, true>)
-                                      : reinterpret_cast<const void *>(&query_count<false, false, false>), lds_f)) != PCPP_OK) return rc;
-        if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&query_count<true, false, true>)
-                                      : reinterpret_cast<const void *>(&query_count<true, false, false>), lds_b)) != PCPP_OK) return rc;
-    }
-    if (lds_fill > (size_t)32 * 1024) {
-        if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&query_fill<false, true>)
-                                      : reinterpret_cast<const void *>(&query_fill<false, false>), lds_fill)) != PCPP_OK) return rc;
-        if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&query_fill<true, true>)
-                                      : reinterpret_cast<const void *>(&query_fill<true, false>), lds_fill)) != PCPP_OK) return rc;
-    }
     const bool want_plan = plan && !count_only;
     const bool want_bwd = want_plan && (plan_flags & PCPP_PLAN_BWD_INPUT);
     const bool spatial = want_plan && (plan_flags & PCPP_PLAN_SPATIAL);
     const bool self = out_xyz == in_xyz && n_out == n_in && in_batch_offsets == out_batch_offsets;
-
-    // A cloud queried against itself: one pass counts both sides of the plan (while two [K][64] tables fit the
-    // LDS that one block may allocate, beside the lists).
-    bool one_pass = want_bwd && self && 2 * lds <= (size_t)72 * 1024;
-    if (one_pass && 2 * lds_f > (size_t)32 * 1024) {
-        int dev = 0, per_block = 0;
-        PCPP_HIP_CHECK(hipGetDevice(&dev));
-        PCPP_HIP_CHECK(hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-        if (2 * lds_f + 1024 > (size_t)per_block) one_pass = false;
-        else if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&query_count<false, true, true>)
-                                           : reinterpret_cast<const void *>(&query_count<false, true, false>), 2 * lds_f)) != PCPP_OK)
-            return rc;
-    }
 
     // the offsets of everything but the |T|-sized arrays do not depend on |T|
     const PlanLayout pl = want_plan ? plan_layout(n_in, n_out, K, 0, plan_flags) : PlanLayout{};
@@ -1110,42 +1274,120 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         return PCPP_ERR_WORKSPACE;
     }
     char *pb = static_cast<char *>(plan);
-    uint32_t *f_ptr = reinterpret_cast<uint32_t *>(ws + bs.fwd_ptr_off);
-    uint32_t *f_cnt = reinterpret_cast<uint32_t *>(ws + bs.fwd_cnt_off);
-    uint32_t *b_cnt = reinterpret_cast<uint32_t *>(ws + bs.bwd_cnt_off);
-    uint32_t *b_sum = reinterpret_cast<uint32_t *>(ws + bs.bwd_ptr_off);   // per-(k, tile) sums of the swapped side
-    const CountOut none{nullptr, nullptr, nullptr};
-    // the plan's own tables, when the first pass already runs in the plan's order (a plain plan)
-    const bool fwd_direct = want_plan && !spatial;
-    uint32_t *f_off = fwd_direct ? reinterpret_cast<uint32_t *>(pb + pl.fwd.tile_ptr_off) : f_ptr;
+    auto words = [](char *base, size_t off) { return reinterpret_cast<uint32_t *>(base + off); };
+    GridView grid_out = grid_in;
+    if (want_bwd && !self) {
+        if ((rc = build_grid(out_xyz, n_out, gm, out_batch_offsets, n_batches, ws, bs.grid_out, scan_scratch(SCAN_GRID_OUT),
+                             nullptr, 0, err, &grid_out, stream)) != PCPP_OK)
+            return rc;
+    }
 
-    // ---- the public list: centres = outputs in index order, candidates = inputs ------------------------------
-    // With a plan in spatial order the same neighbourhoods are counted again in slot order: given the room, this pass
-    // leaves its lists where that one can read them while it writes its own.
-    const bool reuse_lists = keep_hits && spatial && !ext && !count_only && workspace_bytes >= bs.end_with_reuse;
-    uint32_t *pub_hits = reuse_lists ? reinterpret_cast<uint32_t *>(ws + bs.pub_hits_off) : f_hits;
-    uint32_t *pub_n = reuse_lists ? reinterpret_cast<uint32_t *>(ws + bs.n_hits_off) : nullptr;
-    const Reuse from_public{reuse_lists ? pub_hits : nullptr, pub_n, in_xyz};
-    if (nt_o > 0) {
-        const CountOut fwd_out{count_only ? nullptr : f_cnt, f_ptr, pub_hits, pub_n};
-        if (one_pass && !spatial)
-            {
-                if (ext) query_count<false, true, true><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds_f, stream>>>(
-                out_xyz, n_out, nullptr, grid_in, q, K, nt_o, fwd_out, CountOut{b_cnt, b_sum, b_hits}, bs.fwd_stride, err, no_reuse);
-                else query_count<false, true, false><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds_f, stream>>>(
-                out_xyz, n_out, nullptr, grid_in, q, K, nt_o, fwd_out, CountOut{b_cnt, b_sum, b_hits}, bs.fwd_stride, err, no_reuse);
+    // ---- every centre's neighbours ----------------------------------------------------------------------------
+    // Centres = outputs, candidates = inputs; for the input gradient centres = inputs, candidates = outputs: the same
+    // predicate with the roles swapped, so the set is identical and only the grouping changes to (k, i, o).  A cloud
+    // queried against itself is searched once for both.
+    const bool f_lists = bs.fwd_stride != 0, b_lists = want_bwd && bs.bwd_stride != 0;
+    uint32_t *f_hits = f_lists ? words(ws, bs.fwd_hits_off) : nullptr, *f_n = words(ws, bs.fwd_n_off);
+    uint32_t *b_hits = b_lists ? words(ws, bs.bwd_hits_off) : nullptr, *b_n = self ? f_n : words(ws, bs.bwd_n_off);
+    auto search = [&](Form form, const float4 *order, const float *centres, int64_t n, const GridView &g, const QueryParams &qp,
+                      uint32_t *n_hits, uint32_t stride) -> int {
+        if (n <= 0) return PCPP_OK;
+        int per_wave = 1;                          // centres: as many as leave enough waves for the device
+        while (per_wave < 32 && n / (2 * per_wave) >= SEARCH_WAVES) per_wave *= 2;
+        const SearchArgs sa{order, centres, n, g, qp, f_hits, b_hits, n_hits, stride, per_wave, err};
+        auto kern = form == BOTH ? (ext ? search_cells<BOTH, true> : search_cells<BOTH, false>)
+                                 : form == INPUTS ? (ext ? search_cells<INPUTS, true> : search_cells<INPUTS, false>)
+                                                  : (ext ? search_cells<OUTPUTS, true> : search_cells<OUTPUTS, false>);
+        kern<<<(unsigned)ceil_div(ceil_div(n, per_wave), 4), 256, 0, stream>>>(sa);
+        PCPP_HIP_CHECK(hipGetLastError());
+        return PCPP_OK;
+    };
+    if (f_lists)
+        if ((rc = search(self && b_lists ? BOTH : OUTPUTS, self ? grid_in.pts : (want_bwd ? grid_out.pts : nullptr), out_xyz, n_out,
+                         grid_in, q, f_n, bs.fwd_stride)) != PCPP_OK)
+            return rc;
+    if (b_lists && !self)
+        if ((rc = search(INPUTS, grid_in.pts, in_xyz, n_in, grid_out, qs, b_n, bs.bwd_stride)) != PCPP_OK) return rc;
+
+    // ---- the centres' orders --------------------------------------------------------------------------------------
+    const int32_t *perm_o = nullptr, *perm_i = nullptr;
+    if (spatial) {
+        // cells of half the radius: a tile of 64 centres then spans a few radii at the densities the layers see
+        const double pitch = 0.5 * R;
+        int32_t *po = reinterpret_cast<int32_t *>(pb + pl.fwd.perm_off);
+        if ((rc = spatial_order(out_xyz, n_out, pitch, po, ws + bs.sort_off, scan_scratch(SCAN_SORT_OUT), bs.scan_stride,
+                                err, stream)) != PCPP_OK)
+            return rc;
+        perm_o = po;
+        if (want_bwd) {
+            int32_t *pi = reinterpret_cast<int32_t *>(pb + pl.bwd.perm_off);
+            if (self) {
+                PCPP_HIP_CHECK(hipMemcpyAsync(pi, po, (size_t)n_in * 4, hipMemcpyDeviceToDevice, stream));
+            } else if ((rc = spatial_order(in_xyz, n_in, pitch, pi, ws + bs.sort_off, scan_scratch(SCAN_SORT_IN),
+                                           bs.scan_stride, err, stream)) != PCPP_OK) {
+                return rc;
             }
-        else
-            {
-                if (ext) query_count<false, false, true><<<(unsigned)nt_o, SEARCH_THREADS, lds_f, stream>>>(
-                out_xyz, n_out, nullptr, grid_in, q, K, nt_o, fwd_out, none, bs.fwd_stride, err, no_reuse);
-                else query_count<false, false, false><<<(unsigned)nt_o, SEARCH_THREADS, lds_f, stream>>>(
-                out_xyz, n_out, nullptr, grid_in, q, K, nt_o, fwd_out, none, bs.fwd_stride, err, no_reuse);
-            }
+            perm_i = pi;
+        }
+    }
+
+    // ---- the sides: the public list in index order, the plan's forward side where that differs, its input-gradient side ----
+    const uint32_t tri_cap = (uint32_t)(capacity < (int64_t)INT32_MAX ? capacity : (int64_t)INT32_MAX);
+    // how many triplets the |T|-sized arrays of the plan have room for
+    uint32_t tail_cap = 0;
+    if (want_plan && pl.n_tail > 0) {
+        const size_t room = (plan_bytes - pl.tail_off) / (size_t)pl.n_tail / 256 * 256 / 4;
+        tail_cap = (uint32_t)(room < (size_t)tri_cap ? room : (size_t)tri_cap);
+    }
+    auto lanes_log2 = [](uint32_t stride) { return stride >= 256 ? 6 : (stride > 64 ? 5 : 4); };    // (lists are half full)
+    Sides sides{};
+    ScanJob jobs[MAX_SIDES] = {};
+    int n_sides = 0;
+    auto add_side = [&](bool outputs, const int32_t *perm, uint32_t *sums, uint32_t *ptr, int which, unsigned long long *total64,
+                        uint32_t *run_start, int64_t *seg, const FillOut &out) {
+        Side &d = sides.s[n_sides];
+        d.centres = outputs ? out_xyz : in_xyz;
+        d.perm = perm;
+        d.n_centres = outputs ? n_out : n_in;
+        d.n_tiles = outputs ? nt_o : nt_i;
+        d.g = outputs ? grid_in : grid_out;
+        d.q = outputs ? q : qs;
+        d.hits = outputs ? f_hits : b_hits;
+        d.n_hits = outputs ? f_n : b_n;
+        d.stride = outputs ? bs.fwd_stride : bs.bwd_stride;
+        d.lanes_log2 = lanes_log2(d.stride);
+        d.sums = sums; d.mirror_sums = nullptr;
+        d.ptr = ptr;
+        d.run_start = run_start; d.seg_out = seg;
+        d.out = out;
+        jobs[n_sides++] = ScanJob{sums, ptr, (int64_t)K * d.n_tiles, scan_scratch(which), total64};
+    };
+    // (the sums of a plan's side lie in its own offset table, which the prefix sum replaces in place)
+    uint32_t *f_ptr = want_plan ? words(pb, pl.fwd.tile_ptr_off) : nullptr, *b_ptr = want_bwd ? words(pb, pl.bwd.tile_ptr_off) : nullptr;
+    uint32_t *pub_ptr = want_plan && !spatial ? f_ptr : words(ws, bs.fwd_ptr_off);
+    add_side(true, nullptr, pub_ptr, pub_ptr, SCAN_PUBLIC, total_dev, want_plan && !spatial ? words(pb, pl.fwd.run_start_off) : nullptr,
+             count_only || nt_o == 0 ? nullptr : seg_offsets, FillOut{tri_o, tri_i, tri_k, nullptr, -1, tri_cap});
+    if (spatial)
+        add_side(true, perm_o, f_ptr, f_ptr, SCAN_FWD_SIDE, nullptr, words(pb, pl.fwd.run_start_off), nullptr,
+                 FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.fwd.gather_index, tail_cap});
+    int counted = n_sides;
+    if (want_bwd) {
+        add_side(false, perm_i, b_ptr, b_ptr, SCAN_BWD_SIDE, nullptr, words(pb, pl.bwd.run_start_off), nullptr,
+                 FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.bwd.gather_index, tail_cap});
+        // without lists one search counts both sides of a cloud against itself (same tiles on both)
+        if (self && !b_lists) sides.s[counted - 1].mirror_sums = b_ptr;
+        else counted = n_sides;
+    }
+    if (count_only) sides.s[0].n_hits = nullptr;
+    const int64_t most_tiles = want_bwd && nt_i > nt_o ? nt_i : nt_o;
+    if (most_tiles > 0) {
+        const dim3 grid((unsigned)most_tiles, (unsigned)counted);
+        const size_t lds = count_lds_bytes(K, sides.s[counted - 1].mirror_sums != nullptr);
+        if (ext) tile_count<true><<<grid, COUNT_THREADS, lds, stream>>>(sides, K, err);
+        else tile_count<false><<<grid, COUNT_THREADS, lds, stream>>>(sides, K, err);
         PCPP_HIP_CHECK(hipGetLastError());
     }
-    if ((rc = scan_exclusive_u32(f_ptr, f_off, (int64_t)K * nt_o, scan_scratch(SCAN_PUBLIC), total_dev, err, stream)) != PCPP_OK)
-        return rc;
+    if ((rc = scan_exclusive_u32_jobs(jobs, n_sides, err, stream)) != PCPP_OK) return rc;
     CallEvent landed;
     unsigned long long total = 0;
     bool have_total = false;
@@ -1179,121 +1421,23 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         return rc;
     }
     if (count_only) return wait_total();
-
-    const uint32_t tri_cap = (uint32_t)(capacity < (int64_t)INT32_MAX ? capacity : (int64_t)INT32_MAX);
-    // how many triplets the |T|-sized arrays of the plan have room for
-    uint32_t tail_cap = 0;
-    if (want_plan && pl.n_tail > 0) {
-        const size_t room = (plan_bytes - pl.tail_off) / (size_t)pl.n_tail / 256 * 256 / 4;
-        tail_cap = (uint32_t)(room < (size_t)tri_cap ? room : (size_t)tri_cap);
-    }
-    if (nt_o > 0) {
-        uint32_t *f_runs = fwd_direct ? reinterpret_cast<uint32_t *>(pb + pl.fwd.run_start_off) : nullptr;
-        {
-                if (ext) query_fill<false, true><<<(unsigned)nt_o, SEARCH_THREADS, lds_fill, stream>>>(
-            out_xyz, n_out, nullptr, grid_in, q, K, nt_o, f_cnt, f_off, FillOut{tri_o, tri_i, tri_k, nullptr, -1, tri_cap},
-            f_runs, list_cap, pub_hits, bs.fwd_stride, lanes_log2(bs.fwd_stride), seg_offsets, err);
-                else query_fill<false, false><<<(unsigned)nt_o, SEARCH_THREADS, lds_fill, stream>>>(
-            out_xyz, n_out, nullptr, grid_in, q, K, nt_o, f_cnt, f_off, FillOut{tri_o, tri_i, tri_k, nullptr, -1, tri_cap},
-            f_runs, list_cap, pub_hits, bs.fwd_stride, lanes_log2(bs.fwd_stride), seg_offsets, err);
-            }
-        PCPP_HIP_CHECK(hipGetLastError());
-    } else {
+    if (nt_o == 0) {
         // no outputs: every run starts at 0
         if ((rc = fill_u64(reinterpret_cast<unsigned long long *>(seg_offsets), 0ull, K + 1, stream)) != PCPP_OK) return rc;
     }
-
-    // ---- the plan's sides ---------------------------------------------------------------------------------------
-    GridView grid_out = grid_in;
-    if (want_bwd && !self) {
-        if ((rc = build_grid(out_xyz, n_out, gm, out_batch_offsets, n_batches, ws, bs.grid_out, scan_scratch(SCAN_GRID_OUT),
-                             nullptr, 0, err, &grid_out, stream)) != PCPP_OK)
-            return rc;
-    }
-    const int32_t *perm_o = nullptr, *perm_i = nullptr;
-    if (spatial) {
-        // cells of half the radius: a tile of 64 centres then spans a few radii at the densities the layers see
-        const double pitch = 0.5 * R;
-        int32_t *po = reinterpret_cast<int32_t *>(pb + pl.fwd.perm_off);
-        if ((rc = spatial_order(out_xyz, n_out, pitch, po, ws + bs.sort_off, scan_scratch(SCAN_SORT_OUT), bs.scan_stride,
-                                err, stream)) != PCPP_OK)
-            return rc;
-        perm_o = po;
-        if (want_bwd) {
-            int32_t *pi = reinterpret_cast<int32_t *>(pb + pl.bwd.perm_off);
-            if (self) {
-                PCPP_HIP_CHECK(hipMemcpyAsync(pi, po, (size_t)n_in * 4, hipMemcpyDeviceToDevice, stream));
-            } else if ((rc = spatial_order(in_xyz, n_in, pitch, pi, ws + bs.sort_off, scan_scratch(SCAN_SORT_IN),
-                                           bs.scan_stride, err, stream)) != PCPP_OK) {
+    if (most_tiles > 0) {
+        // four blocks of 8 waves per CU where a tile's neighbours (two thirds of the capacity, as a guess) fit their lists
+        FillShape shape = fill_shape_of(K, 512);
+        if (ceil_div(capacity, nt_o > 0 ? nt_o : 1) * 2 / 3 > (int64_t)shape.list_cap) shape = fill_shape_of(K, 1024);
+        if (test_flags & PCPP_BUILD_TEST_SHORT_LISTS) shape.list_cap = 40;
+        if (shape.lds > (size_t)32 * 1024)
+            if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&tile_fill<true>) : reinterpret_cast<const void *>(&tile_fill<false>),
+                                      shape.lds)) != PCPP_OK)
                 return rc;
-            }
-            perm_i = pi;
-        }
-        // forward side in the spatial order: same search, centres taken through the permutation
-        uint32_t *sf_ptr = reinterpret_cast<uint32_t *>(pb + pl.fwd.tile_ptr_off);
-        if (nt_o > 0) {
-            const CountOut fwd_out{f_cnt, f_ptr, f_hits};
-            if (one_pass)
-                {
-                if (ext) query_count<false, true, true><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds_f, stream>>>(
-                    out_xyz, n_out, perm_o, grid_in, q, K, nt_o, fwd_out, CountOut{b_cnt, b_sum, b_hits}, bs.fwd_stride, err, from_public);
-                else query_count<false, true, false><<<(unsigned)nt_o, SEARCH_THREADS, 2 * lds_f, stream>>>(
-                    out_xyz, n_out, perm_o, grid_in, q, K, nt_o, fwd_out, CountOut{b_cnt, b_sum, b_hits}, bs.fwd_stride, err, from_public);
-            }
-            else
-                {
-                if (ext) query_count<false, false, true><<<(unsigned)nt_o, SEARCH_THREADS, lds_f, stream>>>(
-                    out_xyz, n_out, perm_o, grid_in, q, K, nt_o, fwd_out, none, bs.fwd_stride, err, from_public);
-                else query_count<false, false, false><<<(unsigned)nt_o, SEARCH_THREADS, lds_f, stream>>>(
-                    out_xyz, n_out, perm_o, grid_in, q, K, nt_o, fwd_out, none, bs.fwd_stride, err, from_public);
-            }
-            PCPP_HIP_CHECK(hipGetLastError());
-        }
-        if ((rc = scan_exclusive_u32(f_ptr, sf_ptr, (int64_t)K * nt_o, scan_scratch(SCAN_FWD_SIDE), nullptr, err, stream)) != PCPP_OK)
-            return rc;
-        if (nt_o > 0) {
-            {
-                if (ext) query_fill<false, true><<<(unsigned)nt_o, SEARCH_THREADS, lds_fill, stream>>>(
-                out_xyz, n_out, perm_o, grid_in, q, K, nt_o, f_cnt, sf_ptr,
-                FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.fwd.gather_index, tail_cap},
-                reinterpret_cast<uint32_t *>(pb + pl.fwd.run_start_off), list_cap, f_hits, bs.fwd_stride, lanes_log2(bs.fwd_stride), nullptr, err);
-                else query_fill<false, false><<<(unsigned)nt_o, SEARCH_THREADS, lds_fill, stream>>>(
-                out_xyz, n_out, perm_o, grid_in, q, K, nt_o, f_cnt, sf_ptr,
-                FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.fwd.gather_index, tail_cap},
-                reinterpret_cast<uint32_t *>(pb + pl.fwd.run_start_off), list_cap, f_hits, bs.fwd_stride, lanes_log2(bs.fwd_stride), nullptr, err);
-            }
-            PCPP_HIP_CHECK(hipGetLastError());
-        }
-    }
-    if (want_bwd) {
-        // input-gradient side: centres = inputs, candidates = outputs; same predicate with the roles
-        // swapped, so the set is identical and only the grouping changes to (k, i, o)
-        uint32_t *b_ptr = reinterpret_cast<uint32_t *>(pb + pl.bwd.tile_ptr_off);
-        uint32_t *b_runs = reinterpret_cast<uint32_t *>(pb + pl.bwd.run_start_off);
-        if (nt_i > 0 && !one_pass) {
-            {
-                if (ext) query_count<true, false, true><<<(unsigned)nt_i, SEARCH_THREADS, lds_b, stream>>>(
-                in_xyz, n_in, perm_i, grid_out, qs, K, nt_i, CountOut{b_cnt, b_sum, b_hits}, none, bs.bwd_stride, err, no_reuse);
-                else query_count<true, false, false><<<(unsigned)nt_i, SEARCH_THREADS, lds_b, stream>>>(
-                in_xyz, n_in, perm_i, grid_out, qs, K, nt_i, CountOut{b_cnt, b_sum, b_hits}, none, bs.bwd_stride, err, no_reuse);
-            }
-            PCPP_HIP_CHECK(hipGetLastError());
-        }
-        if ((rc = scan_exclusive_u32(b_sum, b_ptr, (int64_t)K * nt_i, scan_scratch(SCAN_BWD_SIDE), nullptr, err, stream)) != PCPP_OK)
-            return rc;
-        if (nt_i > 0) {
-            {
-                if (ext) query_fill<true, true><<<(unsigned)nt_i, SEARCH_THREADS, lds_fill, stream>>>(
-                in_xyz, n_in, perm_i, grid_out, qs, K, nt_i, b_cnt, b_ptr,
-                FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.bwd.gather_index, tail_cap}, b_runs, list_cap,
-                b_hits, bs.bwd_stride, lanes_log2(bs.bwd_stride), nullptr, err);
-                else query_fill<true, false><<<(unsigned)nt_i, SEARCH_THREADS, lds_fill, stream>>>(
-                in_xyz, n_in, perm_i, grid_out, qs, K, nt_i, b_cnt, b_ptr,
-                FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.bwd.gather_index, tail_cap}, b_runs, list_cap,
-                b_hits, bs.bwd_stride, lanes_log2(bs.bwd_stride), nullptr, err);
-            }
-            PCPP_HIP_CHECK(hipGetLastError());
-        }
+        const dim3 grid((unsigned)most_tiles, (unsigned)n_sides);
+        if (ext) tile_fill<true><<<grid, shape.threads, shape.lds, stream>>>(sides, K, shape.list_cap, err);
+        else tile_fill<false><<<grid, shape.threads, shape.lds, stream>>>(sides, K, shape.list_cap, err);
+        PCPP_HIP_CHECK(hipGetLastError());
     }
     // everything is queued; now compare the count with what the caller provided
     if ((rc = wait_total()) != PCPP_OK) return rc;

@@ -104,6 +104,16 @@ size_t scan_scratch_bytes(int64_t n);
 // when it is already set the last block stores ~0 as the total.
 int scan_exclusive_u32(const uint32_t *in, uint32_t *out, int64_t n, void *scratch,
                        unsigned long long *total64, uint32_t *err, hipStream_t stream);
+// Several independent prefix sums in one launch, each with a scratch of its own as above.
+struct ScanJob {
+    const uint32_t *in;
+    uint32_t *out;
+    int64_t n;
+    void *scratch;
+    unsigned long long *total64;
+};
+constexpr int MAX_SCAN_JOBS = 3;
+int scan_exclusive_u32_jobs(const ScanJob *jobs, int n_jobs, uint32_t *err, hipStream_t stream);
 int fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t stream);
 int fill_u64(unsigned long long *p, unsigned long long v, int64_t n, hipStream_t stream);
 

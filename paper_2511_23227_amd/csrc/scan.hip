@@ -55,11 +55,17 @@ __device__ inline unsigned long long block_incl_scan_u64(unsigned long long v, u
 // blocks at a time: it adds the published sums down to the nearest block whose whole prefix is known
 // (the position before block 0 counts as a known prefix of 0).  Value and flag share one 64-bit word,
 // written and read with single agent-scope accesses, so no ordering between two words is relied on.
-__global__ __launch_bounds__(SCAN_THREADS) void scan_chained(const uint32_t *in, uint32_t *out,
-                                                             int64_t n, unsigned long long *__restrict__ status,
-                                                             int64_t n_blocks, unsigned long long *__restrict__ total64,
-                                                             uint32_t *__restrict__ err)
+// blockIdx.y picks one of several independent sums; blocks past the end of a shorter one leave before they take a ticket.
+struct ScanJobs { ScanJob job[MAX_SCAN_JOBS]; };
+
+__global__ __launch_bounds__(SCAN_THREADS) void scan_chained(const ScanJobs jobs, uint32_t *__restrict__ err)
 {
+    const ScanJob &jb = jobs.job[blockIdx.y];
+    const uint32_t *in = jb.in;
+    uint32_t *out = jb.out;
+    const int64_t n = jb.n, n_blocks = n > 0 ? (n + SCAN_BLOCK - 1) / SCAN_BLOCK : 1;
+    unsigned long long *status = static_cast<unsigned long long *>(jb.scratch), *total64 = jb.total64;
+    if ((int64_t)blockIdx.x >= n_blocks) return;
     __shared__ unsigned long long shared_word[2];       // ticket, then the block's exclusive prefix
     const int lane = threadIdx.x & 63;
     if (threadIdx.x == 0) shared_word[0] = atomicAdd(&status[n_blocks], 1ull);
@@ -157,21 +163,25 @@ size_t scan_scratch_bytes(int64_t n)
     return align_up((size_t)(ceil_div(n > 0 ? n : 1, SCAN_BLOCK) + 1) * sizeof(unsigned long long));
 }
 
+int scan_exclusive_u32_jobs(const ScanJob *jobs, int n_jobs, uint32_t *err, hipStream_t stream)
+{
+    ScanJobs js{};
+    int64_t blocks = 1;
+    for (int j = 0; j < n_jobs && j < MAX_SCAN_JOBS; ++j) {
+        js.job[j] = jobs[j];
+        const int64_t nb = ceil_div(jobs[j].n, SCAN_BLOCK);
+        if (nb > blocks) blocks = nb;
+    }
+    scan_chained<<<dim3((unsigned)blocks, (unsigned)n_jobs), SCAN_THREADS, 0, stream>>>(js, err);
+    PCPP_HIP_CHECK(hipGetLastError());
+    return PCPP_OK;
+}
+
 int scan_exclusive_u32(const uint32_t *in, uint32_t *out, int64_t n, void *scratch,
                        unsigned long long *total64, uint32_t *err, hipStream_t stream)
 {
-    auto *status = static_cast<unsigned long long *>(scratch);
-    if (n <= 0) {
-        // out[0] = 0, total = 0
-        fill_u32_kernel<<<1, 64, 0, stream>>>(out, 0u, 1);
-        if (total64) fill_u64_kernel<<<1, 64, 0, stream>>>(total64, 0ull, 1);
-        PCPP_HIP_CHECK(hipGetLastError());
-        return PCPP_OK;
-    }
-    const int64_t n_blocks = ceil_div(n, SCAN_BLOCK);
-    scan_chained<<<(unsigned)n_blocks, SCAN_THREADS, 0, stream>>>(in, out, n, status, n_blocks, total64, err);
-    PCPP_HIP_CHECK(hipGetLastError());
-    return PCPP_OK;
+    const ScanJob job{in, out, n, scratch, total64};
+    return scan_exclusive_u32_jobs(&job, 1, err, stream);
 }
 
 int fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t stream)

@@ -1,5 +1,5 @@
-"""Triplet builds whose tiles of 64 centres hold more neighbours than the fill pass keeps on chip at a time (12 276 with 27
-cells, 3 834 with 216): tiles in several parts, and single centres that are past it."""
+"""Triplet builds whose tiles of 64 centres hold more neighbours than the fill pass keeps on chip at a time (8 192 in crowded
+clouds): tiles in several parts, and single centres that are past it; and neighbour lists of every length."""
 import numpy as np
 import pytest
 import torch
@@ -8,8 +8,8 @@ import oracle
 from parity_util import assert_close, oracle_bwd_input, oracle_fwd
 
 # points in a ball of the radius, outputs among them (0: all), t, what the sizes are for
-CASES = [(700, 0, 3, "parts of 17 centres"), (300, 0, 6, "parts of 12 centres, 216 cells"), (12_500, 3, 3, "single centres"),
-         (4_000, 70, 6, "single centres, 216 cells, a second tile of 6")]
+CASES = [(700, 0, 3, "parts of 11 centres"), (300, 0, 6, "parts of 27 centres, 216 cells"), (12_500, 3, 3, "single centres"),
+         (4_000, 70, 6, "parts of 2 centres, 216 cells, a second tile of 6")]
 
 
 @pytest.mark.gpu
@@ -37,3 +37,49 @@ def test_tiles_past_the_list(n, n_out, t, what, spatial):
     dx = m.pcpp_mvmr_bwd_input(torch.from_numpy(dy).cuda(), torch.from_numpy(w).cuda(), T)
     assert_close(y.cpu().numpy(), *oracle_fwd(x, w, o, i, k, len(out)), 1e-4, "y")
     assert_close(dx.cpu().numpy(), *oracle_bwd_input(dy, w, o, i, k, n), 1e-4, "dx")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("spatial,same", [(False, True), (False, False), (True, True), (True, False)])
+@pytest.mark.parametrize("t", [2, 3, 5])
+def test_workspace_between_the_sizes(t, spatial, same, batched):
+    """Neighbour lists as long as the workspace has room for: none (8 cells), inside the per-centre tables (26 and 124 words),
+    shorter than the capacity asks for, and as long.  Centres with more neighbours are searched again: the same list and plan."""
+    import ctypes
+    import paper_2511_23227_amd as m
+    from paper_2511_23227_amd import binding as B
+    L = m.library()
+    rng = np.random.default_rng(7 * t + spatial)
+    p = np.concatenate([rng.random((900, 3)) * 1.2, 0.5 + rng.random((300, 3)) * 0.1]).astype(np.float32)
+    p = p[rng.permutation(len(p))]
+    out = p if same else p[::3].copy()
+    r = np.float32(0.2)
+    cuts = [0, 500, len(p)] if batched else [0, len(p)]
+    ocuts = cuts if same else [-(-c // 3) for c in cuts]
+    o, i, k, seg = oracle.build_triplets_general(p, out, r, t, in_offsets=np.array(cuts, np.int32), out_offsets=np.array(ocuts, np.int32))
+    n_of = np.bincount(o, minlength=len(out))
+    assert n_of.max() > 100 and (n_of < 27).any()
+    d = torch.from_numpy(p).cuda()
+    do = d if same else torch.from_numpy(out).cuda()
+    off_i = torch.tensor(cuts, dtype=torch.int32, device="cuda") if batched else None
+    off_o = off_i if same else torch.tensor(ocuts, dtype=torch.int32, device="cuda") if batched else None
+    least, most = L.pcpp_build_triplets_workspace_bytes(len(p), len(out), t), L.pcpp_build_triplets_workspace_bytes_for(len(p), len(out), t, len(o))
+    flags = B.PLAN_FWD | B.PLAN_BWD_INPUT | (B.PLAN_SPATIAL if spatial else 0)
+    plans = []
+    for size in (least, least + (most - least) // 4, most):
+        ws = torch.full((size,), 255, dtype=torch.uint8, device="cuda")
+        tri = [torch.empty(len(o), dtype=torch.int32, device="cuda") for _ in range(3)]
+        sg = torch.empty(t ** 3 + 1, dtype=torch.int64, device="cuda")
+        plan = torch.zeros(L.pcpp_plan_bytes(len(p), len(out), t, len(o), flags), dtype=torch.uint8, device="cuda")
+        n = ctypes.c_int64(0)
+        rc = L.pcpp_build_triplets_batched(B._ptr(d), len(p), B._ptr(do), len(out), B._ptr(off_i), B._ptr(off_o), len(cuts) - 1,
+                                           float(r), t, *[B._ptr(x) for x in tri], len(o), B._ptr(sg), ctypes.byref(n), B._ptr(plan),
+                                           plan.numel(), flags, B._ptr(ws), size, B._stream())
+        assert rc == 0, L.pcpp_last_error()
+        torch.cuda.synchronize()
+        assert n.value == len(o) and np.array_equal(sg.cpu().numpy(), seg)
+        for got, want in zip(tri, (o, i, k)):
+            assert np.array_equal(got.cpu().numpy(), want)
+        plans.append(plan.cpu().numpy()[256:])
+    assert np.array_equal(plans[0], plans[2]) and np.array_equal(plans[1], plans[2])
