@@ -100,16 +100,16 @@ __device__ inline unsigned long long mix_batch(unsigned long long key, int batch
 
 // ---- hashed grid over the candidate set ------------------------------------------------------
 
-// empty table: no keys, zero populations (slots + 1 entries, the input of the prefix sum), zero cursors;
+// empty table: no keys, zero populations (slots + 1 entries, the input of the prefix sum);
 // the first call of a build also zeroes the status words of all its prefix sums
 __global__ __launch_bounds__(256) void grid_clear(unsigned long long *__restrict__ keys, uint32_t *__restrict__ cnt,
-                                                  uint32_t *__restrict__ cursor, int64_t slots,
+                                                  int64_t slots,
                                                   unsigned long long *__restrict__ scan_status, int64_t scan_words)
 {
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i <= slots; i += stride) {
         cnt[i] = 0u;
-        if (i < slots) { keys[i] = EMPTY_KEY; cursor[i] = 0u; }
+        if (i < slots) keys[i] = EMPTY_KEY;
     }
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < scan_words; i += stride) scan_status[i] = 0ull;
 }
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void grid_insert(const float *__restrict__ xyz
                                                    const int32_t *__restrict__ batch_off, int n_batches,
                                                    unsigned long long *__restrict__ keys,
                                                    uint32_t *__restrict__ slot_cnt, uint32_t mask,
-                                                   uint32_t *__restrict__ point_slot)
+                                                   uint2 *__restrict__ point_at)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
@@ -129,24 +129,24 @@ __global__ __launch_bounds__(256) void grid_insert(const float *__restrict__ xyz
     uint32_t slot = hash_key(key) & mask;
     // the table has at least twice as many slots as points, so an empty slot is always reached
     for (;;) {
-        unsigned long long prev = atomicCAS(&keys[slot], EMPTY_KEY, key);
+        // (most points find their cell's key there already: a read is cheaper than a swap)
+        unsigned long long prev = __hip_atomic_load(&keys[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (prev == EMPTY_KEY) prev = atomicCAS(&keys[slot], EMPTY_KEY, key);
         if (prev == EMPTY_KEY || prev == key) break;
         slot = (slot + 1) & mask;
     }
-    atomicAdd(&slot_cnt[slot], 1u);
-    point_slot[p] = slot;
+    point_at[p] = make_uint2(slot, atomicAdd(&slot_cnt[slot], 1u));      // its slot, and its place there
 }
 
 __global__ __launch_bounds__(256) void grid_scatter(const float *__restrict__ xyz, int64_t n,
-                                                    const uint32_t *__restrict__ point_slot,
-                                                    const uint32_t *__restrict__ slot_start,
-                                                    uint32_t *__restrict__ cursor, float4 *__restrict__ pts,
+                                                    const uint2 *__restrict__ point_at,
+                                                    const uint32_t *__restrict__ slot_start, float4 *__restrict__ pts,
                                                     const uint32_t *__restrict__ err)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n || *err) return;                       // err: the slot offsets come from a prefix sum that gave up
-    const uint32_t slot = point_slot[p];
-    const uint32_t pos = slot_start[slot] + atomicAdd(&cursor[slot], 1u);
+    const uint2 at = point_at[p];
+    const uint32_t pos = slot_start[at.x] + at.y;
     pts[pos] = make_float4(xyz[3 * p], xyz[3 * p + 1], xyz[3 * p + 2], __int_as_float((int)p));
 }
 
@@ -207,6 +207,10 @@ __device__ inline int here(int v)
 
 __device__ inline uint32_t lane_value(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
 __device__ inline float lane_value(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+
+// The block's LDS traffic done, then its barrier.  No wait for memory: what the passes below read ahead stays on its way, and
+// nobody waits for stores; the waves of a block share nothing but LDS.
+__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Candidates around one grid cell, held across the lanes of a wave: lane j < 27 owns stencil cell j.
 // Every method must be called by all 64 lanes of the wave (it uses cross-lane reads).
@@ -348,7 +352,7 @@ constexpr uint32_t HIT_INDEX_MASK = (1u << HIT_INDEX_BITS) - 1u;
 // order), and those of one cell together: the stencil is probed and the candidates are read, placed and converted once for
 // all of them, 256 at a time in registers, and a centre costs its binary64 tests, the cells of its neighbours and the stores.
 // Bound by instruction issue.  One search per centre, in the order of the tiles and with the tiles' tables in LDS: 1 M points
-// of a ground scene, 32 neighbours in 125 cells, 1215 us.
+// of a ground scene, 32 neighbours in 125 cells, 1215 us; now 325.
 constexpr int GROUP_SETS = 4;             // sets of 64 candidates in registers
 constexpr int64_t SEARCH_WAVES = 8192;    // waves wanted before a wave takes more centres
 
@@ -484,7 +488,6 @@ struct Side {
     const uint32_t *hits;
     uint32_t *n_hits;
     uint32_t stride;
-    int lanes_log2;               // lanes that read one list
     uint32_t *sums, *mirror_sums;
     const uint32_t *ptr;
     uint32_t *run_start;          // [n_tiles][K][TILE], NULL: not wanted
@@ -494,21 +497,20 @@ struct Side {
 constexpr int MAX_SIDES = 3;
 struct Sides { Side s[MAX_SIDES]; };
 
-// What the passes keep in LDS of a tile's centres.
+// What the fill pass keeps in LDS of a tile's centres.
 struct TileCentres {
     uint32_t n[TILE], off[TILE];  // neighbours of each, and of the centres before it
     int32_t at[TILE];             // its own index
     uint32_t searched;            // centres without a complete list: whether there are any
 
-    // by wave 0; a barrier follows.  `whole`: centres without a complete list count with what they have, else with nothing.
-    __device__ inline void open(const Side &s, int64_t tile, bool whole, int lane)
+    // by wave 0; a barrier follows
+    __device__ inline void open(const Side &s, int64_t tile, int lane)
     {
         const int64_t slot = tile * TILE + lane;
         const bool on = slot < s.n_centres;
         const int32_t c = on ? (s.perm ? s.perm[slot] : (int32_t)slot) : 0;
-        uint32_t m = on && (whole || s.stride) ? s.n_hits[c] : 0u;
+        const uint32_t m = on ? s.n_hits[c] : 0u;
         const unsigned long long past = __ballot(on && (m > s.stride || !s.stride));
-        if (!whole && m > s.stride) m = 0u;
         at[lane] = c;
         n[lane] = m;
         off[lane] = wave_incl_scan_u32(m) - m;
@@ -533,71 +535,129 @@ struct TileCentres {
     }
 };
 
+// The tile of a block.  Blocks go round the eight XCDs; of many tiles, 16 consecutive ones (a cache line of an offset table's
+// row) go to one XCD, whose L2 then reads the line once and completes the lines that the ends of their output share.
+constexpr int XCD_TILES = 16, NUM_XCD = 8;
+__host__ __device__ inline bool tiles_by_xcd(int64_t n_tiles) { return n_tiles >= 32 * XCD_TILES * NUM_XCD; }
+__device__ inline int64_t tile_of_block(int64_t block, int64_t n_tiles)
+{
+    if (!tiles_by_xcd(n_tiles)) return block;
+    const int64_t r = block / NUM_XCD;
+    return (r / XCD_TILES * NUM_XCD + block % NUM_XCD) * XCD_TILES + r % XCD_TILES;
+}
+// ... and how many blocks n_tiles tiles take (the last ones may find no tile)
+inline int64_t blocks_of_tiles(int64_t n_tiles)
+{
+    return tiles_by_xcd(n_tiles) ? ceil_div(n_tiles, XCD_TILES * NUM_XCD) * (XCD_TILES * NUM_XCD) : n_tiles;
+}
+
 // ---- pass 1: neighbours per (cell, tile) ----------------------------------------------------------
-// A thread takes four consecutive neighbours of the tile, whose list words are on their way at a time.  Consecutive neighbours
-// often fall in one cell, so that every lane of a half wave has a column of counters of its own.
-constexpr int COUNT_THREADS = 512;
+// Eight lanes read a centre's list, four words each at a time.  Consecutive neighbours often fall in one cell, so that every
+// lane of a half wave has a column of counters of its own.  A block takes several consecutive tiles where there are enough for
+// the device, so that the three reads that depend on each other (centre, length, list) are on their way two, one and one tile
+// ahead: bound by their latency otherwise (three sides of 1 M points with 32 neighbours: 236 us, one tile per block).
+constexpr int COUNT_THREADS = 8 * TILE;
+constexpr int64_t COUNT_BLOCKS = 2048;                     // blocks wanted before a block takes more tiles
 constexpr int COUNT_COLS = 32, COUNT_PITCH = COUNT_COLS + 1;
-constexpr int COUNT_AHEAD = 4;                             // list words in flight per thread
-constexpr size_t count_lds_bytes(int K, bool mirror) { return (size_t)K * COUNT_PITCH * sizeof(uint32_t) * (mirror ? 2 : 1); }
+constexpr int COUNT_TILES = 16;                            // at most that many tiles per block, whose sums are written together
+constexpr size_t count_lds_bytes(int K, bool mirror) { return (size_t)K * (COUNT_PITCH + COUNT_TILES) * sizeof(uint32_t) * (mirror ? 2 : 1); }
+typedef uint32_t list_words __attribute__((ext_vector_type(4), aligned(4)));     // (a list may start at any word)
 
 template <bool EXT>
-__global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides, int K, const uint32_t *__restrict__ err)
+__global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides, int K, int tiles_per_block, const uint32_t *__restrict__ err)
 {
-    extern __shared__ uint32_t tbl[];                      // [K][COUNT_PITCH], twice with mirror_sums
-    __shared__ TileCentres tc;
+    extern __shared__ uint32_t tbl[];                      // [K][COUNT_PITCH] and [K][COUNT_TILES], each twice with mirror_sums
+    __shared__ uint32_t searched[2];                       // tile's parity: a centre of it has no complete list
     const Side &s = sides.s[blockIdx.y];
-    const int64_t tile = blockIdx.x;
-    if (*err || tile >= s.n_tiles) return;                 // block-uniform: the grid's offsets are not to be trusted
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t t0 = (int64_t)blockIdx.x * tiles_per_block;
+    const int64_t t1 = t0 + tiles_per_block < s.n_tiles ? t0 + tiles_per_block : s.n_tiles;
+    if (*err || t0 >= t1) return;                          // block-uniform: the grid's offsets are not to be trusted
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int PITCH = COUNT_PITCH, WAVES = COUNT_THREADS / 64;
     const bool mirror = s.mirror_sums != nullptr;
-    uint32_t *tbl2 = tbl + K * PITCH, *col = tbl + (threadIdx.x & 31);
-    if (wave == 0) tc.open(s, tile, false, lane);
-    for (int i = threadIdx.x; i < K * PITCH * (mirror ? 2 : 1); i += COUNT_THREADS) tbl[i] = 0u;
-    __syncthreads();
-    const uint32_t listed = tc.off[TILE - 1] + tc.n[TILE - 1];
-    for (uint32_t p0 = COUNT_AHEAD * threadIdx.x; p0 < listed; p0 += COUNT_AHEAD * COUNT_THREADS) {
-        uint32_t key[COUNT_AHEAD];
-        TileCentres::Cursor c = tc.cursor(p0);
+    uint32_t *tbl2 = tbl + K * PITCH, *col = tbl + (tid & 31);
+    uint32_t *sums = tbl + K * PITCH * (mirror ? 2 : 1), *sums2 = sums + K * COUNT_TILES;
+    const int al = tid >> 3, l = tid & 7;
+    auto centre_of = [&](int64_t tile) -> int32_t {        // -1: none
+        const int64_t slot = tile * TILE + al;
+        return tile < t1 && slot < s.n_centres ? (s.perm ? s.perm[slot] : (int32_t)slot) : -1;
+    };
+    auto length_of = [&](int32_t c) -> uint32_t { return c >= 0 && s.stride ? s.n_hits[c] : 0u; };
+    auto words_of = [&](int32_t c, uint32_t n, uint32_t e) -> list_words {
+        // (a last piece may read past the list, not past the lists' end)
+        return n <= s.stride && e < n ? *reinterpret_cast<const list_words *>(s.hits + (size_t)c * s.stride + e) : list_words{0u, 0u, 0u, 0u};
+    };
+    int32_t c_now = centre_of(t0), c_next = centre_of(t0 + 1), c_after = centre_of(t0 + 2);
+    uint32_t n_now = length_of(c_now), n_next = length_of(c_next);
+    list_words w_now = words_of(c_now, n_now, 4u * l);
+    for (int i = tid; i < K * PITCH * (mirror ? 2 : 1); i += COUNT_THREADS) tbl[i] = 0u;
+    if (tid < 2) searched[tid] = 0u;
+    lds_barrier();
+    for (int64_t tile = t0; tile < t1; ++tile) {
+        const list_words w_next = words_of(c_next, n_next, 4u * l);
+        const uint32_t n_after = length_of(c_after);
+        const int32_t c_third = centre_of(tile + 3);
+        const uint32_t n = n_now <= s.stride ? n_now : 0u;
+        list_words w = w_now;
+        for (uint32_t e = 4u * l; e < n;) {
 #pragma unroll
-        for (int j = 0; j < COUNT_AHEAD; ++j)
-            if (p0 + j < listed) {
-                tc.advance(c, p0 + j);
-                key[j] = s.hits[(size_t)tc.at[c.al] * s.stride + (p0 + j - tc.off[c.al])];
-            }
-#pragma unroll
-        for (int j = 0; j < COUNT_AHEAD; ++j)
-            if (p0 + j < listed) atomicAdd(&col[(key[j] >> HIT_INDEX_BITS) * PITCH], 1u);
-    }
-    if (tc.searched)                                       // (block-uniform)
-        for (int al = wave; al < TILE; al += WAVES) {
-            const int64_t slot = tile * TILE + al;
-            if (slot >= s.n_centres) break;                // wave-uniform
-            const int64_t c = tc.at[al];
-            if (s.stride && (uint32_t)__builtin_amdgcn_readfirstlane((int)s.n_hits[c]) <= s.stride) continue;
-            Candidates<EXT> cand;
-            cand.open(s.centres, c, s.g, s.q, lane);
-            uint32_t n = 0;
-            for (uint32_t base = 0; base < cand.st.total; base += 64) {
-                int b, k, k2;
-                const bool hit = cand.fetch(base + lane, s.g, s.q, b, k, k2);
-                if (hit) {
-                    atomicAdd(&col[k * PITCH], 1u);
-                    if (mirror) atomicAdd(&tbl2[k2 * PITCH + (threadIdx.x & 31)], 1u);
-                }
-                n += (uint32_t)__popcll(__ballot(hit));
-            }
-            if (!s.stride && s.n_hits && lane == 0) s.n_hits[c] = n;
+            for (int j = 0; j < 4; ++j)
+                if (e + j < n) atomicAdd(&col[(w[j] >> HIT_INDEX_BITS) * PITCH], 1u);
+            e += 32u;
+            if (e < n) w = words_of(c_now, n, e);
         }
-    __syncthreads();
-    for (int k0 = 2 * wave; k0 < K; k0 += 2 * WAVES) {     // a half wave per cell
-        const int k = k0 + (lane >> 5), l = lane & 31;
-        const uint32_t v = half_incl_scan_u32(k < K ? tbl[k * PITCH + l] : 0u);
-        if (k < K && l == 31) s.sums[(size_t)k * s.n_tiles + tile] = v;
-        if (mirror) {
-            const uint32_t v2 = half_incl_scan_u32(k < K ? tbl2[k * PITCH + l] : 0u);
-            if (k < K && l == 31) s.mirror_sums[(size_t)k * s.n_tiles + tile] = v2;
+        if (c_now >= 0 && (n_now > s.stride || !s.stride)) searched[tile & 1] = 1u;
+        lds_barrier();
+        if (tid == 0) searched[(tile + 1) & 1] = 0u;       // (read before the last barrier, written behind the next)
+        if (searched[tile & 1]) {                          // (block-uniform)
+            // centres without a complete list: searched, one wave per centre
+            for (int a = wave; a < TILE; a += WAVES) {
+                const int64_t slot = tile * TILE + a;
+                if (slot >= s.n_centres) break;            // wave-uniform
+                const int64_t c = s.perm ? (int64_t)s.perm[slot] : slot;
+                if (s.stride && (uint32_t)__builtin_amdgcn_readfirstlane((int)s.n_hits[c]) <= s.stride) continue;
+                Candidates<EXT> cand;
+                cand.open(s.centres, c, s.g, s.q, lane);
+                uint32_t found = 0;
+                for (uint32_t base = 0; base < cand.st.total; base += 64) {
+                    int b, k, k2;
+                    const bool hit = cand.fetch(base + lane, s.g, s.q, b, k, k2);
+                    if (hit) {
+                        atomicAdd(&col[k * PITCH], 1u);
+                        if (mirror) atomicAdd(&tbl2[k2 * PITCH + (tid & 31)], 1u);
+                    }
+                    found += (uint32_t)__popcll(__ballot(hit));
+                }
+                if (!s.stride && s.n_hits && lane == 0) s.n_hits[c] = found;
+            }
+            lds_barrier();
+        }
+        for (int i = tid; i < 4 * K; i += COUNT_THREADS) { // four threads per cell, which also clear its counters
+            const int k = i >> 2;
+            auto row_sum = [&](uint32_t *row) -> uint32_t {
+                uint32_t v = 0u;
+#pragma unroll
+                for (int j = 0; j < COUNT_COLS / 4; ++j) { v += row[j]; row[j] = 0u; }
+                v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true);       // neighbours in the group of four
+                return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, true);
+            };
+            const uint32_t at = (uint32_t)(k * PITCH + (i & 3) * (COUNT_COLS / 4));
+            const uint32_t v = row_sum(tbl + at), v2 = mirror ? row_sum(tbl2 + at) : 0u;
+            if ((i & 3) == 0) {
+                sums[k * COUNT_TILES + (int)(tile - t0)] = v;
+                if (mirror) sums2[k * COUNT_TILES + (int)(tile - t0)] = v2;
+            }
+        }
+        lds_barrier();
+        c_now = c_next; n_now = n_next; w_now = w_next;
+        c_next = c_after; n_next = n_after;
+        c_after = c_third;
+    }
+    for (int i = tid; i < K * COUNT_TILES; i += COUNT_THREADS) {
+        const int64_t tile = t0 + i % COUNT_TILES, at = (int64_t)(i / COUNT_TILES) * s.n_tiles + tile;
+        if (tile < t1) {
+            s.sums[at] = sums[i];
+            if (mirror) s.mirror_sums[at] = sums2[i];
         }
     }
 }
@@ -610,32 +670,41 @@ __global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides
 // output does, so that a wave's stores cover a few contiguous pieces of the output.  Tiles with more neighbours than the list holds are done some
 // centres at a time.
 //   LDS: [K][FILL_PITCH] runs, two centres to a word (a list has fewer than 2^16 places); [K] first triplet of the tile (or of
-//   its part) in cell k; [K] how many there are; [K] where they start in the list; the list: candidate index, (cell | centre << 8)
-// What bounds it: the table (1 M points, 125 cells: 500 MB of run starts) and the barriers between the phases.
+//   its part) in cell k; [K] how many there are; [K] where they start in the list; [K] whether run_start wants the row; the list: candidate index, (cell | centre << 8)
+// What bounds it: the vector instructions (about 100 per 64 neighbours) and, where K is large, the table and its way to memory
+// (1 M points, 125 cells, three sides: 660 us; 766 with every row of run_start written).
 constexpr int FILL_PITCH = TILE / 2 + 1;  // (a half wave works on one centre, i.e. one column)
 constexpr int FILL_ROUNDS = 8;           // places of the list per thread
-constexpr size_t fill_table_bytes(int K) { return (size_t)K * (FILL_PITCH + 3) * sizeof(uint32_t); }
-// A block's threads and places: four blocks of 8 waves share a CU, or two of 16 where a tile's neighbours need the room.
+constexpr size_t fill_table_bytes(int K) { return (size_t)K * (FILL_PITCH + 4) * sizeof(uint32_t); }
+// A block's threads and places.  Small blocks wait less at the phases' barriers (eight clouds of 100 000 points, 27 cells: the
+// build 680 us with 256 threads, 713 with 512), as long as the neighbours of a tile, `load` as a guess, fit their list.
 struct FillShape { int threads; uint32_t list_cap; size_t lds; };
 constexpr FillShape fill_shape_of(int K, int threads)
 {
-    const size_t most = threads == 512 ? 39 * 1024 : 79 * 1024, table = fill_table_bytes(K);
-    size_t n = (most - table) / 6 / 2 * 2;
+    const size_t most = (size_t)(threads / 256 * 20 - 1) * 1024, table = fill_table_bytes(K);       // (160 KB per CU)
+    size_t n = table < most ? (most - table) / 6 / 2 * 2 : 0;
     if (n > (size_t)FILL_ROUNDS * threads) n = (size_t)FILL_ROUNDS * threads;
     return FillShape{threads, (uint32_t)n, table + n * 6};
 }
-static_assert(fill_table_bytes(MAX_K) + 6 * 1024 <= 39 * 1024, "the list has room beside the largest table");
+constexpr FillShape fill_shape(int K, int64_t load)
+{
+    for (int threads = 256; threads < 1024; threads *= 2)
+        if ((int64_t)fill_shape_of(K, threads).list_cap >= load && fill_shape_of(K, threads).list_cap >= 1024) return fill_shape_of(K, threads);
+    return fill_shape_of(K, 1024);
+}
+static_assert(fill_shape_of(MAX_K, 1024).list_cap >= 4096, "the list has room beside the largest table");
 static_assert(FILL_ROUNDS * 1024 < 65536, "runs count in 16 bits");
 
 template <bool EXT>
-__global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, uint32_t list_cap, const uint32_t *__restrict__ err)
+__global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, int64_t most_tiles, uint32_t list_cap,
+                                                    const uint32_t *__restrict__ err)
 {
-    extern __shared__ uint32_t tbl[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t tbl[];
     __shared__ TileCentres tc;
     const Side &s = sides.s[blockIdx.y];
-    const int64_t tile = blockIdx.x;
+    const int64_t tile = tile_of_block(blockIdx.x, most_tiles);
     if (*err || tile >= s.n_tiles) return;                 // block-uniform: a prefix sum of this build gave up
-    uint32_t *first = tbl + K * FILL_PITCH, *row_n = first + K, *to_list = row_n + K, *list = to_list + K;
+    uint32_t *first = tbl + K * FILL_PITCH, *row_n = first + K, *to_list = row_n + K, *read = to_list + K, *list = read + K;
     uint16_t *list_at = reinterpret_cast<uint16_t *>(list + list_cap);
     const int threads = blockDim.x, n_waves = threads >> 6;
     int tid = threadIdx.x, lane = tid & 63;
@@ -651,18 +720,30 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, u
     if (flag_last)
         out_b = reinterpret_cast<int32_t *>(s.out.tail + (size_t)s.out.tail_index * (((size_t)total * 4 + 255) / 256 * 256));
     int32_t *out_c = s.out.out_c, *out_k = s.out.out_k;
+    auto clear = [&]() {
+        for (uint32_t i = tid; i < (uint32_t)(K * FILL_PITCH) / 4u; i += threads) reinterpret_cast<uint4 *>(tbl)[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (tid < ((K * FILL_PITCH) & 3)) tbl[((K * FILL_PITCH) & ~3) + tid] = 0u;
+    };
     auto emit = [&](uint32_t pos, int al, int k, uint32_t b, bool last) {
         if (pos >= out_cap) return;
         if (out_c) out_c[pos] = tc.at[al];
         if (out_b) out_b[pos] = (int32_t)(flag_last && last ? b | GATHER_LAST : b);
         if (out_k) out_k[pos] = k;
     };
-    for (int i = tid; i < K * FILL_PITCH; i += threads) tbl[i] = 0u;
-    for (int k = tid; k < K; k += threads) first[k] = s.ptr[(size_t)k * s.n_tiles + tile];
-    if (wave == 0) tc.open(s, tile, true, lane);
-    __syncthreads();
+    clear();
+    // The rows of run_start that no pass reads are not written either: those of cells without a triplet in this tile and in the
+    // one beside it (a kernel that takes tiles in pairs reads both rows of a cell; 1 M points of a ground scene in spatial order,
+    // 125 cells: six rows in ten).
+    const int64_t pair = tile & ~(int64_t)1, pair_end = pair + 2 < s.n_tiles ? pair + 2 : s.n_tiles;
+    for (int k = tid; k < K; k += threads) {
+        const uint32_t *ptr = s.ptr + (size_t)k * s.n_tiles;
+        first[k] = ptr[tile];
+        read[k] = ptr[pair] != ptr[pair_end];
+    }
+    if (wave == 0) tc.open(s, tile, lane);
+    lds_barrier();
     const uint32_t upto = tc.off[lane] + tc.n[lane];
-    uint32_t *run_start = s.run_start ? s.run_start + (size_t)tile * K * TILE : nullptr;
+    char *run_start = s.run_start ? reinterpret_cast<char *>(s.run_start + (size_t)tile * K * TILE) : nullptr;
     // as many centres at a time as the list holds: usually all of them
     int c0 = 0;
     for (;;) {
@@ -673,14 +754,14 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, u
         if (c1 == c0) {
             // a centre with more neighbours than the list holds: rank each one by scanning the candidates again
             for (int k = tid; k < K; k += threads) row_n[k] = 0u;
-            __syncthreads();
+            lds_barrier();
             Candidates<EXT> cand;
             cand.open(s.centres, tc.at[c0], s.g, s.q, lane);
             for (uint32_t base = (uint32_t)wave * 64u; base < cand.st.total; base += (uint32_t)threads) {
                 int b, k, k2;
                 if (cand.fetch(base + lane, s.g, s.q, b, k, k2)) atomicAdd(&row_n[k], 1u);
             }
-            __syncthreads();
+            lds_barrier();
             for (uint32_t base = (uint32_t)wave * 64u; base < cand.st.total; base += (uint32_t)threads) {
                 int b, k, k2;
                 const bool hit = cand.fetch(base + lane, s.g, s.q, b, k, k2);
@@ -693,11 +774,12 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, u
                 if (hit) emit(first[k] + rank, c0, k, (uint32_t)b, rank + 1u == row_n[k]);
             }
             if (run_start)
-                for (int k = tid; k < K; k += threads) run_start[k * TILE + c0] = first[k];
-            __syncthreads();
+                for (int k = tid; k < K; k += threads)
+                    if (read[k]) reinterpret_cast<uint32_t *>(run_start)[k * TILE + c0] = first[k];
+            lds_barrier();
             for (int k = tid; k < K; k += threads) first[k] += row_n[k];
             if (++c0 == TILE) break;
-            __syncthreads();
+            lds_barrier();
             continue;
         }
         const uint32_t n = lane_value(upto, c1 - 1) - before;
@@ -722,7 +804,7 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, u
                     at += (uint32_t)__popcll(mask);
                 }
             }
-            __syncthreads();
+            lds_barrier();
         }
         // ---- a thread's consecutive neighbours: candidate index; cell | centre << 8 | place in the run << 14 -----------------
         const int rounds = (int)((n + (uint32_t)threads - 1u) / (uint32_t)threads);       // at most FILL_ROUNDS
@@ -757,12 +839,11 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, u
                     at_of[j] = (at_of[j] & 0x3fffu) | ((was >> sh) & 0xffffu) << 14;
                 }
         }
-        __syncthreads();
+        lds_barrier();
         // ---- counts -> starts within the part's triplets of the cell, eight cells per wave --------------------------------
         for (int k0 = 8 * wave; k0 < K; k0 += 8 * n_waves) {
             const int k = k0 + (lane >> 3), l = lane & 7;  // eight lanes per cell, eight centres per lane
-            const int kc = k < K ? k : K - 1;
-            uint32_t *word = tbl + kc * FILL_PITCH + 4 * l;
+            uint32_t *word = tbl + (k < K ? k : K - 1) * FILL_PITCH + 4 * l;
             uint32_t v[4], s0[4], s1[4], sum = 0u;
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] = word[i];
@@ -772,33 +853,33 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, u
                 s1[i] = sum + (v[i] & 0xffffu);
                 sum = s1[i] + (v[i] >> 16);
             }
-            uint32_t incl = sum;                           // over the eight lanes: shifts inside a row of sixteen, for both halves
-#pragma unroll
-            for (int d = 1; d < 8; d <<= 1) {
-                const uint32_t u = __shfl_up(incl, d, 8);
-                if (l >= d) incl += u;
-            }
+            uint32_t incl = sum;                           // over the eight lanes: shifts inside a row of sixteen, which holds two cells
+            const uint32_t u1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x111, 0xf, 0xf, true);
+            incl += l >= 1 ? u1 : 0u;
+            const uint32_t u2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x112, 0xf, 0xf, true);
+            incl += l >= 2 ? u2 : 0u;
+            const uint32_t u4 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x114, 0xf, 0xf, true);
+            incl += l >= 4 ? u4 : 0u;
             const uint32_t lead = incl - sum;
             if (k < K) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) word[i] = (lead + s0[i]) | (lead + s1[i]) << 16;
-                if (l == 7) { row_n[k] = incl; tbl[k * FILL_PITCH + 32] = incl; }
-                if (run_start) {
-                    const uint32_t f = first[k] + lead;
-                    uint32_t *at = run_start + k * TILE + 8 * l;
+                if (l == 7) { row_n[k] = incl; word[4] = incl; }
+                if (run_start && read[k]) {
+                    const uint32_t f = first[k] + lead, at = (uint32_t)(k * TILE + 8 * l) * 4u;
                     if (c0 == 0 && c1 == TILE) {
 #pragma unroll
                         for (int i = 0; i < 2; ++i)
-                            reinterpret_cast<uint4 *>(at)[i] = make_uint4(f + s0[2 * i], f + s1[2 * i], f + s0[2 * i + 1], f + s1[2 * i + 1]);
+                            *reinterpret_cast<uint4 *>(run_start + at + 16 * i) = make_uint4(f + s0[2 * i], f + s1[2 * i], f + s0[2 * i + 1], f + s1[2 * i + 1]);
                     } else {
 #pragma unroll
                         for (int i = 0; i < 8; ++i)
-                            if (8 * l + i >= c0 && 8 * l + i < c1) at[i] = f + (i & 1 ? s1[i / 2] : s0[i / 2]);
+                            if (8 * l + i >= c0 && 8 * l + i < c1) *reinterpret_cast<uint32_t *>(run_start + at + 4 * i) = f + (i & 1 ? s1[i / 2] : s0[i / 2]);
                     }
                 }
             }
         }
-        __syncthreads();
+        lds_barrier();
         // ---- places ----------------------------------------------------------------------------------------------------
         if (wave == 0) {
             uint32_t run = 0;
@@ -810,7 +891,7 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, u
                 run += lane_value(incl, 63);
             }
         }
-        __syncthreads();
+        lds_barrier();
 #pragma unroll
         for (int j = 0; j < FILL_ROUNDS; ++j)
             if (j < rounds && (uint32_t)j < mine) {
@@ -819,14 +900,14 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, u
                 list[place] = b_of[j];
                 list_at[place] = (uint16_t)(at_of[j] & 0x3fffu);
             }
-        __syncthreads();
+        lds_barrier();
         // ---- ranks, and out ----------------------------------------------------------------------------------------------
         for (uint32_t p = tid; p < n; p += threads) {
             const uint32_t b = list[p], at = list_at[p];
             const int k = (int)(at & 255u), al = (int)(at >> 8);
             const uint32_t *word = tbl + k * FILL_PITCH + (al >> 1);       // (behind the last centre: the end of its run)
-            const uint32_t prev = al & 1 ? word[0] >> 16 : word[0] & 0xffffu;
-            const uint32_t m = (al & 1 ? word[1] & 0xffffu : word[0] >> 16) - prev;
+            const uint32_t bounds = __builtin_amdgcn_alignbit(word[1], word[0], 16u * (al & 1u));
+            const uint32_t prev = bounds & 0xffffu, m = (bounds >> 16) - prev;
             const uint32_t *run = list + to_list[k] + prev;
             uint32_t rank = 0;
             for (uint32_t j = 0; j < m; j += 4) {          // (reads past the run stay inside the block's LDS)
@@ -836,10 +917,10 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, u
             emit(first[k] + prev + rank, al, k, b, rank + 1u == m);
         }
         if (c1 == TILE) break;
-        __syncthreads();
-        for (int i = tid; i < K * FILL_PITCH; i += threads) tbl[i] = 0u;
+        lds_barrier();
+        clear();
         for (int k = tid; k < K; k += threads) first[k] += row_n[k];
-        __syncthreads();
+        lds_barrier();
         c0 = c1;
     }
 }
@@ -899,7 +980,7 @@ __global__ __launch_bounds__(256) void sub_scatter(int64_t n, const uint32_t *__
 // ---- host side ------------------------------------------------------------------------------
 
 struct GridScratch {
-    size_t keys_off, cnt_off, cursor_off, point_slot_off, pts_off, end;
+    size_t keys_off, cnt_off, point_at_off, pts_off, end;
     int64_t slots;
 };
 
@@ -938,8 +1019,7 @@ GridScratch grid_scratch(size_t base, int64_t n)
     size_t off = base;
     s.keys_off = off;        off += align_up((size_t)s.slots * 8);
     s.cnt_off = off;         off += align_up((size_t)(s.slots + 1) * 4);
-    s.cursor_off = off;      off += align_up((size_t)s.slots * 4);
-    s.point_slot_off = off;  off += align_up((size_t)(n > 0 ? n : 1) * 4);
+    s.point_at_off = off;    off += align_up((size_t)(n > 0 ? n : 1) * 8);
     s.pts_off = off;         off += align_up((size_t)(n > 0 ? n : 1) * 16);
     s.end = off;
     return s;
@@ -1041,26 +1121,25 @@ int build_grid(const float *xyz, int64_t n, const GridMap &gm, const int32_t *ba
 {
     auto *keys = reinterpret_cast<unsigned long long *>(ws + gs.keys_off);
     auto *cnt = reinterpret_cast<uint32_t *>(ws + gs.cnt_off);
-    auto *cursor = reinterpret_cast<uint32_t *>(ws + gs.cursor_off);
-    auto *point_slot = reinterpret_cast<uint32_t *>(ws + gs.point_slot_off);
+    auto *point_at = reinterpret_cast<uint2 *>(ws + gs.point_at_off);
     auto *pts = reinterpret_cast<float4 *>(ws + gs.pts_off);
     int rc;
     {
         int64_t blocks = ceil_div(gs.slots + 1, 256);
         if (blocks > 4096) blocks = 4096;
-        grid_clear<<<(unsigned)blocks, 256, 0, stream>>>(keys, cnt, cursor, gs.slots, clear_from, clear_words);
+        grid_clear<<<(unsigned)blocks, 256, 0, stream>>>(keys, cnt, gs.slots, clear_from, clear_words);
         PCPP_HIP_CHECK(hipGetLastError());
     }
     if (n > 0) {
         const unsigned blocks = (unsigned)ceil_div(n, 256);
         grid_insert<<<blocks, 256, 0, stream>>>(xyz, n, gm, batch_off, n_batches, keys, cnt, (uint32_t)(gs.slots - 1),
-                                                point_slot);
+                                                point_at);
         PCPP_HIP_CHECK(hipGetLastError());
     }
     if ((rc = scan_exclusive_u32(cnt, cnt, gs.slots, scan_scratch, nullptr, err, stream)) != PCPP_OK) return rc;
     if (n > 0) {
         const unsigned blocks = (unsigned)ceil_div(n, 256);
-        grid_scatter<<<blocks, 256, 0, stream>>>(xyz, n, point_slot, cnt, cursor, pts, err);
+        grid_scatter<<<blocks, 256, 0, stream>>>(xyz, n, point_at, cnt, pts, err);
         PCPP_HIP_CHECK(hipGetLastError());
     }
     view->keys = keys;
@@ -1339,7 +1418,6 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         const size_t room = (plan_bytes - pl.tail_off) / (size_t)pl.n_tail / 256 * 256 / 4;
         tail_cap = (uint32_t)(room < (size_t)tri_cap ? room : (size_t)tri_cap);
     }
-    auto lanes_log2 = [](uint32_t stride) { return stride >= 256 ? 6 : (stride > 64 ? 5 : 4); };    // (lists are half full)
     Sides sides{};
     ScanJob jobs[MAX_SIDES] = {};
     int n_sides = 0;
@@ -1355,7 +1433,6 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         d.hits = outputs ? f_hits : b_hits;
         d.n_hits = outputs ? f_n : b_n;
         d.stride = outputs ? bs.fwd_stride : bs.bwd_stride;
-        d.lanes_log2 = lanes_log2(d.stride);
         d.sums = sums; d.mirror_sums = nullptr;
         d.ptr = ptr;
         d.run_start = run_start; d.seg_out = seg;
@@ -1381,10 +1458,12 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     if (count_only) sides.s[0].n_hits = nullptr;
     const int64_t most_tiles = want_bwd && nt_i > nt_o ? nt_i : nt_o;
     if (most_tiles > 0) {
-        const dim3 grid((unsigned)most_tiles, (unsigned)counted);
+        int64_t per_block = most_tiles * counted / COUNT_BLOCKS;
+        per_block = per_block < 1 ? 1 : (per_block > COUNT_TILES ? COUNT_TILES : per_block);
+        const dim3 grid((unsigned)ceil_div(most_tiles, per_block), (unsigned)counted);
         const size_t lds = count_lds_bytes(K, sides.s[counted - 1].mirror_sums != nullptr);
-        if (ext) tile_count<true><<<grid, COUNT_THREADS, lds, stream>>>(sides, K, err);
-        else tile_count<false><<<grid, COUNT_THREADS, lds, stream>>>(sides, K, err);
+        if (ext) tile_count<true><<<grid, COUNT_THREADS, lds, stream>>>(sides, K, (int)per_block, err);
+        else tile_count<false><<<grid, COUNT_THREADS, lds, stream>>>(sides, K, (int)per_block, err);
         PCPP_HIP_CHECK(hipGetLastError());
     }
     if ((rc = scan_exclusive_u32_jobs(jobs, n_sides, err, stream)) != PCPP_OK) return rc;
@@ -1426,17 +1505,16 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         if ((rc = fill_u64(reinterpret_cast<unsigned long long *>(seg_offsets), 0ull, K + 1, stream)) != PCPP_OK) return rc;
     }
     if (most_tiles > 0) {
-        // four blocks of 8 waves per CU where a tile's neighbours (two thirds of the capacity, as a guess) fit their lists
-        FillShape shape = fill_shape_of(K, 512);
-        if (ceil_div(capacity, nt_o > 0 ? nt_o : 1) * 2 / 3 > (int64_t)shape.list_cap) shape = fill_shape_of(K, 1024);
+        // (capacities are on the generous side)
+        FillShape shape = fill_shape(K, ceil_div(capacity, nt_o > 0 ? nt_o : 1) * 2 / 3);
         if (test_flags & PCPP_BUILD_TEST_SHORT_LISTS) shape.list_cap = 40;
         if (shape.lds > (size_t)32 * 1024)
             if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&tile_fill<true>) : reinterpret_cast<const void *>(&tile_fill<false>),
                                       shape.lds)) != PCPP_OK)
                 return rc;
-        const dim3 grid((unsigned)most_tiles, (unsigned)n_sides);
-        if (ext) tile_fill<true><<<grid, shape.threads, shape.lds, stream>>>(sides, K, shape.list_cap, err);
-        else tile_fill<false><<<grid, shape.threads, shape.lds, stream>>>(sides, K, shape.list_cap, err);
+        const dim3 grid((unsigned)blocks_of_tiles(most_tiles), (unsigned)n_sides);
+        if (ext) tile_fill<true><<<grid, shape.threads, shape.lds, stream>>>(sides, K, most_tiles, shape.list_cap, err);
+        else tile_fill<false><<<grid, shape.threads, shape.lds, stream>>>(sides, K, most_tiles, shape.list_cap, err);
         PCPP_HIP_CHECK(hipGetLastError());
     }
     // everything is queued; now compare the count with what the caller provided

@@ -74,12 +74,19 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_chained(const ScanJobs jobs
     const int64_t base = bid * SCAN_BLOCK + (int64_t)threadIdx.x * SCAN_ITEMS;
     uint32_t v[SCAN_ITEMS];
     unsigned long long s = 0;
+    const bool whole = base + SCAN_ITEMS <= n;          // (both arrays start at a multiple of 16 bytes)
+    if (whole) {
 #pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) {
-        const int64_t idx = base + j;
-        v[j] = idx < n ? in[idx] : 0u;
-        s += v[j];
+        for (int j = 0; j < SCAN_ITEMS; j += 4) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(in + base + j);
+            v[j] = q.x; v[j + 1] = q.y; v[j + 2] = q.z; v[j + 3] = q.w;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < SCAN_ITEMS; ++j) v[j] = base + j < n ? in[base + j] : 0u;
     }
+#pragma unroll
+    for (int j = 0; j < SCAN_ITEMS; ++j) s += v[j];
     unsigned long long tot;
     const unsigned long long inc = block_incl_scan_u64(s, &tot);    // its barriers also order every read of
                                                                     // `in` before any write (out may alias in)
@@ -128,11 +135,20 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_chained(const ScanJobs jobs
     __syncthreads();
     const unsigned long long before = shared_word[1];
     unsigned long long run = before + inc - s;
+    uint32_t o[SCAN_ITEMS];
 #pragma unroll
     for (int j = 0; j < SCAN_ITEMS; ++j) {
-        const int64_t idx = base + j;
-        if (idx < n) out[idx] = (uint32_t)run;
+        o[j] = (uint32_t)run;
         run += v[j];
+    }
+    if (whole) {
+#pragma unroll
+        for (int j = 0; j < SCAN_ITEMS; j += 4)
+            *reinterpret_cast<uint4 *>(out + base + j) = make_uint4(o[j], o[j + 1], o[j + 2], o[j + 3]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < SCAN_ITEMS; ++j)
+            if (base + j < n) out[base + j] = o[j];
     }
     if (bid == n_blocks - 1 && threadIdx.x == 0) {
         out[n] = (uint32_t)(before + tot);
