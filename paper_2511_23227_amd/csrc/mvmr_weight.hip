@@ -491,42 +491,45 @@ __global__ __launch_bounds__(WAVES * 64, (any_min_waves<SO, SI>())) void weight_
 }
 
 // dw[k][e] = (partial of the run's head, if it starts inside a chunk) + partials of the chunks whose first
-// triplet lies in run k.  A block of four waves owns 64 consecutive elements of one cell: wave w adds chunks
-// c0 + w, c0 + w + 4, ... in ascending order, 32 at a time (each read is 256 contiguous bytes), then these sums, and the four
+// triplet lies in run k.  A block of WAVES waves owns 64 VEC consecutive elements of one cell: wave w adds chunks
+// c0 + w, c0 + w + WAVES, ... in ascending order, 32 at a time (each read is 256 VEC contiguous bytes), then these sums, and the
 // waves' sums are added in order of w, so the result is reproducible.  (One long sum per wave loses precision: 20 -> 36 fp32, one
-// cell, 6.6 M triplets, 8562 chunks: relative error 1.65e-6, by 32 2.3e-7, vector ALUs 5.0e-7.)  grid = (ceil(c_out*c_in / 64), K), block = 256
-constexpr int REDUCE_WAVES = 4;
-
-__global__ __launch_bounds__(REDUCE_WAVES * 64) void weight_reduce(const float *__restrict__ part, float *__restrict__ dw,
-                                                                   const int64_t *__restrict__ seg, int n_elem, int chunk,
-                                                                   int64_t n_chunks)
+// cell, 6.6 M triplets, 8562 chunks: relative error 1.65e-6, by 32 2.3e-7, vector ALUs 5.0e-7.)  grid = (ceil(c_out*c_in / 64 VEC), K)
+// Bound by the latency of the reads of one wave behind the other in small layers, which have few blocks, and by memory in large
+// ones.  With four waves and one element per lane / as launch_reduce chooses, us: 32 -> 32 with 247 chunks a cell 15.3 / 6.3; 64 ->
+// 64 with 100 10.8 / 8.8; 64 -> 128 with 60 8.4 / 7.7 (one element, sixteen waves: 15.3); 256 -> 256, 2046 chunks in all, 172 / 111.
+template <int VEC, int WAVES_>
+__global__ __launch_bounds__(WAVES_ * 64) void weight_reduce(const float *__restrict__ part, float *__restrict__ dw,
+                                                             const int64_t *__restrict__ seg, int n_elem, int chunk,
+                                                             int64_t n_chunks)
 {
-    __shared__ float sums[REDUCE_WAVES][64];
+    typedef float vec __attribute__((ext_vector_type(VEC)));
+    __shared__ vec sums[WAVES_][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int e = blockIdx.x * 64 + lane;
+    const int e = (blockIdx.x * 64 + lane) * VEC;                       // (VEC divides n_elem)
     const int k = blockIdx.y;
     const int64_t s = seg[k], t = seg[k + 1];
-    float v = 0.f, sum = 0.f;
+    vec v = 0.f, sum = 0.f;
     if (t > s && e < n_elem) {
         const int64_t c0 = (s + chunk - 1) / chunk, c1 = (t + chunk - 1) / chunk;
-        const float *src = part + (size_t)e;
+        auto of = [&](int64_t c) -> vec { return *reinterpret_cast<const vec *>(part + (size_t)c * n_elem + e); };
         int64_t c = c0 + wave;
         int n = 0;
-        for (; c + 3 * REDUCE_WAVES < c1; c += 4 * REDUCE_WAVES) {      // four independent reads in flight
-            const float v0 = src[(size_t)c * n_elem], v1 = src[(size_t)(c + REDUCE_WAVES) * n_elem];
-            const float v2 = src[(size_t)(c + 2 * REDUCE_WAVES) * n_elem], v3 = src[(size_t)(c + 3 * REDUCE_WAVES) * n_elem];
+        for (; c + 3 * WAVES_ < c1; c += 4 * WAVES_) {                  // four independent reads in flight
+            const vec v0 = of(c), v1 = of(c + WAVES_), v2 = of(c + 2 * WAVES_), v3 = of(c + 3 * WAVES_);
             v += (v0 + v1) + (v2 + v3);
             if (++n % 8 == 0) { sum += v; v = 0.f; }
         }
-        for (; c < c1; c += REDUCE_WAVES) v += src[(size_t)c * n_elem];
+        for (; c < c1; c += WAVES_) v += of(c);
     }
     sums[wave][lane] = sum + v;
     __syncthreads();
     if (wave == 0 && e < n_elem) {
-        float r = (t > s && s % chunk != 0) ? part[(size_t)(n_chunks + k) * n_elem + e] : 0.f;
+        vec r = 0.f;
+        if (t > s && s % chunk != 0) r = *reinterpret_cast<const vec *>(part + (size_t)(n_chunks + k) * n_elem + e);
 #pragma unroll
-        for (int w = 0; w < REDUCE_WAVES; ++w) r += sums[w][lane];
-        dw[(size_t)k * n_elem + e] = r;
+        for (int w = 0; w < WAVES_; ++w) r += sums[w][lane];
+        *reinterpret_cast<vec *>(dw + (size_t)k * n_elem + e) = r;
     }
 }
 
@@ -549,7 +552,14 @@ bool lds_shape(int in_dtype, int c_in, int c_out) { return in_dtype == PCPP_BF16
 
 int launch_reduce(const float *part, float *dw, const int64_t *seg, int n_elem, int K, int chunk, int64_t n_chunks, hipStream_t stream)
 {
-    weight_reduce<<<dim3((unsigned)ceil_div(n_elem, 64), (unsigned)K), REDUCE_WAVES * 64, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
+    // four elements per lane where that leaves enough blocks and dW's rows start at a multiple of 16 bytes
+    if (n_elem >= 4096 && n_elem % 4 == 0 && (reinterpret_cast<uintptr_t>(dw) & 15) == 0) {
+        const dim3 grid((unsigned)ceil_div(n_elem, 256), (unsigned)K);
+        if (n_elem >= 16384) weight_reduce<4, 4><<<grid, 256, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
+        else weight_reduce<4, 8><<<grid, 512, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
+    }
+    else
+        weight_reduce<1, 16><<<dim3((unsigned)ceil_div(n_elem, 64), (unsigned)K), 1024, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
     PCPP_HIP_CHECK(hipGetLastError());
     return PCPP_OK;
 }
