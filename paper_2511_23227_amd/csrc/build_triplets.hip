@@ -151,11 +151,19 @@ __global__ __launch_bounds__(256) void grid_scatter(const float *__restrict__ xy
 }
 
 struct GridView {
-    const unsigned long long *keys;
+    const unsigned long long *keys;   // NULL: no grid, every candidate is looked at (small clouds)
     const uint32_t *slot_start;   // [slots + 1]
     const float4 *pts;            // candidates grouped by grid cell; .w carries the original index
     uint32_t mask;
     GridMap map;
+    const float *xyz;             // without a grid: the candidates [n][3]
+    int n;
+
+    __device__ inline float4 candidate(uint32_t at) const
+    {
+        if (keys) return pts[at];
+        return make_float4(xyz[3 * (size_t)at], xyz[3 * (size_t)at + 1], xyz[3 * (size_t)at + 2], __int_as_float((int)at));
+    }
 };
 
 // Ball mode (Sec. 3.2 "Definition"): R, r2, inv_cell.  Voxel mode (the degraded operator of Sec. 3.2, "Voxel
@@ -224,7 +232,9 @@ struct Stencil {
     {
         uint32_t cnt = 0;
         my_start = 0;
-        if (lane < 27) {
+        if (!g.keys) {                     // one cell that holds all candidates
+            if (lane == 0) cnt = (uint32_t)g.n;
+        } else if (lane < 27) {
             unsigned long long key = pack_key(gx + lane / 9 - 1, gy + (lane / 3) % 3 - 1, gz + lane % 3 - 1);
             if (batch >= 0) key = mix_batch(key, batch);
             uint32_t slot = hash_key(key) & g.mask;
@@ -323,7 +333,7 @@ struct Candidates {
         bool hit = false;
         b = 0; k = 0; k2 = 0;
         if (in_range) {
-            const float4 p = g.pts[at];
+            const float4 p = g.candidate(at);
             b = __float_as_int(p.w);
             if (EXT && q.voxel_mode) {
                 const double ox = q.sign * (voxel_of(p.x, q.R) - cx), oy = q.sign * (voxel_of(p.y, q.R) - cy), oz = q.sign * (voxel_of(p.z, q.R) - cz);
@@ -354,6 +364,7 @@ constexpr uint32_t HIT_INDEX_MASK = (1u << HIT_INDEX_BITS) - 1u;
 // Bound by instruction issue.  One search per centre, in the order of the tiles and with the tiles' tables in LDS: 1 M points
 // of a ground scene, 32 neighbours in 125 cells, 1215 us; now 325.
 constexpr int GROUP_SETS = 4;             // sets of 64 candidates in registers
+constexpr int64_t NO_GRID_POINTS = 8192, NO_GRID_PAIRS = (int64_t)1 << 23;     // most that a search without a grid looks at
 constexpr int64_t SEARCH_WAVES = 8192;    // waves wanted before a wave takes more centres
 
 struct SearchArgs {
@@ -365,11 +376,28 @@ struct SearchArgs {
     uint32_t *hits, *mirror, *n_hits;
     uint32_t stride;
     int per_wave;
-    const uint32_t *err;
+    uint32_t *err;
+    unsigned long long *clear_from;      // without a grid: what its clearing kernel would have cleared
+    int64_t clear_words;
 };
 
 // FORM: centres are outputs, centres are inputs (the offset input minus output is the other way round), or both in one.
 enum Form { OUTPUTS, INPUTS, BOTH };
+
+// a neighbour at offset d = candidate - centre (of their voxels in voxel mode)
+template <Form FORM, bool EXT>
+__device__ inline void store_hit(const SearchArgs &a, size_t at, double dx, double dy, double dz, uint32_t b)
+{
+    const bool cube = EXT && a.q.voxel_mode;
+    if constexpr (FORM != INPUTS) {
+        const int k = cube ? cube_cell(dx, dy, dz, a.q) : ball_cell(dx, dy, dz, a.q);
+        a.hits[at] = ((uint32_t)k << HIT_INDEX_BITS) | b;
+    }
+    if constexpr (FORM != OUTPUTS) {
+        const int k = cube ? cube_cell(-dx, -dy, -dz, a.q) : ball_cell(-dx, -dy, -dz, a.q);
+        a.mirror[at] = ((uint32_t)k << HIT_INDEX_BITS) | b;
+    }
+}
 
 template <Form FORM, bool EXT>
 __global__ __launch_bounds__(256, 6) void search_cells(const SearchArgs a)
@@ -441,23 +469,93 @@ __global__ __launch_bounds__(256, 6) void search_cells(const SearchArgs a)
                     const unsigned long long m = __ballot(hit);
                     const uint32_t slot = filled + (uint32_t)__popcll(m & below);
                     filled += (uint32_t)__popcll(m);
-                    if (hit && slot < a.stride) {
-                        const bool cube = EXT && a.q.voxel_mode;
-                        if constexpr (FORM != INPUTS) {
-                            const int k = cube ? cube_cell(dx, dy, dz, a.q) : ball_cell(dx, dy, dz, a.q);
-                            a.hits[row + slot] = ((uint32_t)k << HIT_INDEX_BITS) | pb[s];
-                        }
-                        if constexpr (FORM != OUTPUTS) {
-                            const int k2 = cube ? cube_cell(-dx, -dy, -dz, a.q) : ball_cell(-dx, -dy, -dz, a.q);
-                            a.mirror[row + slot] = ((uint32_t)k2 << HIT_INDEX_BITS) | pb[s];
-                        }
-                    }
+                    if (hit && slot < a.stride) store_hit<FORM, EXT>(a, row + slot, dx, dy, dz, pb[s]);
                 }
                 if (lane == c) filled_of = filled;
             }
         }
     }
     if (mine) a.n_hits[index] = filled_of;
+}
+
+// The same for small clouds, without a grid: every centre looks at every candidate, one wave per centre, and a test in 32 bits
+// passes over those that are far away (its bound leaves room for its rounding: a difference of two coordinates and a sum of
+// three squares are off by less than 2^-21 together, and by less than 1e-37 where they underflow).
+constexpr int ALL_CHUNK = 4096;           // candidates in LDS at a time
+
+template <Form FORM, bool EXT>
+__global__ __launch_bounds__(256) void search_all(const SearchArgs a)
+{
+    constexpr int LOADS = 24;
+    extern __shared__ float cand[];                // [ALL_CHUNK][3], or as many as there are
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (blockIdx.x == 0)
+        for (int64_t i = tid; i < a.clear_words; i += 256) a.clear_from[i] = 0ull;
+    const int64_t index = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool on = index < a.n_centres;           // wave-uniform
+    float fx = 0.f, fy = 0.f, fz = 0.f;
+    int d_lo = 0, d_hi = a.g.n;
+    if (on) {
+        fx = a.centres[3 * index]; fy = a.centres[3 * index + 1]; fz = a.centres[3 * index + 2];
+        if (EXT && a.q.c_off) {
+            const int batch = find_batch(a.q.c_off, a.q.n_batches, (int)index);
+            d_lo = a.q.d_off[batch]; d_hi = a.q.d_off[batch + 1];
+        }
+    } else {
+        d_hi = 0;
+    }
+    const bool cube = EXT && a.q.voxel_mode;
+    double cx = fx, cy = fy, cz = fz;
+    if (cube) { cx = voxel_of(fx, a.q.R); cy = voxel_of(fy, a.q.R); cz = voxel_of(fz, a.q.R); }
+    const float near2 = (float)(a.q.r2 * (1.0 + 1.0 / 1048576.0)) + 1e-37f;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    uint32_t filled = 0;
+    const size_t row = (size_t)index * a.stride;
+    for (int c0 = 0; c0 < a.g.n; c0 += ALL_CHUNK) {
+        const int m = a.g.n - c0 < ALL_CHUNK ? a.g.n - c0 : ALL_CHUNK;
+        if (c0 > 0) __syncthreads();
+        for (int i0 = tid; i0 < 3 * m; i0 += 256 * LOADS) {        // (all of a step's loads on their way at a time)
+            float v[LOADS];
+#pragma unroll
+            for (int j = 0; j < LOADS; ++j) v[j] = i0 + 256 * j < 3 * m ? a.g.xyz[3 * (size_t)c0 + i0 + 256 * j] : 0.f;
+#pragma unroll
+            for (int j = 0; j < LOADS; ++j)
+                if (i0 + 256 * j < 3 * m) cand[i0 + 256 * j] = v[j];
+        }
+        __syncthreads();
+        const int lo = d_lo > c0 ? (d_lo - c0) & ~63 : 0, hi = d_hi - c0 < m ? d_hi - c0 : m;     // the centre's own cloud
+        for (int first = lo; first < hi; first += 64 * GROUP_SETS) {
+            float x[GROUP_SETS], y[GROUP_SETS], z[GROUP_SETS];
+            bool in[GROUP_SETS], near[GROUP_SETS], any = false;
+#pragma unroll
+            for (int s = 0; s < GROUP_SETS; ++s) {
+                const int i = first + 64 * s + lane;
+                in[s] = i < hi && (!EXT || c0 + i >= d_lo);
+                const int at = 3 * (in[s] ? i : first);
+                x[s] = cand[at]; y[s] = cand[at + 1]; z[s] = cand[at + 2];
+            }
+#pragma unroll
+            for (int s = 0; s < GROUP_SETS; ++s) {
+                const float ax = x[s] - fx, ay = y[s] - fy, az = z[s] - fz;
+                near[s] = in[s] && (cube || ax * ax + ay * ay + az * az <= near2);
+                any = any || near[s];
+            }
+            if (!__ballot(any)) continue;
+#pragma unroll
+            for (int s = 0; s < GROUP_SETS; ++s) {
+                if (!__ballot(near[s])) continue;
+                double dx, dy, dz;
+                if (cube) { dx = voxel_of(x[s], a.q.R) - cx; dy = voxel_of(y[s], a.q.R) - cy; dz = voxel_of(z[s], a.q.R) - cz; }
+                else { dx = __dsub_rn((double)x[s], cx); dy = __dsub_rn((double)y[s], cy); dz = __dsub_rn((double)z[s], cz); }
+                const bool hit = in[s] && (cube ? inside_cube(dx, dy, dz, a.q) : inside_ball(dx, dy, dz, a.q));
+                const unsigned long long mask = __ballot(hit);
+                const uint32_t slot = filled + (uint32_t)__popcll(mask & below);
+                filled += (uint32_t)__popcll(mask);
+                if (hit && slot < a.stride) store_hit<FORM, EXT>(a, row + slot, dx, dy, dz, (uint32_t)(c0 + first + 64 * s + lane));
+            }
+        }
+    }
+    if (on && lane == 0) a.n_hits[index] = filled;
 }
 
 // ---- one side's order of the triplets -------------------------------------------------------------
@@ -731,14 +829,15 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, i
         if (out_k) out_k[pos] = k;
     };
     clear();
-    // The rows of run_start that no pass reads are not written either: those of cells without a triplet in this tile and in the
-    // one beside it (a kernel that takes tiles in pairs reads both rows of a cell; 1 M points of a ground scene in spatial order,
-    // 125 cells: six rows in ten).
+    // In spatial order the rows of run_start that no kernel reads are not written either: those of cells without a triplet in
+    // this tile and in the one beside it (a kernel that takes tiles in pairs reads both rows of a cell; 1 M points of a ground
+    // scene, 125 cells: six rows in ten).  In index order nearly all cells hold one, and a kernel that need not look at the
+    // tiles' bounds starts sooner (64 -> 128 strided layer: 1 %).
     const int64_t pair = tile & ~(int64_t)1, pair_end = pair + 2 < s.n_tiles ? pair + 2 : s.n_tiles;
     for (int k = tid; k < K; k += threads) {
         const uint32_t *ptr = s.ptr + (size_t)k * s.n_tiles;
         first[k] = ptr[tile];
-        read[k] = ptr[pair] != ptr[pair_end];
+        read[k] = !s.perm || ptr[pair] != ptr[pair_end];
     }
     if (wave == 0) tc.open(s, tile, lane);
     lds_barrier();
@@ -1147,6 +1246,8 @@ int build_grid(const float *xyz, int64_t n, const GridMap &gm, const int32_t *ba
     view->pts = pts;
     view->mask = (uint32_t)(gs.slots - 1);
     view->map = gm;
+    view->xyz = xyz;
+    view->n = (int)n;
     return PCPP_OK;
 }
 
@@ -1331,15 +1432,6 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     qs.c_off = in_batch_offsets;
     qs.d_off = out_batch_offsets;
 
-    int rc;
-    GridView grid_in;
-    // the clearing kernel of the first grid zeroes the error word, the total and all status words (contiguous)
-    if ((rc = build_grid(in_xyz, n_in, gm, in_batch_offsets, n_batches, ws, bs.grid_in, scan_scratch(SCAN_GRID_IN),
-                         reinterpret_cast<unsigned long long *>(ws + bs.err_off),
-                         (int64_t)((512 + N_SCANS * bs.scan_stride) / sizeof(unsigned long long)), err, &grid_in,
-                         stream)) != PCPP_OK)
-        return rc;
-
     const int64_t nt_o = ceil_div(n_out, TILE), nt_i = ceil_div(n_in, TILE);
     const bool want_plan = plan && !count_only;
     const bool want_bwd = want_plan && (plan_flags & PCPP_PLAN_BWD_INPUT);
@@ -1354,10 +1446,27 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     }
     char *pb = static_cast<char *>(plan);
     auto words = [](char *base, size_t off) { return reinterpret_cast<uint32_t *>(base + off); };
+
+    // ---- the candidates ----------------------------------------------------------------------------------------
+    // Small clouds do without a grid: every centre looks at every candidate, which takes less than the four launches of a grid
+    // (with one and without, us: 2048 points, build and forward pass, 82 and 72; the build of 2800 points 62 and 58; of 4096, past
+    // the line, 65 and 78).
+    const bool f_lists = bs.fwd_stride != 0, b_lists = want_bwd && bs.bwd_stride != 0;
+    const bool no_grid = f_lists && n_in > 0 && n_out > 0 && n_in <= NO_GRID_POINTS && n_out <= NO_GRID_POINTS && n_in * n_out <= NO_GRID_PAIRS;
+    int rc;
+    GridView grid_in{nullptr, nullptr, nullptr, 0u, gm, in_xyz, (int)n_in};
+    // the error word, the total and all status words (contiguous) start at zero: the clearing kernel of the first grid sees to it
+    auto *clear_from = reinterpret_cast<unsigned long long *>(ws + bs.err_off);
+    const int64_t clear_words = (int64_t)((512 + N_SCANS * bs.scan_stride) / sizeof(unsigned long long));
+    if (!no_grid)
+        if ((rc = build_grid(in_xyz, n_in, gm, in_batch_offsets, n_batches, ws, bs.grid_in, scan_scratch(SCAN_GRID_IN), clear_from,
+                             clear_words, err, &grid_in, stream)) != PCPP_OK)
+            return rc;
     GridView grid_out = grid_in;
     if (want_bwd && !self) {
-        if ((rc = build_grid(out_xyz, n_out, gm, out_batch_offsets, n_batches, ws, bs.grid_out, scan_scratch(SCAN_GRID_OUT),
-                             nullptr, 0, err, &grid_out, stream)) != PCPP_OK)
+        if (no_grid) grid_out = GridView{nullptr, nullptr, nullptr, 0u, gm, out_xyz, (int)n_out};
+        else if ((rc = build_grid(out_xyz, n_out, gm, out_batch_offsets, n_batches, ws, bs.grid_out, scan_scratch(SCAN_GRID_OUT),
+                                  nullptr, 0, err, &grid_out, stream)) != PCPP_OK)
             return rc;
     }
 
@@ -1365,7 +1474,6 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     // Centres = outputs, candidates = inputs; for the input gradient centres = inputs, candidates = outputs: the same
     // predicate with the roles swapped, so the set is identical and only the grouping changes to (k, i, o).  A cloud
     // queried against itself is searched once for both.
-    const bool f_lists = bs.fwd_stride != 0, b_lists = want_bwd && bs.bwd_stride != 0;
     uint32_t *f_hits = f_lists ? words(ws, bs.fwd_hits_off) : nullptr, *f_n = words(ws, bs.fwd_n_off);
     uint32_t *b_hits = b_lists ? words(ws, bs.bwd_hits_off) : nullptr, *b_n = self ? f_n : words(ws, bs.bwd_n_off);
     auto search = [&](Form form, const float4 *order, const float *centres, int64_t n, const GridView &g, const QueryParams &qp,
@@ -1373,11 +1481,15 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         if (n <= 0) return PCPP_OK;
         int per_wave = 1;                          // centres: as many as leave enough waves for the device
         while (per_wave < 32 && n / (2 * per_wave) >= SEARCH_WAVES) per_wave *= 2;
-        const SearchArgs sa{order, centres, n, g, qp, f_hits, b_hits, n_hits, stride, per_wave, err};
-        auto kern = form == BOTH ? (ext ? search_cells<BOTH, true> : search_cells<BOTH, false>)
-                                 : form == INPUTS ? (ext ? search_cells<INPUTS, true> : search_cells<INPUTS, false>)
-                                                  : (ext ? search_cells<OUTPUTS, true> : search_cells<OUTPUTS, false>);
-        kern<<<(unsigned)ceil_div(ceil_div(n, per_wave), 4), 256, 0, stream>>>(sa);
+        const SearchArgs sa{order, centres, n, g, qp, f_hits, b_hits, n_hits, stride, per_wave, err, clear_from, form == INPUTS ? 0 : clear_words};
+        const size_t lds = no_grid ? (size_t)(g.n < ALL_CHUNK ? g.n : ALL_CHUNK) * 3 * sizeof(float) : 0;
+        auto pick = [&](auto cells, auto cells_ext, auto all, auto all_ext) { return no_grid ? (ext ? all_ext : all) : (ext ? cells_ext : cells); };
+        auto kern = form == BOTH ? pick(search_cells<BOTH, false>, search_cells<BOTH, true>, search_all<BOTH, false>, search_all<BOTH, true>)
+                    : form == INPUTS ? pick(search_cells<INPUTS, false>, search_cells<INPUTS, true>, search_all<INPUTS, false>, search_all<INPUTS, true>)
+                                     : pick(search_cells<OUTPUTS, false>, search_cells<OUTPUTS, true>, search_all<OUTPUTS, false>, search_all<OUTPUTS, true>);
+        if (lds > (size_t)32 * 1024)
+            if (int r = raise_lds_limit(reinterpret_cast<const void *>(kern), lds)) return r;
+        kern<<<(unsigned)ceil_div(ceil_div(n, no_grid ? 1 : per_wave), 4), 256, lds, stream>>>(sa);
         PCPP_HIP_CHECK(hipGetLastError());
         return PCPP_OK;
     };

@@ -168,9 +168,11 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
                 b[p] = 0u;
                 if (k < a.K) b[p] = slot < TILE ? run_tile[(size_t)k * TILE + slot] : a.side.tile_ptr[(size_t)k * a.side.n_tiles + tile + 1];
             }
-            // (a cell without a triplet in the whole tile may have no row in run_start)
-            const uint32_t *tp = a.side.tile_ptr + (size_t)(k < a.K ? k : 0) * a.side.n_tiles + tile;
-            const bool on = tp[0] != tp[1] && k < a.K && b[0] != b[NP];
+            bool on = k < a.K && b[0] != b[NP];
+            if (a.side.perm) {                           // a cell without a triplet in the whole tile may have no row in run_start
+                const uint32_t *tp = a.side.tile_ptr + (size_t)(k < a.K ? k : 0) * a.side.n_tiles + tile;
+                on = on && tp[0] != tp[1];
+            }
             const unsigned long long msk = __ballot(on);
             const int at = cnt + __popcll(msk & ((1ull << lane) - 1ull));
             if (on) {

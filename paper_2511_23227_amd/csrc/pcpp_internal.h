@@ -38,8 +38,8 @@ constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 //                                          order, k-major; last entry = |T|
 //   run_start uint32 [n_tiles][K][TILE]    start of the (cell k, slot tile*TILE + a) run; it ends where
 //                                          the next slot's run starts (for a = TILE-1: at the end of
-//                                          the (k, tile) run).  The row of a cell that has no triplet in the
-//                                          tiles 2 j and 2 j + 1 is not written for either
+//                                          the (k, tile) run).  Spatial plans: the row of a cell that has no
+//                                          triplet in the tiles 2 j and 2 j + 1 is not written for either
 //   gather    int32  [|T|]                 source row of each triplet in (k, slot, source) order, bit 31 set on
 //                                          the last triplet of a (k, slot) run.  The input-gradient side always has
 //                                          one; the forward side has one in spatial plans and otherwise gathers

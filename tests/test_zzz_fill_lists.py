@@ -83,3 +83,30 @@ def test_workspace_between_the_sizes(t, spatial, same, batched):
             assert np.array_equal(got.cpu().numpy(), want)
         plans.append(plan.cpu().numpy()[256:])
     assert np.array_equal(plans[0], plans[2]) and np.array_equal(plans[1], plans[2])
+
+
+def _lattice(n):
+    g = np.stack(np.meshgrid(*[np.arange(18)] * 3, indexing="ij"), -1).reshape(-1, 3).astype(np.float32)
+    return g[np.random.default_rng(n).permutation(len(g))[:n]] * 0.25 + 1000.0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", ["plain", "batched", "voxel", "lattice"])
+@pytest.mark.parametrize("n", [1, 65, 2896, 2897, 4500])
+def test_search_with_and_without_a_grid(n, mode):
+    """Up to 2^23 pairs the search does without a grid (2896 points against themselves) and passes over far candidates by a test
+    in 32 bits; a lattice far from the origin has neighbours at exactly the radius."""
+    import paper_2511_23227_amd as m
+    rng = np.random.default_rng(n)
+    p = _lattice(n) if mode == "lattice" else rng.random((n, 3)).astype(np.float32) * (n / 400.0) ** (1 / 3)
+    size = np.float32(0.5 if mode == "lattice" else 0.2 if mode != "voxel" else 0.11)
+    cuts = [0, n // 3, n // 3, n] if mode == "batched" else None
+    o, i, k, seg = oracle.build_triplets_general(p, p, size, 3, mode=oracle.MODE_VOXEL if mode == "voxel" else oracle.MODE_BALL,
+                                                 in_offsets=cuts, out_offsets=cuts)
+    d = torch.from_numpy(p).cuda()
+    off = torch.tensor(cuts, dtype=torch.int32, device="cuda") if cuts else None
+    T = m.pcpp_build_triplets(d, d, float(size), 3, capacity=len(o), in_offsets=off, out_offsets=off,
+                              plan_flags=m.PLAN_FWD | m.PLAN_BWD_INPUT | (m.BUILD_VOXEL if mode == "voxel" else 0))
+    assert T.n_triplets == len(o) and np.array_equal(T.seg_offsets.cpu().numpy(), seg)
+    for got, want in ((T.tri_o, o), (T.tri_i, i), (T.tri_k, k)):
+        assert np.array_equal(got.cpu().numpy(), want)
