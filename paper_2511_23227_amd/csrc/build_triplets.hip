@@ -1616,17 +1616,26 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         // no outputs: every run starts at 0
         if ((rc = fill_u64(reinterpret_cast<unsigned long long *>(seg_offsets), 0ull, K + 1, stream)) != PCPP_OK) return rc;
     }
-    if (most_tiles > 0) {
-        // (capacities are on the generous side)
-        FillShape shape = fill_shape(K, ceil_div(capacity, nt_o > 0 ? nt_o : 1) * 2 / 3);
+    for (int from = 0; from < n_sides;) {
+        // sides whose tiles ask for blocks of one size go in one launch (capacities are on the generous side)
+        auto shape_of = [&](const Side &d) { return fill_shape(K, ceil_div(capacity, d.n_tiles > 0 ? d.n_tiles : 1) * 2 / 3); };
+        FillShape shape = shape_of(sides.s[from]);
+        Sides part{};
+        int n = 0;
+        int64_t tiles = 0;
+        for (; from < n_sides && shape_of(sides.s[from]).threads == shape.threads; ++from) {
+            part.s[n++] = sides.s[from];
+            if (sides.s[from].n_tiles > tiles) tiles = sides.s[from].n_tiles;
+        }
+        if (tiles == 0) continue;
         if (test_flags & PCPP_BUILD_TEST_SHORT_LISTS) shape.list_cap = 40;
         if (shape.lds > (size_t)32 * 1024)
             if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&tile_fill<true>) : reinterpret_cast<const void *>(&tile_fill<false>),
                                       shape.lds)) != PCPP_OK)
                 return rc;
-        const dim3 grid((unsigned)blocks_of_tiles(most_tiles), (unsigned)n_sides);
-        if (ext) tile_fill<true><<<grid, shape.threads, shape.lds, stream>>>(sides, K, most_tiles, shape.list_cap, err);
-        else tile_fill<false><<<grid, shape.threads, shape.lds, stream>>>(sides, K, most_tiles, shape.list_cap, err);
+        const dim3 grid((unsigned)blocks_of_tiles(tiles), (unsigned)n);
+        if (ext) tile_fill<true><<<grid, shape.threads, shape.lds, stream>>>(part, K, tiles, shape.list_cap, err);
+        else tile_fill<false><<<grid, shape.threads, shape.lds, stream>>>(part, K, tiles, shape.list_cap, err);
         PCPP_HIP_CHECK(hipGetLastError());
     }
     // everything is queued; now compare the count with what the caller provided
