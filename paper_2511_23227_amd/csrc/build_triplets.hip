@@ -1145,11 +1145,16 @@ struct BuildScratch {
     size_t fwd_n_off, bwd_n_off, fwd_hits_off = 0, bwd_hits_off = 0, end_with_lists = 0;
 };
 
-// list length per centre: twice the mean neighbour count, within [32, most]
+// List length per centre: twice the mean neighbour count, within [32, most]; longer lists lie further apart (three times the mean:
+// builds of 0.8 and 1 M points 2.5 % slower).  In crowded clouds, which are mostly uneven ones, the longest: a centre that does not
+// fit is searched again in each pass (115 200 points of a spinning lidar, 146 neighbours, up to 460, capacity as needed: 768 us
+// with twice the mean, 486 so).
+constexpr int64_t CROWDED = 128;
 uint32_t hit_stride_for(int64_t capacity, int64_t n_centres, int64_t most)
 {
     if (n_centres <= 0 || capacity <= 0) return 0;
-    int64_t s = (2 * ceil_div(capacity, n_centres) + 15) / 16 * 16;
+    const int64_t mean = ceil_div(capacity, n_centres);
+    int64_t s = mean >= CROWDED ? most : (2 * mean + 15) / 16 * 16;
     if (s < 32) s = 32;
     if (s > most) s = most;
     return (uint32_t)s;
