@@ -89,10 +89,13 @@ _landing = threading.local()
 
 
 def _landing_word():
-    """Pinned host word that pcpp_build_triplets lets the device write |T| into (one per host thread)."""
-    if getattr(_landing, "word", None) is None:
-        _landing.word = torch.zeros(8, dtype=torch.int64, pin_memory=True)
-    return _landing.word
+    """Pinned host word that the device writes a count into (one per host thread), as the pointer that the calls take; word[0] is
+    the count."""
+    word = getattr(_landing, "word", None)
+    if word is None:
+        _landing.memory = torch.zeros(8, dtype=torch.int64, pin_memory=True)
+        word = _landing.word = ctypes.cast(_landing.memory.data_ptr(), ctypes.POINTER(ctypes.c_int64))
+    return word
 
 
 def _check(rc: int):
@@ -154,8 +157,7 @@ def pcpp_count_triplets(in_xyz: torch.Tensor, out_xyz: torch.Tensor, radius: flo
     ws = workspace if workspace is not None else _bytes(ws_bytes, in_xyz.device)
     n = _landing_word()
     _check(L.pcpp_build_triplets(_ptr(in_xyz), n_in, _ptr(out_xyz), n_out, float(radius), int(t), None, None, None,
-                                 0, None, ctypes.cast(n.data_ptr(), ctypes.POINTER(ctypes.c_int64)), None, 0, 0,
-                                 _ptr(ws), ws.numel(), _stream()))
+                                 0, None, n, None, 0, 0, _ptr(ws), ws.numel(), _stream()))
     return int(n[0])
 
 
@@ -190,13 +192,12 @@ def pcpp_build_triplets(in_xyz: torch.Tensor, out_xyz: torch.Tensor, radius: flo
     n_in, n_out = int(in_xyz.shape[0]), int(out_xyz.shape[0])
     K = t ** 3
     buffers = buffers or {}
-    ws_bytes = L.pcpp_build_triplets_workspace_bytes(n_in, n_out, t)
-    if ws_bytes == 0:
-        raise PcppError(-1, "invalid sizes or t")
     ws = buffers.get("workspace")
     cap = max(int(capacity), 1)
-    # room for the neighbour lists that let the second pass skip its search
-    ws_bytes = max(ws_bytes, L.pcpp_build_triplets_workspace_bytes_for(n_in, n_out, t, cap))
+    # with room for the neighbour lists that all passes read
+    ws_bytes = L.pcpp_build_triplets_workspace_bytes_for(n_in, n_out, t, cap)
+    if ws_bytes == 0:
+        raise PcppError(-1, "invalid sizes or t")
     if ws is None or ws.numel() < ws_bytes:
         ws = _bytes(ws_bytes, dev)
 
@@ -222,8 +223,7 @@ def pcpp_build_triplets(in_xyz: torch.Tensor, out_xyz: torch.Tensor, radius: flo
         n_batches = in_offsets.numel() - 1
     rc = L.pcpp_build_triplets_batched(_ptr(in_xyz), n_in, _ptr(out_xyz), n_out, _ptr(in_offsets), _ptr(out_offsets),
                                        n_batches, float(radius), int(t),
-                                       _ptr(tri_o), _ptr(tri_i), _ptr(tri_k), cap, _ptr(seg),
-                                       ctypes.cast(n.data_ptr(), ctypes.POINTER(ctypes.c_int64)),
+                                       _ptr(tri_o), _ptr(tri_i), _ptr(tri_k), cap, _ptr(seg), n,
                                        _ptr(plan) if want_plan else None, plan.numel() if want_plan else 0, plan_flags,
                                        _ptr(ws), ws.numel(), _stream())
     nt = int(n[0])
@@ -242,9 +242,7 @@ def pcpp_voxel_subsample(xyz: torch.Tensor, pitch: float) -> torch.Tensor:
     kept = torch.empty(max(n, 1), dtype=torch.int32, device=xyz.device)
     ws = _bytes(L.pcpp_voxel_subsample_workspace_bytes(n), xyz.device)
     cnt = _landing_word()
-    _check(L.pcpp_voxel_subsample(_ptr(xyz), n, float(pitch), _ptr(kept),
-                                  ctypes.cast(cnt.data_ptr(), ctypes.POINTER(ctypes.c_int64)), _ptr(ws), ws.numel(),
-                                  _stream()))
+    _check(L.pcpp_voxel_subsample(_ptr(xyz), n, float(pitch), _ptr(kept), cnt, _ptr(ws), ws.numel(), _stream()))
     return kept[:int(cnt[0])]
 
 
