@@ -1579,6 +1579,10 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         per_block = per_block < 1 ? 1 : (per_block > COUNT_TILES ? COUNT_TILES : per_block);
         const dim3 grid((unsigned)ceil_div(most_tiles, per_block), (unsigned)counted);
         const size_t lds = count_lds_bytes(K, sides.s[counted - 1].mirror_sums != nullptr);
+        if (lds > (size_t)32 * 1024)                   // (both sides of 125 cells 49 KB, of 216 cells 85 KB)
+            if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&tile_count<true>) : reinterpret_cast<const void *>(&tile_count<false>),
+                                      lds)) != PCPP_OK)
+                return rc;
         if (ext) tile_count<true><<<grid, COUNT_THREADS, lds, stream>>>(sides, K, (int)per_block, err);
         else tile_count<false><<<grid, COUNT_THREADS, lds, stream>>>(sides, K, (int)per_block, err);
         PCPP_HIP_CHECK(hipGetLastError());
