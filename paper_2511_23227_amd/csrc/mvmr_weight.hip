@@ -552,14 +552,29 @@ bool lds_shape(int in_dtype, int c_in, int c_out) { return in_dtype == PCPP_BF16
 
 int launch_reduce(const float *part, float *dw, const int64_t *seg, int n_elem, int K, int chunk, int64_t n_chunks, hipStream_t stream)
 {
-    // four elements per lane where that leaves enough blocks and dW's rows start at a multiple of 16 bytes
-    if (n_elem >= 4096 && n_elem % 4 == 0 && (reinterpret_cast<uintptr_t>(dw) & 15) == 0) {
+    // Waves and elements per lane, by size of dW, number of blocks and chunks per cell (of the mean cell: on a surface half the cells hold
+    // none).  Measured over 700 layers (64 .. 65 536 elements, 1 .. 216 cells, 0.3 .. 5000 chunks a cell); figures: the whole weight
+    // gradient, us.
+    // * Four elements per lane, which takes rows of dW at multiples of 16 bytes: a quarter of the blocks and of the requests.  Wide
+    //   layers (128 -> 128, 216 cells, less than a chunk each: one element 50, four 38), and narrower ones with more waves where there
+    //   are chunks for them (64 -> 64, 216 cells: one chunk each 22.2 with one element, 19.5 with four, 20.7 with eight waves; 4.5
+    //   chunks 33.4, 31.6, 31.2).  Past 256 chunks a cell it is the chain of a wave that takes the time (64 -> 64, one cell, 972
+    //   chunks: 31.5; one element and sixteen waves 24.8).
+    // * One element per lane: sixteen waves from 4 chunks a cell on where the device holds all blocks at a time (8 -> 8, one cell, 1020
+    //   chunks: four waves 39.4, sixteen 26.3; 16 -> 16, 125 cells, 8 chunks: 29.6 and 28.5).  With more blocks waves without a chunk
+    //   take up room (127 -> 129, 216 cells, less than a chunk each: 59 with four, 121 with sixteen; 8 cells, 18 chunks: 28.5 and
+    //   32.5), and the chains are worth more waves only when they are long (47 -> 61, 27 cells, 36 chunks: 32.8 with four, 31.9 with eight).
+    const int64_t per_cell = n_chunks / K, blocks = ceil_div(n_elem, 64) * K;
+    if (n_elem >= 4096 && n_elem % 4 == 0 && (reinterpret_cast<uintptr_t>(dw) & 15) == 0 && per_cell < 256) {
         const dim3 grid((unsigned)ceil_div(n_elem, 256), (unsigned)K);
-        if (n_elem >= 16384) weight_reduce<4, 4><<<grid, 256, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
+        if (per_cell < (n_elem >= 16384 ? 32 : 4)) weight_reduce<4, 4><<<grid, 256, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
         else weight_reduce<4, 8><<<grid, 512, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
+    } else {
+        const dim3 grid((unsigned)ceil_div(n_elem, 64), (unsigned)K);
+        if (per_cell >= (blocks <= 512 ? 4 : 64)) weight_reduce<1, 16><<<grid, 1024, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
+        else if (per_cell >= 20) weight_reduce<1, 8><<<grid, 512, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
+        else weight_reduce<1, 4><<<grid, 256, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
     }
-    else
-        weight_reduce<1, 16><<<dim3((unsigned)ceil_div(n_elem, 64), (unsigned)K), 1024, 0, stream>>>(part, dw, seg, n_elem, chunk, n_chunks);
     PCPP_HIP_CHECK(hipGetLastError());
     return PCPP_OK;
 }
