@@ -110,9 +110,14 @@ PCPP_API int pcpp_version(void);
  *   workspace            scratch of pcpp_build_triplets_workspace_bytes(...) bytes, 256-byte
  *                        aligned; contents are undefined afterwards.  With
  *                        pcpp_build_triplets_workspace_bytes_for(..., capacity) bytes every centre's
- *                        neighbours are searched once and kept, and all later passes read those lists;
- *                        with less room the lists are shorter, and centres with more neighbours are
- *                        searched again in each pass (same results).
+ *                        neighbours are searched once and kept, and all later passes read those lists.
+ *                        That takes, per side, lists of 4 bytes times twice the mean of the capacity's
+ *                        triplets per centre (128 bytes to 2 KB a centre; 2 KB from a mean of 128 on) and
+ *                        room for longer ones, 4.5 bytes per triplet of the capacity; clouds of up to 8192
+ *                        points and 2^23 pairs, which are searched without a grid, 4 bytes per pair.  So a
+ *                        generous capacity costs memory.  With less room the lists are shorter; in the
+ *                        smallest workspace a call either finds room for them among its tables or searches
+ *                        again in each pass (same results).
  * in_xyz [n_in,3] and out_xyz [n_out,3] may alias (outputs at the inputs).
  * Errors: INVALID_ARG (null xyz with n > 0, radius not finite or <= 0, t outside 1..PCPP_MAX_T,
  * some but not all tri_* NULL, unknown flag bits), CAPACITY, WORKSPACE, UNSUPPORTED (|T| >= 2^31), HIP.

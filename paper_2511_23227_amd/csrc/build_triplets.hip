@@ -194,17 +194,6 @@ __device__ inline uint32_t wave_incl_scan_u32(uint32_t v)
     return v;
 }
 
-// the same within each half of the wave
-__device__ inline uint32_t half_incl_scan_u32(uint32_t v)
-{
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
-    return v;
-}
-
 // A value that the compiler has to work out at this place: what rarely taken code derives from it is not kept in registers
 // all along the loops around it (the fill pass spilled twenty for that).
 __device__ inline int here(int v)
@@ -349,22 +338,37 @@ struct Candidates {
     }
 };
 
-constexpr uint32_t KEEP_MAX = 512;        // longest neighbour list that is kept per centre
+constexpr uint32_t KEEP_MAX = 512;        // largest stride of the neighbour lists
 constexpr int HIT_INDEX_BITS = 24;        // a stored hit = cell << 24 | candidate index
 constexpr uint32_t HIT_INDEX_MASK = (1u << HIT_INDEX_BITS) - 1u;
 
+// The neighbour lists of one side's centres.  found[c] says how many neighbours centre c has, up to `stride`, whose list lies at
+// c stride; or, with LONG_LIST set, where its list lies behind those, in units of LONG_UNIT words and behind a word that says how many
+// there are.  The search hands out that room where it finds a list that is too long.  Only a call with more triplets than it has room
+// for runs out of it, and what matters then is that the triplets are counted: such a centre has NO_LIST and the count searches it again.
+constexpr uint32_t LONG_LIST = 0x80000000u, NO_LIST = 0xffffffffu, LONG_UNIT = 4;
+struct Lists {
+    uint32_t *hits;               // cell << 24 | index, in arrival order; NULL: no lists at all
+    uint32_t *found;              // [n_centres]; without lists the count pass writes the numbers
+    uint32_t stride;
+    size_t long_from;
+
+    __device__ inline size_t long_at(uint32_t f) const { return long_from + (size_t)(f & ~LONG_LIST) * LONG_UNIT; }
+};
+
 // ---- search: every centre's neighbours, in arrival order ----------------------------------------
-//   hits   [n_centres][stride]   a centre's first neighbours, cell << 24 | index, where the centres are outputs
-//   mirror the same where they are inputs.  A cloud queried against itself has both: the pair (centre c, candidate b) is also
-//          the pair (c, b) of the side with the roles swapped, in the cell of the opposite offset
-//   n_hits [n_centres]           how many neighbours it has
+// into the lists of the side where the centres are outputs, or `mirror` where they are inputs.  A cloud queried against itself
+// has both: the pair (centre c, candidate b) is also the pair (c, b) of the side with the roles swapped, in the cell of the opposite
+// offset, at the same place of its lists.
 // A wave takes `per_wave` consecutive centres of `order`, which holds the centres grouped by grid cell (without it: in index
 // order), and those of one cell together: the stencil is probed and the candidates are read, placed and converted once for
 // all of them, 256 at a time in registers, and a centre costs its binary64 tests, the cells of its neighbours and the stores.
 // Bound by instruction issue.  One search per centre, in the order of the tiles and with the tiles' tables in LDS: 1 M points
 // of a ground scene, 32 neighbours in 125 cells, 1215 us; now 325.
+// Centres with a long list are searched a second time here, where they still share their candidates, and not by the later passes, one
+// wave per centre: 20 000 points with a quarter of them in a blob, two sides, 2.9 M triplets, the build with both further
+// searches 457 us, so 241; without a grid 2896 points, one side, 350 and 66.
 constexpr int GROUP_SETS = 4;             // sets of 64 candidates in registers
-constexpr int64_t NO_GRID_POINTS = 8192, NO_GRID_PAIRS = (int64_t)1 << 23;     // most that a search without a grid looks at
 constexpr int64_t SEARCH_WAVES = 8192;    // waves wanted before a wave takes more centres
 
 struct SearchArgs {
@@ -373,8 +377,10 @@ struct SearchArgs {
     int64_t n_centres;
     GridView g;
     QueryParams q;
-    uint32_t *hits, *mirror, *n_hits;
-    uint32_t stride;
+    Lists lists;
+    uint32_t *mirror;
+    unsigned long long long_units;       // room for lists longer than the stride
+    unsigned long long *long_used;       // how much of it has been handed out; without a grid every centre has its own, for all candidates
     int per_wave;
     uint32_t *err;
     unsigned long long *clear_from;      // without a grid: what its clearing kernel would have cleared
@@ -391,12 +397,20 @@ __device__ inline void store_hit(const SearchArgs &a, size_t at, double dx, doub
     const bool cube = EXT && a.q.voxel_mode;
     if constexpr (FORM != INPUTS) {
         const int k = cube ? cube_cell(dx, dy, dz, a.q) : ball_cell(dx, dy, dz, a.q);
-        a.hits[at] = ((uint32_t)k << HIT_INDEX_BITS) | b;
+        a.lists.hits[at] = ((uint32_t)k << HIT_INDEX_BITS) | b;
     }
     if constexpr (FORM != OUTPUTS) {
         const int k = cube ? cube_cell(-dx, -dy, -dz, a.q) : ball_cell(-dx, -dy, -dz, a.q);
         a.mirror[at] = ((uint32_t)k << HIT_INDEX_BITS) | b;
     }
+}
+
+// a long list's word in front
+template <Form FORM>
+__device__ inline void store_length(const SearchArgs &a, size_t at, uint32_t n)
+{
+    if constexpr (FORM != INPUTS) a.lists.hits[at] = n;
+    if constexpr (FORM != OUTPUTS) a.mirror[at] = n;
 }
 
 template <Form FORM, bool EXT>
@@ -422,60 +436,78 @@ __global__ __launch_bounds__(256, 6) void search_cells(const SearchArgs a)
         if (EXT && a.q.c_off) batch = find_batch(a.q.c_off, a.q.n_batches, index);
     }
     const unsigned long long below = (1ull << lane) - 1ull;
-    uint32_t filled_of = 0;                        // neighbours of this lane's centre so far
+    uint32_t filled_of = 0;                        // where the next neighbour of this lane's centre goes in its list, or among the long lists
     unsigned long long open = __ballot(mine);
-    while (open) {
-        const int lead = __builtin_ctzll(open);
-        const int lx = (int)lane_value((uint32_t)gx, lead), ly = (int)lane_value((uint32_t)gy, lead), lz = (int)lane_value((uint32_t)gz, lead);
-        const int lb = EXT ? (int)lane_value((uint32_t)batch, lead) : -1;
-        const unsigned long long group = __ballot(gx == lx && gy == ly && gz == lz && (!EXT || batch == lb)) & open;
-        open &= ~group;
-        Stencil st;
-        st.open(lx, ly, lz, lb, a.g, lane);
-        int d_lo = 0, d_hi = 0x7fffffff;
-        if (EXT && a.q.c_off) { d_lo = a.q.d_off[lb]; d_hi = a.q.d_off[lb + 1]; }
-        for (uint32_t first = 0; first < st.total; first += 64 * GROUP_SETS) {
-            double px[GROUP_SETS], py[GROUP_SETS], pz[GROUP_SETS];
-            uint32_t pb[GROUP_SETS];
+    // once over the candidates for all centres, once more for those whose list turned out to be a long one
+    for (bool again = false;; again = true) {
+        const uint32_t limit = again ? 0xffffffffu : a.lists.stride;
+        while (open) {
+            const int lead = __builtin_ctzll(open);
+            const int lx = (int)lane_value((uint32_t)gx, lead), ly = (int)lane_value((uint32_t)gy, lead), lz = (int)lane_value((uint32_t)gz, lead);
+            const int lb = EXT ? (int)lane_value((uint32_t)batch, lead) : -1;
+            const unsigned long long group = __ballot(gx == lx && gy == ly && gz == lz && (!EXT || batch == lb)) & open;
+            open &= ~group;
+            Stencil st;
+            st.open(lx, ly, lz, lb, a.g, lane);
+            int d_lo = 0, d_hi = 0x7fffffff;
+            if (EXT && a.q.c_off) { d_lo = a.q.d_off[lb]; d_hi = a.q.d_off[lb + 1]; }
+            for (uint32_t first = 0; first < st.total; first += 64 * GROUP_SETS) {
+                double px[GROUP_SETS], py[GROUP_SETS], pz[GROUP_SETS];
+                uint32_t pb[GROUP_SETS];
 #pragma unroll
-            for (int s = 0; s < GROUP_SETS; ++s) {
-                px[s] = INFINITY; py[s] = 0.0; pz[s] = 0.0; pb[s] = 0u;       // infinitely far: no neighbour of any centre
-                const uint32_t idx = first + 64u * s + (uint32_t)lane;
-                if (first + 64u * s < st.total) {  // wave-uniform
-                    const uint32_t pos = st.place(idx < st.total ? idx : 0u);
-                    if (idx < st.total) {
-                        const float4 p = a.g.pts[pos];
-                        pb[s] = (uint32_t)__float_as_int(p.w);
-                        if (!EXT || ((int)pb[s] >= d_lo && (int)pb[s] < d_hi)) {
-                            if (EXT && a.q.voxel_mode) { px[s] = voxel_of(p.x, a.q.R); py[s] = voxel_of(p.y, a.q.R); pz[s] = voxel_of(p.z, a.q.R); }
-                            else { px[s] = (double)p.x; py[s] = (double)p.y; pz[s] = (double)p.z; }
+                for (int s = 0; s < GROUP_SETS; ++s) {
+                    px[s] = INFINITY; py[s] = 0.0; pz[s] = 0.0; pb[s] = 0u;       // infinitely far: no neighbour of any centre
+                    const uint32_t idx = first + 64u * s + (uint32_t)lane;
+                    if (first + 64u * s < st.total) {  // wave-uniform
+                        const uint32_t pos = st.place(idx < st.total ? idx : 0u);
+                        if (idx < st.total) {
+                            const float4 p = a.g.pts[pos];
+                            pb[s] = (uint32_t)__float_as_int(p.w);
+                            if (!EXT || ((int)pb[s] >= d_lo && (int)pb[s] < d_hi)) {
+                                if (EXT && a.q.voxel_mode) { px[s] = voxel_of(p.x, a.q.R); py[s] = voxel_of(p.y, a.q.R); pz[s] = voxel_of(p.z, a.q.R); }
+                                else { px[s] = (double)p.x; py[s] = (double)p.y; pz[s] = (double)p.z; }
+                            }
                         }
                     }
                 }
-            }
-            for (unsigned long long rest = group; rest; rest &= rest - 1) {
-                const int c = __builtin_ctzll(rest);
-                const float sx = lane_value(fx, c), sy = lane_value(fy, c), sz = lane_value(fz, c);
-                double cx, cy, cz;
-                if (EXT && a.q.voxel_mode) { cx = voxel_of(sx, a.q.R); cy = voxel_of(sy, a.q.R); cz = voxel_of(sz, a.q.R); }
-                else { cx = (double)sx; cy = (double)sy; cz = (double)sz; }
-                const size_t row = (size_t)lane_value((uint32_t)index, c) * a.stride;
-                uint32_t filled = lane_value(filled_of, c);
+                for (unsigned long long rest = group; rest; rest &= rest - 1) {
+                    const int c = __builtin_ctzll(rest);
+                    const float sx = lane_value(fx, c), sy = lane_value(fy, c), sz = lane_value(fz, c);
+                    double cx, cy, cz;
+                    if (EXT && a.q.voxel_mode) { cx = voxel_of(sx, a.q.R); cy = voxel_of(sy, a.q.R); cz = voxel_of(sz, a.q.R); }
+                    else { cx = (double)sx; cy = (double)sy; cz = (double)sz; }
+                    const size_t row = again ? a.lists.long_from : (size_t)lane_value((uint32_t)index, c) * a.lists.stride;
+                    uint32_t filled = lane_value(filled_of, c);
 #pragma unroll
-                for (int s = 0; s < GROUP_SETS; ++s) {
-                    if (first + 64u * s >= st.total) break;                   // wave-uniform
-                    const double dx = __dsub_rn(px[s], cx), dy = __dsub_rn(py[s], cy), dz = __dsub_rn(pz[s], cz);
-                    const bool hit = EXT && a.q.voxel_mode ? inside_cube(dx, dy, dz, a.q) : inside_ball(dx, dy, dz, a.q);
-                    const unsigned long long m = __ballot(hit);
-                    const uint32_t slot = filled + (uint32_t)__popcll(m & below);
-                    filled += (uint32_t)__popcll(m);
-                    if (hit && slot < a.stride) store_hit<FORM, EXT>(a, row + slot, dx, dy, dz, pb[s]);
+                    for (int s = 0; s < GROUP_SETS; ++s) {
+                        if (first + 64u * s >= st.total) break;                   // wave-uniform
+                        const double dx = __dsub_rn(px[s], cx), dy = __dsub_rn(py[s], cy), dz = __dsub_rn(pz[s], cz);
+                        const bool hit = EXT && a.q.voxel_mode ? inside_cube(dx, dy, dz, a.q) : inside_ball(dx, dy, dz, a.q);
+                        const unsigned long long m = __ballot(hit);
+                        const uint32_t slot = filled + (uint32_t)__popcll(m & below);
+                        filled += (uint32_t)__popcll(m);
+                        if (hit && slot < limit) store_hit<FORM, EXT>(a, row + slot, dx, dy, dz, pb[s]);
+                    }
+                    if (lane == c) filled_of = filled;
                 }
-                if (lane == c) filled_of = filled;
             }
         }
+        if (again) break;
+        uint32_t found = filled_of;
+        if (mine && filled_of > a.lists.stride) {
+            const uint32_t units = (filled_of + LONG_UNIT) / LONG_UNIT;          // (its length in front)
+            const unsigned long long from = atomicAdd(a.long_used, (unsigned long long)units);
+            found = NO_LIST;
+            if (from + units <= a.long_units) {
+                found = (uint32_t)from | LONG_LIST;
+                store_length<FORM>(a, a.lists.long_at(found), filled_of);
+                filled_of = (uint32_t)from * LONG_UNIT + 1u;
+            }
+        }
+        if (mine) a.lists.found[index] = found;
+        open = __ballot(mine && (found & LONG_LIST) && found != NO_LIST);
+        if (!open) break;
     }
-    if (mine) a.n_hits[index] = filled_of;
 }
 
 // The same for small clouds, without a grid: every centre looks at every candidate, one wave per centre, and a test in 32 bits
@@ -509,61 +541,76 @@ __global__ __launch_bounds__(256) void search_all(const SearchArgs a)
     if (cube) { cx = voxel_of(fx, a.q.R); cy = voxel_of(fy, a.q.R); cz = voxel_of(fz, a.q.R); }
     const float near2 = (float)(a.q.r2 * (1.0 + 1.0 / 1048576.0)) + 1e-37f;
     const unsigned long long below = (1ull << lane) - 1ull;
+    // once over the candidates, and once more if the list turned out to be a long one
     uint32_t filled = 0;
-    const size_t row = (size_t)index * a.stride;
-    for (int c0 = 0; c0 < a.g.n; c0 += ALL_CHUNK) {
-        const int m = a.g.n - c0 < ALL_CHUNK ? a.g.n - c0 : ALL_CHUNK;
-        if (c0 > 0) __syncthreads();
-        for (int i0 = tid; i0 < 3 * m; i0 += 256 * LOADS) {        // (all of a step's loads on their way at a time)
-            float v[LOADS];
+    bool is_long = false;
+    const uint32_t long_units = ((uint32_t)a.g.n + LONG_UNIT) / LONG_UNIT, long_of = (uint32_t)index * long_units;
+    for (bool again = false;; again = true) {
+        const size_t row = again ? a.lists.long_at(long_of) + 1 : (size_t)index * a.lists.stride;
+        const uint32_t limit = again ? 0xffffffffu : a.lists.stride;
+        for (int c0 = 0; c0 < a.g.n; c0 += ALL_CHUNK) {
+            const int m = a.g.n - c0 < ALL_CHUNK ? a.g.n - c0 : ALL_CHUNK;
+            if (!again || a.g.n > ALL_CHUNK) {             // (otherwise they are all there still)
+                if (again || c0 > 0) __syncthreads();
+                for (int i0 = tid; i0 < 3 * m; i0 += 256 * LOADS) {        // (all of a step's loads on their way at a time)
+                    float v[LOADS];
 #pragma unroll
-            for (int j = 0; j < LOADS; ++j) v[j] = i0 + 256 * j < 3 * m ? a.g.xyz[3 * (size_t)c0 + i0 + 256 * j] : 0.f;
+                    for (int j = 0; j < LOADS; ++j) v[j] = i0 + 256 * j < 3 * m ? a.g.xyz[3 * (size_t)c0 + i0 + 256 * j] : 0.f;
 #pragma unroll
-            for (int j = 0; j < LOADS; ++j)
-                if (i0 + 256 * j < 3 * m) cand[i0 + 256 * j] = v[j];
+                    for (int j = 0; j < LOADS; ++j)
+                        if (i0 + 256 * j < 3 * m) cand[i0 + 256 * j] = v[j];
+                }
+                __syncthreads();
+            }
+            if (again && !is_long) continue;               // (wave-uniform)
+            const int lo = d_lo > c0 ? (d_lo - c0) & ~63 : 0, hi = d_hi - c0 < m ? d_hi - c0 : m;     // the centre's own cloud
+            for (int first = lo; first < hi; first += 64 * GROUP_SETS) {
+                float x[GROUP_SETS], y[GROUP_SETS], z[GROUP_SETS];
+                bool in[GROUP_SETS], near[GROUP_SETS], any = false;
+#pragma unroll
+                for (int s = 0; s < GROUP_SETS; ++s) {
+                    const int i = first + 64 * s + lane;
+                    in[s] = i < hi && (!EXT || c0 + i >= d_lo);
+                    const int at = 3 * (in[s] ? i : first);
+                    x[s] = cand[at]; y[s] = cand[at + 1]; z[s] = cand[at + 2];
+                }
+#pragma unroll
+                for (int s = 0; s < GROUP_SETS; ++s) {
+                    const float ax = x[s] - fx, ay = y[s] - fy, az = z[s] - fz;
+                    near[s] = in[s] && (cube || ax * ax + ay * ay + az * az <= near2);
+                    any = any || near[s];
+                }
+                if (!__ballot(any)) continue;
+#pragma unroll
+                for (int s = 0; s < GROUP_SETS; ++s) {
+                    if (!__ballot(near[s])) continue;
+                    double dx, dy, dz;
+                    if (cube) { dx = voxel_of(x[s], a.q.R) - cx; dy = voxel_of(y[s], a.q.R) - cy; dz = voxel_of(z[s], a.q.R) - cz; }
+                    else { dx = __dsub_rn((double)x[s], cx); dy = __dsub_rn((double)y[s], cy); dz = __dsub_rn((double)z[s], cz); }
+                    const bool hit = in[s] && (cube ? inside_cube(dx, dy, dz, a.q) : inside_ball(dx, dy, dz, a.q));
+                    const unsigned long long mask = __ballot(hit);
+                    const uint32_t slot = filled + (uint32_t)__popcll(mask & below);
+                    filled += (uint32_t)__popcll(mask);
+                    if (hit && slot < limit) store_hit<FORM, EXT>(a, row + slot, dx, dy, dz, (uint32_t)(c0 + first + 64 * s + lane));
+                }
+            }
         }
-        __syncthreads();
-        const int lo = d_lo > c0 ? (d_lo - c0) & ~63 : 0, hi = d_hi - c0 < m ? d_hi - c0 : m;     // the centre's own cloud
-        for (int first = lo; first < hi; first += 64 * GROUP_SETS) {
-            float x[GROUP_SETS], y[GROUP_SETS], z[GROUP_SETS];
-            bool in[GROUP_SETS], near[GROUP_SETS], any = false;
-#pragma unroll
-            for (int s = 0; s < GROUP_SETS; ++s) {
-                const int i = first + 64 * s + lane;
-                in[s] = i < hi && (!EXT || c0 + i >= d_lo);
-                const int at = 3 * (in[s] ? i : first);
-                x[s] = cand[at]; y[s] = cand[at + 1]; z[s] = cand[at + 2];
-            }
-#pragma unroll
-            for (int s = 0; s < GROUP_SETS; ++s) {
-                const float ax = x[s] - fx, ay = y[s] - fy, az = z[s] - fz;
-                near[s] = in[s] && (cube || ax * ax + ay * ay + az * az <= near2);
-                any = any || near[s];
-            }
-            if (!__ballot(any)) continue;
-#pragma unroll
-            for (int s = 0; s < GROUP_SETS; ++s) {
-                if (!__ballot(near[s])) continue;
-                double dx, dy, dz;
-                if (cube) { dx = voxel_of(x[s], a.q.R) - cx; dy = voxel_of(y[s], a.q.R) - cy; dz = voxel_of(z[s], a.q.R) - cz; }
-                else { dx = __dsub_rn((double)x[s], cx); dy = __dsub_rn((double)y[s], cy); dz = __dsub_rn((double)z[s], cz); }
-                const bool hit = in[s] && (cube ? inside_cube(dx, dy, dz, a.q) : inside_ball(dx, dy, dz, a.q));
-                const unsigned long long mask = __ballot(hit);
-                const uint32_t slot = filled + (uint32_t)__popcll(mask & below);
-                filled += (uint32_t)__popcll(mask);
-                if (hit && slot < a.stride) store_hit<FORM, EXT>(a, row + slot, dx, dy, dz, (uint32_t)(c0 + first + 64 * s + lane));
-            }
+        if (again) break;
+        is_long = on && filled > a.lists.stride;           // (wave-uniform)
+        if (on && lane == 0) {
+            a.lists.found[index] = is_long ? long_of | LONG_LIST : filled;
+            if (is_long) store_length<FORM>(a, a.lists.long_at(long_of), filled);
         }
+        if (a.g.n > ALL_CHUNK ? !__syncthreads_or(is_long) : !is_long) break;
+        filled = 0u;
     }
-    if (on && lane == 0) a.n_hits[index] = filled;
 }
 
 // ---- one side's order of the triplets -------------------------------------------------------------
 // The public list (centres = outputs in index order) and the plan's sides.  Tile = 64 consecutive slots.
 //   perm     centre index of each slot (NULL: slots are centre indices); lists are indexed by centre
-//   hits     the centres' neighbours as the search left them; a centre with more than `stride` is searched again, every
-//            centre where there are no lists (stride 0).  n_hits: how many neighbours each has (without lists the count pass
-//            writes it, and where mirror_sums is given, the sums of the swapped side too)
+//   lists    the centres' neighbours as the search left them.  Without lists both passes search again (the count pass writes the
+//            numbers of neighbours, and where mirror_sums is given, the sums of the swapped side too)
 //   sums     [K * n_tiles]      k-major: neighbours of tile's centres in cell k
 //   ptr      [K * n_tiles + 1]  exclusive prefix sum of `sums`
 struct FillOut {
@@ -583,9 +630,7 @@ struct Side {
     int64_t n_centres, n_tiles;
     GridView g;
     QueryParams q;
-    const uint32_t *hits;
-    uint32_t *n_hits;
-    uint32_t stride;
+    Lists lists;
     uint32_t *sums, *mirror_sums;
     const uint32_t *ptr;
     uint32_t *run_start;          // [n_tiles][K][TILE], NULL: not wanted
@@ -597,22 +642,23 @@ struct Sides { Side s[MAX_SIDES]; };
 
 // What the fill pass keeps in LDS of a tile's centres.
 struct TileCentres {
-    uint32_t n[TILE], off[TILE];  // neighbours of each, and of the centres before it
+    uint32_t off[TILE + 1];       // neighbours of the centres before each
     int32_t at[TILE];             // its own index
-    uint32_t searched;            // centres without a complete list: whether there are any
+    uint32_t found[TILE];
 
+    __device__ inline uint32_t n(int al) const { return off[al + 1] - off[al]; }
     // by wave 0; a barrier follows
     __device__ inline void open(const Side &s, int64_t tile, int lane)
     {
         const int64_t slot = tile * TILE + lane;
         const bool on = slot < s.n_centres;
         const int32_t c = on ? (s.perm ? s.perm[slot] : (int32_t)slot) : 0;
-        const uint32_t m = on ? s.n_hits[c] : 0u;
-        const unsigned long long past = __ballot(on && (m > s.stride || !s.stride));
+        const uint32_t f = on ? s.lists.found[c] : 0u, m = !(f & LONG_LIST) ? f : f != NO_LIST ? s.lists.hits[s.lists.long_at(f)] : 0u;
+        const uint32_t incl = wave_incl_scan_u32(m);
         at[lane] = c;
-        n[lane] = m;
-        off[lane] = wave_incl_scan_u32(m) - m;
-        if (lane == 0) searched = past != 0ull;
+        found[lane] = f;
+        off[lane] = incl - m;
+        if (lane == TILE - 1) off[TILE] = incl;
     }
     // the centre that a neighbour of the tile belongs to, for a thread that goes through consecutive ones
     struct Cursor { int al; uint32_t end; };
@@ -622,13 +668,13 @@ struct TileCentres {
 #pragma unroll
         for (int step = TILE / 2; step >= 1; step >>= 1)
             if (off[al + step] <= p) al += step;
-        return Cursor{al, off[al] + n[al]};
+        return Cursor{al, off[al + 1]};
     }
     __device__ inline void advance(Cursor &c, uint32_t p) const
     {
         while (p >= c.end) {               // (p is below the tile's number of neighbours)
             ++c.al;
-            c.end = off[c.al] + n[c.al];
+            c.end = off[c.al + 1];
         }
     }
 };
@@ -665,7 +711,7 @@ template <bool EXT>
 __global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides, int K, int tiles_per_block, const uint32_t *__restrict__ err)
 {
     extern __shared__ uint32_t tbl[];                      // [K][COUNT_PITCH] and [K][COUNT_TILES], each twice with mirror_sums
-    __shared__ uint32_t searched[2];                       // tile's parity: a centre of it has no complete list
+    __shared__ uint32_t searched[2];                       // tile's parity: a centre of it has no list
     const Side &s = sides.s[blockIdx.y];
     const int64_t t0 = (int64_t)blockIdx.x * tiles_per_block;
     const int64_t t1 = t0 + tiles_per_block < s.n_tiles ? t0 + tiles_per_block : s.n_tiles;
@@ -680,40 +726,51 @@ __global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides
         const int64_t slot = tile * TILE + al;
         return tile < t1 && slot < s.n_centres ? (s.perm ? s.perm[slot] : (int32_t)slot) : -1;
     };
-    auto length_of = [&](int32_t c) -> uint32_t { return c >= 0 && s.stride ? s.n_hits[c] : 0u; };
-    auto words_of = [&](int32_t c, uint32_t n, uint32_t e) -> list_words {
-        // (a last piece may read past the list, not past the lists' end)
-        return n <= s.stride && e < n ? *reinterpret_cast<const list_words *>(s.hits + (size_t)c * s.stride + e) : list_words{0u, 0u, 0u, 0u};
+    auto found_of = [&](int32_t c) -> uint32_t { return c >= 0 && s.lists.hits ? s.lists.found[c] : 0u; };
+    auto words_of = [&](size_t list, uint32_t n, uint32_t e) -> list_words {
+        // (a last piece may read past the list, not past the room behind the lists)
+        return e < n ? *reinterpret_cast<const list_words *>(s.lists.hits + list + e) : list_words{0u, 0u, 0u, 0u};
     };
+    // (the few long lists are not read ahead)
+    auto ahead_of = [&](int32_t c, uint32_t f) -> list_words { return words_of((size_t)c * s.lists.stride, f & LONG_LIST ? 0u : f, 4u * l); };
     int32_t c_now = centre_of(t0), c_next = centre_of(t0 + 1), c_after = centre_of(t0 + 2);
-    uint32_t n_now = length_of(c_now), n_next = length_of(c_next);
-    list_words w_now = words_of(c_now, n_now, 4u * l);
+    uint32_t f_now = found_of(c_now), f_next = found_of(c_next);
+    list_words w_now = ahead_of(c_now, f_now);
     for (int i = tid; i < K * PITCH * (mirror ? 2 : 1); i += COUNT_THREADS) tbl[i] = 0u;
     if (tid < 2) searched[tid] = 0u;
     lds_barrier();
     for (int64_t tile = t0; tile < t1; ++tile) {
-        const list_words w_next = words_of(c_next, n_next, 4u * l);
-        const uint32_t n_after = length_of(c_after);
+        const list_words w_next = ahead_of(c_next, f_next);
+        const uint32_t f_after = found_of(c_after);
         const int32_t c_third = centre_of(tile + 3);
-        const uint32_t n = n_now <= s.stride ? n_now : 0u;
+        uint32_t n = f_now;
+        size_t list = (size_t)c_now * s.lists.stride;
         list_words w = w_now;
+        if (f_now & LONG_LIST) {
+            n = 0u;
+            if (f_now != NO_LIST) {
+                list = s.lists.long_at(f_now) + 1;
+                n = s.lists.hits[list - 1];
+                w = words_of(list, n, 4u * l);
+            }
+        }
         for (uint32_t e = 4u * l; e < n;) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (e + j < n) atomicAdd(&col[(w[j] >> HIT_INDEX_BITS) * PITCH], 1u);
             e += 32u;
-            if (e < n) w = words_of(c_now, n, e);
+            if (e < n) w = words_of(list, n, e);
         }
-        if (c_now >= 0 && (n_now > s.stride || !s.stride)) searched[tile & 1] = 1u;
+        if (c_now >= 0 && (!s.lists.hits || f_now == NO_LIST)) searched[tile & 1] = 1u;
         lds_barrier();
         if (tid == 0) searched[(tile + 1) & 1] = 0u;       // (read before the last barrier, written behind the next)
         if (searched[tile & 1]) {                          // (block-uniform)
-            // centres without a complete list: searched, one wave per centre
+            // centres without a list: searched, one wave per centre
             for (int a = wave; a < TILE; a += WAVES) {
                 const int64_t slot = tile * TILE + a;
                 if (slot >= s.n_centres) break;            // wave-uniform
                 const int64_t c = s.perm ? (int64_t)s.perm[slot] : slot;
-                if (s.stride && (uint32_t)__builtin_amdgcn_readfirstlane((int)s.n_hits[c]) <= s.stride) continue;
+                if (s.lists.hits && (uint32_t)__builtin_amdgcn_readfirstlane((int)s.lists.found[c]) != NO_LIST) continue;
                 Candidates<EXT> cand;
                 cand.open(s.centres, c, s.g, s.q, lane);
                 uint32_t found = 0;
@@ -726,7 +783,7 @@ __global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides
                     }
                     found += (uint32_t)__popcll(__ballot(hit));
                 }
-                if (!s.stride && s.n_hits && lane == 0) s.n_hits[c] = found;
+                if (!s.lists.hits && lane == 0) s.lists.found[c] = found;
             }
             lds_barrier();
         }
@@ -747,8 +804,8 @@ __global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides
             }
         }
         lds_barrier();
-        c_now = c_next; n_now = n_next; w_now = w_next;
-        c_next = c_after; n_next = n_after;
+        c_now = c_next; f_now = f_next; w_now = w_next;
+        c_next = c_after; f_next = f_after;
         c_after = c_third;
     }
     for (int i = tid; i < K * COUNT_TILES; i += COUNT_THREADS) {
@@ -841,7 +898,7 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, i
     }
     if (wave == 0) tc.open(s, tile, lane);
     lds_barrier();
-    const uint32_t upto = tc.off[lane] + tc.n[lane];
+    const uint32_t upto = tc.off[lane + 1];
     char *run_start = s.run_start ? reinterpret_cast<char *>(s.run_start + (size_t)tile * K * TILE) : nullptr;
     // as many centres at a time as the list holds: usually all of them
     int c0 = 0;
@@ -882,11 +939,10 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, i
             continue;
         }
         const uint32_t n = lane_value(upto, c1 - 1) - before;
-        // ---- neighbours without a list: searched again, one wave per centre, left in the list for the threads that take them --
-        if (tc.searched) {                                 // (block-uniform)
+        // ---- without lists: searched again, one wave per centre, left in the list for the threads that take them -------------
+        if (!s.lists.hits) {                               // (block-uniform)
             for (int al = c0 + wave; al < c1; al += n_waves) {
-                const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)tc.n[al]);
-                if (m == 0u || m <= s.stride) continue;
+                if (__builtin_amdgcn_readfirstlane((int)tc.n(al)) == 0) continue;
                 const int lane = here(tid & 63);
                 Candidates<EXT> cand;
                 cand.open(s.centres, tc.at[al], s.g, s.q, lane);
@@ -918,8 +974,11 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, i
                     const uint32_t p = p0 + before + j;
                     tc.advance(c, p);
                     at_of[j] = (uint32_t)c.al << 8;
-                    if (c.end - tc.off[c.al] <= s.stride) {
-                        b_of[j] = s.hits[(size_t)tc.at[c.al] * s.stride + (p - tc.off[c.al])];
+                    if (s.lists.hits) {
+                        const uint32_t first = tc.off[c.al];
+                        size_t at = (size_t)tc.at[c.al] * s.lists.stride;
+                        if (c.end - first > s.lists.stride) at = s.lists.long_at(tc.found[c.al]) + 1;
+                        b_of[j] = s.lists.hits[at + (p - first)];
                     } else {
                         b_of[j] = list[p0 + j];
                         at_of[j] |= list_at[p0 + j] | 1u << 31;
@@ -1137,31 +1196,51 @@ struct BuildScratch {
     size_t scan_off;                 // status words of the prefix sums: N_SCANS regions of scan_stride bytes
     size_t scan_stride;
     size_t fwd_ptr_off, bwd_ptr_off; // per-(k, tile) sums; of the public list, their offsets
+    size_t fwd_tbl_off, bwd_tbl_off; // K words per centre of a tile: neighbour lists in the smallest workspace
     size_t sort_off;                 // scratch of the spatial sorts
     size_t end;                      // what a call needs
-    // The centres' neighbour lists and their lengths.  With a workspace made for the triplet capacity they lie behind `end`;
-    // otherwise a length per centre and K - 1 words of list fit the per-centre tables.
-    uint32_t fwd_stride = 0, bwd_stride = 0;
-    size_t fwd_n_off, bwd_n_off, fwd_hits_off = 0, bwd_hits_off = 0, end_with_lists = 0;
+    // The centres' neighbour lists.  How many neighbours each has lies where the grids kept their points' places.
+    struct SideLists {
+        bool on = false;
+        uint32_t stride = 0;
+        size_t found_off = 0, hits_off = 0;
+        int64_t long_units = 0;          // room behind the lists of the stride
+    };
+    SideLists fwd, bwd;
+    bool grid = true;
+    size_t end_with_lists;
 };
 
-// List length per centre: twice the mean neighbour count, within [32, most]; longer lists lie further apart (three times the mean:
-// builds of 0.8 and 1 M points 2.5 % slower).  In crowded clouds, which are mostly uneven ones, the longest: a centre that does not
-// fit is searched again in each pass (115 200 points of a spinning lidar, 146 neighbours, up to 460, capacity as needed: 768 us
-// with twice the mean, 486 so).
-constexpr int64_t CROWDED = 128;
+// Small clouds do without a grid: every centre looks at every candidate, which takes less than the four launches of a grid
+// (with one and without, us: 2048 points, build and forward pass, 82 and 72; the build of 2800 points 62 and 58; of 4096, past
+// the line, 65 and 78).
+constexpr int64_t NO_GRID_POINTS = 8192, NO_GRID_PAIRS = (int64_t)1 << 23;     // most that a search without a grid looks at
+bool small_clouds(int64_t n_in, int64_t n_out)
+{
+    return n_in > 0 && n_out > 0 && n_in <= NO_GRID_POINTS && n_out <= NO_GRID_POINTS && n_in * n_out <= NO_GRID_PAIRS;
+}
+
+// Stride of the lists: twice the mean neighbour count, within [32, most]; longer ones lie further apart (three times the mean: builds
+// of 0.8 and 1 M points 2.5 % slower).  In crowded clouds, which are mostly uneven ones, `most`: a centre with more neighbours is
+// searched a second time to fill its long list (115 200 points of a spinning lidar, 162 neighbours, up to 460 and more, both sides: 714 us
+// with 256, 654 so; 30 000 points with 338 neighbours 434 and 306).
+constexpr int64_t CROWDED = 128, MIN_STRIDE = 32;
 uint32_t hit_stride_for(int64_t capacity, int64_t n_centres, int64_t most)
 {
     if (n_centres <= 0 || capacity <= 0) return 0;
     const int64_t mean = ceil_div(capacity, n_centres);
     int64_t s = mean >= CROWDED ? most : (2 * mean + 15) / 16 * 16;
-    if (s < 32) s = 32;
+    if (s < MIN_STRIDE) s = MIN_STRIDE;
     if (s > most) s = most;
     return (uint32_t)s;
 }
 
-// Lists of at most `most` neighbours behind `end`.
-BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K, int64_t capacity = -1, int64_t most = KEEP_MAX)
+constexpr int64_t LIST_SLACK = 4;        // words that a read of four words may take past the last list
+// Room for the long lists of a call with `capacity` triplets, in units: a list of n > 32 words takes at most (n + 4) / 4.
+constexpr int64_t long_units_for(int64_t capacity) { return (capacity + capacity / 8) / LONG_UNIT + 1; }
+static_assert(8 * (int64_t)LONG_UNIT <= MIN_STRIDE, "the lengths and the unused words of long lists are an eighth at most");
+
+BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K)
 {
     BuildScratch b;
     b.grid_in = grid_scratch(0, n_in);
@@ -1178,42 +1257,72 @@ BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K, int64_t capacity 
     b.scan_stride = scan_scratch_bytes(scan_n);
     b.scan_off = off;    off += N_SCANS * b.scan_stride;
     b.fwd_ptr_off = off; off += align_up((size_t)(K * nt_o + 1) * 4);
-    b.fwd_n_off = off;   off += align_up((size_t)(nt_o > 0 ? nt_o : 1) * K * TILE * 4);
+    b.fwd_tbl_off = off; off += align_up((size_t)(nt_o > 0 ? nt_o : 1) * K * TILE * 4);
     b.bwd_ptr_off = off; off += align_up((size_t)(K * nt_i + 1) * 4);
-    b.bwd_n_off = off;   off += align_up((size_t)(nt_i > 0 ? nt_i : 1) * K * TILE * 4);
+    b.bwd_tbl_off = off; off += align_up((size_t)(nt_i > 0 ? nt_i : 1) * K * TILE * 4);
     b.sort_off = off;    off += spatial_order_scratch_bytes(n_max);
     b.end = off;
     b.end_with_lists = off;
-    // stored hits carry the candidate index in HIT_INDEX_BITS bits
-    if (n_in >= (1 << HIT_INDEX_BITS) || n_out >= (1 << HIT_INDEX_BITS)) return b;
-    if (capacity > 0) {
-        b.fwd_stride = hit_stride_for(capacity, n_out, most);
-        b.bwd_stride = hit_stride_for(capacity, n_in, most);
-        b.fwd_hits_off = off; off += align_up((size_t)n_out * b.fwd_stride * 4);
-        b.bwd_hits_off = off; off += align_up((size_t)n_in * b.bwd_stride * 4);
-        b.end_with_lists = off;
-    }
+    b.fwd.found_off = b.grid_out.point_at_off;
+    b.bwd.found_off = b.grid_in.point_at_off;
     return b;
 }
 
-// The scratch of a call whose workspace has `bytes` bytes: as long lists as fit.  With fewer than 27 cells the lists inside
-// the per-centre tables would mostly be too short to spare the later passes their search (8 cells: 7 neighbours); such a
-// call does without.
+// Lists with a stride of at most `most` words behind `end`, and room for the longer ones: all neighbours that a call has room for, or
+// without a grid all candidates of each centre (whose blocks have no counter yet that they could share the room by).
+BuildScratch build_scratch_with_lists(int64_t n_in, int64_t n_out, int K, int64_t capacity, int64_t most, bool grid)
+{
+    BuildScratch b = build_scratch(n_in, n_out, K);
+    b.grid = grid;
+    auto side = [&](BuildScratch::SideLists &l, int64_t n_centres, int64_t n_candidates) {
+        if (n_centres <= 0) return;
+        l.stride = hit_stride_for(capacity, n_centres, most);
+        l.on = l.stride > 0;
+        l.long_units = l.stride >= n_candidates ? 0 : grid ? long_units_for(capacity) : n_centres * ((n_candidates + LONG_UNIT) / LONG_UNIT);
+        l.hits_off = b.end_with_lists;
+        b.end_with_lists += align_up((size_t)(n_centres * l.stride + l.long_units * LONG_UNIT + LIST_SLACK) * 4);
+    };
+    side(b.fwd, n_out, n_in);
+    side(b.bwd, n_in, n_out);
+    return b;
+}
+
+// The scratch of a call whose workspace has `bytes` bytes: as long lists as fit, behind `end` or inside the tables of the
+// smallest workspace; a side whose neighbours have no room there does without.
 BuildScratch build_scratch_within(int64_t n_in, int64_t n_out, int K, int64_t capacity, size_t bytes)
 {
-    if (capacity > 0)
-        for (int64_t most = KEEP_MAX; most >= 32; most /= 2) {
-            const BuildScratch b = build_scratch(n_in, n_out, K, capacity, most);
-            if (b.fwd_stride == 0 && b.bwd_stride == 0) break;
-            if (bytes >= b.end_with_lists) return b;
-        }
     BuildScratch b = build_scratch(n_in, n_out, K);
-    if (capacity > 0 && K >= 27 && n_in < (1 << HIT_INDEX_BITS) && n_out < (1 << HIT_INDEX_BITS)) {
-        b.fwd_stride = b.bwd_stride = (uint32_t)(K - 1);
-        b.fwd_hits_off = b.fwd_n_off + (size_t)n_out * 4;
-        b.bwd_hits_off = b.bwd_n_off + (size_t)n_in * 4;
+    // stored hits carry the candidate index in HIT_INDEX_BITS bits; places among the long lists take 32
+    if (capacity <= 0 || n_in >= (1 << HIT_INDEX_BITS) || n_out >= (1 << HIT_INDEX_BITS)) return b;
+    if (capacity > INT32_MAX) capacity = INT32_MAX;
+    if (small_clouds(n_in, n_out)) {
+        const BuildScratch l = build_scratch_with_lists(n_in, n_out, K, capacity, KEEP_MAX, false);
+        if (bytes >= l.end_with_lists) return l;
     }
+    for (int64_t most = KEEP_MAX; most >= 32; most /= 2) {
+        const BuildScratch l = build_scratch_with_lists(n_in, n_out, K, capacity, most, true);
+        if (bytes >= l.end_with_lists) return l;
+    }
+    auto side = [&](BuildScratch::SideLists &l, int64_t n_centres, size_t table) {
+        const int64_t room = ceil_div(n_centres, TILE) * TILE * K - LIST_SLACK - long_units_for(capacity) * LONG_UNIT;
+        if (n_centres <= 0 || room < 0) return;
+        const int64_t stride = hit_stride_for(capacity, n_centres, KEEP_MAX), fits = room / n_centres;
+        if (fits < stride) return;         // (most lists would be long ones, and the counter of their room takes one wave after the other)
+        l.on = true;
+        l.stride = (uint32_t)stride;
+        l.long_units = long_units_for(capacity);
+        l.hits_off = table;
+    };
+    side(b.fwd, n_out, b.fwd_tbl_off);
+    side(b.bwd, n_in, b.bwd_tbl_off);
     return b;
+}
+
+// What the query for a workspace with lists answers.
+size_t build_bytes_for(int64_t n_in, int64_t n_out, int K, int64_t capacity)
+{
+    if (capacity <= 0 || n_in >= (1 << HIT_INDEX_BITS) || n_out >= (1 << HIT_INDEX_BITS)) return build_scratch(n_in, n_out, K).end;
+    return build_scratch_with_lists(n_in, n_out, K, capacity < INT32_MAX ? capacity : INT32_MAX, KEEP_MAX, !small_clouds(n_in, n_out)).end_with_lists;
 }
 
 // scan_scratch: the status words of this grid's prefix sum.  clear_words > 0: the first grid of a build, whose
@@ -1303,7 +1412,7 @@ size_t pcpp_build_triplets_workspace_bytes(int64_t n_in, int64_t n_out, int t)
 size_t pcpp_build_triplets_workspace_bytes_for(int64_t n_in, int64_t n_out, int t, int64_t capacity)
 {
     if (n_in < 0 || n_out < 0 || t < 1 || t > PCPP_MAX_T || capacity < 0) return 0;
-    return build_scratch(n_in, n_out, t * t * t, capacity).end_with_lists;
+    return build_bytes_for(n_in, n_out, t * t * t, capacity);
 }
 
 size_t pcpp_plan_bytes(int64_t n_in, int64_t n_out, int t, int64_t n_triplets, int plan_flags)
@@ -1453,11 +1562,7 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     auto words = [](char *base, size_t off) { return reinterpret_cast<uint32_t *>(base + off); };
 
     // ---- the candidates ----------------------------------------------------------------------------------------
-    // Small clouds do without a grid: every centre looks at every candidate, which takes less than the four launches of a grid
-    // (with one and without, us: 2048 points, build and forward pass, 82 and 72; the build of 2800 points 62 and 58; of 4096, past
-    // the line, 65 and 78).
-    const bool f_lists = bs.fwd_stride != 0, b_lists = want_bwd && bs.bwd_stride != 0;
-    const bool no_grid = f_lists && n_in > 0 && n_out > 0 && n_in <= NO_GRID_POINTS && n_out <= NO_GRID_POINTS && n_in * n_out <= NO_GRID_PAIRS;
+    const bool f_lists = bs.fwd.on, b_lists = want_bwd && bs.bwd.on, no_grid = !bs.grid;
     int rc;
     GridView grid_in{nullptr, nullptr, nullptr, 0u, gm, in_xyz, (int)n_in};
     // the error word, the total and all status words (contiguous) start at zero: the clearing kernel of the first grid sees to it
@@ -1479,14 +1584,21 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     // Centres = outputs, candidates = inputs; for the input gradient centres = inputs, candidates = outputs: the same
     // predicate with the roles swapped, so the set is identical and only the grouping changes to (k, i, o).  A cloud
     // queried against itself is searched once for both.
-    uint32_t *f_hits = f_lists ? words(ws, bs.fwd_hits_off) : nullptr, *f_n = words(ws, bs.fwd_n_off);
-    uint32_t *b_hits = b_lists ? words(ws, bs.bwd_hits_off) : nullptr, *b_n = self ? f_n : words(ws, bs.bwd_n_off);
-    auto search = [&](Form form, const float4 *order, const float *centres, int64_t n, const GridView &g, const QueryParams &qp,
-                      uint32_t *n_hits, uint32_t stride) -> int {
+    auto lists_of = [&](const BuildScratch::SideLists &l, bool on, int64_t n_centres) {
+        return Lists{on ? words(ws, l.hits_off) : nullptr, words(ws, l.found_off), on ? l.stride : 0u,
+                     (size_t)n_centres * l.stride};
+    };
+    const Lists f_l = lists_of(bs.fwd, f_lists, n_out);
+    Lists b_l = lists_of(bs.bwd, b_lists, n_in);
+    if (self) b_l.found = f_l.found;               // (one search or count for both)
+    unsigned long long *long_used = reinterpret_cast<unsigned long long *>(ws + bs.err_off + 64);      // of the two searches; cleared with the error word
+    auto search = [&](Form form, const float4 *order, const float *centres, int64_t n, const GridView &g, const QueryParams &qp) -> int {
         if (n <= 0) return PCPP_OK;
         int per_wave = 1;                          // centres: as many as leave enough waves for the device
         while (per_wave < 32 && n / (2 * per_wave) >= SEARCH_WAVES) per_wave *= 2;
-        const SearchArgs sa{order, centres, n, g, qp, f_hits, b_hits, n_hits, stride, per_wave, err, clear_from, form == INPUTS ? 0 : clear_words};
+        const bool in = form == INPUTS;
+        const SearchArgs sa{order, centres, n, g, qp, in ? b_l : f_l, b_l.hits, (unsigned long long)(in ? bs.bwd : bs.fwd).long_units,
+                            long_used + (in ? 1 : 0), per_wave, err, clear_from, in ? 0 : clear_words};
         const size_t lds = no_grid ? (size_t)(g.n < ALL_CHUNK ? g.n : ALL_CHUNK) * 3 * sizeof(float) : 0;
         auto pick = [&](auto cells, auto cells_ext, auto all, auto all_ext) { return no_grid ? (ext ? all_ext : all) : (ext ? cells_ext : cells); };
         auto kern = form == BOTH ? pick(search_cells<BOTH, false>, search_cells<BOTH, true>, search_all<BOTH, false>, search_all<BOTH, true>)
@@ -1500,10 +1612,10 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     };
     if (f_lists)
         if ((rc = search(self && b_lists ? BOTH : OUTPUTS, self ? grid_in.pts : (want_bwd ? grid_out.pts : nullptr), out_xyz, n_out,
-                         grid_in, q, f_n, bs.fwd_stride)) != PCPP_OK)
+                         grid_in, q)) != PCPP_OK)
             return rc;
     if (b_lists && !self)
-        if ((rc = search(INPUTS, grid_in.pts, in_xyz, n_in, grid_out, qs, b_n, bs.bwd_stride)) != PCPP_OK) return rc;
+        if ((rc = search(INPUTS, grid_in.pts, in_xyz, n_in, grid_out, qs)) != PCPP_OK) return rc;
 
     // ---- the centres' orders --------------------------------------------------------------------------------------
     const int32_t *perm_o = nullptr, *perm_i = nullptr;
@@ -1547,9 +1659,7 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         d.n_tiles = outputs ? nt_o : nt_i;
         d.g = outputs ? grid_in : grid_out;
         d.q = outputs ? q : qs;
-        d.hits = outputs ? f_hits : b_hits;
-        d.n_hits = outputs ? f_n : b_n;
-        d.stride = outputs ? bs.fwd_stride : bs.bwd_stride;
+        d.lists = outputs ? f_l : b_l;
         d.sums = sums; d.mirror_sums = nullptr;
         d.ptr = ptr;
         d.run_start = run_start; d.seg_out = seg;
@@ -1572,7 +1682,6 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         if (self && !b_lists) sides.s[counted - 1].mirror_sums = b_ptr;
         else counted = n_sides;
     }
-    if (count_only) sides.s[0].n_hits = nullptr;
     const int64_t most_tiles = want_bwd && nt_i > nt_o ? nt_i : nt_o;
     if (most_tiles > 0) {
         int64_t per_block = most_tiles * counted / COUNT_BLOCKS;
