@@ -701,6 +701,10 @@ inline int64_t blocks_of_tiles(int64_t n_tiles)
 // the device, so that the three reads that depend on each other (centre, length, list) are on their way two, one and one tile
 // ahead: bound by their latency otherwise (three sides of 1 M points with 32 neighbours: 236 us, one tile per block).
 constexpr int COUNT_THREADS = 8 * TILE;
+// Without lists (2^24 points and more, most calls with the smallest workspace) this pass and the next search, one wave per centre:
+// sixteen waves per tile, as the latency of a search wants company (20 000 -> 5 000 points, 23 neighbours, 27 cells, smallest workspace:
+// the build 104 us with eight waves here and four in the next pass, so 62).
+constexpr int SEARCH_THREADS = 1024;
 constexpr int64_t COUNT_BLOCKS = 2048;                     // blocks wanted before a block takes more tiles
 constexpr int COUNT_COLS = 32, COUNT_PITCH = COUNT_COLS + 1;
 constexpr int COUNT_TILES = 16;                            // at most that many tiles per block, whose sums are written together
@@ -708,7 +712,7 @@ constexpr size_t count_lds_bytes(int K, bool mirror) { return (size_t)K * (COUNT
 typedef uint32_t list_words __attribute__((ext_vector_type(4), aligned(4)));     // (a list may start at any word)
 
 template <bool EXT>
-__global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides, int K, int tiles_per_block, const uint32_t *__restrict__ err)
+__global__ __launch_bounds__(SEARCH_THREADS, 8) void tile_count(const Sides sides, int K, int tiles_per_block, const uint32_t *__restrict__ err)
 {
     extern __shared__ uint32_t tbl[];                      // [K][COUNT_PITCH] and [K][COUNT_TILES], each twice with mirror_sums
     __shared__ uint32_t searched[2];                       // tile's parity: a centre of it has no list
@@ -717,14 +721,15 @@ __global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides
     const int64_t t1 = t0 + tiles_per_block < s.n_tiles ? t0 + tiles_per_block : s.n_tiles;
     if (*err || t0 >= t1) return;                          // block-uniform: the grid's offsets are not to be trusted
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr int PITCH = COUNT_PITCH, WAVES = COUNT_THREADS / 64;
+    constexpr int PITCH = COUNT_PITCH;
+    const int threads = blockDim.x, waves = threads >> 6;
     const bool mirror = s.mirror_sums != nullptr;
     uint32_t *tbl2 = tbl + K * PITCH, *col = tbl + (tid & 31);
     uint32_t *sums = tbl + K * PITCH * (mirror ? 2 : 1), *sums2 = sums + K * COUNT_TILES;
     const int al = tid >> 3, l = tid & 7;
     auto centre_of = [&](int64_t tile) -> int32_t {        // -1: none
         const int64_t slot = tile * TILE + al;
-        return tile < t1 && slot < s.n_centres ? (s.perm ? s.perm[slot] : (int32_t)slot) : -1;
+        return al < TILE && tile < t1 && slot < s.n_centres ? (s.perm ? s.perm[slot] : (int32_t)slot) : -1;
     };
     auto found_of = [&](int32_t c) -> uint32_t { return c >= 0 && s.lists.hits ? s.lists.found[c] : 0u; };
     auto words_of = [&](size_t list, uint32_t n, uint32_t e) -> list_words {
@@ -736,7 +741,7 @@ __global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides
     int32_t c_now = centre_of(t0), c_next = centre_of(t0 + 1), c_after = centre_of(t0 + 2);
     uint32_t f_now = found_of(c_now), f_next = found_of(c_next);
     list_words w_now = ahead_of(c_now, f_now);
-    for (int i = tid; i < K * PITCH * (mirror ? 2 : 1); i += COUNT_THREADS) tbl[i] = 0u;
+    for (int i = tid; i < K * PITCH * (mirror ? 2 : 1); i += threads) tbl[i] = 0u;
     if (tid < 2) searched[tid] = 0u;
     lds_barrier();
     for (int64_t tile = t0; tile < t1; ++tile) {
@@ -766,7 +771,7 @@ __global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides
         if (tid == 0) searched[(tile + 1) & 1] = 0u;       // (read before the last barrier, written behind the next)
         if (searched[tile & 1]) {                          // (block-uniform)
             // centres without a list: searched, one wave per centre
-            for (int a = wave; a < TILE; a += WAVES) {
+            for (int a = wave; a < TILE; a += waves) {
                 const int64_t slot = tile * TILE + a;
                 if (slot >= s.n_centres) break;            // wave-uniform
                 const int64_t c = s.perm ? (int64_t)s.perm[slot] : slot;
@@ -787,7 +792,7 @@ __global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides
             }
             lds_barrier();
         }
-        for (int i = tid; i < 4 * K; i += COUNT_THREADS) { // four threads per cell, which also clear its counters
+        for (int i = tid; i < 4 * K; i += threads) { // four threads per cell, which also clear its counters
             const int k = i >> 2;
             auto row_sum = [&](uint32_t *row) -> uint32_t {
                 uint32_t v = 0u;
@@ -808,7 +813,7 @@ __global__ __launch_bounds__(COUNT_THREADS, 8) void tile_count(const Sides sides
         c_next = c_after; f_next = f_after;
         c_after = c_third;
     }
-    for (int i = tid; i < K * COUNT_TILES; i += COUNT_THREADS) {
+    for (int i = tid; i < K * COUNT_TILES; i += threads) {
         const int64_t tile = t0 + i % COUNT_TILES, at = (int64_t)(i / COUNT_TILES) * s.n_tiles + tile;
         if (tile < t1) {
             s.sums[at] = sums[i];
@@ -1692,8 +1697,11 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
             if ((rc = raise_lds_limit(ext ? reinterpret_cast<const void *>(&tile_count<true>) : reinterpret_cast<const void *>(&tile_count<false>),
                                       lds)) != PCPP_OK)
                 return rc;
-        if (ext) tile_count<true><<<grid, COUNT_THREADS, lds, stream>>>(sides, K, (int)per_block, err);
-        else tile_count<false><<<grid, COUNT_THREADS, lds, stream>>>(sides, K, (int)per_block, err);
+        int threads = COUNT_THREADS;
+        for (int i = 0; i < counted; ++i)
+            if (!sides.s[i].lists.hits) threads = SEARCH_THREADS;
+        if (ext) tile_count<true><<<grid, threads, lds, stream>>>(sides, K, (int)per_block, err);
+        else tile_count<false><<<grid, threads, lds, stream>>>(sides, K, (int)per_block, err);
         PCPP_HIP_CHECK(hipGetLastError());
     }
     if ((rc = scan_exclusive_u32_jobs(jobs, n_sides, err, stream)) != PCPP_OK) return rc;
@@ -1736,7 +1744,9 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     }
     for (int from = 0; from < n_sides;) {
         // sides whose tiles ask for blocks of one size go in one launch (capacities are on the generous side)
-        auto shape_of = [&](const Side &d) { return fill_shape(K, ceil_div(capacity, d.n_tiles > 0 ? d.n_tiles : 1) * 2 / 3); };
+        auto shape_of = [&](const Side &d) {
+            return d.lists.hits ? fill_shape(K, ceil_div(capacity, d.n_tiles > 0 ? d.n_tiles : 1) * 2 / 3) : fill_shape_of(K, SEARCH_THREADS);
+        };
         FillShape shape = shape_of(sides.s[from]);
         Sides part{};
         int n = 0;
