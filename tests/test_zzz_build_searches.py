@@ -129,3 +129,35 @@ def test_workspaces_of_every_size(n, n_out, t):
             assert np.array_equal(a.cpu().numpy(), b)
         first = plan if first is None else first
         assert torch.equal(first[256:], plan[256:])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,n_out", [(0, 0), (0, 70), (70, 0), (1, 1), (64, 64), (2896, 2896), (2897, 2897), (8192, 1024), (700, 8256), (17_000, 17_000), (17_000, 4_032)])
+@pytest.mark.parametrize("mode,t", [("ball", 1), ("ball", 3), ("batched", 2), ("voxel", 3), ("voxel", 1)])
+def test_count_only(n, n_out, mode, t):
+    """The number of triplets, with the smallest workspace, into pageable and pinned memory."""
+    import ctypes
+    import paper_2511_23227_amd as m
+    from paper_2511_23227_amd import binding as B
+    L = m.library()
+    p = _uneven(n, n + t) if n else np.zeros((0, 3), np.float32)
+    same = n == n_out
+    q = p if same else _uneven(n_out, n) if n_out else np.zeros((0, 3), np.float32)
+    size = np.float32(0.02 if mode == "voxel" else 0.04)
+    cuts = ocuts = None
+    if mode == "batched":
+        cuts, ocuts = np.array([0, n // 3, n], np.int32), np.array([0, n_out // 3, n_out], np.int32)
+    want = len(oracle.build_triplets_general(p, q, size, t, mode=oracle.MODE_VOXEL if mode == "voxel" else oracle.MODE_BALL,
+                                             in_offsets=cuts, out_offsets=ocuts)[0]) if n and n_out else 0
+    d = torch.from_numpy(p).cuda()
+    dq = d if same else torch.from_numpy(q).cuda()
+    off = torch.from_numpy(cuts).cuda() if cuts is not None else None
+    oo = off if same else torch.from_numpy(ocuts).cuda() if cuts is not None else None
+    ws = torch.full((L.pcpp_build_triplets_workspace_bytes(n, n_out, t),), 255, dtype=torch.uint8, device="cuda")
+    word = torch.full((1,), -1, dtype=torch.int64, pin_memory=True)
+    pinned = ctypes.cast(word.data_ptr(), ctypes.POINTER(ctypes.c_int64))
+    for target in (ctypes.pointer(ctypes.c_int64(-1)), pinned):
+        rc = L.pcpp_build_triplets_batched(B._ptr(d), n, B._ptr(dq), n_out, B._ptr(off), B._ptr(oo), 2 if cuts is not None else 1,
+                                           float(size), t, None, None, None, 0, None, target, None, 0,
+                                           m.BUILD_VOXEL if mode == "voxel" else 0, B._ptr(ws), ws.numel(), B._stream())
+        assert rc == 0 and target[0] == want, (L.pcpp_last_error(), target[0], want)
