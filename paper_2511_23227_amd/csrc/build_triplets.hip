@@ -634,6 +634,7 @@ struct Side {
     uint32_t *sums, *mirror_sums;
     const uint32_t *ptr;
     uint32_t *run_start;          // [n_tiles][K][TILE], NULL: not wanted
+    unsigned long long *rows;     // [n_tiles][mask_words(K)], which rows of run_start are written (NULL: all)
     int64_t *seg_out;             // [K + 1], NULL: not wanted
     FillOut out;
 };
@@ -896,10 +897,17 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, i
     // scene, 125 cells: six rows in ten).  In index order nearly all cells hold one, and a kernel that need not look at the
     // tiles' bounds starts sooner (64 -> 128 strided layer: 1 %).
     const int64_t pair = tile & ~(int64_t)1, pair_end = pair + 2 < s.n_tiles ? pair + 2 : s.n_tiles;
-    for (int k = tid; k < K; k += threads) {
-        const uint32_t *ptr = s.ptr + (size_t)k * s.n_tiles;
-        first[k] = ptr[tile];
-        read[k] = !s.perm || ptr[pair] != ptr[pair_end];
+    for (int k0 = 64 * wave; k0 < K; k0 += threads) {
+        const int k = k0 + lane;
+        bool wanted = false;
+        if (k < K) {
+            const uint32_t *ptr = s.ptr + (size_t)k * s.n_tiles;
+            first[k] = ptr[tile];
+            wanted = !s.rows || ptr[pair] != ptr[pair_end];
+            read[k] = wanted;
+        }
+        const unsigned long long mask = __ballot(wanted);
+        if (s.rows && lane == 0) s.rows[tile * mask_words(K) + (k0 >> 6)] = mask;
     }
     if (wave == 0) tc.open(s, tile, lane);
     lds_barrier();
@@ -1390,6 +1398,8 @@ PlanLayout plan_layout(int64_t n_in, int64_t n_out, int K, int64_t n_triplets, i
         if (spatial) off += align_up((size_t)(n_centres > 0 ? n_centres : 1) * 4);
         s.tile_ptr_off = off;  off += align_up((size_t)(K * s.n_tiles + 1) * 4);
         s.run_start_off = off; off += align_up((size_t)(s.n_tiles > 0 ? s.n_tiles : 1) * K * TILE * 4);
+        s.rows_off = off;
+        if (spatial) off += align_up((size_t)(s.n_tiles > 0 ? s.n_tiles : 1) * mask_words(K) * 8);
         if (with_gather) s.gather_index = p.n_tail++;
     };
     if (flags & PCPP_PLAN_FWD) side(p.fwd, n_out, spatial);
@@ -1700,7 +1710,7 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     ScanJob jobs[MAX_SIDES] = {};
     int n_sides = 0;
     auto add_side = [&](bool outputs, const int32_t *perm, uint32_t *sums, uint32_t *ptr, int which, unsigned long long *total64,
-                        uint32_t *run_start, int64_t *seg, const FillOut &out) {
+                        uint32_t *run_start, unsigned long long *rows, int64_t *seg, const FillOut &out) {
         Side &d = sides.s[n_sides];
         d.centres = outputs ? out_xyz : in_xyz;
         d.perm = perm;
@@ -1711,21 +1721,22 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         d.lists = outputs ? f_l : b_l;
         d.sums = sums; d.mirror_sums = nullptr;
         d.ptr = ptr;
-        d.run_start = run_start; d.seg_out = seg;
+        d.run_start = run_start; d.rows = rows; d.seg_out = seg;
         d.out = out;
         jobs[n_sides++] = ScanJob{sums, ptr, (int64_t)K * d.n_tiles, scan_scratch(which), total64};
     };
     // (the sums of a plan's side lie in its own offset table, which the prefix sum replaces in place)
     uint32_t *f_ptr = want_plan ? words(pb, pl.fwd.tile_ptr_off) : nullptr, *b_ptr = want_bwd ? words(pb, pl.bwd.tile_ptr_off) : nullptr;
+    auto rows_of = [&](const SideLayout &l) { return spatial ? reinterpret_cast<unsigned long long *>(pb + l.rows_off) : nullptr; };
     uint32_t *pub_ptr = want_plan && !spatial ? f_ptr : words(ws, bs.fwd_ptr_off);
     add_side(true, nullptr, pub_ptr, pub_ptr, SCAN_PUBLIC, total_dev, want_plan && !spatial ? words(pb, pl.fwd.run_start_off) : nullptr,
-             nt_o == 0 ? nullptr : seg_offsets, FillOut{tri_o, tri_i, tri_k, nullptr, -1, tri_cap});
+             nullptr, nt_o == 0 ? nullptr : seg_offsets, FillOut{tri_o, tri_i, tri_k, nullptr, -1, tri_cap});
     if (spatial)
-        add_side(true, perm_o, f_ptr, f_ptr, SCAN_FWD_SIDE, nullptr, words(pb, pl.fwd.run_start_off), nullptr,
+        add_side(true, perm_o, f_ptr, f_ptr, SCAN_FWD_SIDE, nullptr, words(pb, pl.fwd.run_start_off), rows_of(pl.fwd), nullptr,
                  FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.fwd.gather_index, tail_cap});
     int counted = n_sides;
     if (want_bwd) {
-        add_side(false, perm_i, b_ptr, b_ptr, SCAN_BWD_SIDE, nullptr, words(pb, pl.bwd.run_start_off), nullptr,
+        add_side(false, perm_i, b_ptr, b_ptr, SCAN_BWD_SIDE, nullptr, words(pb, pl.bwd.run_start_off), rows_of(pl.bwd), nullptr,
                  FillOut{nullptr, nullptr, nullptr, pb + pl.tail_off, pl.bwd.gather_index, tail_cap});
         // without lists one search counts both sides of a cloud against itself (same tiles on both)
         if (self && !b_lists) sides.s[counted - 1].mirror_sums = b_ptr;

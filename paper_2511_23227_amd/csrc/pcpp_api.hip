@@ -113,6 +113,7 @@ PlanSideView side_view(const void *plan, const SideLayout &s, bool spatial)
     v.run_start = reinterpret_cast<const uint32_t *>(pb + s.run_start_off);
     v.gather = s.gather_index >= 0 ? reinterpret_cast<const int32_t *>(pb + s.gather_off) : nullptr;
     v.perm = spatial ? reinterpret_cast<const int32_t *>(pb + s.perm_off) : nullptr;
+    v.rows = spatial ? reinterpret_cast<const unsigned long long *>(pb + s.rows_off) : nullptr;
     v.n_tiles = s.n_tiles;
     return v;
 }

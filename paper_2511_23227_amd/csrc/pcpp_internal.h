@@ -40,6 +40,7 @@ constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 //                                          the next slot's run starts (for a = TILE-1: at the end of
 //                                          the (k, tile) run).  Spatial plans: the row of a cell that has no
 //                                          triplet in the tiles 2 j and 2 j + 1 is not written for either
+//   rows      uint64 [n_tiles][mask_words(K)]  (spatial plans only) bit k: the row of run_start is written
 //   gather    int32  [|T|]                 source row of each triplet in (k, slot, source) order, bit 31 set on
 //                                          the last triplet of a (k, slot) run.  The input-gradient side always has
 //                                          one; the forward side has one in spatial plans and otherwise gathers
@@ -51,6 +52,7 @@ struct SideLayout {
     size_t perm_off = 0;
     size_t tile_ptr_off = 0;
     size_t run_start_off = 0;
+    size_t rows_off = 0;
     int gather_index = -1;       // position among the |T|-sized arrays, -1: none
     size_t gather_off = 0;       // = tail_off + gather_index * align_up(n_triplets * 4)
 };
@@ -67,11 +69,14 @@ constexpr int PLAN_FLAG_MASK = PCPP_PLAN_FWD | PCPP_PLAN_BWD_INPUT | PCPP_PLAN_S
 constexpr uint32_t GATHER_LAST = 0x80000000u;     // flag on the last triplet of a run in a plan's gather array
 constexpr uint32_t GATHER_INDEX = 0x7fffffffu;
 
+constexpr int mask_words(int K) { return (K + 63) / 64; }
+
 PlanLayout plan_layout(int64_t n_in, int64_t n_out, int K, int64_t n_triplets, int flags);
 
 struct PlanSideView {
     const uint32_t *tile_ptr;
     const uint32_t *run_start;
+    const unsigned long long *rows;   // NULL: all rows of run_start are written
     const int32_t *gather;     // NULL when the side gathers through tri_i
     const int32_t *perm;       // NULL when slots are centre indices
     int64_t n_tiles;
