@@ -1209,7 +1209,7 @@ struct BuildScratch {
     size_t scan_off;                 // status words of the prefix sums: N_SCANS regions of scan_stride bytes
     size_t scan_stride;
     size_t fwd_ptr_off, bwd_ptr_off; // per-(k, tile) sums; of the public list, their offsets
-    size_t fwd_tbl_off, bwd_tbl_off; // K words per centre of a tile: neighbour lists in the smallest workspace
+    size_t fwd_tbl_off = 0, bwd_tbl_off = 0;         // K words per centre of a tile: neighbour lists in the smallest workspace
     size_t sort_off;                 // scratch of the spatial sorts
     size_t end;                      // what a call needs
     // The centres' neighbour lists.  How many neighbours each has lies where the grids kept their points' places.
@@ -1253,7 +1253,7 @@ constexpr int64_t LIST_SLACK = 4;        // words that a read of four words may 
 constexpr int64_t long_units_for(int64_t capacity) { return (capacity + capacity / 8) / LONG_UNIT + 1; }
 static_assert(8 * (int64_t)LONG_UNIT <= MIN_STRIDE, "the lengths and the unused words of long lists are an eighth at most");
 
-BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K)
+BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K, bool tables = true)
 {
     BuildScratch b;
     b.grid_in = grid_scratch(0, n_in);
@@ -1270,9 +1270,11 @@ BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K)
     b.scan_stride = scan_scratch_bytes(scan_n);
     b.scan_off = off;    off += N_SCANS * b.scan_stride;
     b.fwd_ptr_off = off; off += align_up((size_t)(K * nt_o + 1) * 4);
-    b.fwd_tbl_off = off; off += align_up((size_t)(nt_o > 0 ? nt_o : 1) * K * TILE * 4);
+    b.fwd_tbl_off = off;
+    if (tables) off += align_up((size_t)(nt_o > 0 ? nt_o : 1) * K * TILE * 4);
     b.bwd_ptr_off = off; off += align_up((size_t)(K * nt_i + 1) * 4);
-    b.bwd_tbl_off = off; off += align_up((size_t)(nt_i > 0 ? nt_i : 1) * K * TILE * 4);
+    b.bwd_tbl_off = off;
+    if (tables) off += align_up((size_t)(nt_i > 0 ? nt_i : 1) * K * TILE * 4);
     b.sort_off = off;    off += spatial_order_scratch_bytes(n_max);
     b.end = off;
     b.end_with_lists = off;
@@ -1281,11 +1283,11 @@ BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K)
     return b;
 }
 
-// Lists with a stride of at most `most` words behind `end`, and room for the longer ones: all neighbours that a call has room for, or
+// Lists with a stride of at most `most` words in place of the tables, and room for the longer ones: all neighbours that a call has room for, or
 // without a grid all candidates of each centre (whose blocks have no counter yet that they could share the room by).
 BuildScratch build_scratch_with_lists(int64_t n_in, int64_t n_out, int K, int64_t capacity, int64_t most, bool grid)
 {
-    BuildScratch b = build_scratch(n_in, n_out, K);
+    BuildScratch b = build_scratch(n_in, n_out, K, false);
     b.grid = grid;
     auto side = [&](BuildScratch::SideLists &l, int64_t n_centres, int64_t n_candidates) {
         if (n_centres <= 0) return;
@@ -1297,11 +1299,13 @@ BuildScratch build_scratch_with_lists(int64_t n_in, int64_t n_out, int K, int64_
     };
     side(b.fwd, n_out, n_in);
     side(b.bwd, n_in, n_out);
+    b.end = build_scratch(n_in, n_out, K).end;             // (no call does with less)
+    if (b.end_with_lists < b.end) b.end_with_lists = b.end;
     return b;
 }
 
-// The scratch of a call whose workspace has `bytes` bytes: as long lists as fit, behind `end` or inside the tables of the
-// smallest workspace; a side whose neighbours have no room there does without.
+// The scratch of a call whose workspace has `bytes` bytes: as long lists as fit, or lists inside the tables of
+// the smallest workspace; a side whose neighbours have no room there does without.
 BuildScratch build_scratch_within(int64_t n_in, int64_t n_out, int K, int64_t capacity, size_t bytes)
 {
     BuildScratch b = build_scratch(n_in, n_out, K);
