@@ -344,9 +344,11 @@ constexpr uint32_t HIT_INDEX_MASK = (1u << HIT_INDEX_BITS) - 1u;
 
 // The neighbour lists of one side's centres.  found[c] says how many neighbours centre c has, up to `stride`, whose list lies at
 // c stride; or, with LONG_LIST set, where its list lies behind those, in units of LONG_UNIT words and behind a word that says how many
-// there are.  The search hands out that room where it finds a list that is too long.  Only a call with more triplets than it has room
-// for runs out of it, and what matters then is that the triplets are counted: such a centre has NO_LIST and the count searches it again.
-constexpr uint32_t LONG_LIST = 0x80000000u, NO_LIST = 0xffffffffu, LONG_UNIT = 4;
+// there are.  The search hands out that room where it finds a list that is too long.  A centre that finds none left has its number with
+// NO_LIST set, and the passes search it again: in the smallest workspace, or when there are more triplets than the call has room for.
+constexpr uint32_t LONG_LIST = 0x80000000u, NO_LIST = 0xc0000000u, LONG_UNIT = 4;
+__device__ inline bool has_no_list(uint32_t f) { return (f & NO_LIST) == NO_LIST; }
+__device__ inline bool has_long_list(uint32_t f) { return (f & NO_LIST) == LONG_LIST; }
 struct Lists {
     uint32_t *hits;               // cell << 24 | index, in arrival order; NULL: no lists at all
     uint32_t *found;              // [n_centres]; without lists the count pass writes the numbers, or a search that only counts
@@ -380,7 +382,7 @@ struct SearchArgs {
     Lists lists;
     uint32_t *mirror;
     unsigned long long long_units;       // room for lists longer than the stride
-    unsigned long long *long_used;       // how much of it has been handed out; without a grid every centre has its own, for all candidates
+    unsigned long long *long_used;       // how much of it has been handed out (NULL: every centre has its own, for all candidates)
     int per_wave;
     uint32_t *err;
     unsigned long long *clear_from;      // without a grid: what its clearing kernel would have cleared
@@ -496,8 +498,8 @@ __global__ __launch_bounds__(256, 6) void search_cells(const SearchArgs a)
         uint32_t found = filled_of;
         if (mine && a.lists.hits && filled_of > a.lists.stride) {
             const uint32_t units = (filled_of + LONG_UNIT) / LONG_UNIT;          // (its length in front)
-            const unsigned long long from = atomicAdd(a.long_used, (unsigned long long)units);
-            found = NO_LIST;
+            const unsigned long long from = a.long_units ? atomicAdd(a.long_used, (unsigned long long)units) : 0ull;
+            found = filled_of | NO_LIST;
             if (from + units <= a.long_units) {
                 found = (uint32_t)from | LONG_LIST;
                 store_length<FORM>(a, a.lists.long_at(found), filled_of);
@@ -505,7 +507,7 @@ __global__ __launch_bounds__(256, 6) void search_cells(const SearchArgs a)
             }
         }
         if (mine) a.lists.found[index] = found;
-        open = __ballot(mine && (found & LONG_LIST) && found != NO_LIST);
+        open = __ballot(mine && has_long_list(found));
         if (!open) break;
     }
 }
@@ -544,7 +546,7 @@ __global__ __launch_bounds__(256) void search_all(const SearchArgs a)
     // once over the candidates, and once more if the list turned out to be a long one
     uint32_t filled = 0;
     bool is_long = false;
-    const uint32_t long_units = ((uint32_t)a.g.n + LONG_UNIT) / LONG_UNIT, long_of = (uint32_t)index * long_units;
+    uint32_t long_of = 0;
     for (bool again = false;; again = true) {
         const size_t row = again ? a.lists.long_at(long_of) + 1 : (size_t)index * a.lists.stride;
         const uint32_t limit = again ? 0xffffffffu : a.lists.stride;
@@ -596,9 +598,24 @@ __global__ __launch_bounds__(256) void search_all(const SearchArgs a)
             }
         }
         if (again) break;
-        is_long = on && a.lists.hits && filled > a.lists.stride;      // (wave-uniform)
+        // (wave-uniform, as the numbers are)
+        const bool past = on && a.lists.hits && filled > a.lists.stride;
+        uint32_t found = filled;
+        if (past && !a.long_used) {
+            long_of = (uint32_t)index * (((uint32_t)a.g.n + LONG_UNIT) / LONG_UNIT);
+            is_long = true;
+        } else if (past) {
+            const uint32_t units = (filled + LONG_UNIT) / LONG_UNIT;
+            unsigned long long from = 0ull;
+            if (lane == 0) from = atomicAdd(a.long_used, (unsigned long long)units);
+            from = __shfl(from, 0, 64);
+            is_long = from + units <= a.long_units;
+            long_of = (uint32_t)from;
+            found = filled | NO_LIST;
+        }
+        if (is_long) found = long_of | LONG_LIST;
         if (on && lane == 0) {
-            a.lists.found[index] = is_long ? long_of | LONG_LIST : filled;
+            a.lists.found[index] = found;
             if (is_long) store_length<FORM>(a, a.lists.long_at(long_of), filled);
         }
         if (a.g.n > ALL_CHUNK ? !__syncthreads_or(is_long) : !is_long) break;
@@ -646,6 +663,7 @@ struct TileCentres {
     uint32_t off[TILE + 1];       // neighbours of the centres before each
     int32_t at[TILE];             // its own index
     uint32_t found[TILE];
+    uint32_t searched;            // centres without a list: whether there are any
 
     __device__ inline uint32_t n(int al) const { return off[al + 1] - off[al]; }
     // by wave 0; a barrier follows
@@ -654,12 +672,16 @@ struct TileCentres {
         const int64_t slot = tile * TILE + lane;
         const bool on = slot < s.n_centres;
         const int32_t c = on ? (s.perm ? s.perm[slot] : (int32_t)slot) : 0;
-        const uint32_t f = on ? s.lists.found[c] : 0u, m = !(f & LONG_LIST) ? f : f != NO_LIST ? s.lists.hits[s.lists.long_at(f)] : 0u;
+        const uint32_t f = on ? s.lists.found[c] : 0u;
+        uint32_t m = f & LONG_LIST ? f & ~NO_LIST : f;
+        if (has_long_list(f)) m = s.lists.hits[s.lists.long_at(f)];
+        const unsigned long long none = __ballot(on && (!s.lists.hits || has_no_list(f)));
         const uint32_t incl = wave_incl_scan_u32(m);
         at[lane] = c;
         found[lane] = f;
         off[lane] = incl - m;
         if (lane == TILE - 1) off[TILE] = incl;
+        if (lane == 0) searched = none != 0ull;
     }
     // the centre that a neighbour of the tile belongs to, for a thread that goes through consecutive ones
     struct Cursor { int al; uint32_t end; };
@@ -702,9 +724,11 @@ inline int64_t blocks_of_tiles(int64_t n_tiles)
 // the device, so that the three reads that depend on each other (centre, length, list) are on their way two, one and one tile
 // ahead: bound by their latency otherwise (three sides of 1 M points with 32 neighbours: 236 us, one tile per block).
 constexpr int COUNT_THREADS = 8 * TILE;
-// Without lists (2^24 points and more, most calls with the smallest workspace) this pass and the next search, one wave per centre:
-// sixteen waves per tile, as the latency of a search wants company (20 000 -> 5 000 points, 23 neighbours, 27 cells, smallest workspace:
-// the build 104 us with eight waves here and four in the next pass, so 62).
+// Without lists (2^24 points and more, most calls with the smallest workspace) this pass and the next search, one wave per centre.  The
+// latency of a search wants company: with few tiles sixteen waves per tile (20 000 -> 5 000 points, 23 neighbours, 27 cells, smallest
+// workspace: the build 104 us with eight waves here and four in the next pass, so 62); with many there is enough, and small
+// blocks wait less (250 000 points, 21 neighbours: 486 us, with sixteen waves 551).
+constexpr int64_t MANY_TILES = 2048;
 constexpr int SEARCH_THREADS = 1024;
 constexpr int64_t COUNT_BLOCKS = 2048;                     // blocks wanted before a block takes more tiles
 constexpr int COUNT_COLS = 32, COUNT_PITCH = COUNT_COLS + 1;
@@ -754,7 +778,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void tile_count(const Sides side
         list_words w = w_now;
         if (f_now & LONG_LIST) {
             n = 0u;
-            if (f_now != NO_LIST) {
+            if (has_long_list(f_now)) {
                 list = s.lists.long_at(f_now) + 1;
                 n = s.lists.hits[list - 1];
                 w = words_of(list, n, 4u * l);
@@ -767,7 +791,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void tile_count(const Sides side
             e += 32u;
             if (e < n) w = words_of(list, n, e);
         }
-        if (c_now >= 0 && (!s.lists.hits || f_now == NO_LIST)) searched[tile & 1] = 1u;
+        if (c_now >= 0 && (!s.lists.hits || has_no_list(f_now))) searched[tile & 1] = 1u;
         lds_barrier();
         if (tid == 0) searched[(tile + 1) & 1] = 0u;       // (read before the last barrier, written behind the next)
         if (searched[tile & 1]) {                          // (block-uniform)
@@ -776,7 +800,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void tile_count(const Sides side
                 const int64_t slot = tile * TILE + a;
                 if (slot >= s.n_centres) break;            // wave-uniform
                 const int64_t c = s.perm ? (int64_t)s.perm[slot] : slot;
-                if (s.lists.hits && (uint32_t)__builtin_amdgcn_readfirstlane((int)s.lists.found[c]) != NO_LIST) continue;
+                if (s.lists.hits && !has_no_list((uint32_t)__builtin_amdgcn_readfirstlane((int)s.lists.found[c]))) continue;
                 Candidates<EXT> cand;
                 cand.open(s.centres, c, s.g, s.q, lane);
                 uint32_t found = 0;
@@ -952,10 +976,10 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, i
             continue;
         }
         const uint32_t n = lane_value(upto, c1 - 1) - before;
-        // ---- without lists: searched again, one wave per centre, left in the list for the threads that take them -------------
-        if (!s.lists.hits) {                               // (block-uniform)
+        // ---- neighbours without a list: searched again, one wave per centre, left in the list for the threads that take them --
+        if (tc.searched) {                                 // (block-uniform)
             for (int al = c0 + wave; al < c1; al += n_waves) {
-                if (__builtin_amdgcn_readfirstlane((int)tc.n(al)) == 0) continue;
+                if (__builtin_amdgcn_readfirstlane((int)(tc.n(al) == 0u || (s.lists.hits && !has_no_list(tc.found[al]))))) continue;
                 const int lane = here(tid & 63);
                 Candidates<EXT> cand;
                 cand.open(s.centres, tc.at[al], s.g, s.q, lane);
@@ -987,10 +1011,14 @@ __global__ __launch_bounds__(1024, 8) void tile_fill(const Sides sides, int K, i
                     const uint32_t p = p0 + before + j;
                     tc.advance(c, p);
                     at_of[j] = (uint32_t)c.al << 8;
-                    if (s.lists.hits) {
-                        const uint32_t first = tc.off[c.al];
-                        size_t at = (size_t)tc.at[c.al] * s.lists.stride;
-                        if (c.end - first > s.lists.stride) at = s.lists.long_at(tc.found[c.al]) + 1;
+                    const uint32_t first = tc.off[c.al];
+                    size_t at = (size_t)tc.at[c.al] * s.lists.stride;
+                    bool listed = c.end - first <= s.lists.stride;
+                    if (!listed && has_long_list(tc.found[c.al])) {
+                        at = s.lists.long_at(tc.found[c.al]) + 1;
+                        listed = true;
+                    }
+                    if (listed) {
                         b_of[j] = s.lists.hits[at + (p - first)];
                     } else {
                         b_of[j] = list[p0 + j];
@@ -1221,6 +1249,7 @@ struct BuildScratch {
     };
     SideLists fwd, bwd;
     bool grid = true;
+    bool own_rows = false;           // without a grid: room for all candidates of each centre
     size_t end_with_lists;
 };
 
@@ -1248,6 +1277,7 @@ uint32_t hit_stride_for(int64_t capacity, int64_t n_centres, int64_t most)
     return (uint32_t)s;
 }
 
+constexpr int64_t LARGE_CLOUD = 1 << 16;
 constexpr int64_t LIST_SLACK = 4;        // words that a read of four words may take past the last list
 // Room for the long lists of a call with `capacity` triplets, in units: a list of n > 32 words takes at most (n + 4) / 4.
 constexpr int64_t long_units_for(int64_t capacity) { return (capacity + capacity / 8) / LONG_UNIT + 1; }
@@ -1283,18 +1313,19 @@ BuildScratch build_scratch(int64_t n_in, int64_t n_out, int K, bool tables = tru
     return b;
 }
 
-// Lists with a stride of at most `most` words in place of the tables, and room for the longer ones: all neighbours that a call has room for, or
-// without a grid all candidates of each centre (whose blocks have no counter yet that they could share the room by).
-BuildScratch build_scratch_with_lists(int64_t n_in, int64_t n_out, int K, int64_t capacity, int64_t most, bool grid)
+// Lists with a stride of at most `most` words in place of the tables, and room for the longer ones: for all neighbours that a call
+// has room for, or (own_rows) for all candidates of each centre, which needs no counter that a launch in front would have to clear.
+BuildScratch build_scratch_with_lists(int64_t n_in, int64_t n_out, int K, int64_t capacity, int64_t most, bool own_rows)
 {
     BuildScratch b = build_scratch(n_in, n_out, K, false);
-    b.grid = grid;
+    b.grid = !small_clouds(n_in, n_out);
+    b.own_rows = own_rows;
     auto side = [&](BuildScratch::SideLists &l, int64_t n_centres, int64_t n_candidates) {
+        l.hits_off = b.end_with_lists;
         if (n_centres <= 0) return;
         l.stride = hit_stride_for(capacity, n_centres, most);
         l.on = l.stride > 0;
-        l.long_units = l.stride >= n_candidates ? 0 : grid ? long_units_for(capacity) : n_centres * ((n_candidates + LONG_UNIT) / LONG_UNIT);
-        l.hits_off = b.end_with_lists;
+        l.long_units = l.stride >= n_candidates ? 0 : own_rows ? n_centres * ((n_candidates + LONG_UNIT) / LONG_UNIT) : long_units_for(capacity);
         b.end_with_lists += align_up((size_t)(n_centres * l.stride + l.long_units * LONG_UNIT + LIST_SLACK) * 4);
     };
     side(b.fwd, n_out, n_in);
@@ -1304,34 +1335,53 @@ BuildScratch build_scratch_with_lists(int64_t n_in, int64_t n_out, int K, int64_
     return b;
 }
 
+// Whether most centres of an even cloud have no more than `stride` neighbours: long lists cost a second search, and the counter of
+// their room takes one wave after the other (400 000 centres: 1000 us).
+bool enough_for_most(int64_t stride, int64_t capacity, int64_t n_centres) { return 4 * stride >= 5 * ceil_div(capacity, n_centres); }
+
 // The scratch of a call whose workspace has `bytes` bytes: as long lists as fit, or lists inside the tables of
 // the smallest workspace; a side whose neighbours have no room there does without.
 BuildScratch build_scratch_within(int64_t n_in, int64_t n_out, int K, int64_t capacity, size_t bytes)
 {
     BuildScratch b = build_scratch(n_in, n_out, K);
-    // stored hits carry the candidate index in HIT_INDEX_BITS bits; places among the long lists take 32
+    // stored hits carry the candidate index in HIT_INDEX_BITS bits; places among the long lists take 30
     if (capacity <= 0 || n_in >= (1 << HIT_INDEX_BITS) || n_out >= (1 << HIT_INDEX_BITS)) return b;
     if (capacity > INT32_MAX) capacity = INT32_MAX;
-    if (small_clouds(n_in, n_out)) {
-        const BuildScratch l = build_scratch_with_lists(n_in, n_out, K, capacity, KEEP_MAX, false);
+    const bool small = small_clouds(n_in, n_out);
+    if (small) {
+        const BuildScratch l = build_scratch_with_lists(n_in, n_out, K, capacity, KEEP_MAX, true);
         if (bytes >= l.end_with_lists) return l;
     }
     for (int64_t most = KEEP_MAX; most >= 32; most /= 2) {
-        const BuildScratch l = build_scratch_with_lists(n_in, n_out, K, capacity, most, true);
+        const BuildScratch l = build_scratch_with_lists(n_in, n_out, K, capacity, most, false);
+        if (most < KEEP_MAX && ((n_out > 0 && !enough_for_most(l.fwd.stride, capacity, n_out)) || (n_in > 0 && !enough_for_most(l.bwd.stride, capacity, n_in))))
+            break;
         if (bytes >= l.end_with_lists) return l;
     }
-    auto side = [&](BuildScratch::SideLists &l, int64_t n_centres, size_t table) {
-        const int64_t room = ceil_div(n_centres, TILE) * TILE * K - LIST_SLACK - long_units_for(capacity) * LONG_UNIT;
-        if (n_centres <= 0 || room < 0) return;
-        const int64_t stride = hit_stride_for(capacity, n_centres, KEEP_MAX), fits = room / n_centres;
-        if (fits < stride) return;         // (most lists would be long ones, and the counter of their room takes one wave after the other)
+    // Inside the tables.  Without a grid a centre without a list costs a search of all candidates in each pass, so that there must be room
+    // for every list; with one, three quarters of the room are for the lists of the stride.  Large clouds, where the passes that
+    // search wait less, gain from whatever has a list (400 000 points with 24 neighbours, 27 cells, one side: 1062 us without, 673 so).
+    auto side = [&](BuildScratch::SideLists &l, int64_t n_centres, size_t table, bool whole) -> bool {
+        if (n_centres <= 0) return true;
+        const int64_t room = ceil_div(n_centres, TILE) * TILE * K - LIST_SLACK, mean = ceil_div(capacity, n_centres);
+        int64_t stride = whole ? (room - long_units_for(capacity) * LONG_UNIT) / n_centres : room / n_centres * 3 / 4;
+        if (stride > 2 * mean) stride = 2 * mean;
+        const bool most = stride > 0 && enough_for_most(stride, capacity, n_centres), some = !whole && n_centres >= LARGE_CLOUD && K >= 27;
+        if (!most && !some) return false;
+        if (!most) stride = room / n_centres;
         l.on = true;
         l.stride = (uint32_t)stride;
-        l.long_units = long_units_for(capacity);
+        l.long_units = most ? (room - n_centres * stride) / LONG_UNIT : 0;
         l.hits_off = table;
+        return true;
     };
-    side(b.fwd, n_out, b.fwd_tbl_off);
-    side(b.bwd, n_in, b.bwd_tbl_off);
+    if (small && side(b.fwd, n_out, b.fwd_tbl_off, true) && side(b.bwd, n_in, b.bwd_tbl_off, true)) {
+        b.grid = false;
+        return b;
+    }
+    b.fwd.on = b.bwd.on = false;
+    side(b.fwd, n_out, b.fwd_tbl_off, false);
+    side(b.bwd, n_in, b.bwd_tbl_off, false);
     return b;
 }
 
@@ -1339,7 +1389,7 @@ BuildScratch build_scratch_within(int64_t n_in, int64_t n_out, int K, int64_t ca
 size_t build_bytes_for(int64_t n_in, int64_t n_out, int K, int64_t capacity)
 {
     if (capacity <= 0 || n_in >= (1 << HIT_INDEX_BITS) || n_out >= (1 << HIT_INDEX_BITS)) return build_scratch(n_in, n_out, K).end;
-    return build_scratch_with_lists(n_in, n_out, K, capacity < INT32_MAX ? capacity : INT32_MAX, KEEP_MAX, !small_clouds(n_in, n_out)).end_with_lists;
+    return build_scratch_with_lists(n_in, n_out, K, capacity < INT32_MAX ? capacity : INT32_MAX, KEEP_MAX, small_clouds(n_in, n_out)).end_with_lists;
 }
 
 // scan_scratch: the status words of this grid's prefix sum.  clear_words > 0: the first grid of a build, whose
@@ -1587,6 +1637,8 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     // the error word, the total and all status words (contiguous) start at zero: the clearing kernel of the first grid sees to it
     auto *clear_from = reinterpret_cast<unsigned long long *>(ws + bs.err_off);
     const int64_t clear_words = (int64_t)((512 + N_SCANS * bs.scan_stride) / sizeof(unsigned long long));
+    const bool clear_first = no_grid && !count_only && !bs.own_rows;       // (its blocks share a counter)
+    if (clear_first && (rc = fill_u64(clear_from, 0ull, clear_words, stream)) != PCPP_OK) return rc;
     if (!no_grid)
         if ((rc = build_grid(in_xyz, n_in, gm, in_batch_offsets, n_batches, ws, bs.grid_in, scan_scratch(SCAN_GRID_IN), clear_from,
                              clear_words, err, &grid_in, stream)) != PCPP_OK)
@@ -1652,7 +1704,7 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
         while (per_wave < 32 && n / (2 * per_wave) >= SEARCH_WAVES) per_wave *= 2;
         const bool in = form == INPUTS;
         const SearchArgs sa{order, centres, n, g, qp, in ? b_l : f_l, b_l.hits, (unsigned long long)(in ? bs.bwd : bs.fwd).long_units,
-                            long_used + (in ? 1 : 0), per_wave, err, clear_from, in ? 0 : clear_words};
+                            no_grid && bs.own_rows ? nullptr : long_used + (in ? 1 : 0), per_wave, err, clear_from, in || clear_first ? 0 : clear_words};
         const size_t lds = no_grid ? (size_t)(g.n < ALL_CHUNK ? g.n : ALL_CHUNK) * 3 * sizeof(float) : 0;
         auto pick = [&](auto cells, auto cells_ext, auto all, auto all_ext) { return no_grid ? (ext ? all_ext : all) : (ext ? cells_ext : cells); };
         auto kern = form == BOTH ? pick(search_cells<BOTH, false>, search_cells<BOTH, true>, search_all<BOTH, false>, search_all<BOTH, true>)
@@ -1758,7 +1810,7 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
                 return rc;
         int threads = COUNT_THREADS;
         for (int i = 0; i < counted; ++i)
-            if (!sides.s[i].lists.hits) threads = SEARCH_THREADS;
+            if (!sides.s[i].lists.hits && sides.s[i].n_tiles < MANY_TILES) threads = SEARCH_THREADS;
         if (ext) tile_count<true><<<grid, threads, lds, stream>>>(sides, K, (int)per_block, err);
         else tile_count<false><<<grid, threads, lds, stream>>>(sides, K, (int)per_block, err);
         PCPP_HIP_CHECK(hipGetLastError());
@@ -1772,7 +1824,7 @@ int pcpp_build_triplets_batched(const float *in_xyz, int64_t n_in, const float *
     for (int from = 0; from < n_sides;) {
         // sides whose tiles ask for blocks of one size go in one launch (capacities are on the generous side)
         auto shape_of = [&](const Side &d) {
-            return d.lists.hits ? fill_shape(K, ceil_div(capacity, d.n_tiles > 0 ? d.n_tiles : 1) * 2 / 3) : fill_shape_of(K, SEARCH_THREADS);
+            return d.lists.hits || d.n_tiles >= MANY_TILES ? fill_shape(K, ceil_div(capacity, d.n_tiles > 0 ? d.n_tiles : 1) * 2 / 3) : fill_shape_of(K, SEARCH_THREADS);
         };
         FillShape shape = shape_of(sides.s[from]);
         Sides part{};
