@@ -9,7 +9,8 @@ pcpp_mvmr_bwd_weight.  The headline workload is the largest scene (scene 5: 1M p
 per second with and without the triplet build, the roofline of the forward op (algorithmic bytes over the
 HBM peak for the gather-bound layers, nominal flops 2 |T| C_in C_out over the bf16 matrix-core peak for the
 256 -> 256 layer) and the CPU oracle timed on a bounded sample (cpu_baseline).
-One JSON line is printed.
+One JSON line is printed, short enough for a log's tail; `--details FILE` writes every op's roofline, the other scenes' full
+records and the variants to a file.
 """
 from __future__ import annotations
 
@@ -412,6 +413,23 @@ def measure_variants(steps: int, warmup: int) -> dict:
     return out
 
 
+ROOFLINE_KEYS = ("op", "ms", "bound", "achieved", "peak", "unit", "frac", "traffic", "algorithmic_bytes", "compulsory_floor_ms")
+
+
+def one_line(result: dict) -> dict:
+    """What the printed line holds of the full record: the headline whole, of everything else the figures without their notes."""
+    line = {k: v for k, v in result.items() if k not in ("roofline", "roofline_top_op", "roofline_per_op", "scenes", "variants",
+                                                         "cpu_baseline", "plan_order_tuner", "op_ms_median", "op_ms_min")}
+    line["roofline"] = {k: result["roofline"][k] for k in ROOFLINE_KEYS if k in (result["roofline"] or {})} or None
+    line["roofline_frac"] = {op: r["frac"] for op, r in result["roofline_per_op"].items()}
+    line["scenes"] = {name: {"value": r["value"], "value_with_build": r["value_with_build"], "op_ms": r["op_ms"],
+                             "roofline_frac": {op: q["frac"] for op, q in r["roofline_per_op"].items()}}
+                      for name, r in result["scenes"].items()}
+    if "cpu_baseline" in result:
+        line["cpu_baseline"] = {k: result["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind") if k in result["cpu_baseline"]}
+    return line
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -429,6 +447,7 @@ def main() -> int:
     ap.add_argument("--copy-calibration", action="store_true",
                     help="run only a 256 MiB device-to-device copy (the kernel of known size against which the "
                          "FETCH_SIZE / WRITE_SIZE counters are scaled) and exit")
+    ap.add_argument("--details", metavar="FILE", help="write the full record of all scenes, ops and variants there")
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
         print("bench.py: this build is single-GPU only (the paper's operator is a one-GPU kernel); "
@@ -540,7 +559,11 @@ def main() -> int:
     for key in ("cpu_baseline", "plan_order_tuner"):
         if key in head:
             result[key] = head[key]
-    print(json.dumps(result))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(result, f, indent=1)
+            f.write("\n")
+    print(json.dumps(one_line(result)))
     return 0
 
 
