@@ -61,8 +61,8 @@ extern "C" {
                                     triplet arrays, every result and every tolerance are unchanged; the build
                                     takes about twice as long. */
 /* testing aids, accepted in plan_flags by pcpp_build_triplets only; results are identical with or without */
-#define PCPP_BUILD_TEST_SHORT_LISTS  0x100  /* keep at most 40 neighbours of a centre on chip: longer lists take
-                                               the path that ranks by scanning the candidates again          */
+#define PCPP_BUILD_TEST_SHORT_LISTS  0x100  /* order at most 40 neighbours at a time on chip: tiles in many parts, and
+                                               centres with more are ranked by scanning the candidates again */
 #define PCPP_BUILD_TEST_WIDE_KEYS    0x200  /* treat cell and index as too wide to share one 32-bit word, as for
                                                clouds of 2^24 points or more                                  */
 

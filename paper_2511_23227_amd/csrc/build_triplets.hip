@@ -365,8 +365,9 @@ struct Lists {
 // A wave takes `per_wave` consecutive centres of `order`, which holds the centres grouped by grid cell (without it: in index
 // order), and those of one cell together: the stencil is probed and the candidates are read, placed and converted once for
 // all of them, 256 at a time in registers, and a centre costs its binary64 tests, the cells of its neighbours and the stores.
-// Bound by instruction issue.  One search per centre, in the order of the tiles and with the tiles' tables in LDS: 1 M points
-// of a ground scene, 32 neighbours in 125 cells, 1215 us; now 325.
+// The vector ALU issues in 84 % of the cycles (1 M points of a ground scene, 32 neighbours in 125 cells, shuffled); the candidates, whose
+// cells the hash scatters, come from memory, 1.7 GB of them.  One search per centre, in the order of the tiles and with the tiles'
+// tables in LDS: 1215 us; now 325.
 // Centres with a long list are searched a second time here, where they still share their candidates, and not by the later passes, one
 // wave per centre: 20 000 points with a quarter of them in a blob, two sides, 2.9 M triplets, the build with both further
 // searches 457 us, so 241; without a grid 2896 points, one side, 350 and 66.
@@ -721,8 +722,9 @@ inline int64_t blocks_of_tiles(int64_t n_tiles)
 // ---- pass 1: neighbours per (cell, tile) ----------------------------------------------------------
 // Eight lanes read a centre's list, four words each at a time.  Consecutive neighbours often fall in one cell, so that every
 // lane of a half wave has a column of counters of its own.  A block takes several consecutive tiles where there are enough for
-// the device, so that the three reads that depend on each other (centre, length, list) are on their way two, one and one tile
-// ahead: bound by their latency otherwise (three sides of 1 M points with 32 neighbours: 236 us, one tile per block).
+// the device, so that the sums of its tiles lie side by side in its stores: one tile per block stored six million words one by one
+// (three sides of 1 M points with 32 neighbours: 236 us, so 155).  The three reads that depend on each other (centre, length, list)
+// are on their way two, one and one tile ahead, as a block has no other to wait beside (with one tile per block that changed nothing).
 constexpr int COUNT_THREADS = 8 * TILE;
 // Without lists (2^24 points and more, most calls with the smallest workspace) this pass and the next search, one wave per centre.  The
 // latency of a search wants company: with few tiles sixteen waves per tile (20 000 -> 5 000 points, 23 neighbours, 27 cells, smallest
@@ -856,8 +858,8 @@ __global__ __launch_bounds__(SEARCH_THREADS, 8) void tile_count(const Sides side
 // centres at a time.
 //   LDS: [K][FILL_PITCH] runs, two centres to a word (a list has fewer than 2^16 places); [K] first triplet of the tile (or of
 //   its part) in cell k; [K] how many there are; [K] where they start in the list; [K] whether run_start wants the row; the list: candidate index, (cell | centre << 8)
-// What bounds it: the vector instructions (about 100 per 64 neighbours) and, where K is large, the table and its way to memory
-// (1 M points, 125 cells, three sides: 660 us; 766 with every row of run_start written).
+// With 125 cells the vector ALU issues in 70 % of the cycles and 2 GB pass at 2.9 TB/s (1 M points, three sides: 660 us); a fifth of
+// the vector instructions less changed nothing, the rows of run_start that nobody reads left out took 766 to 660.
 constexpr int FILL_PITCH = TILE / 2 + 1;  // (a half wave works on one centre, i.e. one column)
 constexpr int FILL_ROUNDS = 8;           // places of the list per thread
 constexpr size_t fill_table_bytes(int K) { return (size_t)K * (FILL_PITCH + 4) * sizeof(uint32_t); }

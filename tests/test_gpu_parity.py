@@ -171,8 +171,8 @@ def test_dense_cluster_uses_rescan_path(pcpp):
 
 
 def test_wide_key_path(pcpp):
-    """Lists of more than 160 neighbours when cell and index do not share a word (as for clouds of 2^24 points):
-    per-cell buckets filled with wave ballots.  Same triplets and same plan as the packed-key path."""
+    """When cell and index do not share a word (as for clouds of 2^24 points) there are no neighbour lists, and both passes
+    search, here for centres with up to a few hundred neighbours.  Same triplets and same plan as with lists."""
     rng = np.random.default_rng(5)
     p = np.concatenate([rng.normal(0.5, 0.02, (900, 3)), rng.uniform(0, 1, (600, 3))]).astype(np.float32)
     r, t = 0.05, 5

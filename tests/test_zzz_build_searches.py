@@ -161,3 +161,29 @@ def test_count_only(n, n_out, mode, t):
                                            float(size), t, None, None, None, 0, None, target, None, 0,
                                            m.BUILD_VOXEL if mode == "voxel" else 0, B._ptr(ws), ws.numel(), B._stream())
         assert rc == 0 and target[0] == want, (L.pcpp_last_error(), target[0], want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("spatial", [False, True])
+@pytest.mark.parametrize("blob,sparse,t", [(3000, 3000, 1), (3000, 3000, 3), (4300, 1000, 1), (4300, 1000, 3)])
+def test_centres_past_the_list_of_a_small_block(blob, sparse, t, spatial):
+    """Few outputs inside a blob and many in sparse surroundings: the fill takes blocks of 256 or 512 threads, whose list holds 2048
+    or 4096 neighbours, and each output in the blob has more; in other tiles nothing of the kind."""
+    import paper_2511_23227_amd as m
+    rng = np.random.default_rng(blob + t)
+    p = np.concatenate([rng.uniform(0.0, 0.05, (blob, 3)), rng.uniform(-1.0, 1.0, (5000, 3))]).astype(np.float32)
+    q = np.concatenate([p[rng.choice(blob, 20, replace=False)], rng.uniform(-1.0, 1.0, (sparse, 3)).astype(np.float32)])
+    q = np.concatenate([q[20:720], q[:20], q[720:]])                 # the twenty in one tile, or in two
+    r = np.float32(0.1)
+    ref = oracle.build_triplets(p, q, r, t)
+    of = np.bincount(ref[0], minlength=len(q))
+    load = len(ref[0]) / (len(q) / 64) * 2 / 3
+    assert (of > (2048 if blob == 3000 else 4096)).sum() >= 20 and (load < 2000 if blob == 3000 else 2200 < load < 4000)
+    flags = m.PLAN_FWD | m.PLAN_BWD_INPUT | (m.PLAN_SPATIAL if spatial else 0)
+    plans = []
+    for test in (0, m.BUILD_TEST_SHORT_LISTS):
+        plans.append(_plan(m, len(p), len(q), t, len(ref[0]), flags))
+        T = m.pcpp_build_triplets(torch.from_numpy(p).cuda(), torch.from_numpy(q).cuda(), float(r), t, plan_flags=flags | test,
+                                  capacity=len(ref[0]), buffers={"plan": plans[-1]})
+        _same(T, ref)
+    assert torch.equal(plans[0][256:], plans[1][256:])

@@ -44,8 +44,8 @@ def test_tiles_past_the_list(n, n_out, t, what, spatial):
 @pytest.mark.parametrize("spatial,same", [(False, True), (False, False), (True, True), (True, False)])
 @pytest.mark.parametrize("t", [2, 3, 5])
 def test_workspace_between_the_sizes(t, spatial, same, batched):
-    """Neighbour lists as long as the workspace has room for: none (8 cells), inside the per-centre tables (26 and 124 words),
-    shorter than the capacity asks for, and as long.  Centres with more neighbours are searched again: the same list and plan."""
+    """Neighbour lists as the workspace has room for: none, inside the tables of the smallest, with shorter strides, as long as the
+    capacity asks for; what has no list is searched again: the same triplets and plan."""
     import ctypes
     import paper_2511_23227_amd as m
     from paper_2511_23227_amd import binding as B
