@@ -1327,7 +1327,8 @@ BuildScratch build_scratch_with_lists(int64_t n_in, int64_t n_out, int K, int64_
         if (n_centres <= 0) return;
         l.stride = hit_stride_for(capacity, n_centres, most);
         l.on = l.stride > 0;
-        l.long_units = l.stride >= n_candidates ? 0 : own_rows ? n_centres * ((n_candidates + LONG_UNIT) / LONG_UNIT) : long_units_for(capacity);
+        const int64_t all = n_centres * ((n_candidates + LONG_UNIT) / LONG_UNIT), needed = long_units_for(capacity);
+        l.long_units = l.stride >= n_candidates ? 0 : own_rows || all < needed ? all : needed;
         b.end_with_lists += align_up((size_t)(n_centres * l.stride + l.long_units * LONG_UNIT + LIST_SLACK) * 4);
     };
     side(b.fwd, n_out, n_in);
