@@ -25,8 +25,8 @@
 // these cuts add up (relative errors with one accumulator, apart, and of fp32 sums on the vector ALUs, all values positive:
 // 256 -> 256 fp32, 1.5 M triplets, 8.9e-6, 4.2e-7, 1.06e-6; 512 -> 256 bf16 with 270 neighbours 2.1e-6, 6.4e-7, 1.6e-6).
 // What bounds it: with 32 to 64 channels in fp32 the vector instructions, most of which split rows and sums into terms (32 ->
-// 32: issued in 73 % of the cycles), in bf16 the latency of the rows (a 64 -> 64 layer of 17 M triplets moves 2.2 GB of them through
-// L1 and L2 in 153 us, 0.58 L1 accesses per cycle and CU, matrix pipe 12 %); with more channels W's way from L2.  Layers whose channel counts are no power of two, which the vector ALUs had served before: 20 -> 36 fp32, 0.49 M
+// 32: issued in 73 % of the cycles), in bf16 the rows' way through the L1 caches (a 64 -> 64 layer of 17 M triplets moves 2.2 GB of
+// them in 141 us, 0.71 L1 accesses per cycle and CU, matrix pipe 13 %); with more channels W's way from L2.  Layers whose channel counts are no power of two, which the vector ALUs had served before: 20 -> 36 fp32, 0.49 M
 // triplets, 29 us (349); 128 -> 128 bf16, 0.97 M triplets, 130 us (7938).
 // Every destination row is written once, by one block: no atomics, fixed summation order.
 //
@@ -470,54 +470,77 @@ int launch_tile(const TileArgs &t, hipStream_t stream)
     return PCPP_OK;
 }
 
-// Which form, by measurement over layers of 16 .. 256 channels and 2 000 .. 300 000 points (times in us).  A cell is crowded
+// Which form, by measurement over layers of 16 .. 256 channels and 2 000 .. 400 000 points (times in us).  A cell is crowded
 // when it has more than 48 triplets per 32 centres on average, i.e. more than a window and a half.
-//   - small clouds: split over eight waves and 16 centres per block, so that there are enough waves.  2048 points, 16 -> 16
-//     fp32: 8.4, four waves 10.5, 32 centres 12.1, cooperative 27.  8000 points, 64 -> 64 bf16: 12.2 / 13.2 / 14.5 / 29.
+//   - small clouds: split over more waves and 16 centres per block while all waves fit on the device at once (2 to 5 per SIMD by
+//     the registers of the form; a second round costs more than the longer chains of fewer waves).
+//     Up to 64 destination channels, 8192 centres (fp32: 6144): eight waves.  2048 points, 16 -> 16 fp32: 8.4, four waves 10.5, 32
+//     centres 12.1, cooperative 27.  8000 points, 64 -> 64 bf16: 12.2 / 13.2 / 14.5 / 29.  Four waves up to 12288 centres in fp32 and,
+//     with more than one chunk of rows or eight lanes to a row, exact bf16: 8000 points, 64 -> 64 fp32 36.4 -> 30.6 (eight waves
+//     before), 12 000 points, 20 -> 36 fp32 35.1 -> 29.8, 128 -> 64 with 125 cells in bf16 100.9 -> 83.7 (32 centres before).
+//     65 .. 128 channels: eight waves, up to 4096 centres 16 per block, up to 8192 32.  2000 points, 128 -> 128 bf16 39.8 -> 26.7; 4000
+//     points, 64 -> 128 fp32 46.2 -> 30.5; 8000 points 47.7 -> 37.7 (four waves, 32 centres before; at 12 000 points 59.1, eight 65.6).
 //   - exact sums, up to 128 destination channels: split over four waves, 32 centres, since the terms of a sum would take three
 //     times the LDS (40 000 points, 128 -> 128 bf16: 130 per direction; cooperative, 16 centres per wave, about 165)
 //     fp32, 17 .. 32 destination channels, more than 65536 centres with up to 16 neighbours: 64 centres, which fill a window
 //     better (32 -> 32, 200 000 points with 10 neighbours: 120, 32 centres 132; 100 000 with 13.5: 74, 78; with 24: 90, 86;
 //     24 000 with 14.5, too few blocks: 28.6, 24.6).
 //   - rounded sums, up to 64: the same (strided layer's input gradient, 128 -> 64: 253, 16 centres 346, cooperative 312).
-//     Crowded 64-wide layers: cooperative, 16 centres per wave, which fill their windows and read W a quarter as often (115 000 points with
-//     148 neighbours, 64 -> 64: 153, split 163 .. 174).
-//   - rounded sums to 65 .. 128 channels: split up to 32768 centres, crowded: over two waves (25 000 points with 368 neighbours,
-//     64 -> 128: 52, four waves 61); above, cooperative, 32 centres per wave, crowded: 16 (strided layer, 64 -> 128: 97, split
-//     107).
+//     Crowded: 16 centres, which fill their windows, over two waves, or four where the cloud is too small to fill the device with
+//     that (64 -> 64, cooperative with 16 centres per wave / four waves / two: 115 000 points with 148 neighbours 162 / 145 / 141 and in
+//     spatial order 178 / 146 / 143; 57 600 with 74 71 / 57 / 54; 150 000 with 48 in spatial order 152 / 143 / 128; 40 000 with 50
+//     61 / 53 / 57; 10 000 with 50 41 / 19 / 24).  Two chunks of rows (128 -> 64) need more than 80 triplets per 32 centres for it:
+//     25 000 points with 100 neighbours 113 / 78 / 78 (32 centres 88), 60 000 with 60 135 / 142 / 145 (127).
+//   - rounded sums to 65 .. 128 channels: split up to 32768 centres, crowded from 16384 on: over two waves (25 000 points with 368
+//     neighbours, 64 -> 128: 52, four waves 61; 12 500 points with 80: 46, 37); above, cooperative, 32 centres per wave, crowded: 16
+//     (strided layer, 64 -> 128: 97, split 107).
 //   - wider: cooperative, so that W is read once per 64 centres; 32 centres per wave (100 000 points, 125 cells, 128 -> 256 with
 //     rounded sums: 777; 16 centres 958, split 864), 16 where the exact bf16 sums of 32 would leave a CU one block, and in crowded
 //     layers with rounded sums (115 000 points with 148 neighbours, 256 -> 256: 907 in spatial order and 860 in index order,
 //     32 centres 1102 and 1026; 100 000 points with 24 neighbours, not crowded: 673, 32 centres 618).
+template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NW>
+int launch_tile_split(const TileArgs &t, hipStream_t stream)
+{
+    if constexpr (EXACT) {                               // (layers with rounded sums have four tiles or more)
+        if (t.ndt == 1) return launch_tile<F32, EXACT, RL, NARROW, GA, 1, NW, 1, 1, true>(t, stream);
+        if (t.ndt == 2) return launch_tile<F32, EXACT, RL, NARROW, GA, 1, NW, 1, 2, true>(t, stream);
+    }
+    return launch_tile<F32, EXACT, RL, NARROW, GA, 1, NW, 1, 4, true>(t, stream);
+}
+
 template <bool F32, bool EXACT, int RL, bool NARROW>
 int launch_tile_form(const TileArgs &t, hipStream_t stream)
 {
-    if (t.n_centres <= 8192 && t.ndt <= 4) {
-        if constexpr (EXACT) {                           // (layers with rounded sums have four tiles or more)
-            if (t.ndt == 1) return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 1, true>(t, stream);
-            if (t.ndt == 2) return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 2, true>(t, stream);
-        }
-        return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 4, true>(t, stream);
+    if (t.ndt <= 4) {
+        if (t.n_centres <= (F32 ? 6144 : 8192)) return launch_tile_split<F32, EXACT, RL, NARROW, 1, 8>(t, stream);
+        if constexpr (EXACT && (F32 || RL == 8))
+            if (t.n_centres <= 12288) return launch_tile_split<F32, EXACT, RL, NARROW, 1, 4>(t, stream);
+    } else if (t.ndt <= 8) {
+        if (t.n_centres <= 4096) return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 8, true>(t, stream);
+        if (t.n_centres <= 8192) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 8, 1, 8, true>(t, stream);
     }
-    const bool crowded = (int64_t)(t.gather_bytes / 4) * 32 > 48 * t.n_centres * (int64_t)t.K;
-    [[maybe_unused]] const bool few = t.n_centres > 65536 && (int64_t)(t.gather_bytes / 4) <= 16 * t.n_centres;
+    const int64_t per_cell = t.n_centres * (int64_t)t.K, triplets = (int64_t)(t.gather_bytes / 4);
+    const bool crowded = triplets * 32 > 48 * per_cell;
     if constexpr (EXACT) {
-        if (t.ndt == 1) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 1, true>(t, stream);
         if constexpr (F32)
-            if (t.ndt == 2 && few) return launch_tile<F32, EXACT, RL, NARROW, 4, 1, 4, 1, 2, true>(t, stream);
-        if (t.ndt == 2) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 2, true>(t, stream);
-        if (t.ndt <= 4) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
+            if (t.ndt == 2 && t.n_centres > 65536 && triplets <= 16 * t.n_centres)
+                return launch_tile<F32, EXACT, RL, NARROW, 4, 1, 4, 1, 2, true>(t, stream);
+        if (t.ndt <= 4) return launch_tile_split<F32, EXACT, RL, NARROW, 2, 4>(t, stream);
         if (t.ndt <= 8) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
         if constexpr (F32) return launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 4, false>(t, stream);
         else return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false, true>(t, stream)
                             : launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false>(t, stream);
     } else {
-        if (t.ndt <= 4) return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 1, false>(t, stream)
-                                       : launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
+        if (t.ndt <= 4) {
+            if (t.n_chunks == 1 ? !crowded : triplets * 32 <= 80 * per_cell)
+                return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
+            return t.n_centres > 49152 ? launch_tile<F32, EXACT, RL, NARROW, 1, 1, 2, 1, 4, true>(t, stream)
+                                       : launch_tile<F32, EXACT, RL, NARROW, 1, 1, 4, 1, 4, true>(t, stream);
+        }
         if (t.ndt <= 8) {
             if (t.n_centres <= 32768)
-                return crowded ? launch_tile<F32, EXACT, RL, NARROW, 2, 1, 2, 1, 8, true>(t, stream)
-                               : launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
+                return crowded && t.n_centres > 16384 ? launch_tile<F32, EXACT, RL, NARROW, 2, 1, 2, 1, 8, true>(t, stream)
+                                                      : launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
             return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 2, false>(t, stream)
                            : launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 2, false>(t, stream);
         }

@@ -1,0 +1,45 @@
+"""The forms of the rows kernel for any channel counts, either side of the lines between them: number of centres, triplets per
+cell, channels.  Forward and input gradient against the oracle, on a cloud with a crowded corner (runs longer than a window of
+32 triplets) whose last tile and last group of sixteen centres are not full."""
+import numpy as np
+import pytest
+import torch
+
+import scenes
+from parity_util import TOL, assert_close, oracle_bwd_input, oracle_fwd
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,cin,cout,dt,t,neighbours", [
+    # eight waves, 16 and 32 centres per block, up to 128 destination channels
+    (4091, 72, 100, "bf16", 2, 6), (4097, 72, 100, "bf16", 2, 6), (8179, 40, 72, "f32", 2, 6), (8193, 40, 72, "f32", 2, 6),
+    (4091, 64, 128, "bf16", 2, 6), (4097, 64, 128, "bf16", 2, 6),
+    # up to 64: eight waves, four waves, 32 centres
+    (6143, 20, 36, "f32", 2, 6), (6145, 20, 36, "f32", 2, 6), (12283, 16, 16, "f32", 1, 4), (12289, 16, 16, "f32", 1, 4),
+    (8193, 72, 40, "bf16", 2, 6), (12289, 72, 40, "bf16", 1, 4), (9001, 24, 40, "bf16", 2, 6),
+    # rounded sums, crowded cells: four waves, two waves; two chunks of rows
+    (8193, 64, 64, "bf16", 1, 6), (49153, 64, 64, "bf16", 1, 4), (8193, 128, 64, "bf16", 1, 2.2), (8193, 128, 64, "bf16", 1, 6),
+    (16391, 64, 128, "bf16", 1, 6), (16379, 64, 128, "bf16", 1, 6),
+])
+def test_forms_of_the_tile_kernel(n, cin, cout, dt, t, neighbours):
+    import paper_2511_23227_amd as pcpp
+    rng = np.random.default_rng(n * 31 + cin)
+    p = rng.uniform(0, 1, (n, 3)).astype(np.float32)
+    r = float(np.float32((neighbours / n / (4.0 / 3.0 * np.pi)) ** (1 / 3)))
+    p[:150] = (p[0] * 0.8 + 0.1) + rng.uniform(-0.5, 0.5, (150, 3)).astype(np.float32) * np.float32(r)
+    K = t ** 3
+    d = torch.from_numpy(p).cuda()
+    T = pcpp.pcpp_build_triplets(d, d, r, t, plan_flags=pcpp.PLAN_FWD | pcpp.PLAN_BWD_INPUT)
+    o, i, k = (a.cpu().numpy() for a in (T.tri_o, T.tri_i, T.tri_k))
+    x = rng.standard_normal((n, cin)).astype(np.float32)
+    w = (rng.standard_normal((K, cout, cin)) / np.sqrt(K * cin)).astype(np.float32)
+    dy = rng.standard_normal((n, cout)).astype(np.float32)
+    tdt = torch.float32
+    if dt == "bf16":
+        x, w, dy, tdt = scenes.round_to_bf16(x), scenes.round_to_bf16(w), scenes.round_to_bf16(dy), torch.bfloat16
+    dev = lambda a: torch.from_numpy(a).cuda().to(tdt)
+    ref, scale = oracle_fwd(x, w, o, i, k, n)
+    assert_close(pcpp.pcpp_mvmr_fwd(dev(x), dev(w), T).cpu().numpy(), ref, scale, TOL[dt], "fwd")
+    ref, scale = oracle_bwd_input(dy, w, o, i, k, n)
+    assert_close(pcpp.pcpp_mvmr_bwd_input(dev(dy), dev(w), T).cpu().numpy(), ref, scale, TOL[dt], "bwd_input")
