@@ -464,9 +464,11 @@ __global__ __launch_bounds__(PC_THREADS) void rows_pc_kernel(const void *__restr
 // 94 000 with 25 in 8 cells: 273, 243).  The average does not tell the two apart, so the line gives up 3 to 15 % of the one for a
 // factor of three of the other; below it this kernel is the faster one on even clouds by more (50 000 points with 60 neighbours:
 // 409, 362).
+// So do small clouds, whose blocks of 128 centres leave most of the device idle (27 cells, 24 neighbours, the kernel here and the
+// tile kernel: 2000 points 117 and 39 us, 5000 122 and 65, 12 000 118 .. 127 and 105 .. 122; 30 000 123 .. 132 and 201 .. 231).
 bool mvmr_rows_pc_usable(const MvmrArgs &a)
 {
-    return a.n_triplets > 0 && a.n_triplets <= 3 * a.n_centres * (int64_t)a.K && a.in_dtype == PCPP_BF16 && a.c_src == 256 && a.c_dst == 256 && a.side.gather != nullptr &&
+    return a.n_triplets > 0 && a.n_centres > 10240 && a.n_triplets <= 3 * a.n_centres * (int64_t)a.K && a.in_dtype == PCPP_BF16 && a.c_src == 256 && a.c_dst == 256 && a.side.gather != nullptr &&
            (size_t)a.n_src * a.c_src * 2 <= MAX_BUFFER_BYTES;
 }
 

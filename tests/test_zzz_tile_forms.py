@@ -21,8 +21,15 @@ pytestmark = pytest.mark.gpu
     # rounded sums, crowded cells: four waves, two waves; two chunks of rows
     (8193, 64, 64, "bf16", 1, 6), (49153, 64, 64, "bf16", 1, 4), (8193, 128, 64, "bf16", 1, 2.2), (8193, 128, 64, "bf16", 1, 6),
     (16391, 64, 128, "bf16", 1, 6), (16379, 64, 128, "bf16", 1, 6),
+    # more than 128 destination channels: eight waves with 16 centres, four and eight with 32, cooperative
+    (3067, 32, 136, "bf16", 2, 6), (3073, 32, 136, "bf16", 2, 6), (6145, 32, 136, "bf16", 2, 6), (12289, 32, 136, "bf16", 1, 4),
+    (3067, 24, 140, "f32", 2, 6), (6139, 24, 140, "f32", 2, 6), (12283, 24, 140, "f32", 1, 4), (2049, 16, 264, "f32", 2, 6),
+    (3067, 256, 256, "bf16", 2, 6), (6139, 256, 256, "bf16", 2, 6), (12289, 256, 256, "bf16", 1, 4),
+    # 256 -> 256 in spatial order: tile kernel, producer and consumer waves
+    (10235, 256, 256, "bf16", -2, 6), (10241, 256, 256, "bf16", -2, 6), (10305, 256, 256, "bf16", -1, 2.2),
 ])
 def test_forms_of_the_tile_kernel(n, cin, cout, dt, t, neighbours):
+    spatial, t = t < 0, abs(t)
     import paper_2511_23227_amd as pcpp
     rng = np.random.default_rng(n * 31 + cin)
     p = rng.uniform(0, 1, (n, 3)).astype(np.float32)
@@ -30,7 +37,7 @@ def test_forms_of_the_tile_kernel(n, cin, cout, dt, t, neighbours):
     p[:150] = (p[0] * 0.8 + 0.1) + rng.uniform(-0.5, 0.5, (150, 3)).astype(np.float32) * np.float32(r)
     K = t ** 3
     d = torch.from_numpy(p).cuda()
-    T = pcpp.pcpp_build_triplets(d, d, r, t, plan_flags=pcpp.PLAN_FWD | pcpp.PLAN_BWD_INPUT)
+    T = pcpp.pcpp_build_triplets(d, d, r, t, plan_flags=pcpp.PLAN_FWD | pcpp.PLAN_BWD_INPUT | (pcpp.PLAN_SPATIAL if spatial else 0))
     o, i, k = (a.cpu().numpy() for a in (T.tri_o, T.tri_i, T.tri_k))
     x = rng.standard_normal((n, cin)).astype(np.float32)
     w = (rng.standard_normal((K, cout, cin)) / np.sqrt(K * cin)).astype(np.float32)
