@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import scenes
-from parity_util import TOL, assert_close, oracle_bwd_input, oracle_fwd
+from parity_util import TOL, assert_close, oracle_bwd_input, oracle_bwd_weight, oracle_fwd
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +50,20 @@ def test_forms_of_the_tile_kernel(n, cin, cout, dt, t, neighbours):
     assert_close(pcpp.pcpp_mvmr_fwd(dev(x), dev(w), T).cpu().numpy(), ref, scale, TOL[dt], "fwd")
     ref, scale = oracle_bwd_input(dy, w, o, i, k, n)
     assert_close(pcpp.pcpp_mvmr_bwd_input(dev(dy), dev(w), T).cpu().numpy(), ref, scale, TOL[dt], "bwd_input")
+
+
+@pytest.mark.parametrize("n,neighbours,cin,cout", [(20011, 27, 72, 100), (20011, 33, 72, 100), (30011, 36, 40, 72), (30011, 44, 72, 40), (257, 6, 136, 72)])
+def test_sub_blocks_of_the_weight_gradient(n, neighbours, cin, cout):
+    """bf16, either side of the numbers of triplets up to which sub-blocks have 64 x 64 channels."""
+    import paper_2511_23227_amd as pcpp
+    rng = np.random.default_rng(n + cin)
+    p = rng.uniform(0, 1, (n, 3)).astype(np.float32)
+    r = float(np.float32((neighbours / n / (4.0 / 3.0 * np.pi)) ** (1 / 3)))
+    d = torch.from_numpy(p).cuda()
+    T = pcpp.pcpp_build_triplets(d, d, r, 2)
+    o, i, k = (a.cpu().numpy() for a in (T.tri_o, T.tri_i, T.tri_k))
+    x = scenes.round_to_bf16(rng.standard_normal((n, cin)).astype(np.float32))
+    dy = scenes.round_to_bf16(rng.standard_normal((n, cout)).astype(np.float32))
+    dev = lambda a: torch.from_numpy(a).cuda().bfloat16()
+    ref, scale = oracle_bwd_weight(x, dy, o, i, k, 8)
+    assert_close(pcpp.pcpp_mvmr_bwd_weight(dev(x), dev(dy), T).cpu().numpy(), ref, scale, TOL["bf16"], f"bwd_weight {len(o)} triplets")
