@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     # rounded sums, crowded cells: four waves, two waves; two chunks of rows
     (8193, 64, 64, "bf16", 1, 6), (49153, 64, 64, "bf16", 1, 4), (8193, 128, 64, "bf16", 1, 2.2), (8193, 128, 64, "bf16", 1, 6),
     (16391, 64, 128, "bf16", 1, 6), (16379, 64, 128, "bf16", 1, 6),
+    # large clouds: two waves
+    (131075, 64, 64, "bf16", 2, 6), (131075, 64, 64, "bf16", 3, 18), (131075, 40, 72, "bf16", 1, 2),
     # more than 128 destination channels: eight waves with 16 centres, four and eight with 32, cooperative
     (3067, 32, 136, "bf16", 2, 6), (3073, 32, 136, "bf16", 2, 6), (6145, 32, 136, "bf16", 2, 6), (12289, 32, 136, "bf16", 1, 4),
     (3067, 24, 140, "f32", 2, 6), (6139, 24, 140, "f32", 2, 6), (12283, 24, 140, "f32", 1, 4), (2049, 16, 264, "f32", 2, 6),
