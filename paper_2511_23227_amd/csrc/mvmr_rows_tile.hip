@@ -474,15 +474,15 @@ int launch_tile(const TileArgs &t, hipStream_t stream)
 // when it has more than 48 triplets per 32 centres on average, i.e. more than a window and a half.
 //   - small clouds: split over more waves and 16 centres per block while all waves fit on the device at once (2 to 5 per SIMD by
 //     the registers of the form; a second round costs more than the longer chains of fewer waves).
-//     Up to 64 destination channels, 8192 centres (fp32: 6144): eight waves.  2048 points, 16 -> 16 fp32: 8.4, four waves 10.5, 32
-//     centres 12.1, cooperative 27.  8000 points, 64 -> 64 bf16: 12.2 / 13.2 / 14.5 / 29.  Four waves up to 12288 centres in fp32 and,
-//     with more than one chunk of rows or eight lanes to a row, exact bf16: 8000 points, 64 -> 64 fp32 36.4 -> 30.6 (eight waves
-//     before), 12 000 points, 20 -> 36 fp32 35.1 -> 29.8, 128 -> 64 with 125 cells in bf16 100.9 -> 83.7 (32 centres before).
+//     Up to 64 destination channels, 8192 centres: eight waves (fp32 with 33 .. 64 channels from 6144 on with 32 centres: 8000 points,
+//     64 -> 64 36.4, 29.5).  2048 points, 16 -> 16 fp32: 8.4, four waves 10.5, 32 centres 12.1, cooperative 27.  8000 points, 64 -> 64
+//     bf16: 12.2 / 13.2 / 14.5 / 29.  Four waves up to 12288 centres in fp32 and, with eight lanes to a row, exact bf16 (32 centres
+//     before): 12 000 points, 20 -> 36 fp32 35.1 -> 29.8, 128 -> 64 with 125 cells in bf16 100.9 -> 83.7.
 //     65 .. 128 channels: eight waves, up to 4096 centres 16 per block, up to 8192 32.  2000 points, 128 -> 128 bf16 39.8 -> 26.7; 4000
 //     points, 64 -> 128 fp32 46.2 -> 30.5; 8000 points 47.7 -> 37.7 (four waves, 32 centres before; at 12 000 points 59.1, eight 65.6).
 //     Wider: blocks of 128 destination channels, each with its own sums.  Up to 6144 / 12288 / 24576 centres times such blocks eight
 //     waves with 16 centres, four and eight with 32.  2000 points, 256 -> 256 bf16 117 -> 39, fp32 460 -> 87; 5000, 128 -> 256 126 ->
-//     52; 12 000 129 -> 88 (cooperative before; at 30 000 points 153, four waves with 32 centres 168, eight 208).
+//     52; 12 000 129 -> 88 (cooperative before; exact sums keep their small products apart as they did there; at 30 000 points 153, four waves with 32 centres 168, eight 208).
 //   - exact sums, up to 128 destination channels: split over four waves, 32 centres, since the terms of a sum would take three
 //     times the LDS (40 000 points, 128 -> 128 bf16: 130 per direction; cooperative, 16 centres per wave, about 165)
 //     fp32, 17 .. 32 destination channels, more than 65536 centres with up to 16 neighbours: 64 centres, which fill a window
@@ -518,7 +518,9 @@ template <bool F32, bool EXACT, int RL, bool NARROW>
 int launch_tile_form(const TileArgs &t, hipStream_t stream)
 {
     if (t.ndt <= 4) {
-        if (t.n_centres <= (F32 ? 6144 : 8192)) return launch_tile_split<F32, EXACT, RL, NARROW, 1, 8>(t, stream);
+        if constexpr (F32)
+            if (t.ndt > 2 && t.n_centres > 6144 && t.n_centres <= 8192) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 8, 1, 4, true>(t, stream);
+        if (t.n_centres <= 8192) return launch_tile_split<F32, EXACT, RL, NARROW, 1, 8>(t, stream);
         if constexpr (EXACT && (F32 || RL == 8))
             if (t.n_centres <= 12288) return launch_tile_split<F32, EXACT, RL, NARROW, 1, 4>(t, stream);
     } else if (t.ndt <= 8) {
@@ -526,9 +528,9 @@ int launch_tile_form(const TileArgs &t, hipStream_t stream)
         if (t.n_centres <= 8192) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 8, 1, 8, true>(t, stream);
     } else {
         const int64_t parts = t.n_centres * ceil_div(t.ndt, 8);
-        if (parts <= 6144) return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 8, true>(t, stream);
-        if (parts <= 12288) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
-        if (parts <= 24576) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 8, 1, 8, true>(t, stream);
+        if (parts <= 6144) return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 8, true, EXACT>(t, stream);
+        if (parts <= 12288) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true, EXACT>(t, stream);
+        if (parts <= 24576) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 8, 1, 8, true, EXACT>(t, stream);
     }
     const int64_t per_cell = t.n_centres * (int64_t)t.K, triplets = (int64_t)(t.gather_bytes / 4);
     const bool crowded = triplets * 32 > 48 * per_cell;
