@@ -452,6 +452,9 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
 // bf16: in crowded layers of the cooperative form only, where sums have low terms (8 % of its time; 128 -> 256 with 37
 // neighbours, not crowded: 3.7e-7, vector ALUs 7.0e-7); the split form's waves add up too few (1024 -> 64, 216 cells, crowded:
 // 7.3e-7, vector ALUs 7.2e-6).
+// Eight waves for 65 .. 128 destination channels, which larger clouds have four for: from half as many steps on, so that no layer has
+// larger errors than with four (128 -> 128, 27 cells, 12 steps: one accumulator 2.5e-7 and, values of one sign, 1.1e-7; apart 1.35e-7
+// and 7.5e-8; four waves, apart, 1.6e-7 and 9.4e-8).  4000 points, 128 -> 128: 49.6 us apart, 57.1 in one accumulator.
 constexpr int64_t APART_FROM = 16;
 
 template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NP, int NW, int WD, int DTW, bool SPLITK, bool APART = F32 && !SPLITK>
@@ -459,7 +462,7 @@ int launch_tile(const TileArgs &t, hipStream_t stream)
 {
     using C = TileCfg<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK>;
     if constexpr (F32 && SPLITK && !APART)
-        if (ceil_div(t.K, NW) * t.n_chunks > APART_FROM)
+        if (ceil_div(t.K, NW) * t.n_chunks > (NW == 8 && DTW == 8 ? APART_FROM / 2 : APART_FROM))
             return launch_tile<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK, true>(t, stream);
     auto kern = rows_tile_kernel<F32, EXACT, RL, NARROW, GA, NP, NW, WD, DTW, SPLITK, APART>;
     if (C::LDS > 64 * 1024)

@@ -96,6 +96,23 @@ def test_rows_keep_32_bit_sums(n, per, t, c_in, c_out, dt, positive):
     assert e_fwd < bound(K * -(-c_in // 32)) and e_bwd < bound(K * -(-c_out // 32))
 
 
+# Clouds on either side of a line between two forms of the rows kernel: which form runs may not cost precision.  More waves than the
+# form before shorten a wave's sums; the error may not be larger than beyond the line for that (the margin is for other values).
+@gpu
+@pytest.mark.parametrize("positive", [False, True])
+@pytest.mark.parametrize("n,beyond,per,t,c_in,c_out,dt", [
+    (4000, 9000, 24, 3, 128, 128, "f32"), (8000, 9000, 24, 3, 96, 100, "f32"), (4000, 9000, 24, 4, 40, 72, "f32"),
+    (8000, 9000, 20, 5, 32, 128, "f32"), (3000, 9000, 24, 2, 512, 128, "f32"),
+])
+def test_forms_do_not_differ_in_precision(n, beyond, per, t, c_in, c_out, dt, positive):
+    errors = []
+    for points in (n, beyond):
+        m, T, K, x, w, dy = layer(points, per, t, c_in, c_out, dt, positive)
+        y, dx = wide(T, K, x, w, dy, True)
+        errors.append((err(m.pcpp_mvmr_fwd(x, w, T), y), err(m.pcpp_mvmr_bwd_input(dy, w, T), dx)))
+    assert errors[0][0] < 1.1 * errors[1][0] and errors[0][1] < 1.1 * errors[1][1]
+
+
 # the longest sums: chunks that are summed in three parts (1024 -> 1024: more than 16384 triplets), fp32 chunks of more than 768 triplets
 # (256 -> 256), many chunks to one cell
 @gpu
