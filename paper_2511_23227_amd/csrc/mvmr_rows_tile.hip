@@ -491,10 +491,12 @@ int launch_tile(const TileArgs &t, hipStream_t stream)
 //     fp32, 17 .. 32 destination channels, more than 65536 centres with up to 16 neighbours: 64 centres, which fill a window
 //     better (32 -> 32, 200 000 points with 10 neighbours: 120, 32 centres 132; 100 000 with 13.5: 74, 78; with 24: 90, 86;
 //     24 000 with 14.5, too few blocks: 28.6, 24.6).
-//     bf16, more than 131072 centres and up to 27 cells: two waves, whose sums are added half as often (128 -> 128, 400 000 points: 992,
-//     949; rounded, 64 -> 64 with 10 neighbours 229, 204, with 24 264, 246, in spatial order 250, 215; 150 000 points with 10: 104,
-//     98).  fp32 gains nothing (32 -> 32, 150 000 points: 109, 111).
+//     (Two waves are up to 4 % faster on large bf16 clouds, but each adds up twice as much: 128 -> 128, 300 000 points, relative error
+//     2.0e-7, four waves 1.5e-7; values of one sign 1.4e-7 and 8.7e-8.)
 //   - rounded sums, up to 64: the same (strided layer's input gradient, 128 -> 64: 253, 16 centres 346, cooperative 312).
+//     More than 131072 centres and up to 27 cells: two waves, whose sums are added half as often; the rounding of the sums is 10 000
+//     times the error of the longer ones (64 -> 64, 400 000 points with 10 neighbours 229, 204, with 24 264, 246, in spatial order 250, 215; 150 000 points with
+//     10: 104, 98).
 //     Crowded: 16 centres, which fill their windows, over two waves, or four where the cloud is too small to fill the device with
 //     that (64 -> 64, cooperative with 16 centres per wave / four waves / two: 115 000 points with 148 neighbours 162 / 145 / 141 and in
 //     spatial order 178 / 146 / 143; 57 600 with 74 71 / 57 / 54; 150 000 with 48 in spatial order 152 / 143 / 128; 40 000 with 50
@@ -537,20 +539,18 @@ int launch_tile_form(const TileArgs &t, hipStream_t stream)
     }
     const int64_t per_cell = t.n_centres * (int64_t)t.K, triplets = (int64_t)(t.gather_bytes / 4);
     const bool crowded = triplets * 32 > 48 * per_cell;
-    [[maybe_unused]] const bool large = t.n_centres > 131072 && t.K <= 27;
     if constexpr (EXACT) {
         if constexpr (F32)
             if (t.ndt == 2 && t.n_centres > 65536 && triplets <= 16 * t.n_centres)
                 return launch_tile<F32, EXACT, RL, NARROW, 4, 1, 4, 1, 2, true>(t, stream);
         if (t.ndt <= 4) return launch_tile_split<F32, EXACT, RL, NARROW, 2, 4>(t, stream);
-        if constexpr (!F32)
-            if (t.ndt <= 8 && large) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 2, 1, 8, true>(t, stream);
         if (t.ndt <= 8) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
         if constexpr (F32) return launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 4, false>(t, stream);
         else return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false, true>(t, stream)
                             : launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false>(t, stream);
     } else {
         if (t.ndt <= 4) {
+            const bool large = t.n_centres > 131072 && t.K <= 27;
             if (t.n_chunks == 1 ? !crowded : triplets * 32 <= 80 * per_cell)
                 return large ? launch_tile<F32, EXACT, RL, NARROW, 2, 1, 2, 1, 4, true>(t, stream)
                              : launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);

@@ -103,6 +103,7 @@ def test_rows_keep_32_bit_sums(n, per, t, c_in, c_out, dt, positive):
 @pytest.mark.parametrize("n,beyond,per,t,c_in,c_out,dt", [
     (4000, 9000, 24, 3, 128, 128, "f32"), (8000, 9000, 24, 3, 96, 100, "f32"), (4000, 9000, 24, 4, 40, 72, "f32"),
     (8000, 9000, 20, 5, 32, 128, "f32"), (3000, 9000, 24, 2, 512, 128, "f32"),
+    (132000, 130000, 12, 3, 128, 128, "bf16"), (132000, 130000, 12, 3, 32, 100, "bf16"),
 ])
 def test_forms_do_not_differ_in_precision(n, beyond, per, t, c_in, c_out, dt, positive):
     errors = []
