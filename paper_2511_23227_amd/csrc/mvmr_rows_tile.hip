@@ -486,12 +486,17 @@ int launch_tile(const TileArgs &t, hipStream_t stream)
 //     Wider: blocks of 128 destination channels, each with its own sums.  Up to 6144 / 12288 / 24576 centres times such blocks eight
 //     waves with 16 centres, four and eight with 32.  2000 points, 256 -> 256 bf16 117 -> 39, fp32 460 -> 87; 5000, 128 -> 256 126 ->
 //     52; 12 000 129 -> 88 (cooperative before; exact sums keep their small products apart as they did there; at 30 000 points 153, four waves with 32 centres 168, eight 208).
+//     One cell (1 x 1 x 1 kernels) keeps one wave of a split block at work.  Wide layers take that form only while there are
+//     few blocks (2000 points with 60 neighbours, 256 -> 256 bf16 45.4, cooperative 51.3; 2500 with 40 55.9, 35.4; 9000 188, 48; 300 -> 200 fp32 104 / 183 and 593 / 223), crowded ones
+//     with rounded sums up to 8192 centres (20 000 points with 40 neighbours, 64 -> 64: 24.2, 18.5; 400 000 with 12 in spatial order 103, 73).
+//     Exact bf16 sums to 65 .. 128 channels on large clouds have two waves, of which one is idle, instead of four (128 -> 128, 150 000 points with
+//     40 neighbours: 230, 396).
 //   - exact sums, up to 128 destination channels: split over four waves, 32 centres, since the terms of a sum would take three
 //     times the LDS (40 000 points, 128 -> 128 bf16: 130 per direction; cooperative, 16 centres per wave, about 165)
 //     fp32, 17 .. 32 destination channels, more than 65536 centres with up to 16 neighbours: 64 centres, which fill a window
 //     better (32 -> 32, 200 000 points with 10 neighbours: 120, 32 centres 132; 100 000 with 13.5: 74, 78; with 24: 90, 86;
 //     24 000 with 14.5, too few blocks: 28.6, 24.6).
-//     (Two waves are up to 4 % faster on large bf16 clouds, but each adds up twice as much: 128 -> 128, 300 000 points, relative error
+//     (With more cells two waves are up to 4 % faster on large bf16 clouds, but each adds up twice as much: 128 -> 128, 300 000 points, relative error
 //     2.0e-7, four waves 1.5e-7; values of one sign 1.4e-7 and 8.7e-8.)
 //   - rounded sums, up to 64: the same (strided layer's input gradient, 128 -> 64: 253, 16 centres 346, cooperative 312).
 //     More than 131072 centres and up to 27 cells: two waves, whose sums are added half as often; the rounding of the sums is 10 000
@@ -522,6 +527,7 @@ int launch_tile_split(const TileArgs &t, hipStream_t stream)
 template <bool F32, bool EXACT, int RL, bool NARROW>
 int launch_tile_form(const TileArgs &t, hipStream_t stream)
 {
+    const bool cells = t.K > 1;                          // (one cell: see above)
     if (t.ndt <= 4) {
         if constexpr (F32)
             if (t.ndt > 2 && t.n_centres > 6144 && t.n_centres <= 8192) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 8, 1, 4, true>(t, stream);
@@ -533,9 +539,9 @@ int launch_tile_form(const TileArgs &t, hipStream_t stream)
         if (t.n_centres <= 8192) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 8, 1, 8, true>(t, stream);
     } else {
         const int64_t parts = t.n_centres * ceil_div(t.ndt, 8);
-        if (parts <= 6144) return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 8, true, EXACT>(t, stream);
-        if (parts <= 12288) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true, EXACT>(t, stream);
-        if (parts <= 24576) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 8, 1, 8, true, EXACT>(t, stream);
+        if (parts <= (cells || F32 ? 6144 : 4096)) return launch_tile<F32, EXACT, RL, NARROW, 1, 1, 8, 1, 8, true, EXACT>(t, stream);
+        if (cells && parts <= 12288) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true, EXACT>(t, stream);
+        if (cells && parts <= 24576) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 8, 1, 8, true, EXACT>(t, stream);
     }
     const int64_t per_cell = t.n_centres * (int64_t)t.K, triplets = (int64_t)(t.gather_bytes / 4);
     const bool crowded = triplets * 32 > 48 * per_cell;
@@ -544,12 +550,15 @@ int launch_tile_form(const TileArgs &t, hipStream_t stream)
             if (t.ndt == 2 && t.n_centres > 65536 && triplets <= 16 * t.n_centres)
                 return launch_tile<F32, EXACT, RL, NARROW, 4, 1, 4, 1, 2, true>(t, stream);
         if (t.ndt <= 4) return launch_tile_split<F32, EXACT, RL, NARROW, 2, 4>(t, stream);
+        if constexpr (!F32)
+            if (!cells && t.ndt <= 8 && t.n_centres > 131072) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 2, 1, 8, true>(t, stream);
         if (t.ndt <= 8) return launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 8, true>(t, stream);
         if constexpr (F32) return launch_tile<F32, EXACT, RL, NARROW, 2, 2, 4, 4, 4, false>(t, stream);
         else return crowded ? launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false, true>(t, stream)
                             : launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false>(t, stream);
     } else {
         if (t.ndt <= 4) {
+            if (crowded && !cells) return launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 1, false>(t, stream);
             const bool large = t.n_centres > 131072 && t.K <= 27;
             if (t.n_chunks == 1 ? !crowded : triplets * 32 <= 80 * per_cell)
                 return large ? launch_tile<F32, EXACT, RL, NARROW, 2, 1, 2, 1, 4, true>(t, stream)

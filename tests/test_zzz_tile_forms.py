@@ -69,3 +69,29 @@ def test_sub_blocks_of_the_weight_gradient(n, neighbours, cin, cout):
     dev = lambda a: torch.from_numpy(a).cuda().bfloat16()
     ref, scale = oracle_bwd_weight(x, dy, o, i, k, 8)
     assert_close(pcpp.pcpp_mvmr_bwd_weight(dev(x), dev(dy), T).cpu().numpy(), ref, scale, TOL["bf16"], f"bwd_weight {len(o)} triplets")
+
+
+@pytest.mark.parametrize("n,beyond,neighbours,cin,cout,dt", [(5100, 12600, 60, 256, 256, "bf16"), (11000, 12600, 40, 256, 256, "bf16"), (11000, 12600, 40, 200, 136, "f32")])
+def test_one_cell_costs_no_more_than_on_a_larger_cloud(n, beyond, neighbours, cin, cout, dt):
+    """1 x 1 x 1 kernels: forms that split the cells over the waves leave all but one wave idle (11 000 points took 2.7 to 3.6 times
+    as long as 12 600 beyond the line).  The larger cloud has more work, so the order holds with any clock."""
+    import paper_2511_23227_amd as pcpp
+    times = []
+    for points in (n, beyond):
+        g = torch.Generator(device="cuda").manual_seed(points)
+        d = torch.rand(points, 3, generator=g, device="cuda")
+        T = pcpp.pcpp_build_triplets(d, d, (neighbours / points / (4.0 / 3.0 * np.pi)) ** (1 / 3), 1, plan_flags=pcpp.PLAN_FWD)
+        tdt = torch.bfloat16 if dt == "bf16" else torch.float32
+        x = torch.randn(points, cin, generator=g, device="cuda").to(tdt)
+        w = (torch.randn(1, cout, cin, generator=g, device="cuda") / cin ** 0.5).to(tdt)
+        best = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                pcpp.pcpp_mvmr_fwd(x, w, T)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        times.append(best)
+    assert times[0] < 1.3 * times[1], times
