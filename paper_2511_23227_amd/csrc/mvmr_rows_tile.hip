@@ -507,6 +507,10 @@ int launch_tile(const TileArgs &t, hipStream_t stream)
 //     spatial order 178 / 146 / 143; 57 600 with 74 71 / 57 / 54; 150 000 with 48 in spatial order 152 / 143 / 128; 40 000 with 50
 //     61 / 53 / 57; 10 000 with 50 41 / 19 / 24).  Two chunks of rows (128 -> 64) need more than 80 triplets per 32 centres for it:
 //     25 000 points with 100 neighbours 113 / 78 / 78 (32 centres 88), 60 000 with 60 135 / 142 / 145 (127).
+//     More than 131072 centres and up to 27 cells: 32 centres over two waves up to 256 triplets per 32 centres (400 000 points, 64 ->
+//     64, 43 neighbours cooperative 372, 16 centres 394, 32 343; in spatial order 293 and 249), with two chunks up to 128 in spatial order (400 000
+//     points with 70 neighbours: 788, 861, 663; in index order 200 000 with 32: 240, 231, 246).  Above 256 with two chunks in index order the cooperative
+//     form, whose blocks read W a quarter as often (400 000 points with 560 neighbours: 3756, 4626; in spatial order 3435, 3540).
 //   - rounded sums to 65 .. 128 channels: split up to 32768 centres, crowded from 16384 on: over two waves (25 000 points with 368
 //     neighbours, 64 -> 128: 52, four waves 61; 12 500 points with 80: 46, 37); above, cooperative, 32 centres per wave, crowded: 16
 //     (strided layer, 64 -> 128: 97, split 107).
@@ -558,11 +562,14 @@ int launch_tile_form(const TileArgs &t, hipStream_t stream)
                             : launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 4, false>(t, stream);
     } else {
         if (t.ndt <= 4) {
-            if (crowded && !cells) return launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 1, false>(t, stream);
-            const bool large = t.n_centres > 131072 && t.K <= 27;
-            if (t.n_chunks == 1 ? !crowded : triplets * 32 <= 80 * per_cell)
-                return large ? launch_tile<F32, EXACT, RL, NARROW, 2, 1, 2, 1, 4, true>(t, stream)
-                             : launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
+            const bool large = t.n_centres > 131072, spatial = t.side.perm != nullptr, one = t.n_chunks == 1, two = large && t.K <= 27;
+            if ((crowded && !cells) || (large && !one && !spatial && triplets > 8 * per_cell))
+                return launch_tile<F32, EXACT, RL, NARROW, 1, 4, 4, 4, 1, false>(t, stream);
+            int most = one ? 48 : 80;                    // triplets per cell and 32 centres for the forms with 32 centres
+            if (two && cells && (one || spatial)) most = one ? 256 : 128;
+            if (triplets * 32 <= most * per_cell)
+                return two ? launch_tile<F32, EXACT, RL, NARROW, 2, 1, 2, 1, 4, true>(t, stream)
+                           : launch_tile<F32, EXACT, RL, NARROW, 2, 1, 4, 1, 4, true>(t, stream);
             return t.n_centres > 49152 ? launch_tile<F32, EXACT, RL, NARROW, 1, 1, 2, 1, 4, true>(t, stream)
                                        : launch_tile<F32, EXACT, RL, NARROW, 1, 1, 4, 1, 4, true>(t, stream);
         }

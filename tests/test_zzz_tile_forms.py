@@ -19,10 +19,13 @@ pytestmark = pytest.mark.gpu
     (6143, 20, 36, "f32", 2, 6), (6145, 20, 36, "f32", 2, 6), (12283, 16, 16, "f32", 1, 4), (12289, 16, 16, "f32", 1, 4),
     (8193, 72, 40, "bf16", 2, 6), (12289, 72, 40, "bf16", 1, 4), (9001, 24, 40, "bf16", 2, 6),
     # rounded sums, crowded cells: four waves, two waves; two chunks of rows
-    (8193, 64, 64, "bf16", 1, 6), (49153, 64, 64, "bf16", 1, 4), (8193, 128, 64, "bf16", 1, 2.2), (8193, 128, 64, "bf16", 1, 6),
+    (8193, 64, 64, "bf16", 2, 16), (49153, 64, 64, "bf16", 2, 14), (8193, 128, 64, "bf16", 1, 2.2), (8193, 128, 64, "bf16", 2, 24),
     (16391, 64, 128, "bf16", 1, 6), (16379, 64, 128, "bf16", 1, 6),
-    # large clouds: two waves
-    (131075, 64, 64, "bf16", 2, 6), (131075, 64, 64, "bf16", 3, 18), (131075, 40, 72, "bf16", 1, 2),
+    # large clouds: rounded sums over two waves, 32 and 16 centres, cooperative; exact sums over four, with one cell over two
+    (131075, 64, 64, "bf16", 2, 6), (131075, 64, 64, "bf16", 3, 18), (131075, 128, 64, "bf16", -2, 20),
+    (131075, 40, 72, "bf16", 2, 2), (131075, 40, 72, "bf16", 1, 2),
+    # one cell: cooperative
+    (8193, 128, 64, "bf16", -1, 6), (2049, 32, 264, "bf16", 1, 4), (6145, 24, 140, "f32", 1, 4),
     # more than 128 destination channels: eight waves with 16 centres, four and eight with 32, cooperative
     (3067, 32, 136, "bf16", 2, 6), (3073, 32, 136, "bf16", 2, 6), (6145, 32, 136, "bf16", 2, 6), (12289, 32, 136, "bf16", 1, 4),
     (3067, 24, 140, "f32", 2, 6), (6139, 24, 140, "f32", 2, 6), (12283, 24, 140, "f32", 1, 4), (2049, 16, 264, "f32", 2, 6),
