@@ -595,33 +595,31 @@ int launch_weight_lds(const MvmrArgs &a, float *dw, const int32_t *tri_o, const 
 }
 
 // The sub-block of dW that a block of weight_any_kernel owns, as channels of each side, and the chunk of the list.
-// 512 blocks, which the device holds at once whatever the sub-block (two to seven per CU): a block's fixed cost and its partial sum
-// are worth more than a second round.  Chunks no longer than the above: then whole rounds, of bf16 blocks.  us, kernel and sums, with
-// 1024 blocks / 512: 64 -> 64 bf16 with 0.95 M triplets 34.1 / 28.6, 2.4 M 66.7 / 60.7, fp32 0.36 M 39.3 / 33.0, 128 -> 128 with
-// 0.95 M 71.7 / 60.2; 256 blocks: 29.0, 68.7, 32.6, 67.4.  2.4 M triplets and 128 -> 128, 289 chunks: 159, 512: 142.
-// Sub-blocks of 128 x 64 channels read fewer rows, 64 x 64 have twice the waves per SIMD and twice the blocks: the latter up to 0.6 M
-// triplets where both sides are wider than 64 channels (128 -> 128, 0.12 M: 21.5, 128 x 64 29.9; 0.36 M: 34.7, 41.6; 0.95 M: 60.9, 60.2), up to 1.2 M
-// where one is (64 -> 128, 0.36 M: 25.6, 34.2; 0.95 M: 38.3, 44.5; 4.0 M: 124, 109).
+// Enough blocks of up to 128 x 64 channels for four per CU, unless that would leave a wave fewer than two batches, and chunks no longer
+// than the above.  (With half as many chunks the blocks' fixed cost and their partial sums halve, 128 -> 128 bf16 with 0.95 M triplets
+// 74 us, 67, but a wave adds up twice as much: relative error 1.4e-7, 1.8e-7; 64 -> 64 fp32 with 0.35 M 39 us, 33, and 1.2e-7, 1.3e-7.)
+// Sub-blocks of 128 x 64 channels read fewer rows, 64 x 64, of the same chunks, have three waves per SIMD for two: the latter up to 0.6 M triplets where both
+// sides are wider than 64 channels (128 -> 128, 0.14 M: 29.8, 128 x 64 37.1; 0.35 M: 42.7, 47.8; 0.58 M: 54.1, 57.7), up to 1.2 M
+// where one is (64 -> 128, 0.35 M: 33.8, 41.8; 0.93 M: 52.8, 59.4).
 struct AnyShape { int co, ci, n_sub_in, n_sub, chunk; int64_t n_chunks; };
 
 AnyShape any_shape(bool f32, int64_t n_triplets, int c_in, int c_out)
 {
     AnyShape s;
-    const bool narrow = f32 || n_triplets <= (c_in > 64 && c_out > 64 ? 600000 : 1200000);
-    auto channels = [&](int c) { return c <= 32 ? 32 : (c <= 64 || narrow ? 64 : 128); };
-    s.co = channels(c_out);
-    s.ci = channels(c_in);
-    if (s.co == 128 && s.ci == 128) s.ci = 64;             // 128 x 64 channels: 128 accumulator registers
-    s.n_sub_in = (int)ceil_div(c_in, s.ci);
-    s.n_sub = s.n_sub_in * (int)ceil_div(c_out, s.co);
-    int64_t want = 512 / s.n_sub;
+    auto sub_blocks = [&](int widest) {
+        auto channels = [&](int c) { return c <= 32 ? 32 : (c <= 64 || widest == 64 ? 64 : 128); };
+        s.co = channels(c_out);
+        s.ci = channels(c_in);
+        if (s.co == 128 && s.ci == 128) s.ci = 64;         // 128 x 64 channels: 128 accumulator registers
+        s.n_sub_in = (int)ceil_div(c_in, s.ci);
+        return s.n_sub = s.n_sub_in * (int)ceil_div(c_out, s.co);
+    };
+    const int64_t n_sub = sub_blocks(f32 ? 64 : 128);
+    if (!f32 && n_triplets <= (c_in > 64 && c_out > 64 ? 600000 : 1200000)) sub_blocks(64);
+    int64_t want = 1024 / n_sub;
     if (want < 8) want = 8;
     const int64_t short_chunks = ceil_div(n_triplets, f32 ? F32_CHUNK : SEGMENT), room = ((int64_t)1 << 26) / ((int64_t)c_in * c_out);
-    if (short_chunks > want && want < room) {
-        int64_t more = short_chunks;
-        if (!f32 && more < 2 * want) more = 2 * want;
-        want = more < room ? more : room;
-    }
+    if (short_chunks > want && want < room) want = short_chunks < room ? short_chunks : room;
     int64_t chunk = ceil_div(n_triplets > 0 ? n_triplets : 1, want);
     if (chunk < 2 * WINDOW * WAVES) chunk = 2 * WINDOW * WAVES;
     s.chunk = (int)((chunk + WINDOW * WAVES - 1) / (WINDOW * WAVES) * (WINDOW * WAVES));

@@ -57,3 +57,16 @@ def test_size_queries_and_argument_errors_without_gpu():
     assert c >= b + 4 * (1000 + 500 + 20000)
     assert L.pcpp_build_triplets(p, 5, p, 5, 0.1, 3, None, None, None, 0, None, ctypes.byref(n), None, 0, 0x1000,
                                  p, 1 << 20, None) == -1
+
+
+def test_weight_gradient_workspace_stays_the_size_it_was():
+    """A caller may keep the size it once asked for: one slot of c_in * c_out fp32 values per chunk of the triplet list and per cell.
+    The numbers of chunks are those of 1024 / sub-blocks of 128 x 64 channels (fp32: 64 x 64), eight at least, and of no more than
+    8192 (768) triplets while the slots stay below 256 MB; chunks are multiples of 128 triplets, 256 at least."""
+    from paper_2511_23227_amd import binding
+    L = binding.library()
+    for n, c_in, c_out, bf16, chunks in [(73000, 1024, 1024, 1, 9), (70000, 768, 768, 1, 14), (577633, 128, 128, 1, 502),
+                                         (574263, 192, 128, 1, 321), (931013, 64, 128, 1, 910), (2398580, 64, 64, 1, 987),
+                                         (345794, 64, 64, 0, 901), (300000, 1000, 8, 0, 391), (5000000, 700, 600, 1, 159)]:
+        got = L.pcpp_mvmr_workspace_bytes(2, 64, 64, n, c_in, c_out, 8, bf16)
+        assert got == ((chunks + 8) * c_in * c_out * 4 + 255) // 256 * 256, (n, c_in, c_out, got / (4 * c_in * c_out) - 8)

@@ -128,3 +128,15 @@ def test_weight_gradient_keeps_32_bit_sums(n, per, t, c_in, c_out, dt, positive)
     # a wave adds up to 8192 / (4 * 32) batches; the sums of the waves, the parts and the chunks are added up in two steps
     e = err(m.pcpp_mvmr_bwd_weight(x, dy, T), wide(T, K, x, w, dy, False))
     assert e < bound(64)
+
+
+# Chunks of the triplet list: a wave adds up a quarter of a chunk, 32 triplets at a time, and the matrix cores cut every addend at the sum's
+# last place.  bf16 lists are cut into 1024 chunks over the number of sub-blocks of 128 x 64 channels; a random walk of as many cuts is what
+# their sums may be off, half of U each, and U for the rest (the waves' and the chunks' sums).
+@gpu
+@pytest.mark.parametrize("n,c_in,c_out,blocks", [(24583, 128, 128, 2), (24583, 192, 128, 3), (39583, 64, 128, 1), (100000, 64, 64, 1)])
+def test_chunks_are_short_enough(n, c_in, c_out, blocks):
+    m, T, K, x, w, dy = layer(n, 24, 3, c_in, c_out, "bf16", False)
+    steps = -(-(T.n_triplets * blocks // 1024) // 128) + 1
+    e = err(m.pcpp_mvmr_bwd_weight(x, dy, T), wide(T, K, x, w, dy, False))
+    assert e < (1.0 + 0.5 * steps ** 0.5) * U
