@@ -78,7 +78,8 @@ def test_permutation_is_a_space_filling_order(pcpp):
     dict(n_in=1501, n_out=1333, r=0.12, t=3, cin=32, cout=32, dt="f32"),      # whole tiles of channels
     dict(n_in=1300, n_out=1501, r=0.12, t=3, cin=64, cout=64, dt="bf16"),
     dict(n_in=2100, n_out=700, r=0.15, t=3, cin=64, cout=128, dt="bf16"),
-    dict(n_in=1500, n_out=1300, r=0.15, t=5, cin=256, cout=256, dt="bf16"),   # producer/consumer kernel
+    dict(n_in=1500, n_out=1300, r=0.15, t=5, cin=256, cout=256, dt="bf16"),
+    dict(n_in=10500, n_out=10301, r=0.05, t=5, cin=256, cout=256, dt="bf16"), # producer/consumer kernel
     dict(n_in=1000, n_out=1000, r=0.2, t=6, cin=48, cout=24, dt="bf16"),
     dict(n_in=300, n_out=2000, r=0.15, t=4, cin=16, cout=130, dt="bf16"),
 ])
@@ -126,18 +127,20 @@ def test_scene_spatial_matches_plain_plan(pcpp, sid):
     check_all(pcpp, T, s.in_xyz, s.out_xyz, s.radius, s.t, x, w, dy, s.dtype, s.name)
 
 
-def test_determinism_spatial_wide(pcpp):
+@pytest.mark.parametrize("n, r", [(1500, 0.15), (10500, 0.05)])       # tile kernel, producer/consumer kernel
+def test_determinism_spatial_wide(pcpp, n, r):
     rng = np.random.default_rng(8)
-    p = rng.uniform(0, 1, (1500, 3)).astype(np.float32)
+    p = rng.uniform(0, 1, (n, 3)).astype(np.float32)
     c, t = 256, 3
     x = dev(rng.standard_normal((len(p), c)).astype(np.float32), torch.bfloat16)
     w = dev((rng.standard_normal((27, c, c)) / 80).astype(np.float32), torch.bfloat16)
     d = dev(p)
     runs = []
-    n_t = pcpp.pcpp_count_triplets(d, d, 0.15, t)
+    n_t = pcpp.pcpp_count_triplets(d, d, r, t)
+    assert n < 10240 or n_t <= 3 * n * t ** 3
     nbytes = pcpp.library().pcpp_plan_bytes(len(p), len(p), t, n_t, spatial_flags(pcpp))
     for _ in range(2):
-        T = pcpp.pcpp_build_triplets(d, d, 0.15, t, plan_flags=spatial_flags(pcpp), capacity=n_t,
+        T = pcpp.pcpp_build_triplets(d, d, r, t, plan_flags=spatial_flags(pcpp), capacity=n_t,
                                      buffers={"plan": torch.zeros(nbytes, dtype=torch.uint8, device="cuda")})
         runs.append([pcpp.pcpp_mvmr_fwd(x, w, T).cpu().numpy(), pcpp.pcpp_mvmr_bwd_input(x, w, T).cpu().numpy(),
                      T.plan.cpu().numpy()[256:]])

@@ -54,7 +54,7 @@ def check_ops(m, T, ref, n_in, n_out, K, cin, cout, dt, rng, what):
 @pytest.mark.parametrize("case", [
     dict(n_in=3000, n_out=3000, same=True, pitch=0.05, t=3, cin=32, cout=32, dt="f32", spatial=False),
     dict(n_in=2500, n_out=1200, same=False, pitch=0.08, t=3, cin=64, cout=128, dt="bf16", spatial=False),
-    dict(n_in=2000, n_out=2000, same=True, pitch=0.06, t=5, cin=256, cout=256, dt="bf16", spatial=True),
+    dict(n_in=10400, n_out=10400, same=True, pitch=0.02, t=5, cin=256, cout=256, dt="bf16", spatial=True),
     dict(n_in=900, n_out=1500, same=False, pitch=0.11, t=5, cin=12, cout=20, dt="f32", spatial=True),
     dict(n_in=700, n_out=700, same=True, pitch=0.2, t=1, cin=16, cout=16, dt="f32", spatial=False),
 ])
