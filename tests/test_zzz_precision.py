@@ -87,6 +87,7 @@ def err(got, ref):
     (9000, 20, 3, 96, 96, "f32"), (2000, 30, 3, 256, 256, "f32"), (3000, 25, 3, 512, 520, "f32"), (3000, 60, 6, 64, 200, "f32"),
     (70000, 8, 3, 32, 32, "f32"), (1000, 100, 2, 24, 24, "f32"),
     (3000, 400, 3, 512, 256, "bf16"), (9000, 24, 3, 128, 128, "bf16"), (3000, 25, 3, 200, 200, "bf16"),
+    (12500, 20, 3, 40, 136, "f32"), (12500, 60, 2, 128, 136, "bf16"), (12500, 20, 3, 128, 200, "bf16"),     # cooperative
     (3000, 200, 3, 128, 136, "bf16"), (2000, 30, 3, 20, 36, "bf16"), (2000, 300, 3, 24, 160, "bf16"),
 ])
 def test_rows_keep_32_bit_sums(n, per, t, c_in, c_out, dt, positive):
