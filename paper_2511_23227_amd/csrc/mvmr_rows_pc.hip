@@ -465,7 +465,8 @@ __global__ __launch_bounds__(PC_THREADS) void rows_pc_kernel(const void *__restr
 // factor of three of the other; below it this kernel is the faster one on even clouds by more (50 000 points with 60 neighbours:
 // 409, 362).
 // So do small clouds, whose blocks of 128 centres leave most of the device idle (27 cells, 24 neighbours, the kernel here and the
-// tile kernel: 2000 points 117 and 39 us, 5000 122 and 65, 12 000 118 .. 127 and 105 .. 122; 30 000 123 .. 132 and 201 .. 231).
+// tile kernel: 2000 points 117 and 39 us, 5000 122 and 65, 12 000 118 .. 127 and 105 .. 122; 30 000 123 .. 132 and 201 .. 231; 125
+// cells, 32 neighbours: 2000 points 357 and 99, 6000 374 and 189, 10 000 377 and 268; 8 cells, 24 neighbours: 2000 65 and 19, 10 000 75 and 58).
 bool mvmr_rows_pc_usable(const MvmrArgs &a)
 {
     return a.n_triplets > 0 && a.n_centres > 10240 && a.n_triplets <= 3 * a.n_centres * (int64_t)a.K && a.in_dtype == PCPP_BF16 && a.c_src == 256 && a.c_dst == 256 && a.side.gather != nullptr &&

@@ -26,8 +26,9 @@
 // 256 -> 256 fp32, 1.5 M triplets, 8.9e-6, 4.2e-7, 1.06e-6; 512 -> 256 bf16 with 270 neighbours 2.1e-6, 6.4e-7, 1.6e-6).
 // What bounds it: with 32 to 64 channels in fp32 the vector instructions, most of which split rows and sums into terms (32 ->
 // 32: issued in 73 % of the cycles), in bf16 the rows' way through the L1 caches (a 64 -> 64 layer of 17 M triplets moves 2.2 GB of
-// them in 141 us, 0.71 L1 accesses per cycle and CU, matrix pipe 13 %); with more channels W's way from L2.  Layers whose channel counts are no power of two, which the vector ALUs had served before: 20 -> 36 fp32, 0.49 M
-// triplets, 29 us (349); 128 -> 128 bf16, 0.97 M triplets, 130 us (7938).
+// them in 141 us, 0.67 L1 accesses per cycle and CU, matrix pipe 13 %); with more channels W's way from L2.  Layers whose channel
+// counts are no power of two, which the vector ALUs had served before: 20 -> 36 fp32, 0.49 M triplets, 29 us (349); 128 -> 128 bf16,
+// 0.97 M triplets, 130 us (7938).
 // Every destination row is written once, by one block: no atomics, fixed summation order.
 //
 // v_mfma_f32_16x16x32_bf16: A: lane (M = l%16, g = l/16) holds A[M][8g .. 8g+7]; B: lane (N = l%16, g) holds
@@ -449,9 +450,10 @@ __global__ __launch_bounds__(NW * 64) void rows_tile_kernel(const TileArgs a)
 // 32 -> 32 with 64 cells, 2.3e-7; 28 steps, 128 -> 128, 4.6e-7; 128 steps, 1024 -> 64, 2.7e-6), that of fp32 sums on the vector ALUs
 // with the square root (2.6e-7, 7.6e-7, 8.0e-7, 1.6e-6).  Apart: below 1.4e-7 at all of them, and up to 3 % of the time
 // (20 -> 36, 0.49 M triplets: 99 and 102 us for the whole training step).  The cooperative form always has them apart when fp32.
-// bf16: in crowded layers of the cooperative form only, where sums have low terms (8 % of its time; 128 -> 256 with 37
-// neighbours, not crowded: 3.7e-7, vector ALUs 7.0e-7); the split form's waves add up too few (1024 -> 64, 216 cells, crowded:
-// 7.3e-7, vector ALUs 7.2e-6).
+// bf16: in crowded layers of the cooperative form, where sums have low terms (8 % of its time; 128 -> 256 with 37
+// neighbours, not crowded: 3.7e-7, vector ALUs 7.0e-7), and in all layers of more than 128 destination channels in the split form, which
+// takes that form's place on small clouds (128 -> 256, 3000 points: 1.1e-7, cooperative 3.0e-7).  The waves of the other split
+// forms add up too few (1024 -> 64, 216 cells, crowded: 7.3e-7, vector ALUs 7.2e-6).
 // Eight waves for 65 .. 128 destination channels, which larger clouds have four for: from half as many steps on, so that no layer has
 // larger errors than with four (128 -> 128, 27 cells, 12 steps: one accumulator 2.5e-7 and, values of one sign, 1.1e-7; apart 1.35e-7
 // and 7.5e-8; four waves, apart, 1.6e-7 and 9.4e-8).  4000 points, 128 -> 128: 49.6 us apart, 57.1 in one accumulator.
@@ -475,49 +477,55 @@ int launch_tile(const TileArgs &t, hipStream_t stream)
 
 // Which form, by measurement over layers of 16 .. 256 channels and 2 000 .. 400 000 points (times in us).  A cell is crowded
 // when it has more than 48 triplets per 32 centres on average, i.e. more than a window and a half.
-//   - small clouds: split over more waves and 16 centres per block while all waves fit on the device at once (2 to 5 per SIMD by
-//     the registers of the form; a second round costs more than the longer chains of fewer waves).
-//     Up to 64 destination channels, 8192 centres: eight waves (fp32 with 33 .. 64 channels from 6144 on with 32 centres: 8000 points,
-//     64 -> 64 36.4, 29.5).  2048 points, 16 -> 16 fp32: 8.4, four waves 10.5, 32 centres 12.1, cooperative 27.  8000 points, 64 -> 64
-//     bf16: 12.2 / 13.2 / 14.5 / 29.  Four waves up to 12288 centres in fp32 and, with eight lanes to a row, exact bf16 (32 centres
-//     before): 12 000 points, 20 -> 36 fp32 35.1 -> 29.8, 128 -> 64 with 125 cells in bf16 100.9 -> 83.7.
-//     65 .. 128 channels: eight waves, up to 4096 centres 16 per block, up to 8192 32.  2000 points, 128 -> 128 bf16 39.8 -> 26.7; 4000
-//     points, 64 -> 128 fp32 46.2 -> 30.5; 8000 points 47.7 -> 37.7 (four waves, 32 centres before; at 12 000 points 59.1, eight 65.6).
-//     Wider: blocks of 128 destination channels, each with its own sums.  Up to 6144 / 12288 / 24576 centres times such blocks eight
-//     waves with 16 centres, four and eight with 32.  2000 points, 256 -> 256 bf16 117 -> 39, fp32 460 -> 87; 5000, 128 -> 256 126 ->
-//     52; 12 000 129 -> 88 (cooperative before; exact sums keep their small products apart as they did there; at 30 000 points 153, four waves with 32 centres 168, eight 208).
-//     One cell (1 x 1 x 1 kernels) keeps one wave of a split block at work.  Wide layers take that form only while there are
-//     few blocks (2000 points with 60 neighbours, 256 -> 256 bf16 45.4, cooperative 51.3; 2500 with 40 55.9, 35.4; 9000 188, 48; 300 -> 200 fp32 104 / 183 and 593 / 223), crowded ones
-//     with rounded sums up to 8192 centres (20 000 points with 40 neighbours, 64 -> 64: 24.2, 18.5; 400 000 with 12 in spatial order 103, 73).
-//     Exact bf16 sums to 65 .. 128 channels on large clouds have two waves, of which one is idle, instead of four (128 -> 128, 150 000 points with
-//     40 neighbours: 230, 396).
+//   - small clouds: split over more waves and 16 centres per block, up to 128 channels about as far as all waves fit on the device
+//     at once (2 to 5 per SIMD by the registers of the form; a second round costs more than the longer chains of fewer waves).  The
+//     wider layers' lines are where the times cross and lie beyond: 256 -> 256 bf16 with 16 centres (170 registers, a block per CU)
+//     has up to 384 blocks, with 32 (222) up to 768.
+//     Up to 64 destination channels, 8192 centres: eight waves (fp32 with 33 .. 64 channels from 6144 on with 32 centres: 8000
+//     points, 64 -> 64 36.4, 29.5).  2048 points, 16 -> 16 fp32: 8.4, four waves 10.5, 32 centres 12.1, cooperative 27.  8000
+//     points, 64 -> 64 bf16: 12.2 / 13.2 / 14.5 / 29.  Four waves up to 12288 centres in fp32 and, with eight lanes to a row, exact
+//     bf16 (32 centres before): 12 000 points, 20 -> 36 fp32 35.1 -> 29.8, 128 -> 64 with 125 cells in bf16 100.9 -> 83.7.
+//     65 .. 128 channels: eight waves, up to 4096 centres 16 per block, up to 8192 32.  2000 points, 128 -> 128 bf16 39.8 -> 26.7;
+//     4000 points, 64 -> 128 fp32 46.2 -> 30.5; 8000 points 47.7 -> 37.7 (four waves, 32 centres before; at 12 000 points 59.1,
+//     eight 65.6).
+//     Wider: blocks of 128 destination channels, each with its own sums.  Up to 6144 / 12288 / 24576 centres times such blocks
+//     eight waves with 16 centres, four and eight with 32.  2000 points, 256 -> 256 bf16 117 -> 39, fp32 460 -> 87; 5000, 128 ->
+//     256 126 -> 52; 12 000 129 -> 88 (cooperative before; exact sums keep their small products apart as they did there; at 30 000
+//     points 153, four waves with 32 centres 168, eight 208).
+//     One cell (1 x 1 x 1 kernels) keeps one wave of a split block at work.  Wide layers take that form only while there are few
+//     blocks (2000 points with 60 neighbours, 256 -> 256 bf16 45.4, cooperative 51.3; 2500 with 40 55.9, 35.4; 9000 188, 48; 300 ->
+//     200 fp32, 2500 points 104, 183, 9000 593, 223), crowded ones with rounded sums up to 8192 centres (20 000 points with 40
+//     neighbours, 64 -> 64: 24.2, 18.5; 400 000 with 12 in spatial order 103, 73).
+//     Exact bf16 sums to 65 .. 128 channels on large clouds have two waves, of which one is idle, instead of four (128 -> 128,
+//     150 000 points with 40 neighbours: 230, 396).
 //   - exact sums, up to 128 destination channels: split over four waves, 32 centres, since the terms of a sum would take three
 //     times the LDS (40 000 points, 128 -> 128 bf16: 130 per direction; cooperative, 16 centres per wave, about 165)
-//     fp32, 17 .. 32 destination channels, more than 65536 centres with up to 16 neighbours: 64 centres, which fill a window
-//     better (32 -> 32, 200 000 points with 10 neighbours: 120, 32 centres 132; 100 000 with 13.5: 74, 78; with 24: 90, 86;
-//     24 000 with 14.5, too few blocks: 28.6, 24.6).
-//     (With more cells two waves are up to 4 % faster on large bf16 clouds, but each adds up twice as much: 128 -> 128, 300 000 points, relative error
-//     2.0e-7, four waves 1.5e-7; values of one sign 1.4e-7 and 8.7e-8.)
+//     fp32, 17 .. 32 destination channels, more than 65536 centres with up to 16 neighbours: 64 centres, which fill a window better
+//     (32 -> 32, 200 000 points with 10 neighbours: 120, 32 centres 132; 100 000 with 13.5: 74, 78; with 24: 90, 86; 24 000 with
+//     14.5, too few blocks: 28.6, 24.6).
+//     (With more cells two waves are up to 4 % faster on large bf16 clouds, but each adds up twice as much: 128 -> 128, 300 000
+//     points, relative error 2.0e-7, four waves 1.5e-7; values of one sign 1.4e-7 and 8.7e-8.)
 //   - rounded sums, up to 64: the same (strided layer's input gradient, 128 -> 64: 253, 16 centres 346, cooperative 312).
-//     More than 131072 centres and up to 27 cells: two waves, whose sums are added half as often; the rounding of the sums is 10 000
-//     times the error of the longer ones (64 -> 64, 400 000 points with 10 neighbours 229, 204, with 24 264, 246, in spatial order 250, 215; 150 000 points with
-//     10: 104, 98).
+//     More than 131072 centres and up to 27 cells: two waves, whose sums are added half as often; the rounding of the sums is
+//     10 000 times the error of the longer ones (64 -> 64, 400 000 points with 10 neighbours 229, 204, with 24 264, 246, in spatial
+//     order 250, 215; 150 000 points with 10: 104, 98).
 //     Crowded: 16 centres, which fill their windows, over two waves, or four where the cloud is too small to fill the device with
-//     that (64 -> 64, cooperative with 16 centres per wave / four waves / two: 115 000 points with 148 neighbours 162 / 145 / 141 and in
-//     spatial order 178 / 146 / 143; 57 600 with 74 71 / 57 / 54; 150 000 with 48 in spatial order 152 / 143 / 128; 40 000 with 50
-//     61 / 53 / 57; 10 000 with 50 41 / 19 / 24).  Two chunks of rows (128 -> 64) need more than 80 triplets per 32 centres for it:
-//     25 000 points with 100 neighbours 113 / 78 / 78 (32 centres 88), 60 000 with 60 135 / 142 / 145 (127).
-//     More than 131072 centres and up to 27 cells: 32 centres over two waves up to 256 triplets per 32 centres (400 000 points, 64 ->
-//     64, 43 neighbours cooperative 372, 16 centres 394, 32 343; in spatial order 293 and 249), with two chunks up to 128 in spatial order (400 000
-//     points with 70 neighbours: 788, 861, 663; in index order 200 000 with 32: 240, 231, 246).  Above 256 with two chunks in index order the cooperative
-//     form, whose blocks read W a quarter as often (400 000 points with 560 neighbours: 3756, 4626; in spatial order 3435, 3540).
+//     that (64 -> 64, cooperative with 16 centres per wave / four waves / two: 115 000 points with 148 neighbours 162 / 145 / 141
+//     and in spatial order 178 / 146 / 143; 57 600 with 74 71 / 57 / 54; 150 000 with 48 in spatial order 152 / 143 / 128; 40 000
+//     with 50 61 / 53 / 57; 10 000 with 50 41 / 19 / 24).  Two chunks of rows (128 -> 64) need more than 80 triplets per 32 centres
+//     for it: 25 000 points with 100 neighbours 113 / 78 / 78 (32 centres 88), 60 000 with 60 135 / 142 / 145 (127).
+//     More than 131072 centres and up to 27 cells: 32 centres over two waves up to 256 triplets per 32 centres (400 000 points, 64
+//     -> 64, 43 neighbours cooperative 372, 16 centres 394, 32 343; in spatial order 293 and 249), with two chunks up to 128 in
+//     spatial order (400 000 points with 70 neighbours: 788, 861, 663; in index order 200 000 with 32: 240, 231, 246).  Above 256
+//     with two chunks in index order the cooperative form, whose blocks read W a quarter as often (400 000 points with 560
+//     neighbours: 3756, 4626; in spatial order 3435, 3540).
 //   - rounded sums to 65 .. 128 channels: split up to 32768 centres, crowded from 16384 on: over two waves (25 000 points with 368
-//     neighbours, 64 -> 128: 52, four waves 61; 12 500 points with 80: 46, 37); above, cooperative, 32 centres per wave, crowded: 16
-//     (strided layer, 64 -> 128: 97, split 107).
+//     neighbours, 64 -> 128: 52, four waves 61; 12 500 points with 80: 46, 37); above, cooperative, 32 centres per wave, crowded:
+//     16 (strided layer, 64 -> 128: 97, split 107).
 //   - wider: cooperative, so that W is read once per 64 centres; 32 centres per wave (100 000 points, 125 cells, 128 -> 256 with
 //     rounded sums: 777; 16 centres 958, split 864), 16 where the exact bf16 sums of 32 would leave a CU one block, and in crowded
-//     layers with rounded sums (115 000 points with 148 neighbours, 256 -> 256: 907 in spatial order and 860 in index order,
-//     32 centres 1102 and 1026; 100 000 points with 24 neighbours, not crowded: 673, 32 centres 618).
+//     layers with rounded sums (115 000 points with 148 neighbours, 256 -> 256: 907 in spatial order and 860 in index order, 32
+//     centres 1102 and 1026; 100 000 points with 24 neighbours, not crowded: 673, 32 centres 618).
 template <bool F32, bool EXACT, int RL, bool NARROW, int GA, int NW>
 int launch_tile_split(const TileArgs &t, hipStream_t stream)
 {
