@@ -601,7 +601,9 @@ int launch_weight_lds(const MvmrArgs &a, float *dw, const int32_t *tri_o, const 
 // Sub-blocks of 128 x 64 channels read fewer rows, 64 x 64, of the same chunks, have three waves per SIMD for two: the latter up to
 // 1.2 M triplets times the sub-blocks of 128 x 64 (128 -> 128, 0.14 M: 29.8 us, 128 x 64 37.1; 0.35 M: 42.7, 47.8; 0.58 M: 54.1, 57.7;
 // 64 -> 128, 0.35 M: 33.8, 41.8; 0.93 M: 52.8, 59.4; 192 -> 128, 0.35 M: 51.9, 56.8; 0.57 M: 75.7, 70.4; 384 -> 320, 0.06 M: 59.1, 70.1).
-// Beyond, where sub-blocks are many, it is the rows that count (512 -> 512, 0.39 M: 375, 300; 1024 -> 1024, 0.58 M: 2992, 1693).
+// Beyond, where sub-blocks are many, it is the rows that count (512 -> 512, 0.39 M: 375, 300; 1024 -> 1024, 0.58 M: 2992, 1693).  Rows
+// that are no multiple of 16 bytes cost more: 0.7 M (117 -> 211, 0.14 M: 57.2, 56.5; 0.22 M: 75.8, 67.2; 67 -> 91, 0.34 M: 47.8, 50.0; 0.49 M:
+// 63.8, 57.4; 169 -> 123, 0.22 M: 56.7, 58.0; 0.34 M: 72.5, 66.0).
 struct AnyShape { int co, ci, n_sub_in, n_sub, chunk; int64_t n_chunks; };
 
 AnyShape any_shape(bool f32, int64_t n_triplets, int c_in, int c_out)
@@ -616,7 +618,7 @@ AnyShape any_shape(bool f32, int64_t n_triplets, int c_in, int c_out)
         return s.n_sub = s.n_sub_in * (int)ceil_div(c_out, s.co);
     };
     const int64_t n_sub = sub_blocks(f32 ? 64 : 128);
-    if (!f32 && n_triplets * n_sub <= 1200000) sub_blocks(64);
+    if (!f32 && n_triplets * n_sub <= (c_in % 8 == 0 && c_out % 8 == 0 ? 1200000 : 700000)) sub_blocks(64);
     int64_t want = 1024 / n_sub;
     if (want < 8) want = 8;
     const int64_t short_chunks = ceil_div(n_triplets, f32 ? F32_CHUNK : SEGMENT), room = ((int64_t)1 << 26) / ((int64_t)c_in * c_out);

@@ -75,9 +75,11 @@ def test_forms_of_the_tile_kernel(n, cin, cout, dt, t, neighbours, side):
                 assert torch.equal(call(T, out_dtype=torch.bfloat16), got.bfloat16()), f"{what} {order} bf16"
 
 
-@pytest.mark.parametrize("n,neighbours,cin,cout", [(20011, 27, 72, 100), (20011, 33, 72, 100), (30011, 36, 40, 72), (30011, 44, 72, 40), (257, 6, 136, 72)])
+@pytest.mark.parametrize("n,neighbours,cin,cout", [(20011, 27, 72, 100), (20011, 33, 72, 100), (30011, 36, 40, 72), (30011, 44, 72, 40), (257, 6, 136, 72),
+                                                   (10011, 32, 67, 91), (10011, 38, 67, 91)])
 def test_sub_blocks_of_the_weight_gradient(n, neighbours, cin, cout):
-    """bf16, either side of 1.2 M triplets times sub-blocks of 128 x 64 channels, up to which sub-blocks have 64 x 64."""
+    """bf16, either side of 1.2 M triplets times sub-blocks of 128 x 64 channels, up to which sub-blocks have 64 x 64 (0.7 M where a
+    row is no multiple of 16 bytes)."""
     import paper_2511_23227_amd as pcpp
     rng = np.random.default_rng(n + cin)
     p = rng.uniform(0, 1, (n, 3)).astype(np.float32)
